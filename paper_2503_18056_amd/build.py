@@ -15,8 +15,14 @@ LIB = os.path.join(HERE, "libtt.so")
 SOURCES = ["k_gemm.hip", "k_eig.hip", "k_step.hip", "k_adj.hip", "tt_api.hip", "tt_grad.hip",
            "tt_kernels_api.hip", "k_micro.hip", "tt_rand.hip"]
 ARCH = os.environ.get("TT_OFFLOAD_ARCH", "gfx950")
+# -amdgpu-mfma-vgpr-form keeps the MFMA accumulators in VGPRs.  Left to its
+# heuristics the compiler puts them in AGPRs and, in a loop that carries them,
+# copies every one out to VGPRs and back on each trip (256 moves for 64 MFMAs
+# in the wide Gram): the FP64 MFMA microbenchmark runs at 48.8 TFLOP/s that
+# way and at 77.2 with them in VGPRs.
 FLAGS = ["--offload-arch=" + ARCH, "-O3", "-std=c++17", "-fPIC",
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
+         "-mllvm", "-amdgpu-mfma-vgpr-form=1",
          "-Wno-unused-result", "-Wno-unused-value"]
 
 
