@@ -400,12 +400,18 @@ GramPlan gram_plan(int K, int ncap, int lda) {
   p.rows_per_blk = ((K + nb - 1) / nb + 15) / 16 * 16;
   p.nblk = (K + p.rows_per_blk - 1) / p.rows_per_blk;
   if (p.nblk < 1) p.nblk = 1;
-  // wide form: 128-column tile pairs, a multiple of GW_XCD row slices of at
-  // least 1024 rows (at most 64)
+  // wide form: 128-column tile pairs, a multiple of GW_XCD row slices.  Two
+  // blocks fit a CU, so 512 run at once and a block should be a small part of
+  // the launch: slices of at most 8192 rows (2097152 x 896: 31.5 ms with 256
+  // slices, 37.0 with 64, whose blocks took 7 ms each and left the last
+  // round three quarters empty), and of fewer where that gives less than 768
+  // blocks, down to 256 rows (16384 x 641: 0.19 ms with 32 slices, 0.32 with
+  // 16; 4096 x 537: 0.077 against 0.115 ms)
   p.wtiles = (ncap + GW_T - 1) / GW_T;
   p.wpairs = p.wtiles * (p.wtiles + 1) / 2;
-  int ws = K / 1024;
-  ws = ws < GW_XCD ? GW_XCD : (ws > 64 ? 64 : ws);
+  int ws = K / 256 < 768 / p.wpairs ? K / 256 : 768 / p.wpairs;
+  if (ws < K / 8192) ws = K / 8192;
+  ws = ws < GW_XCD ? GW_XCD : (ws > 256 ? 256 : ws);
   ws = ws / GW_XCD * GW_XCD;
   p.wkslice = ((K + ws - 1) / ws + GW_KB - 1) / GW_KB * GW_KB;
   p.wslices = ws;
