@@ -36,10 +36,9 @@ FP64_PEAK_TFLOPS = 78.6
 GRAM_ROWS_MAX = 384          # widest concatenated rank the row-slice Gram holds in LDS
 R1CAP = 5 * 64 + 2 + 1       # crossing beams: B r1_cap + 2 inflow terms + emission slot
 GRAM_KERNEL64 = "k_gram_rows<double> (left Gram X_cat^T X_cat, row slices staged in LDS, FP64 MFMA)"
-GRAM_KERNEL32 = "k_gram_rows_f32<4> (sliced exact Gram on FP32 MFMA, 10 slice products)"
+GRAM_KERNEL32 = "k_gram_rows<float> (FP32 entries, FP64 MFMA)"
 ROUNDING_PHASES = ("gram_tall", "gram_reduce", "eig_bond1", "eig_M1", "eig_bond2", "eig_M2",
                    "x_update", "small_gemm")
-FP32_MFMA_PEAK_TFLOPS = 157.3
 HBM_PEAK_GBS = 8000.0
 RUN_STEPS = 400              # the crossing-beam run
 BREAKDOWN_STEPS = 20         # fully profiled steps after the timed ones
@@ -54,7 +53,7 @@ def gram_rows_digest():
     import hashlib
     s = open(os.path.join(ROOT, "paper_2503_18056_amd", "csrc", "k_gemm.hip")).read()
     a = s.index("// row-slice Gram (k_gram_rows) shape")
-    b = s.index("\n", s.index("template <> struct GrShape<float>"))
+    b = s.index("\n", s.index("template <> struct GrShape<0>"))
     k0 = s.index("template <typename T, int S>\n__device__ __forceinline__ void gram_rows_body(")
     k1 = s.index("__global__ __launch_bounds__(256) void k_gram_rows_reduce")
     return hashlib.sha256((s[a:b] + s[k0:k1]).encode()).hexdigest()[:16]
@@ -329,10 +328,10 @@ def mixed_run(p, ramp, W, K, dt, hist, end64):
         "rank_history_equal_steps": sum(a == b for a, b in zip(histm, hist)),
         "ranks_end": list(sm.ranks()),
         "gram_kernel": {
-            "kernel": GRAM_KERNEL32 if R1CAP <= GRAM_ROWS_MAX else "k_gram_split_wide",
+            "kernel": GRAM_KERNEL32 if R1CAP <= GRAM_ROWS_MAX else "k_gram_wide<float>",
             "avg_launch_ms": gm_ms / gm_n if gm_n else None,
             "achieved_algorithmic_TFLOPs": flops_m / (gm_ms * 1e-3) / 1e12 if gm_ms > 0 else 0.0,
-            "peak_fp32_mfma_TFLOPs": FP32_MFMA_PEAK_TFLOPS,
+            "peak_fp64_mfma_TFLOPs": FP64_PEAK_TFLOPS,
         },
         "kernel_breakdown_ms": {k: {"ms_total": round(v[0], 3), "launches": v[1]}
                                 for k, v in bdm.items()},
@@ -382,7 +381,7 @@ def slice_sweep(p, nsteps, slices=(1, 2, 3, 4, 5, 6), prof_steps=20):
         progress(f"Gram slice sweep: {sl} slices")
         dt, h, e, g = run(TT_FP32_MIXED, sl)
         out["slices"][str(sl)] = {
-            "slice_products": sl * (sl + 1) // 2,
+            "slice_products": sl * (sl + 1) // 2 if sl < 4 else None,  # None: FP64 products
             "steps_per_s": nsteps / dt,
             "gram_avg_launch_ms": g,
             "rank_history_equal_steps": sum(a == b for a, b in zip(h, h64)),
@@ -494,7 +493,7 @@ def thick_3d_run(W, K):
         # concatenated rank at bond 1: (1 + 2 dim) r1 plus the emission slot
         flops = sum(gram_flops(ns, blocks * r1 + 1) for (r1, _) in r_in)
         gms, gn = prof.get("gram_tall", (0.0, 0))
-        peak = FP64_PEAK_TFLOPS if prec == TT_FP64 else FP32_MFMA_PEAK_TFLOPS
+        peak = FP64_PEAK_TFLOPS  # both precisions form the products on FP64 MFMA
         achieved = flops / (gms * 1e-3) / 1e12 if gms > 0 else 0.0
         round_ms = sum(bd.get(k, (0.0, 0))[0] for k in ROUNDING_PHASES) * K / 2.0
         out[name] = {
@@ -505,7 +504,7 @@ def thick_3d_run(W, K):
             "ms_per_rounding": round_ms / K,
             "gram": {"kernel": ("k_gram_wide (FP64 MFMA, 128x128 tile pairs, rows staged through LDS)"
                                 if prec == TT_FP64 else
-                                "k_gram_split_wide (sliced exact Gram on FP32 MFMA, 10 slice products, 128x128 tile pairs)"),
+                                "k_gram_wide<float> (FP32 entries, FP64 MFMA, 128x128 tile pairs)"),
                      "avg_launch_ms": gms / gn if gn else None,
                      "achieved_algorithmic_TFLOPs": achieved,
                      "peak_TFLOPs": peak, "frac": achieved / peak},

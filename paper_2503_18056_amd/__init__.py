@@ -238,7 +238,8 @@ class TTState:
         self._check(self.lib.tt_use_graphs(self.ctx, 1 if on else 0))
 
     def tt_set_gram_slices(self, slices):
-        """11-bit slices per entry of the FP32-mixed Gram (1 .. 6, default 4)."""
+        """Products of the FP32-mixed Gram: 1 .. 3, that many 11-bit slices per
+        entry on FP32 MFMA; 4 .. 6 (default 4), FP64 MFMA on the entries."""
         self._check(self.lib.tt_set_gram_slices(self.ctx, int(slices)))
 
     def tt_set_solver_limits(self, jacobi_max_sweeps):

@@ -426,8 +426,8 @@ void truncate_bond(tt_ctx* c, int bond, const EigSlot& ea, const EigSlot& eb, Ei
 
 // Gram-SVD rounding (App. A Algorithm 1, d = 3) of the TT held in
 // (xc, ldxc) / Thcat / Phcat with concatenated ranks dims[RC1], dims[RC2].
-// xcf != nullptr: the FP32-mixed form (X_cat in FP32, sliced Gram and
-// split-product update on FP32 MFMA, X' written to Xnf); else FP64 (X' to Xn).
+// xcf != nullptr: the FP32-mixed form (X_cat in FP32, X' written to Xnf); else
+// FP64 (X' to Xn).
 void round_pipeline(tt_ctx* c, const double* xc, int ldxc, int ncap1, double tol, int rmax,
                     const float* xcf = nullptr) {
   hipStream_t s = c->st;

@@ -120,9 +120,11 @@ void gram_tall_partial(const GramPlan& p, const double* A, DimExpr n, double* pa
 void gram_tall_reduce(const GramPlan& p, DimExpr n, const double* partial, double* G, int ldg,
                       const int* dims, hipStream_t s);
 
-// ---- FP32-mixed form: sliced (error-free) Gram of an FP32 matrix on FP32
-// MFMA into partial tiles (reduce with gram_split_reduce); colmax is scratch
-// of ncap words; slices: 11-bit slices per entry (1 .. 6; others give 4).
+// ---- FP32-mixed form: Gram of an FP32 matrix into partial tiles (reduce with
+// gram_split_reduce); slices: 1 .. 3, 11-bit slices per entry multiplied on
+// FP32 MFMA (colmax is scratch of ncap words); otherwise FP64 MFMA on the
+// widened entries.
+constexpr int GRAM_SLICES_FP64 = 4;
 constexpr int GRAM_SLICES_DEFAULT = 4;
 void gram_split_partial(const GramPlan& p, const float* A, DimExpr n, unsigned* colmax,
                         double* partial, const int* dims, hipStream_t s,
