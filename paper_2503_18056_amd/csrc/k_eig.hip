@@ -70,8 +70,8 @@ template <int CTRL>
 __device__ inline double dpp_d(double v) {
   const long long b = __double_as_longlong(v);
   const int lo = (int)b, hi = (int)(b >> 32);
-  const int lo2 = __builtin_amdgcn_update_dpp(lo, lo, CTRL, 0xf, 0xf, false);
-  const int hi2 = __builtin_amdgcn_update_dpp(hi, hi, CTRL, 0xf, 0xf, false);
+  const int lo2 = __builtin_amdgcn_mov_dpp(lo, CTRL, 0xf, 0xf, true);
+  const int hi2 = __builtin_amdgcn_mov_dpp(hi, CTRL, 0xf, 0xf, true);
   return __longlong_as_double(((long long)hi2 << 32) | (unsigned int)lo2);
 }
 __device__ inline double lane_d(double v, int l) {
@@ -95,6 +95,13 @@ __device__ inline double wave_sum(double v) {
   return (lane_d(v, 0) + lane_d(v, 16)) + (lane_d(v, 32) + lane_d(v, 48));
 }
 
+// 1 / sqrt(x) to about an ulp for x well inside the normal range: the hardware
+// estimate and one third-order step.
+__device__ inline double rsqrt_d(double x) {
+  const double y = __builtin_amdgcn_rsq(x);
+  const double e = fma(-x * y, y, 1.0);
+  return fma(y * e, fma(0.375, e, 0.5), y);
+}
 // Barrier that orders LDS only: waits for this wavefront's LDS accesses
 // (lgkmcnt 0), not for its global stores, then s_barrier.  For loops whose
 // global stores nothing in the kernel reads back; the signal fences keep the
@@ -2019,41 +2026,216 @@ __global__ __launch_bounds__(256) void k_svd_load(const double* __restrict__ M, 
 // M^T for side 0; p >= q) fits LDS, its columns are orthogonalised by plane
 // rotations, B V = U S, and the right vectors V (the vectors of M's short
 // side) and S come out directly, with no bidiagonalisation and no
-// tridiagonal eigensolve.  The q columns are paired round-robin (q - 1
-// rounds of q / 2 disjoint pairs per sweep); each pair belongs to one row of
-// 16 lanes, whose sums need only the four in-row DPP steps, so the up to 32
-// pairs of a round run side by side on at most eight wavefronts, and a
-// wavefront whose rows all lack a pair skips the round.  (The step is bound
-// by instruction issue: every wave64 VALU instruction holds its SIMD for four
-// cycles, so the work per round is kept on as few wavefronts as the pairs
-// need.)  A pair (i, j) with a = |b_i|^2, b = |b_j|^2, g = b_i . b_j is
-// rotated when g^2 > (p u)^2 a b, by the angle that zeroes g: with d = b - a,
-// t = sign(d) 2 g / (|d| + sqrt(d^2 + 4 g^2)) (the smaller root of
-// t^2 + (d / g) t - 1 = 0), c = 1 / sqrt(1 + t^2), s = c t.  A sweep without
-// a rotation ends the iteration (at most JAC_MAXSW sweeps; more raises the
-// eigensolver flag).  Singular values are the final column norms, sorted
-// descending (index breaks ties); the kept count, the scalings and the sign
-// gauge follow the same rules as the Golub-Kahan path, whose launches then
-// return at once: the Golub-Kahan order dims[J.n_idx] is set to -1 to say so.
+// tridiagonal eigensolve.  V is accumulated over the rotations: M is graded on
+// both sides, and the tiny entries of V that couple a small singular value to
+// a large column keep their relative accuracy that way, on which U = M V S^-1
+// depends (forming V from the orthogonalised rows of a QR factor takes fewer
+// sweeps and loses it: U's columns come out orthogonal to 1e-6, not 1e-12).
+//
+// A round is one latency chain: the exchange of the columns through LDS (its
+// writes the largest part), the sums, the rotation's scalars, the update, a
+// barrier.  So columns move in blocks of two: the nbe blocks are paired
+// round-robin (nbe - 1 rounds of nbe / 2 disjoint block pairs per sweep), half
+// a wavefront holds the four columns of its pair and their V columns in
+// registers for a round and applies the four cross rotations as two steps of
+// two independent ones (and, in round 0, the two inside the blocks).  Lane r
+// holds rows 2 r, 2 r + 1 of every 64, so columns move in 16-byte LDS accesses.
+// Whole calls of tt_kernel_svd (about 65 us besides this kernel) on matrices
+// graded by 1e-4 along the rows and 1e-6 along the columns, before (one pair
+// per 16 lanes and round, three sums a pair, divisions and square roots) and
+// now: 142 x 36 411 -> 300 us, 144 x 63 984 -> 616, 96 x 32 320 -> 213, 62 x 12
+// 113 -> 93.
+//
+// A pair (i, j) with a = |b_i|^2, b = |b_j|^2, g = b_i . b_j is rotated when
+// g^2 > (p u)^2 a b, by the angle that zeroes g to the accuracy of the
+// hardware's reciprocals (jacobi_rotation).  a and b are summed in round 0 of
+// a sweep and follow the rotations from there by a - t g, b + t g; a sweep that
+// rotates nothing, which ends the iteration, has tested summed norms only.
+// More than JAC_MAXSW sweeps raise the eigensolver flag.  Singular values are
+// the final column norms, sorted descending (index breaks ties); the kept
+// count, the scalings and the sign gauge follow the same rules as the
+// Golub-Kahan path, whose launches then return at once: the Golub-Kahan order
+// dims[J.n_idx] is set to -1 to say so.
 constexpr int JAC_QMAX = 64;
-constexpr int JAC_PQ = 12288;   // doubles of B in LDS (96 KB: q columns of p rows padded to 16), plus V
+constexpr int JAC_PQ = 14336;   // doubles of B in LDS (112 KB: columns of p rows padded to 16)
 constexpr int JAC_PMAX = 512;
 constexpr int JAC_MAXSW = 40;
 constexpr int JAC_T = 512;
 constexpr int JAC_WAVES = JAC_T / 64;
+constexpr int JAC_VLD = JAC_QMAX;
 __device__ inline int jacobi_ld(int p) { return (p + 15) & ~15; }
+// columns of B in LDS: an even number of blocks of two, those past q zero
+__device__ inline int jacobi_cols(int q) { return (q + 3) & ~3; }
 __device__ inline bool jacobi_fits(int p, int q) {
-  return q >= 1 && q <= JAC_QMAX && p <= JAC_PMAX && jacobi_ld(p) * q <= JAC_PQ;
+  return q >= 1 && q <= JAC_QMAX && p <= JAC_PMAX && jacobi_ld(p) * jacobi_cols(q) <= JAC_PQ;
 }
 
-// Sum over each row of 16 lanes, returned on every lane of the row (the
-// first four steps of wave_sum).
-__device__ inline double row16_sum(double v) {
+// Sum over each half wavefront, the same bits on all its lanes: the first four
+// steps of wave_sum on each row of 16 lanes, then the row swap puts the two
+// rows' sums side by side on both.
+__device__ inline double half_sum(double v) {
   v += dpp_d<0xB1>(v);   // quad_perm [1, 0, 3, 2]
   v += dpp_d<0x4E>(v);   // quad_perm [2, 3, 0, 1]
   v += dpp_d<0x141>(v);  // row_half_mirror
   v += dpp_d<0x140>(v);  // row_mirror
-  return v;
+  const unsigned long long b = (unsigned long long)__double_as_longlong(v);
+  const unsigned lo = (unsigned)b, hi = (unsigned)(b >> 32);
+  const auto l = __builtin_amdgcn_permlane16_swap(lo, lo, false, false);
+  const auto h = __builtin_amdgcn_permlane16_swap(hi, hi, false, false);
+  return __longlong_as_double((long long)(((unsigned long long)h[0] << 32) | l[0])) +
+         __longlong_as_double((long long)(((unsigned long long)h[1] << 32) | l[1]));
+}
+
+// Rotation by the smaller angle that makes columns x_i, x_j with
+// d = |x_j|^2 - |x_i|^2 and g = x_i . x_j != 0 orthogonal: x_i' = c x_i - s x_j,
+// x_j' = s x_i + c x_j, t = s / c = sign(d) 2 g / (|d| + sqrt(d^2 + 4 g^2)), on d
+// and 2 g scaled by a power of two (exact).  t needs no more than the
+// hardware's reciprocal (square root) estimates, about 2^-23: what a rotation
+// leaves of g is that small part of it, and the next sweep's rotation takes it.
+// c = 1 / sqrt(1 + t^2) and s = c t are to rounding.
+__device__ inline void jacobi_rotation(double d, double g, double& c, double& s, double& t) {
+  const double e2 = 2.0 * g;
+  const int ex = -__builtin_amdgcn_frexp_exp(fmax(fabs(d), fabs(e2)));
+  const double ds = __builtin_amdgcn_ldexp(d, ex), es = __builtin_amdgcn_ldexp(e2, ex);
+  const double h2 = fma(ds, ds, es * es);
+  const double r = __builtin_amdgcn_rcp(fma(h2, __builtin_amdgcn_rsq(h2), fabs(ds)));
+  t = (ds >= 0.0 ? es : -es) * r;
+  c = rsqrt_d(fma(t, t, 1.0));
+  s = c * t;
+}
+
+// A column of 64 C rows and its V column on half a wavefront.
+template <int C>
+struct JacCol {
+  double2 x[C], v;
+  double n2;  // squared norm
+};
+template <int C>
+__device__ inline double jac_dot(const JacCol<C>& a, const JacCol<C>& b) {
+  double s0 = a.x[0].x * b.x[0].x, s1 = a.x[0].y * b.x[0].y;
+#pragma unroll
+  for (int c = 1; c < C; ++c) {
+    s0 = fma(a.x[c].x, b.x[c].x, s0);
+    s1 = fma(a.x[c].y, b.x[c].y, s1);
+  }
+  return half_sum(s0 + s1);
+}
+__device__ inline void jac_turn(double2& a, double2& b, double c, double s) {
+  const double2 x = a, y = b;
+  a.x = fma(c, x.x, -s * y.x);
+  a.y = fma(c, x.y, -s * y.y);
+  b.x = fma(s, x.x, c * y.x);
+  b.y = fma(s, x.y, c * y.y);
+}
+// Rotates the disjoint pairs (a0, b0) and (a1, b1) where they need it; the two
+// chains interleave.  Returns whether a pair of this half was rotated.
+template <int C>
+__device__ inline bool jac_step(JacCol<C>& a0, JacCol<C>& b0, JacCol<C>& a1, JacCol<C>& b1,
+                                double tol2) {
+  const double g0 = jac_dot(a0, b0), g1 = jac_dot(a1, b1);
+  const bool r0 = g0 != 0.0 && g0 * g0 > tol2 * a0.n2 * b0.n2;
+  const bool r1 = g1 != 0.0 && g1 * g1 > tol2 * a1.n2 * b1.n2;
+  if (__any(r0 || r1)) {
+    double c0, s0, t0, c1, s1, t1;
+    jacobi_rotation(b0.n2 - a0.n2, g0, c0, s0, t0);
+    jacobi_rotation(b1.n2 - a1.n2, g1, c1, s1, t1);
+    c0 = r0 ? c0 : 1.0;
+    s0 = r0 ? s0 : 0.0;
+    t0 = r0 ? t0 * g0 : 0.0;
+    c1 = r1 ? c1 : 1.0;
+    s1 = r1 ? s1 : 0.0;
+    t1 = r1 ? t1 * g1 : 0.0;
+#pragma unroll
+    for (int c = 0; c < C; ++c) {
+      jac_turn(a0.x[c], b0.x[c], c0, s0);
+      jac_turn(a1.x[c], b1.x[c], c1, s1);
+    }
+    jac_turn(a0.v, b0.v, c0, s0);
+    jac_turn(a1.v, b1.v, c1, s1);
+    a0.n2 -= t0;
+    b0.n2 += t0;
+    a1.n2 -= t1;
+    b1.n2 += t1;
+  }
+  return r0 || r1;
+}
+
+// LDS of the Jacobi kernel's sweeps.
+struct JacLds {
+  double B[JAC_PQ];                // column j at j ld; rows p .. ld - 1, columns past q zero
+  double V[JAC_QMAX * JAC_VLD];
+  double n2[JAC_QMAX];             // squared norms
+  double pad[2];                   // the rows past ld of a chunk of 64: zeros
+  int rot[2];
+};
+
+// All sweeps over the columns in LDS (64 (C - 1) < p <= 64 C).  Returns the sweeps
+// before the one that rotated nothing; maxsw when the last of them did.
+template <int C>
+__device__ int jacobi_sweeps(JacLds& L, int p, int q, int maxsw) {
+  const int lane = threadIdx.x & 63, rl = lane & 31;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int k = 2 * wave + (lane >> 5);  // block pair of this half
+  const int ld = jacobi_ld(p);
+  const int nbe = jacobi_cols(q) / 2, npair = nbe / 2, m1 = nbe - 1;
+  const double tol2 = ((double)p * U64) * ((double)p * U64);
+  const bool tail = 64 * (C - 1) + 2 * rl < ld;  // this lane's rows of the last chunk
+  int sw = 0;
+  for (; sw < maxsw; ++sw) {
+    const int flag = sw & 1;
+    for (int rnd = 0; rnd < m1; ++rnd) {
+      if (k < npair) {
+        // round-robin: position 0 fixed, the others rotate
+        int xa = k - 1 + rnd, xb = nbe - 2 - k + rnd;
+        if (xa >= m1) xa -= m1;
+        if (xb >= m1) xb -= m1;
+        const int bi = k == 0 ? 0 : 1 + xa, bj = 1 + xb;
+        JacCol<C> w[4];
+        double2 *px[4], *pt[4], *pv[4];
+#pragma unroll
+        for (int m = 0; m < 4; ++m) {
+          const int col = 2 * (m < 2 ? bi : bj) + (m & 1);
+          px[m] = reinterpret_cast<double2*>(L.B + col * ld) + rl;
+          // rows past ld: read and written as the zeros they are
+          pt[m] = tail ? px[m] + 32 * (C - 1) : reinterpret_cast<double2*>(L.pad);
+          pv[m] = reinterpret_cast<double2*>(L.V + col * JAC_VLD) + rl;
+#pragma unroll
+          for (int c = 0; c < C - 1; ++c) w[m].x[c] = px[m][32 * c];
+          w[m].x[C - 1] = *pt[m];
+          w[m].v = *pv[m];
+          w[m].n2 = L.n2[col];
+        }
+        bool rot = false;
+        if (rnd == 0) {
+#pragma unroll
+          for (int m = 0; m < 4; ++m) w[m].n2 = jac_dot(w[m], w[m]);
+          rot = jac_step(w[0], w[1], w[2], w[3], tol2);
+        }
+        rot |= jac_step(w[0], w[2], w[1], w[3], tol2);
+        rot |= jac_step(w[0], w[3], w[1], w[2], tol2);
+        if (rot) {
+#pragma unroll
+          for (int m = 0; m < 4; ++m) {
+#pragma unroll
+            for (int c = 0; c < C - 1; ++c) px[m][32 * c] = w[m].x[c];
+            *pt[m] = w[m].x[C - 1];
+            *pv[m] = w[m].v;
+          }
+        }
+        if (rl == 0 && (rot || rnd == 0)) {
+          *reinterpret_cast<double2*>(&L.n2[2 * bi]) = double2{w[0].n2, w[1].n2};
+          *reinterpret_cast<double2*>(&L.n2[2 * bj]) = double2{w[2].n2, w[3].n2};
+          if (rot) L.rot[flag] = 1;
+        }
+      }
+      lds_barrier();
+    }
+    const int any = L.rot[flag];
+    if (threadIdx.x == 0) L.rot[flag ^ 1] = 0;  // the next sweep's flag
+    lds_barrier();
+    if (!any) break;
+  }
+  return sw;
 }
 
 __global__ __launch_bounds__(JAC_T) void k_svd_jacobi(const double* __restrict__ M, int ldm,
@@ -2063,93 +2245,55 @@ __global__ __launch_bounds__(JAC_T) void k_svd_jacobi(const double* __restrict__
   const int a = dims[a_idx], b = dims[b_idx], side = dims[side_idx];
   const int p = side ? a : b, q = side ? b : a;
   if (!jacobi_fits(p, q)) return;  // the Golub-Kahan path
-  __shared__ double Bs[JAC_PQ];
-  __shared__ double Vs[JAC_QMAX * JAC_QMAX];
+  __shared__ __align__(16) JacLds L;
   __shared__ double ssig[JAC_QMAX];
   __shared__ int spos[JAC_QMAX];
-  __shared__ int s_rot[2];
   __shared__ int s_kept;
+  double *Bs = L.B, *Vs = L.V;
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int rl = lane & 15;              // lane within the row of 16
-  const int k = 4 * wave + (lane >> 4);  // the pair of this row
-  // B column-major (column j at Bs + j ld, rows p .. ld - 1 zero), V = I
-  const int ld = jacobi_ld(p);
-  for (int e = tid; e < ld * q; e += JAC_T) {
-    const int i = e % ld, j = e / ld;
-    Bs[e] = i >= p ? 0.0 : side ? M[(long long)i * ldm + j] : M[(long long)j * ldm + i];
+  // B column-major (column j at Bs + j ld, rows p .. ld - 1 and columns past q
+  // zero), V = I; both read along M's rows
+  const int ld = jacobi_ld(p), nc = jacobi_cols(q);
+  if (side) {
+    for (int e = tid; e < ld * nc; e += JAC_T) {
+      const int i = e / nc, j = e - i * nc;
+      Bs[j * ld + i] = i < p && j < q ? M[(long long)i * ldm + j] : 0.0;
+    }
+  } else {
+    for (int e = tid; e < ld * nc; e += JAC_T) {
+      const int j = e / ld, i = e - j * ld;
+      Bs[e] = i < p && j < q ? M[(long long)j * ldm + i] : 0.0;
+    }
   }
-  for (int e = tid; e < q * q; e += JAC_T) Vs[e] = (e % q) == (e / q) ? 1.0 : 0.0;
-  if (tid < 2) s_rot[tid] = 0;
+  for (int e = tid; e < nc * JAC_VLD; e += JAC_T) Vs[e] = (e % JAC_VLD) == (e / JAC_VLD) ? 1.0 : 0.0;
+  if (tid < JAC_QMAX) L.n2[tid] = 0.0;
+  if (tid < 2) {
+    L.rot[tid] = 0;
+    L.pad[tid] = 0.0;
+  }
   __syncthreads();
-  const int qe = q + (q & 1), npair = qe / 2, m1 = qe - 1;
-  const int nch = ld / 16;
-  const double tol2 = ((double)p * U64) * ((double)p * U64);
   // sweeps allowed: JAC_MAXSW, or fewer when the host caps them (a test of
   // the failure path: the rotations stay finite, only convergence is lost)
   const int capsw = dims[D_JAC_MAXSW];
   const int maxsw = capsw > 0 && capsw < JAC_MAXSW ? capsw : JAC_MAXSW;
-  int sw = 0;
-  for (; sw < maxsw; ++sw) {
-    const int flag = sw & 1;
-    for (int rnd = 0; rnd < m1; ++rnd) {
-      if (4 * wave < npair) {
-        // round-robin: position 0 fixed, the others rotate
-        int xa = k - 1 + rnd, xb = qe - 2 - k + rnd;
-        if (xa >= m1) xa -= m1;
-        if (xb >= m1) xb -= m1;
-        int ci = k == 0 ? 0 : 1 + xa, cj = 1 + xb;
-        if (ci > cj) { const int t = ci; ci = cj; cj = t; }
-        // a row without a pair this round (k >= npair, or the padding
-        // column of an odd q) reads column 0 and never rotates; every load is
-        // in bounds and unconditional (the columns are zero-padded to ld)
-        const bool live = k < npair && cj < q;
-        double* bi = Bs + (size_t)(live ? ci : 0) * ld;
-        double* bj = Bs + (size_t)(live ? cj : 0) * ld;
-        double pa = 0.0, pb = 0.0, pg = 0.0;
-#pragma unroll 8
-        for (int c = 0; c < nch; ++c) {
-          const double xv = bi[rl + 16 * c], yv = bj[rl + 16 * c];
-          pa = fma(xv, xv, pa);
-          pb = fma(yv, yv, pb);
-          pg = fma(xv, yv, pg);
-        }
-        const double aa = row16_sum(pa), bb = row16_sum(pb), g = row16_sum(pg);
-        if (live && g != 0.0 && g * g > tol2 * aa * bb) {
-          const double d = bb - aa, g2 = 2.0 * g;
-          const double t = (d >= 0.0 ? g2 : -g2) / (fabs(d) + sqrt(d * d + g2 * g2));
-          const double cs = 1.0 / sqrt(1.0 + t * t), sn = cs * t;
-          // the columns are read again from LDS: holding them in registers
-          // costs more instructions than the reads (and spills at p = 512)
-#pragma unroll 8
-          for (int c = 0; c < nch; ++c) {
-            const int i = rl + 16 * c;
-            const double xv = bi[i], yv = bj[i];
-            bi[i] = cs * xv - sn * yv;  // padding rows stay zero
-            bj[i] = sn * xv + cs * yv;
-          }
-          double* vi = Vs + (size_t)ci * q;
-          double* vj = Vs + (size_t)cj * q;
-          for (int r = rl; r < q; r += 16) {
-            const double u = vi[r], w = vj[r];
-            vi[r] = cs * u - sn * w;
-            vj[r] = sn * u + cs * w;
-          }
-          if (rl == 0) s_rot[flag] = 1;
-        }
-      }
-      __syncthreads();
-    }
-    const int any = s_rot[flag];
-    if (tid == 0) s_rot[flag ^ 1] = 0;  // the next sweep's flag
-    __syncthreads();
-    if (!any) break;
+  int sw;
+  // C = ceil(ld / 64): every chunk but the last lies wholly within a column
+  switch ((p + 63) / 64) {
+    case 1: sw = jacobi_sweeps<1>(L, p, q, maxsw); break;
+    case 2: sw = jacobi_sweeps<2>(L, p, q, maxsw); break;
+    case 3: sw = jacobi_sweeps<3>(L, p, q, maxsw); break;
+    case 4: sw = jacobi_sweeps<4>(L, p, q, maxsw); break;
+    case 5: sw = jacobi_sweeps<5>(L, p, q, maxsw); break;
+    case 6: sw = jacobi_sweeps<6>(L, p, q, maxsw); break;
+    case 7: sw = jacobi_sweeps<7>(L, p, q, maxsw); break;
+    default: sw = jacobi_sweeps<8>(L, p, q, maxsw);
   }
   if (sw == maxsw && tid == 0) atomicOr(&dims[D_FLAG], FLAG_NOCONV);
   // singular values: column norms; descending order (index breaks ties)
   for (int j = wave; j < q; j += JAC_WAVES) {
     double part = 0.0;
-    for (int i = lane; i < p; i += 64) part = fma(Bs[(size_t)j * ld + i], Bs[(size_t)j * ld + i], part);
+    for (int i = lane; i < p; i += 64) part = fma(Bs[j * ld + i], Bs[j * ld + i], part);
     const double s2 = wave_sum(part);
     if (lane == 0) ssig[j] = sqrt(s2);
   }
@@ -2158,37 +2302,44 @@ __global__ __launch_bounds__(JAC_T) void k_svd_jacobi(const double* __restrict__
     const double v = ssig[tid];
     if (!(v == v)) atomicOr(&dims[D_FLAG], FLAG_EIG);
     int pos = 0;
+    double smax = 0.0;
     for (int kk = 0; kk < q; ++kk) {
       const double w = ssig[kk];
       pos += (w > v) || (w == v && kk < tid);
+      smax = fmax(smax, w);
     }
     spos[tid] = pos;
+    J.lam[pos] = v;
+    // the Golub-Kahan path's clip rule at its order 2q: sigma > clip 2q u sigma_1
+    const double thr = fmax(J.clip * (double)(2 * q) * U64 * smax, 0.0);
+    const bool keep = v > thr;
+    const unsigned long long m = __ballot(keep);
+    if (keep) {
+      J.sq[pos] = v;
+      J.isq[pos] = 1.0 / v;
+    }
+    if (tid == 0) {
+      s_kept = __popcll(m);
+      dims[J.kept_idx] = s_kept;
+      dims[J.n_idx] = -1;
+    }
   }
   __syncthreads();
-  for (int j = tid; j < q; j += JAC_T) J.lam[spos[j]] = ssig[j];
-  for (int e = tid; e < q * q; e += JAC_T) {
-    const int i = e % q, j = e / q;
-    J.V[(size_t)i * J.ldv + spos[j]] = Vs[e];
-  }
-  if (tid == 0) {
-    // the Golub-Kahan path's clip rule at its order 2q: sigma > clip 2q u sigma_1
-    double smax = 0.0;
-    for (int j = 0; j < q; ++j) smax = fmax(smax, ssig[j]);
-    const double thr = fmax(J.clip * (double)(2 * q) * U64 * smax, 0.0);
-    int kk = 0;
-    for (int j = 0; j < q; ++j) kk += ssig[j] > thr;
-    s_kept = kk;
-    dims[J.kept_idx] = kk;
-    dims[J.n_idx] = -1;
-  }
-  __syncthreads();  // J.V and J.lam written by this block
+  // vectors in descending order, of the kept ones the largest-magnitude entry
+  // (first on ties) positive; a wavefront per column, an entry per lane
   const int kept = s_kept;
-  for (int c = tid; c < kept; c += JAC_T) {
-    const double sg = J.lam[c];
-    J.sq[c] = sg;
-    J.isq[c] = 1.0 / sg;
+  for (int j = wave; j < q; j += JAC_WAVES) {
+    const int pos = spos[j];
+    const double x = lane < q ? Vs[j * JAC_VLD + lane] : 0.0;
+    double best = fabs(x), val = x;
+    int bi = lane;
+    for (int o = 32; o > 0; o >>= 1) {
+      const double b2 = __shfl_xor(best, o), v2 = __shfl_xor(val, o);
+      const int i2 = __shfl_xor(bi, o);
+      if (b2 > best || (b2 == best && i2 < bi)) { best = b2; val = v2; bi = i2; }
+    }
+    if (lane < q) J.V[(size_t)lane * J.ldv + pos] = pos < kept && val < 0.0 ? -x : x;
   }
-  if (tid < 256) gauge_columns(J.V, J.ldv, q, kept);
 }
 
 // Householder bidiagonalisation of the p x q work matrix (p >= q): left
@@ -2676,7 +2827,7 @@ int dc_fused_blocks(int N) { return std::min(DCF_MAXP, std::max(8, (N + 3) / 4))
 namespace {
 constexpr size_t LDS_CU = 160 * 1024;
 constexpr size_t ST_SYTRD_GRID = 168, ST_DC_FUSED = 42832, ST_ORMTR = 0, ST_GEBRD_GRID = 168,
-                 ST_SVD_JACOBI = 131856;
+                 ST_SVD_JACOBI = 148768;
 
 size_t static_lds(const void* fn, size_t table, bool runtime) {
   if (!runtime) return table;
