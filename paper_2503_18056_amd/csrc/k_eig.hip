@@ -5,7 +5,7 @@
 // Pipeline (one job per matrix, several jobs run side by side):
 //   1. Householder tridiagonalisation A = Q T Q^T (the only step with O(n)
 //      sequential dependences): the matrix in one block's registers up to
-//      order 160, above that split by rows over 64 blocks' LDS.
+//      order 192, above that split by rows over 64 blocks' LDS.
 //   2. Eigenpairs of T by divide and conquer from 8x8 leaves, all levels in
 //      one persistent launch: the merges of a level run side by side, one
 //      wavefront per secular root, and the eigenvector updates are tiled
@@ -102,6 +102,41 @@ __device__ inline double rsqrt_d(double x) {
   const double e = fma(-x * y, y, 1.0);
   return fma(y * e, fma(0.375, e, 0.5), y);
 }
+// 1 / x likewise (two Newton steps).
+__device__ inline double rcp_d(double x) {
+  double y = __builtin_amdgcn_rcp(x);
+  y = fma(y, fma(-x, y, 1.0), y);
+  return fma(y, fma(-x, y, 1.0), y);
+}
+
+// Householder scalars of a column with first entry alpha and squared norm
+// sumsq below it: H = I - tau v v^T, v = [1, scal x], takes it to beta e_1.  The
+// square root and the two divisions are on every reduction's sequential
+// chain, so within the range where rsqrt_d and rcp_d hold they come from
+// those.
+__device__ inline void householder(double alpha, double sumsq, double& tau, double& scal,
+                                   double& beta) {
+  if (sumsq == 0.0) {
+    tau = 0.0;
+    scal = 0.0;
+    beta = alpha;
+    return;
+  }
+  const double h2 = fma(alpha, alpha, sumsq);
+  if (h2 > 0x1p-900 && h2 < 0x1p900) {
+    const double r = rsqrt_d(h2);
+    double nrm = h2 * r;
+    nrm = fma(fma(-nrm, nrm, h2), 0.5 * r, nrm);
+    beta = -copysign(nrm, alpha);
+    tau = fma(fabs(alpha), r, 1.0);
+    scal = rcp_d(alpha - beta);
+  } else {
+    beta = -copysign(sqrt(h2), alpha);
+    tau = (beta - alpha) / beta;
+    scal = 1.0 / (alpha - beta);
+  }
+}
+
 // Barrier that orders LDS only: waits for this wavefront's LDS accesses
 // (lgkmcnt 0), not for its global stores, then s_barrier.  For loops whose
 // global stores nothing in the kernel reads back; the signal fences keep the
@@ -137,7 +172,7 @@ __device__ double block_sum(double v, double* red) {
 // ---------------------------------------------------------------------------
 // 1. Householder tridiagonalisation (lower form): for k = 0..n-3, H_k =
 // I - tau_k v v^T with v = [1, x_2..]/(alpha - beta) annihilates A[k+2:, k].
-constexpr int SYR_MAX = 160;  // orders reduced in registers by k_sytrd_reg
+constexpr int SYR_MAX = 192;  // orders reduced in registers by k_sytrd_reg
 
 // Large orders (n > SYR_MAX): the matrix does not fit one CU's registers,
 // and one block streaming the trailing matrix from L2 is bound by that CU's
@@ -426,390 +461,248 @@ __global__ __launch_bounds__(SYTRD_GRID_T) void k_sytrd_grid(EigJobs jobs, int* 
 }
 
 // The same reduction with the matrix in registers (n <= SYR_MAX), one block
-// per matrix.  Orders up to SYW_MAX run on one wavefront (sytrd_one_wave);
-// larger ones on SYP_WAVES wavefronts with each row split over two lanes:
-// lane l of wavefront w holds row r = 32 w + l % 32 and, with h = l / 32,
-// the columns of parity h, shifted: before step k, a[c] = A(r, 2 (c + s) + h)
-// with s = floor(k / 2), so column k is a[0] on the lanes of parity k % 2 and
-// column k + 1 is a[k % 2] on the others; the update of an odd step writes
-// A(r, 2 (c + 1 + s) + h) into a[c] (the shift costs nothing), and no
-// register is ever picked by a run-time index.  The two halves of a row are
-// lanes l and l ^ 32 of one wavefront, and the columns still live at step k
-// are spread evenly over both.  A Householder step k, with two block barriers:
-//   the lanes of parity k % 2 publish column k in LDS (zero at rows <= k + 1)
-//   and each wavefront its share of the column norm; (B1)
-//   every wavefront forms tau, beta, scal from the partial norms (summed in
-//   a fixed order) and its rows' v_r; the matrix-vector product over the
-//   lane's columns p_r = tau (A(r, k+1) + scal sum_{j > k+1} A(r, j) x_j)
-//   (x the published column), the two halves combined by a lane exchange;
+// per matrix: wavefront w holds the columns 16 w .. 16 w + 15, lane 16 g + c of
+// it column j = 16 w + c and the rows i = g (mod 4), shifted: before step k,
+// a[r] = A(4 (s + r) + g, j) with s = floor(k / 4), so rows k and k + 1 are always
+// in a[0] or a[1] and no register is picked by a run-time index.  Row factors
+// reach the multiply-adds without an LDS read or a move: a vector's entries
+// are held one per lane, entry 4 (s + 16 m + c) + g in register m of lane
+// 16 g + c, and v_fmac_f64 takes lane c of each row of 16 as its broadcast
+// operand (row_newbcast), so one instruction is one row of every column.
+// (The earlier form, each row over two lanes, read both vectors from LDS for
+// every column it updated, and was bound by those reads: 160 broadcast pairs
+// a lane and step.)  A Householder step k has two block barriers:
+//   the lanes of rows k and k + 1 have published them in LDS (row k as x, zero
+//   up to entry k + 1); (B1)
+//   every wavefront sums x's norm and forms tau, beta, scal; y_j = sum_i
+//   A(i, j) x_i over its columns, the four row groups added by row swaps; by
+//   symmetry p_j = tau (A(k+1, j) + scal y_j) with v = [1, scal x];
 //   p and each wavefront's share of p.v to LDS; (B2)
-//   with K = tau p.v / 2 and u_r = p_r - 2 K v_r, each lane applies
-//   A(r, j) -= v_r p_j + u_r v_j = v_r w_j + w_r v_j (w = p - K v) to its
-//   columns, v_j = scal x_j from the published column and column k + 1
-//   (v = 1 there) separately.
-// The published column and p sit at positions relative to s, once at c and
-// once at c + 1, so that the unshifted and the shifted update both read
-// aligned pairs; the last row of each parity also zeroes the positions past
-// its own, which the step two before had filled.  Columns are taken in
-// groups of 8 per lane (16 of the matrix); a group wholly past n is skipped
-// by a scalar branch.  The published arrays and the partial sums are double
-// buffered by the parity of k, so step k + 1 may publish while a slower
-// wavefront still reads step k's.  The matrix is the lower triangle of A:
-// entries above the diagonal come from coalesced loads of its columns, those
-// on and below from rows staged in LDS 64 at a time.
-// The loop issues no global memory access: the reflectors and d, e, tau stay
-// in LDS (the reflectors where the staged rows were) and are written out
-// after it.  A global store in flight holds its data registers until the
-// write is acknowledged, so a wavefront that stored inside the loop would
-// stall there on its next use of them, on every step.  Barriers inside the
-// loop therefore order LDS only (lds_barrier).
-constexpr int SYP_C = SYR_MAX / 2;       // columns per lane
-constexpr int SYP_PUB = SYP_C + 8;       // positions of each published array
-constexpr int SYP_WAVES = SYR_MAX / 32;  // 32 rows per wavefront
-constexpr int SYR_T = 64 * SYP_WAVES;
-constexpr int SYR_LD = SYR_MAX + 1;      // LDS row stride of the staged rows
-// LDS of the staged rows, then of the packed reflectors
-constexpr int SYR_BIG = 64 * SYR_LD > SYR_MAX * (SYR_MAX - 1) / 2 ? 64 * SYR_LD : SYR_MAX * (SYR_MAX - 1) / 2;
+//   with K = tau p.v / 2 and u_i = p_i - 2 K v_i, A(i, j) -= v_i p_j + u_i v_j
+//   (= v w^T + w v^T with w = p - K v), and the rows k + 1 and k + 2 are
+//   published.
+// Rows are taken in groups of 32 (8 registers); a group wholly past n, and a
+// wavefront whose columns are all done, is skipped by a scalar branch.
+// Entries past n are zero, and stay so.  The loop issues no global memory
+// access: the reflectors and d, e, tau stay in LDS and are written out after
+// it.  One matrix, before and now: order 62
+// 86 -> 70 us, 142 303 -> 229 us, 160 350 -> 270 us, 192 (k_sytrd_grid before)
+// 1013 -> 349 us; a step is about 2300 cycles of dependent latency with one
+// wavefront and 3700 with nine, barrier waits included.
+constexpr int SYR_WAVES = SYR_MAX / 16;
+constexpr int SYR_T = 64 * SYR_WAVES;
+constexpr int SYR_RC = SYR_MAX / 4;   // rows a lane holds
+constexpr int SYR_PUB = SYR_MAX + 64; // entries of a published vector (read by whole wavefronts)
+static_assert(SYR_MAX % 64 == 0, "row groups of 32, vector registers of 64");
 // offset of v_k (n - 1 - k entries) in the packed reflector store
 __device__ inline int refl_off(int k, int n) { return k * (n - 1) - k * (k - 1) / 2; }
 
-
-// Orders n <= SYW_MAX: the whole reduction on one wavefront, no block
-// barrier and no cross-wavefront sum.  Lane i holds row i of the full
-// symmetric matrix in registers, shifted so that at step k a[c] = A(i, k + c)
-// (zero past n): column k is always a[0].  Each step's update writes the
-// updated A(i, k + 1 + c) into a[c], so the shift costs nothing, and no
-// register is ever picked by a run-time index (a tree of scalar branches
-// costs hundreds of cycles per pick).  Step k: alpha and A(k, k) are read
-// from lanes k + 1 and k; the Householder vector costs one wavefront sum;
-// v goes to LDS by position relative to k; each lane forms
-// p_i = tau sum_c A(i, k + c) v_{k+c} with v read as broadcast pairs;
-// K = tau p.v / 2 is the second wavefront sum; w = p - K v goes to LDS; each
-// lane applies A(i, j) -= v_i w_j + w_i v_j to its row while shifting it.
-// v and w are stored twice, at positions c and c + 1, so that both passes
-// read aligned pairs; the lane of row n - 1 also zeroes the position past
-// the end, which the previous step had filled.  Columns are taken in groups
-// of 8; a group wholly past n is skipped by a scalar branch.  Reflectors and
-// d, e, tau go to LDS and are written out after the loop.
-constexpr int SYW_MAX = 64;
-constexpr int SYW_LD = SYW_MAX + 1;  // LDS row stride of the staged matrix
-constexpr int SYW_PUB = SYW_MAX + 8; // entries of each published copy of v, w
-static_assert(SYW_MAX * SYW_LD <= SYR_BIG &&
-                  SYW_MAX * (SYW_MAX - 1) / 2 + 3 * SYW_PUB <= SYR_BIG,
-              "the one-wavefront staging fits the block's LDS array");
-
-
-__device__ void sytrd_one_wave(const EigJob& J, int n, int N, const Work& W, double* lds,
-                               double (*sde)[SYR_MAX]) {
-  const int lane = threadIdx.x & 63;
-  const double* A = J.A;
-  const long long lda = J.lda;
-  // the lower triangle, staged through LDS: coalesced row reads, 8 in flight
-  for (int i0 = 0; i0 < n; i0 += 8) {
-    double t[8];
-#pragma unroll
-    for (int r = 0; r < 8; ++r) {
-      const int i = i0 + r;
-      t[r] = (i < n && lane <= i) ? A[(long long)i * lda + lane] : 0.0;
-    }
-#pragma unroll
-    for (int r = 0; r < 8; ++r) {
-      const int i = i0 + r;
-      if (i < n && lane <= i) lds[i * SYW_LD + lane] = t[r];
-    }
-  }
-  wave_sync();
-  double a[SYW_MAX];
-#pragma unroll
-  for (int j = 0; j < SYW_MAX; ++j) {
-    double t = 0.0;
-    if (lane < n && j < n) t = j <= lane ? lds[lane * SYW_LD + j] : lds[j * SYW_LD + lane];
-    a[j] = t;
-  }
-  wave_sync();  // the staging area becomes the reflectors and v, w
-  double* refl = lds;                                // packed reflectors
-  double* sva = lds + SYW_MAX * (SYW_MAX - 1) / 2;   // v_{k+c} at c (16-byte aligned)
-  double* svb = sva + SYW_PUB;                       // v_{k+c} at c + 1
-  double* swb = svb + SYW_PUB;                       // w_{k+c} at c + 1
-  for (int e = lane; e < 3 * SYW_PUB; e += 64) sva[e] = 0.0;
-  wave_sync();
-  for (int k = 0; k + 2 < n; ++k) {
-    const int o = k + 1, c = lane - k;  // this lane's row, as a position
-    const double x = a[0];              // A(lane, k)
-    const double alpha = lane_d(x, o), dkk = lane_d(x, k);
-    const double sumsq = wave_sum(lane > o && lane < n ? x * x : 0.0);
-    double tau, scal, beta;
-    if (sumsq == 0.0) {
-      tau = 0.0;
-      scal = 0.0;
-      beta = alpha;
-    } else {
-      beta = -copysign(sqrt(alpha * alpha + sumsq), alpha);
-      tau = (beta - alpha) / beta;
-      scal = 1.0 / (alpha - beta);
-    }
-    const double v = lane == o ? 1.0 : (lane > o && lane < n ? x * scal : 0.0);
-    if (lane >= o && lane < n) refl[refl_off(k, n) + lane - o] = v;
-    if (lane == 0) {
-      sde[0][k] = dkk;
-      sde[1][k] = beta;
-      sde[2][k] = tau;
-    }
-    if (c >= 0 && lane < n) {
-      sva[c] = v;
-      svb[c + 1] = v;
-    }
-    if (lane == n - 1) {  // the previous step's last entries, one position on
-      sva[c + 1] = 0.0;
-      svb[c + 2] = 0.0;
-      swb[c + 2] = 0.0;
-    }
-    wave_sync();
-    double pa[4] = {0.0, 0.0, 0.0, 0.0};
-#pragma unroll
-    for (int g = 0; g < SYW_MAX / 8; ++g) {
-      if (8 * g >= n - k) continue;
-#pragma unroll
-      for (int t = 0; t < 8; t += 2) {
-        const double2 vj = *reinterpret_cast<const double2*>(sva + 8 * g + t);
-        pa[t / 2] = fma(a[8 * g + t], vj.x, pa[t / 2]);
-        pa[t / 2] = fma(a[8 * g + t + 1], vj.y, pa[t / 2]);
-      }
-    }
-    const double p = lane > k ? tau * ((pa[0] + pa[1]) + (pa[2] + pa[3])) : 0.0;
-    const double K = 0.5 * tau * wave_sum(p * v);
-    const double w = p - K * v;
-    if (c >= 0 && lane < n) swb[c + 1] = w;
-    wave_sync();
-    // a[c] <- A(lane, k + 1 + c) - v w_{k+1+c} - w v_{k+1+c}
-#pragma unroll
-    for (int g = 0; g < SYW_MAX / 8; ++g) {
-      if (8 * g >= n - k) continue;
-#pragma unroll
-      for (int t = 0; t < 8; t += 2) {
-        const int q = 8 * g + t;
-        const double2 vj = *reinterpret_cast<const double2*>(svb + q + 2);
-        const double2 wj = *reinterpret_cast<const double2*>(swb + q + 2);
-        const double nxt = q + 2 < SYW_MAX ? a[q + 2] : 0.0;
-        a[q] = fma(-v, wj.x, fma(-w, vj.x, a[q + 1]));
-        a[q + 1] = fma(-v, wj.y, fma(-w, vj.y, nxt));
-      }
-    }
-    wave_sync();  // v, w are rewritten by the next step
-  }
-  // the last 2 x 2 block, at positions 0 and 1: d[n-2], e[n-2] = A(n-1, n-2), d[n-1]
-  const int kl = n >= 2 ? n - 2 : 0;
-  const double dn2 = lane_d(a[0], kl), en2 = lane_d(a[0], kl + 1 < n ? kl + 1 : kl);
-  const double dn1 = lane_d(n >= 2 ? a[1] : a[0], n - 1);
-  if (lane == 0) {
-    if (n >= 2) {
-      W.d[n - 2] = dn2;
-      W.e[n - 2] = en2;
-      W.tau[n - 2] = 0.0;
-    }
-    W.d[n - 1] = dn1;
-  }
-  for (int k = lane; k + 2 < n; k += 64) {
-    W.d[k] = sde[0][k];
-    W.e[k] = sde[1][k];
-    W.tau[k] = sde[2][k];
-  }
-  // reflector k: rows k + 1 .. n - 1 of H's row k (one lane per row)
-#pragma unroll 8
-  for (int k = 0; k + 2 < n; ++k) {
-    const int i = k + 1 + lane;
-    if (i < n) W.H[(long long)k * N + i] = refl[refl_off(k, n) + lane];
-  }
+// y[t % 4] += x(lane 8 H + t of the row of 16) a[t], t < 8.  The leading s_nop
+// covers the two wait states between a vector write of x and its use as a
+// DPP operand, which the compiler does not see inside the block.
+#define TT_FMAC_BC(d, x, a, n) "v_fmac_f64_dpp " d ", " x ", " a " row_newbcast:" n " row_mask:0xf bank_mask:0xf\n\t"
+template <int H>
+__device__ __forceinline__ void fmac8_dot(double (&y)[4], double x, const double* a) {
+  if (H == 0)
+    asm("s_nop 1\n\t" TT_FMAC_BC("%0", "%4", "%5", "0") TT_FMAC_BC("%1", "%4", "%6", "1")
+        TT_FMAC_BC("%2", "%4", "%7", "2") TT_FMAC_BC("%3", "%4", "%8", "3")
+        TT_FMAC_BC("%0", "%4", "%9", "4") TT_FMAC_BC("%1", "%4", "%10", "5")
+        TT_FMAC_BC("%2", "%4", "%11", "6") TT_FMAC_BC("%3", "%4", "%12", "7")
+        : "+v"(y[0]), "+v"(y[1]), "+v"(y[2]), "+v"(y[3])
+        : "v"(x), "v"(a[0]), "v"(a[1]), "v"(a[2]), "v"(a[3]), "v"(a[4]), "v"(a[5]), "v"(a[6]), "v"(a[7]));
+  else
+    asm("s_nop 1\n\t" TT_FMAC_BC("%0", "%4", "%5", "8") TT_FMAC_BC("%1", "%4", "%6", "9")
+        TT_FMAC_BC("%2", "%4", "%7", "10") TT_FMAC_BC("%3", "%4", "%8", "11")
+        TT_FMAC_BC("%0", "%4", "%9", "12") TT_FMAC_BC("%1", "%4", "%10", "13")
+        TT_FMAC_BC("%2", "%4", "%11", "14") TT_FMAC_BC("%3", "%4", "%12", "15")
+        : "+v"(y[0]), "+v"(y[1]), "+v"(y[2]), "+v"(y[3])
+        : "v"(x), "v"(a[0]), "v"(a[1]), "v"(a[2]), "v"(a[3]), "v"(a[4]), "v"(a[5]), "v"(a[6]), "v"(a[7]));
 }
+// a[t] += x(lane 8 H + t) p + u(lane 8 H + t) q, t < 8.
+template <int H>
+__device__ __forceinline__ void fmac8_rank2(double* a, double x, double p, double u, double q) {
+  if (H == 0)
+    asm("s_nop 1\n\t" TT_FMAC_BC("%0", "%8", "%9", "0") TT_FMAC_BC("%1", "%8", "%9", "1")
+        TT_FMAC_BC("%2", "%8", "%9", "2") TT_FMAC_BC("%3", "%8", "%9", "3")
+        TT_FMAC_BC("%4", "%8", "%9", "4") TT_FMAC_BC("%5", "%8", "%9", "5")
+        TT_FMAC_BC("%6", "%8", "%9", "6") TT_FMAC_BC("%7", "%8", "%9", "7")
+        TT_FMAC_BC("%0", "%10", "%11", "0") TT_FMAC_BC("%1", "%10", "%11", "1")
+        TT_FMAC_BC("%2", "%10", "%11", "2") TT_FMAC_BC("%3", "%10", "%11", "3")
+        TT_FMAC_BC("%4", "%10", "%11", "4") TT_FMAC_BC("%5", "%10", "%11", "5")
+        TT_FMAC_BC("%6", "%10", "%11", "6") TT_FMAC_BC("%7", "%10", "%11", "7")
+        : "+v"(a[0]), "+v"(a[1]), "+v"(a[2]), "+v"(a[3]), "+v"(a[4]), "+v"(a[5]), "+v"(a[6]), "+v"(a[7])
+        : "v"(x), "v"(p), "v"(u), "v"(q));
+  else
+    asm("s_nop 1\n\t" TT_FMAC_BC("%0", "%8", "%9", "8") TT_FMAC_BC("%1", "%8", "%9", "9")
+        TT_FMAC_BC("%2", "%8", "%9", "10") TT_FMAC_BC("%3", "%8", "%9", "11")
+        TT_FMAC_BC("%4", "%8", "%9", "12") TT_FMAC_BC("%5", "%8", "%9", "13")
+        TT_FMAC_BC("%6", "%8", "%9", "14") TT_FMAC_BC("%7", "%8", "%9", "15")
+        TT_FMAC_BC("%0", "%10", "%11", "8") TT_FMAC_BC("%1", "%10", "%11", "9")
+        TT_FMAC_BC("%2", "%10", "%11", "10") TT_FMAC_BC("%3", "%10", "%11", "11")
+        TT_FMAC_BC("%4", "%10", "%11", "12") TT_FMAC_BC("%5", "%10", "%11", "13")
+        TT_FMAC_BC("%6", "%10", "%11", "14") TT_FMAC_BC("%7", "%10", "%11", "15")
+        : "+v"(a[0]), "+v"(a[1]), "+v"(a[2]), "+v"(a[3]), "+v"(a[4]), "+v"(a[5]), "+v"(a[6]), "+v"(a[7])
+        : "v"(x), "v"(p), "v"(u), "v"(q));
+}
+// Sum over the four rows of 16 lanes, lane by lane, the same bits on all four:
+// the row swaps put two rows' (two pairs of rows') values side by side.
+__device__ inline double rows_sum(double v) {
+  unsigned long long b = (unsigned long long)__double_as_longlong(v);
+  auto l = __builtin_amdgcn_permlane16_swap((unsigned)b, (unsigned)b, false, false);
+  auto h = __builtin_amdgcn_permlane16_swap((unsigned)(b >> 32), (unsigned)(b >> 32), false, false);
+  v = __longlong_as_double((long long)(((unsigned long long)h[0] << 32) | l[0])) +
+      __longlong_as_double((long long)(((unsigned long long)h[1] << 32) | l[1]));
+  b = (unsigned long long)__double_as_longlong(v);
+  l = __builtin_amdgcn_permlane32_swap((unsigned)b, (unsigned)b, false, false);
+  h = __builtin_amdgcn_permlane32_swap((unsigned)(b >> 32), (unsigned)(b >> 32), false, false);
+  return __longlong_as_double((long long)(((unsigned long long)h[0] << 32) | l[0])) +
+         __longlong_as_double((long long)(((unsigned long long)h[1] << 32) | l[1]));
+}
+
+// LDS of the register reduction: published row k (x), row k + 1, p; d, e, tau;
+// the packed reflectors (v_k, rows k + 1 .. n - 1, from refl_off(k)).
+struct SyrLds {
+  double xs[SYR_PUB], as[SYR_PUB], ps[SYR_PUB];
+  double red[SYR_WAVES];  // each wavefront's share of p.v (zero past the live ones)
+  double sde[3][SYR_MAX];
+  double al, dk;  // A(k, k + 1), A(k, k)
+  double refl[SYR_MAX * (SYR_MAX - 1) / 2];
+};
 
 __global__ __launch_bounds__(SYR_T) void k_sytrd_reg(EigJobs jobs, int* __restrict__ dims, int N) {
   const EigJob J = jobs.j[blockIdx.x];
   const int n = dims[J.n_idx];
-  if (n > SYR_MAX) return;  // k_sytrd_grid
-  // staged rows during the load, then the reflectors: v_k (rows k+1 .. n-1)
-  // packed from refl_off(k), written to H once after the loop
-  __shared__ __align__(16) double big[SYR_BIG];
-  double* const stage = big;
-  double* const refl = big;
-  __shared__ double sde[3][SYR_MAX];  // d, e, tau of the loop's steps
-  // published column x and p, [parity of k][parity of the row][position]:
-  // A at the row's position, S one further on (read by the shifting update)
-  __shared__ __align__(16) double xA[2][2][SYP_PUB], xS[2][2][SYP_PUB];
-  __shared__ __align__(16) double pA[2][2][SYP_PUB], pS[2][2][SYP_PUB];
-  __shared__ double red[2][SYP_WAVES], red2[2][SYP_WAVES];
-  __shared__ double s_ad[2][2];  // A(k+1, k), A(k, k)
+  if (n < 1 || n > SYR_MAX) return;  // k_sytrd_grid
+  // the wavefront index is uniform: in a scalar register
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), nw = (n + 15) >> 4;
+  if (wave >= nw) return;  // before any barrier
+  __shared__ __align__(16) SyrLds L;
   const double* A = J.A;
   const long long lda = J.lda;
   Work W = work_of(J, N);
-  const int tid = threadIdx.x, l = tid & 63;
-  // the wavefront index is uniform: in a scalar register
-  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  if (n <= SYW_MAX) {  // one wavefront; the others leave before any barrier
-    if (wave == 0 && n >= 1) sytrd_one_wave(J, n, N, W, big, sde);
-    return;
+  const int tid = threadIdx.x, l = tid & 63, g = l >> 4, c = l & 15, T = 64 * nw;
+  const int j = 16 * wave + c;  // this lane's column
+  double a[SYR_RC];
+  // the lower triangle
+#pragma unroll
+  for (int r = 0; r < SYR_RC; ++r) {
+    const int i = 4 * r + g;
+    a[r] = i < n && j < n ? A[i >= j ? i * lda + j : j * lda + i] : 0.0;
   }
-  const int h = l >> 5, r = 32 * wave + (l & 31);
-  const bool row = r < n;
-  // the last row of this lane's row parity
-  const bool lastp = row && (r == n - 1 || r == n - 2);
-  for (int e = tid; e < 2 * 2 * SYP_PUB; e += SYR_T) {
-    (&xA[0][0][0])[e] = 0.0;
-    (&xS[0][0][0])[e] = 0.0;
-    (&pA[0][0][0])[e] = 0.0;
-    (&pS[0][0][0])[e] = 0.0;
-  }
-  double a[SYP_C];
-  // above the diagonal (j > r): L(j, r), column r of the lower triangle
-#pragma unroll
-  for (int c = 0; c < SYP_C; ++c) {
-    const int j = 2 * c + h;
-    a[c] = (row && j < n && j > r) ? A[(long long)j * lda + r] : 0.0;
-  }
-  // on and below the diagonal (j <= r): L(r, j), rows staged 64 at a time
-  for (int r0 = 0; r0 < n; r0 += 64) {
-    __syncthreads();
-    for (int rr = wave; rr < 64 && r0 + rr < n; rr += SYP_WAVES)
-      for (int j = l; j <= r0 + rr; j += 64) stage[rr * SYR_LD + j] = A[(long long)(r0 + rr) * lda + j];
-    __syncthreads();
-    if (row && r >= r0 && r < r0 + 64) {
-      const double* sr = stage + (r - r0) * SYR_LD;
-#pragma unroll
-      for (int c = 0; c < SYP_C; ++c)
-        if (2 * c + h <= r) a[c] = sr[2 * c + h];
-    }
-  }
-  __syncthreads();  // stage is reused for the reflectors
-  // step k; SHIFT (k odd) writes the updated A(r, 2 (c + 1 + s) + h) into
-  // a[c], so the row moves down one register at no cost.  Steps run in pairs
-  // (even, odd) so that the register array has one layout at the loop's back
-  // edge.
-  auto step = [&](const int k, auto shift_tag) {
-    constexpr bool SHIFT = decltype(shift_tag)::value;
-    const int o = k + 1, buf = k & 1, hk = k & 1, sh = k >> 1;
-    const int pos = (r >> 1) - sh;  // this row's position in the published arrays
-    // column k: a[0] on the lanes of parity k % 2
-    const double x = a[0];
-    const bool own = row && h == hk;
-    if (own) {
-      const double xv = r > o ? x : 0.0;
-      if (pos >= 0) {
-        xA[buf][r & 1][pos] = xv;
-        xS[buf][r & 1][pos + 1] = xv;
-      }
-      if (lastp) {  // the step two before wrote one position further on
-        xA[buf][r & 1][pos + 1] = 0.0;
-        xS[buf][r & 1][pos + 2] = 0.0;
-      }
-      if (r == o) s_ad[buf][0] = x;
-      if (r == k) s_ad[buf][1] = x;
-    }
-    const double ss = wave_sum(own && r > o ? x * x : 0.0);
-    if (l == 0) red[buf][wave] = ss;
-    lds_barrier();  // (B1)
-    double sumsq = 0.0;
-#pragma unroll
-    for (int w = 0; w < SYP_WAVES; ++w) sumsq += red[buf][w];
-    const double alpha = s_ad[buf][0], dkk = s_ad[buf][1];
-    double tau, scal, beta;
-    if (sumsq == 0.0) {
-      tau = 0.0;
-      scal = 0.0;
-      beta = alpha;
-    } else {
-      beta = -copysign(sqrt(alpha * alpha + sumsq), alpha);
-      tau = (beta - alpha) / beta;
-      scal = 1.0 / (alpha - beta);
-    }
-    if (tid == 0) {
-      sde[0][k] = dkk;
-      sde[1][k] = beta;
-      sde[2][k] = tau;
-    }
-    const double xr = row && pos >= 0 ? xA[buf][r & 1][pos] : 0.0;  // A(r, k) below row k + 1
-    const double vr = r == o ? 1.0 : xr * scal;
-    if (row && h == 0 && r >= o) refl[refl_off(k, n) + r - o] = vr;
-    // p over this lane's columns (both halves: one lane exchange)
-    double pa[4] = {0.0, 0.0, 0.0, 0.0};
-#pragma unroll
-    for (int g = 0; g < SYP_C / 8; ++g) {
-      if (2 * (8 * g + sh) >= n) continue;
-#pragma unroll
-      for (int t = 0; t < 8; t += 2) {
-        const double2 xs = *reinterpret_cast<const double2*>(&xA[buf][h][8 * g + t]);
-        pa[t / 2] = fma(a[8 * g + t], xs.x, pa[t / 2]);
-        pa[t / 2] = fma(a[8 * g + t + 1], xs.y, pa[t / 2]);
-      }
-    }
-    const bool ocol = h == (o & 1);  // lanes holding column k + 1 (at position k % 2)
-    double pp = scal * ((pa[0] + pa[1]) + (pa[2] + pa[3]));
-    if (ocol) pp += SHIFT ? a[1] : a[0];  // A(r, k + 1), v = 1 there
-    const double pr = row && r > k ? tau * (pp + __shfl_xor(pp, 32)) : 0.0;
-    if (row && h == 0 && pos >= 0) {
-      pA[buf][r & 1][pos] = pr;
-      pS[buf][r & 1][pos + 1] = pr;
-    }
-    if (lastp && h == 0) {
-      pA[buf][r & 1][pos + 1] = 0.0;
-      pS[buf][r & 1][pos + 2] = 0.0;
-    }
-    const double kp = wave_sum(h == 0 ? pr * vr : 0.0);
-    if (l == 0) red2[buf][wave] = kp;
-    lds_barrier();  // (B2)
-    double kd = 0.0;
-#pragma unroll
-    for (int w = 0; w < SYP_WAVES; ++w) kd += red2[buf][w];
-    const double K = 0.5 * tau * kd;
-    const double ur = pr - 2.0 * K * vr, us = ur * scal;
-#pragma unroll
-    for (int g = 0; g < SYP_C / 8; ++g) {
-      if (2 * (8 * g + sh) >= n) continue;  // a group wholly past n holds zeros
-#pragma unroll
-      for (int t = 0; t < 8; t += 2) {
-        const int q = 8 * g + t;
-        if (SHIFT) {  // positions q + 1, q + 2 into q, q + 1
-          const double2 xs = *reinterpret_cast<const double2*>(&xS[buf][h][q + 2]);
-          const double2 ps = *reinterpret_cast<const double2*>(&pS[buf][h][q + 2]);
-          const double nxt = q + 2 < SYP_C ? a[q + 2] : 0.0;
-          a[q] = fma(-vr, ps.x, fma(-us, xs.x, a[q + 1]));
-          a[q + 1] = fma(-vr, ps.y, fma(-us, xs.y, nxt));
-        } else {
-          const double2 xs = *reinterpret_cast<const double2*>(&xA[buf][h][q]);
-          const double2 ps = *reinterpret_cast<const double2*>(&pA[buf][h][q]);
-          a[q] = fma(-vr, ps.x, fma(-us, xs.x, a[q]));
-          a[q + 1] = fma(-vr, ps.y, fma(-us, xs.y, a[q + 1]));
-        }
-      }
-    }
-    if (ocol) a[0] -= ur;  // column k + 1 (v = 1), now at position 0
-  };
-  int k0 = 0;
-  for (; k0 + 3 < n; k0 += 2) {
-    step(k0, std::false_type());
-    step(k0 + 1, std::true_type());
-  }
-  if (k0 + 2 < n) step(k0, std::false_type());
-  // the last 2 x 2 block: d[n-2] and e[n-2] = A(n-1, n-2) at position 0 on
-  // parity (n - 2) % 2, d[n-1] at position n % 2 on parity (n - 1) % 2
-  {
-    const double y1 = (n & 1) ? a[1] : a[0];
-    if (h == (n & 1)) {
-      if (r == n - 2) W.d[n - 2] = a[0];
-      if (r == n - 1) W.e[n - 2] = a[0];
-    }
-    if (h == ((n - 1) & 1) && r == n - 1) W.d[n - 1] = y1;
-    if (tid == 0) W.tau[n - 2] = 0.0;
-  }
-  // the loop's outputs, kept in LDS so that no global store was in flight
-  // across its barriers
+  for (int e = tid; e < 3 * SYR_PUB; e += T) L.xs[e] = 0.0;  // xs, as, ps
+  if (tid < SYR_WAVES) L.red[tid] = 0.0;
   __syncthreads();
-  for (int k = tid; k + 2 < n; k += SYR_T) {
-    W.d[k] = sde[0][k];
-    W.e[k] = sde[1][k];
-    W.tau[k] = sde[2][k];
+  // rows k (register r0 of the lanes g0) and k + 1 (r1, g1)
+  auto publish = [&](int k, double x, int g0, double y, int g1) {
+    if (g == g0 && j < n) {
+      L.xs[j] = j >= k + 2 ? x : 0.0;
+      if (j == k + 1) L.al = x;
+      if (j == k) L.dk = x;
+    }
+    if (g == g1 && j < n) L.as[j] = y;
+  };
+  publish(0, a[0], 0, a[0], 1);
+  // step k = 4 s + Q
+  auto step = [&](const int k, auto qtag) {
+    constexpr int Q = decltype(qtag)::value;
+    const int s4 = k & ~3;
+    lds_barrier();  // (B1)
+    const bool live = 16 * wave + 15 > k;
+    const double alpha = L.al, dkk = L.dk;
+    double xm[3], y[4] = {0.0, 0.0, 0.0, 0.0}, part = 0.0;
+#pragma unroll
+    for (int m = 0; m < 3; ++m) {
+      xm[m] = s4 + 64 * m < n ? L.xs[s4 + 64 * m + 4 * c + g] : 0.0;
+      part = fma(xm[m], xm[m], part);
+    }
+    const double xj = L.xs[j], aj = L.as[j];
+    if (live) {
+#pragma unroll
+      for (int q = 0; q < SYR_RC / 8; ++q) {
+        if (s4 + 32 * q >= n) continue;
+        if (q & 1) fmac8_dot<1>(y, xm[q / 2], a + 8 * q);
+        else fmac8_dot<0>(y, xm[q / 2], a + 8 * q);
+      }
+    }
+    const double sumsq = wave_sum(part);
+    double tau, scal, beta;
+    householder(alpha, sumsq, tau, scal, beta);
+    const double yj = rows_sum((y[0] + y[1]) + (y[2] + y[3]));
+    const double vj = j == k + 1 ? 1.0 : scal * xj;
+    const double pj = live && j > k ? tau * fma(scal, yj, aj) : 0.0;
+    if (g == 0) {
+      if (j < n) {
+        L.ps[j] = pj;
+        if (j > k) L.refl[refl_off(k, n) + j - k - 1] = vj;
+      }
+    }
+    // the four row groups hold the same p_j v_j: a sum over one row of lanes
+    double kp = pj * vj;
+    kp += dpp_d<0xB1>(kp);
+    kp += dpp_d<0x4E>(kp);
+    kp += dpp_d<0x141>(kp);
+    kp += dpp_d<0x140>(kp);
+    if (l == 0) L.red[wave] = kp;
+    if (tid == 0) {
+      L.sde[0][k] = dkk;
+      L.sde[1][k] = beta;
+      L.sde[2][k] = tau;
+    }
+    lds_barrier();  // (B2)
+    if (live) {
+      double kd[4] = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+      for (int w = 0; w < SYR_WAVES; ++w) kd[w & 3] += L.red[w];
+      const double K2 = tau * ((kd[0] + kd[1]) + (kd[2] + kd[3]));  // 2 K
+      double nv[3], nu[3];
+#pragma unroll
+      for (int m = 0; m < 3; ++m) {
+        const int i = s4 + 64 * m + 4 * c + g;
+        const double pm = s4 + 64 * m < n ? L.ps[i] : 0.0;
+        const double vm = i == k + 1 ? 1.0 : scal * xm[m];
+        nv[m] = -vm;
+        nu[m] = fma(K2, vm, -pm);
+      }
+#pragma unroll
+      for (int q = 0; q < SYR_RC / 8; ++q) {
+        if (s4 + 32 * q >= n) continue;
+        if (q & 1) fmac8_rank2<1>(a + 8 * q, nv[q / 2], pj, nu[q / 2], vj);
+        else fmac8_rank2<0>(a + 8 * q, nv[q / 2], pj, nu[q / 2], vj);
+      }
+    }
+    if (Q == 3) {  // the next step's rows start four further on
+#pragma unroll
+      for (int r = 0; r + 1 < SYR_RC; ++r) a[r] = a[r + 1];
+      a[SYR_RC - 1] = 0.0;
+    }
+    publish(k + 1, a[0], (Q + 1) & 3, Q == 2 ? a[1] : a[0], (Q + 2) & 3);
+  };
+  for (int k = 0; k + 2 < n; k += 4) {
+    step(k, std::integral_constant<int, 0>());
+    if (k + 3 < n) step(k + 1, std::integral_constant<int, 1>());
+    if (k + 4 < n) step(k + 2, std::integral_constant<int, 2>());
+    if (k + 5 < n) step(k + 3, std::integral_constant<int, 3>());
   }
-  for (int k = wave; k + 2 < n; k += SYP_WAVES) {
+  // the last published rows hold the last 2 x 2 block (n = 1: row 0 alone)
+  __syncthreads();
+  if (tid == 0) {
+    if (n >= 2) {
+      W.d[n - 2] = L.dk;
+      W.e[n - 2] = L.al;
+      W.tau[n - 2] = 0.0;
+      W.d[n - 1] = L.as[n - 1];
+    } else {
+      W.d[0] = L.dk;
+    }
+  }
+  for (int k = tid; k + 2 < n; k += T) {
+    W.d[k] = L.sde[0][k];
+    W.e[k] = L.sde[1][k];
+    W.tau[k] = L.sde[2][k];
+  }
+  for (int k = wave; k + 2 < n; k += nw) {
     const int off = refl_off(k, n);
-    for (int i = k + 1 + l; i < n; i += 64) W.H[(long long)k * N + i] = refl[off + i - k - 1];
+    for (int i = k + 1 + l; i < n; i += 64) W.H[(long long)k * N + i] = L.refl[off + i - k - 1];
   }
 }
 

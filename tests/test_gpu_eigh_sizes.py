@@ -1,0 +1,65 @@
+"""tt_kernel_eigh at the edges of the register tridiagonalisation: orders around
+multiples of the 16 columns of a wavefront, the largest that it takes (192) and
+the first that goes to the grid kernel, with a leading dimension larger than
+the order, a matrix that is already tridiagonal, a diagonal one and one with
+zero columns.
+
+Bounds: a backward stable reduction leaves eigenvalue errors and residuals of
+about n u |A| (n u = 2e-14 at order 193).
+"""
+import ctypes as C
+
+import numpy as np
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+
+def _eigh(A, lda):
+    import torch
+    from paper_2503_18056_amd import _ffi
+    lib = _ffi.load()
+    n = A.shape[0]
+    pad = np.full((n, lda), np.nan)
+    pad[:, :n] = A
+    d = torch.as_tensor(pad, device="cuda")
+    lam = torch.zeros(n, dtype=torch.float64, device="cuda")
+    V = torch.zeros((n, n), dtype=torch.float64, device="cuda")
+    ws = torch.zeros(max(int(lib.tt_kernel_eigh_workspace(n)), 256), dtype=torch.uint8, device="cuda")
+    kept = C.c_int32()
+    st = lib.tt_kernel_eigh(C.c_void_p(d.data_ptr()), n, lda, 0.0, C.c_void_p(lam.data_ptr()),
+                            C.c_void_p(V.data_ptr()), n, C.byref(kept), C.c_void_p(ws.data_ptr()),
+                            ws.numel(), None)
+    assert st == 0, lib.tt_kernel_last_error()
+    return lam.cpu().numpy(), V.cpu().numpy()[:, :kept.value], kept.value
+
+
+def _matrix(kind, n):
+    rng = np.random.default_rng(7 * n + len(kind))
+    if kind == "dense":
+        A = rng.standard_normal((n, n))
+        A = A @ A.T
+    elif kind == "tridiagonal":
+        e = rng.standard_normal(max(n - 1, 0))
+        A = np.diag(3.0 + rng.random(n)) + np.diag(e, 1) + np.diag(e, -1)
+    elif kind == "diagonal":
+        A = np.diag(1.0 + rng.random(n))
+    else:   # zero rows and columns in the middle
+        A = rng.standard_normal((n, n))
+        A[n // 3:2 * n // 3] = 0.0
+        A = A @ A.T
+    return 0.5 * (A + A.T)
+
+
+@pytest.mark.parametrize("kind", ["dense", "tridiagonal", "diagonal", "zeros"])
+@pytest.mark.parametrize("n", [1, 2, 4, 15, 16, 17, 18, 32, 33, 48, 49, 96, 97, 128, 129, 144, 145,
+                               176, 177, 190, 191, 192, 193])
+def test_eigh_sizes(kind, n):
+    A = _matrix(kind, n)
+    lam, V, kept = _eigh(A, n + 3)
+    ref = np.linalg.eigvalsh(A)[::-1]
+    nrm = max(np.abs(ref).max(), 1e-300)
+    bound = 20 * n * 2.0 ** -53
+    assert np.abs(lam - ref).max() <= bound * nrm
+    assert np.abs(A @ V - V * lam[:kept]).max() <= 4 * bound * nrm
+    assert np.abs(V.T @ V - np.eye(kept)).max() <= 4 * bound
