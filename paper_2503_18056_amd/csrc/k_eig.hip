@@ -760,32 +760,25 @@ __device__ void dc_init_job(const EigJob& J, const int* __restrict__ dims, int N
   }
 }
 
-// Leaves of DC_LEAF rows, solved directly: block b holds rows
-// [DC_LEAF b, DC_LEAF (b + 1)) of
+// Leaves of DC_LEAF rows, solved directly: leaf r holds rows
+// [DC_LEAF r, DC_LEAF (r + 1)) of
 // T torn only at its two boundary off-diagonals (its diagonal loses |e| at a
-// torn boundary; inside the block T keeps its off-diagonals).  Each block
-// is diagonalised in LDS by parallel cyclic Jacobi (round-robin pairs, all
-// rotations of a round applied together), its eigenvalues sorted ascending
-// with their vectors, and written where the merges up to blocks of 32
-// would have left them: lam[block] and the diagonal block of Q.  One
-// wavefront per leaf, a lane per entry: with R the round's rotations
-// (R[a][a] = R[b][b] = c, R[a][b] = -s, R[b][a] = s on each pair a < b), a
-// round forms A' = R A R^T and V' = V R^T entry by entry into a second
-// buffer, each entry from the two coefficients of its row's and its
-// column's pair, so a round is one pass between two barriers.
+// torn boundary; inside the leaf T keeps its off-diagonals).  One wavefront
+// runs the implicit QL iteration with Wilkinson's shift on a leaf, all in
+// registers with compile-time indexes: every lane carries the same d and e
+// (scaled by a power of two to a largest entry near 1), lane i row i of the
+// vectors.  An off-diagonal is dropped at u / 8 of the leaf's Frobenius norm
+// (the merges above deflate at 8 u ||T|| anyway) or at u of its diagonal
+// neighbours.  The eigenvalues are sorted ascending with their vectors, and
+// written where the merges up to blocks of 8 would have left them:
+// lam[leaf] and the diagonal block of Q.
+// Bound by the latency of the rotations' chain (one reciprocal root and about
+// ten dependent operations each, some 60 rotations a leaf): the leaves of an order-62 job take
+// about 8 us; cyclic Jacobi through LDS, a lane per entry, took 33.
 constexpr int DC_LEAF = 8;
 
-// A wavefront's LDS for one leaf.
-struct LeafLds {
-  double A[2][DC_LEAF][DC_LEAF + 1], V[2][DC_LEAF][DC_LEAF + 1];
-  double al[DC_LEAF], be[DC_LEAF];  // index i: row i of R is al_i e_i + be_i e_pi(i)
-  int pi[DC_LEAF];
-  int ord[DC_LEAF];
-};
-
-
 // Leaf `leaf` of job J, by the calling wavefront (lane = threadIdx.x % 64).
-__device__ void dc_leaf_wave(const EigJob& J, int* __restrict__ dims, int N, int leaf, LeafLds& L) {
+__device__ void dc_leaf_wave(const EigJob& J, int* __restrict__ dims, int N, int leaf) {
   const int n = max(0, dims[J.n_idx]);
   Work W = work_of(J, N);
   DC D = dc_of(W, N);
@@ -793,114 +786,97 @@ __device__ void dc_leaf_wave(const EigJob& J, int* __restrict__ dims, int N, int
   const int r0 = leaf * DC_LEAF;
   if (r0 >= n) return;
   const int nb = min(DC_LEAF, n - r0);
-  const int nbe = nb + (nb & 1);  // even count for the pairing (a decoupled pad)
-  auto& A = L.A;
-  auto& V = L.V;
-  double* s_al = L.al;
-  double* s_be = L.be;
-  int* s_pi = L.pi;
-  int* s_ord = L.ord;
-  const int tid = threadIdx.x & 63, ti = tid / DC_LEAF, tj = tid % DC_LEAF;
-  double a0 = 0.0;
-  if (ti < nb && tj < nb) {
-    const int gi = r0 + ti, gj = r0 + tj;
-    if (ti == tj) {
-      a0 = W.d[gi];
-      if (ti == 0 && gi > 0) a0 -= fabs(W.e[gi - 1]);
-      if (ti == nb - 1 && gi + 1 < n) a0 -= fabs(W.e[gi]);
-    } else if (tj == ti + 1) {
-      a0 = W.e[gi];
-    } else if (ti == tj + 1) {
-      a0 = W.e[gj];
+  const int lane = threadIdx.x & 63, row = lane & (DC_LEAF - 1);
+  // e[k]: off-diagonal (k, k + 1); rows past nb are decoupled zeros
+  double d[DC_LEAF], e[DC_LEAF], v[DC_LEAF];
+#pragma unroll
+  for (int k = 0; k < DC_LEAF; ++k) {
+    d[k] = k < nb ? W.d[r0 + k] : 0.0;
+    e[k] = k < nb && r0 + k + 1 < n ? W.e[r0 + k] : 0.0;
+    v[k] = k == row ? 1.0 : 0.0;
+  }
+  if (r0 > 0) d[0] -= fabs(W.e[r0 - 1]);
+#pragma unroll
+  for (int k = 0; k < DC_LEAF; ++k)
+    if (k == nb - 1) {
+      d[k] -= fabs(e[k]);
+      e[k] = 0.0;
     }
+  double big = 0.0;
+#pragma unroll
+  for (int k = 0; k < DC_LEAF; ++k) big = fmax(big, fmax(fabs(d[k]), fabs(e[k])));
+  const int ex = big > 0.0 && big <= DBL_MAX ? ilogb(big) : 0;
+  double fro = 0.0;
+#pragma unroll
+  for (int k = 0; k < DC_LEAF; ++k) {
+    d[k] = ldexp(d[k], -ex);
+    e[k] = ldexp(e[k], -ex);
+    fro += d[k] * d[k] + 2.0 * e[k] * e[k];
   }
-  A[0][ti][tj] = a0;
-  V[0][ti][tj] = ti == tj ? 1.0 : 0.0;
-  if (tid < DC_LEAF) {
-    s_al[tid] = 1.0;
-    s_be[tid] = 0.0;
-    s_pi[tid] = tid;
-  }
-  const double tiny = U64 * sqrt(wave_sum(a0 * a0));
-  wave_sync();
-  const int npair = nbe / 2, m1 = nbe - 1;
-  int cur = 0;
-  for (int sweep = 0; sweep < 30; ++sweep) {
-    int rot = 0;
-    for (int round = 0; round < m1; ++round) {
-      // round-robin: position 0 fixed, the others rotate
-      if (tid < npair) {
-        const int k = tid;
-        int xa = k - 1 + round, xb = nbe - 2 - k + round;
-        if (xa >= m1) xa -= m1;
-        if (xb >= m1) xb -= m1;
-        int a = k == 0 ? 0 : 1 + xa, b = 1 + xb;
-        if (a > b) { const int t = a; a = b; b = t; }
-        double c = 1.0, sn = 0.0;
-        if (b < nb) {
-          const double apq = A[cur][a][b], app = A[cur][a][a], aqq = A[cur][b][b];
-          // tan(theta) = sign(d) e / (|d| + sqrt(d^2 + e^2)), d = a_qq - a_pp,
-          // e = 2 a_pq; then c = D / q, s = sign(d) e / q with D = |d| + r,
-          // q = sqrt(D^2 + e^2): two square roots and one division, on d and e
-          // scaled by a power of two (exact; c and s do not change)
-          const double dd = aqq - app, ee = 2.0 * apq;
-          const int ex = ilogb(fmax(fabs(dd), fabs(ee)));
-          const double ds = ldexp(dd, -ex), es = ldexp(ee, -ex);
-          const double r = sqrt(ds * ds + es * es);
-          const double Dq = fabs(ds) + r;
-          const double inv = 1.0 / sqrt(Dq * Dq + es * es);
-          // absolute threshold: the merges above deflate at 8 u ||T|| anyway, and a
-          // relative one would chase rounding noise next to near-zero diagonals
-          if (apq != 0.0 && fabs(apq) > 0.125 * tiny && fabs(apq) > U64 * sqrt(fabs(app) * fabs(aqq))) {
-            c = Dq * inv;
-            sn = (dd < 0.0 ? -es : es) * inv;
-            rot = 1;
-          }
+  const double tiny = 0.125 * U64 * sqrt(fro);
+#pragma unroll
+  for (int l = 0; l < DC_LEAF - 1; ++l) {
+    for (int it = 0; it < 40; ++it) {
+      // the unreduced block that starts at l ends at row m; dm = d[m]
+      int m = l;
+      double dm = d[l];
+      bool open = true;
+#pragma unroll
+      for (int k = l; k < DC_LEAF - 1; ++k) {
+        const double ae = fabs(e[k]);
+        if (ae <= tiny || ae <= U64 * (fabs(d[k]) + fabs(d[k + 1]))) {
+          if (open) e[k] = 0.0;
+          open = false;
         }
-        s_al[a] = c;
-        s_be[a] = -sn;
-        s_pi[a] = b;
-        s_al[b] = c;
-        s_be[b] = sn;
-        s_pi[b] = a;
+        if (open) {
+          m = k + 1;
+          dm = d[k + 1];
+        }
       }
-      wave_sync();
-      {
-        const double ai = s_al[ti], bi = s_be[ti], aj = s_al[tj], bj = s_be[tj];
-        const int pi = s_pi[ti], pj = s_pi[tj];
-        const double x00 = A[cur][ti][tj], x01 = A[cur][ti][pj];
-        const double x10 = A[cur][pi][tj], x11 = A[cur][pi][pj];
-        A[cur ^ 1][ti][tj] = ai * (aj * x00 + bj * x01) + bi * (aj * x10 + bj * x11);
-        V[cur ^ 1][ti][tj] = aj * V[cur][ti][tj] + bj * V[cur][ti][pj];
+      if (m == l) break;
+      // shift: the eigenvalue of the leading 2 x 2 nearer d[l]
+      const double del = d[l + 1] - d[l], two = 2.0 * e[l];
+      const double hyp = sqrt(del * del + two * two);
+      double g = dm - d[l] + e[l] * two / (del + copysign(hyp, del));
+      double c = 1.0, s = 1.0, p = 0.0;
+#pragma unroll
+      for (int i = DC_LEAF - 2; i >= l; --i) {
+        if (i < m) {
+          const double f = s * e[i], b = c * e[i];
+          const double h = f * f + g * g;
+          const double rh = h > 1e-280 ? rsqrt_d(h) : 0.0;
+          if (i + 1 < m) e[i + 1] = h * rh;
+          s = f * rh;
+          c = rh > 0.0 ? g * rh : 1.0;
+          const double dn = d[i + 1] - p;
+          const double w = (d[i] - dn) * s + 2.0 * c * b;
+          p = s * w;
+          d[i + 1] = dn + p;
+          g = c * w - b;
+          const double x = v[i + 1], y = v[i];
+          v[i + 1] = s * y + c * x;
+          v[i] = c * y - s * x;
+        }
       }
-      cur ^= 1;
-      wave_sync();
+      d[l] -= p;
+      e[l] = g;
     }
-    if (!__any(rot)) break;
   }
-  // ascending order of the eigenvalues (stable: index breaks ties); the
-  // identity first, so a NaN (flagged below) cannot leave a slot unset
-  if (tid < DC_LEAF) s_ord[tid] = tid < nb ? tid : 0;
-  wave_sync();
-  if (tid < nb) {
-    const double v = A[cur][tid][tid];
+  // ascending (stable: the index breaks ties); a NaN is flagged, its position
+  // stays within the leaf
+  bool bad = !(fro == fro);
+#pragma unroll
+  for (int k = 0; k < DC_LEAF; ++k) {
+    if (k >= nb) continue;
     int pos = 0;
-    for (int j = 0; j < nb; ++j) {
-      const double w = A[cur][j][j];
-      pos += (w < v) || (w == v && j < tid);
-    }
-    s_ord[pos] = tid;
+#pragma unroll
+    for (int j = 0; j < DC_LEAF; ++j)
+      if (j < nb && j != k) pos += d[j] < d[k] || (d[j] == d[k] && j < k);
+    if (lane < nb) D.Qa[(size_t)(r0 + lane) * N2 + r0 + pos] = v[k];
+    if (lane == k) D.lam[r0 + pos] = ldexp(d[k], ex);
+    bad = bad || !(d[k] == d[k]);
   }
-  wave_sync();
-  for (int e = tid; e < nb * nb; e += 64) {
-    const int i = e / nb, c = e % nb;
-    D.Qa[(size_t)(r0 + i) * N2 + r0 + c] = V[cur][i][s_ord[c]];
-  }
-  if (tid < nb) {
-    const double v = A[cur][s_ord[tid]][s_ord[tid]];
-    if (!(v == v)) atomicOr(&dims[D_FLAG], FLAG_EIG);
-    D.lam[r0 + tid] = v;
-  }
+  if (bad && lane == 0) atomicOr(&dims[D_FLAG], FLAG_EIG);
 }
 
 // Dynamic shared-memory bytes per merge element of the sort and deflation
@@ -1538,7 +1514,6 @@ constexpr int DCF_MAXP = 128;
 __global__ __launch_bounds__(256) void k_dc_fused(EigJobs jobs, int njobs, int* __restrict__ dims,
                                                   int N) {
   extern __shared__ double smem[];
-  __shared__ LeafLds leaf_lds[4];
   __shared__ int s_abort;
   const int b = blockIdx.x, P = gridDim.x, wave = threadIdx.x >> 6;
   const GridSync gs = grid_sync_of(jobs.j[0].work, N);
@@ -1557,7 +1532,7 @@ __global__ __launch_bounds__(256) void k_dc_fused(EigJobs jobs, int njobs, int* 
   for (int q = 0; q < njobs; ++q) tot += cnt[q] = (nq[q] + DC_LEAF - 1) / DC_LEAF;
   for (int t = b * 4 + wave; t < tot; t += 4 * P) {
     int q, r;
-    if (dc_item(cnt, njobs, t, q, r)) dc_leaf_wave(jobs.j[q], dims, N, r, leaf_lds[wave]);
+    if (dc_item(cnt, njobs, t, q, r)) dc_leaf_wave(jobs.j[q], dims, N, r);
   }
   for (int S = DC_LEAF, par = 0; S < nmax; S *= 2, par ^= 1) {
     int nm[4] = {0, 0, 0, 0}, tm = 0;
@@ -2719,7 +2694,7 @@ int dc_fused_blocks(int N) { return std::min(DCF_MAXP, std::max(8, (N + 3) / 4))
 // the runtime's own figure is used.
 namespace {
 constexpr size_t LDS_CU = 160 * 1024;
-constexpr size_t ST_SYTRD_GRID = 168, ST_DC_FUSED = 42832, ST_ORMTR = 0, ST_GEBRD_GRID = 168,
+constexpr size_t ST_SYTRD_GRID = 168, ST_DC_FUSED = 32848, ST_ORMTR = 0, ST_GEBRD_GRID = 168,
                  ST_SVD_JACOBI = 148768;
 
 size_t static_lds(const void* fn, size_t table, bool runtime) {

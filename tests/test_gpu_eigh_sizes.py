@@ -1,5 +1,5 @@
 """tt_kernel_eigh at the edges of the register tridiagonalisation: orders around
-multiples of the 16 columns of a wavefront, the largest that it takes (192) and
+multiples of the 8 rows of a leaf and the 16 columns of a wavefront, the largest that it takes (192) and
 the first that goes to the grid kernel, with a leading dimension larger than
 the order, a matrix that is already tridiagonal, a diagonal one and one with
 zero columns.
@@ -52,7 +52,7 @@ def _matrix(kind, n):
 
 
 @pytest.mark.parametrize("kind", ["dense", "tridiagonal", "diagonal", "zeros"])
-@pytest.mark.parametrize("n", [1, 2, 4, 15, 16, 17, 18, 32, 33, 48, 49, 96, 97, 128, 129, 144, 145,
+@pytest.mark.parametrize("n", [1, 2, 4, 6, 7, 8, 9, 15, 16, 17, 18, 32, 33, 48, 49, 96, 97, 128, 129, 144, 145,
                                176, 177, 190, 191, 192, 193])
 def test_eigh_sizes(kind, n):
     A = _matrix(kind, n)
