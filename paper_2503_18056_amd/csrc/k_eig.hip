@@ -7,9 +7,9 @@
 //      sequential dependences): the matrix in one block's registers up to
 //      order 192, above that split by rows over 64 blocks' LDS.
 //   2. Eigenpairs of T by divide and conquer from 8x8 leaves, all levels in
-//      one persistent launch: the merges of a level run side by side, one
-//      wavefront per secular root, and the eigenvector updates are tiled
-//      products, with grid barriers between the phases.
+//      one persistent launch: the merges up to 64 rows on one block each, above
+//      that one wavefront per secular root and products in tiles over the
+//      blocks, with grid barriers between the phases.
 //   3. Back-transformation V = Q Z, one wavefront per kept vector.
 //   4. Descending order, sign gauge (largest |entry| positive), clip rule.
 // The same divide and conquer also serves the small SVD of M (section 5).
@@ -60,7 +60,7 @@ __host__ __device__ inline int next_pow2(int n) {
 // divide and conquer for small N).
 __host__ __device__ inline size_t eig_work_main(int N) {
   const size_t N2 = next_pow2(N);
-  const size_t dc = 3 * N2 * N2 + 17 * N2 + 64;
+  const size_t dc = 2 * N2 * N2 + 17 * N2 + 64;
   const size_t grid = 2 * ((size_t)N + 128 * (size_t)N + 128) + 64;
   return 4 * (size_t)N + (size_t)N * N + N2 + (dc > grid ? dc : grid);
 }
@@ -149,7 +149,7 @@ __device__ inline void lds_barrier() {
 }
 
 // Orders one wavefront's LDS accesses (its lanes' writes before their reads),
-// for code that one wavefront runs alone (the leaves, the order-64 reduction).
+// for code that one wavefront runs alone.
 __device__ inline void wave_sync() {
   __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
   __builtin_amdgcn_wave_barrier();
@@ -708,7 +708,7 @@ __global__ __launch_bounds__(SYR_T) void k_sytrd_reg(EigJobs jobs, int* __restri
 
 // ---------------------------------------------------------------------------
 // 2. Tridiagonal eigenproblem by divide and conquer (Cuppen), bottom-up from
-// 1x1 leaves.  T is torn at every off-diagonal e_m into blocks coupled by
+// leaves of 8 rows.  T is torn at every off-diagonal e_m into blocks coupled by
 // rank-one terms |e_m| w w^T, w = e_m + sign(e_m) e_{m+1}; each merge of two
 // solved halves solves  D + rho z z^T  (z = last row of Q_left, sign-scaled
 // first row of Q_right).  Deflation removes tiny z_j and near-equal d_j
@@ -718,46 +718,21 @@ __global__ __launch_bounds__(SYR_T) void k_sytrd_reg(EigJobs jobs, int* __restri
 // use the Loewner-recomputed z^ so that they are orthogonal to working
 // accuracy.  Vector updates Q <- Q_rot U are tiled products (dc_merge_tile).
 struct DC {
-  double *lam, *Qa, *Qb, *U, *dsl, *zsl, *rc, *rs, *rtau, *zhat, *dK, *zK, *mrho;
-  int *perm, *Kslot, *rp, *rq, *ro, *mk, *mnrot, *mm2;
+  double *lam, *Qa, *Qb, *dsl, *dro, *rc, *rs, *rtau, *zhat, *dK, *zK, *mrho;
+  int *perm, *Kslot, *rp, *rq, *mk, *mnrot, *mm2;
 };
 __device__ inline DC dc_of(const Work& W, int N) {
   const int N2 = next_pow2(N);
   DC D;
-  double* p = W.Z;  // the D&C area starts where the inverse-iteration area was
+  double* p = W.Z;
   D.lam = p; p += N2;
   D.Qa = p; p += (size_t)N2 * N2;
   D.Qb = p; p += (size_t)N2 * N2;
-  D.U = p; p += (size_t)N2 * N2;
-  double** dv[] = {&D.dsl, &D.zsl, &D.rc, &D.rs, &D.rtau, &D.zhat, &D.dK, &D.zK, &D.mrho};
+  double** dv[] = {&D.dsl, &D.dro, &D.rc, &D.rs, &D.rtau, &D.zhat, &D.dK, &D.zK, &D.mrho};
   for (double** q : dv) { *q = p; p += N2; }
-  int** iv[] = {&D.perm, &D.Kslot, &D.rp, &D.rq, &D.ro, &D.mk, &D.mnrot, &D.mm2};
+  int** iv[] = {&D.perm, &D.Kslot, &D.rp, &D.rq, &D.mk, &D.mnrot, &D.mm2};
   for (int** q : iv) { *q = reinterpret_cast<int*>(p); p += N2; }
   return D;
-}
-
-// Q = I (both buffers' live blocks) and the torn diagonal, over blocks b of P.
-__device__ void dc_init_job(const EigJob& J, const int* __restrict__ dims, int N, int b, int P) {
-  const int n = max(0, dims[J.n_idx]);  // -1: an SVD solved by k_svd_jacobi
-  Work W = work_of(J, N);
-  DC D = dc_of(W, N);
-  const int N2 = next_pow2(N);
-  // only the live n x n block of Q is ever read
-  const long long tot = (long long)n * n;
-  for (long long e = b * 256LL + threadIdx.x; e < tot; e += (long long)P * 256) {
-    const int i = (int)(e / n), j = (int)(e % n);
-    D.Qa[(size_t)i * N2 + j] = i == j ? 1.0 : 0.0;
-    D.Qb[(size_t)i * N2 + j] = 0.0;
-  }
-  for (int i = b * 256 + threadIdx.x; i < N2; i += P * 256) {
-    double v = 0.0;
-    if (i < n) {
-      v = W.d[i];
-      if (i > 0) v -= fabs(W.e[i - 1]);
-      if (i + 1 < n) v -= fabs(W.e[i]);
-    }
-    D.lam[i] = v;
-  }
 }
 
 // Leaves of DC_LEAF rows, solved directly: leaf r holds rows
@@ -777,8 +752,10 @@ __device__ void dc_init_job(const EigJob& J, const int* __restrict__ dims, int N
 // about 8 us; cyclic Jacobi through LDS, a lane per entry, took 33.
 constexpr int DC_LEAF = 8;
 
-// Leaf `leaf` of job J, by the calling wavefront (lane = threadIdx.x % 64).
-__device__ void dc_leaf_wave(const EigJob& J, int* __restrict__ dims, int N, int leaf) {
+// Leaf `leaf` of job J, by the calling wavefront (lane = threadIdx.x % 64), its
+// eigenvalues to lam[0 .. 7].
+__device__ void dc_leaf_wave(const EigJob& J, int* __restrict__ dims, int N, int leaf,
+                             double* lam) {
   const int n = max(0, dims[J.n_idx]);
   Work W = work_of(J, N);
   DC D = dc_of(W, N);
@@ -873,346 +850,196 @@ __device__ void dc_leaf_wave(const EigJob& J, int* __restrict__ dims, int N, int
     for (int j = 0; j < DC_LEAF; ++j)
       if (j < nb && j != k) pos += d[j] < d[k] || (d[j] == d[k] && j < k);
     if (lane < nb) D.Qa[(size_t)(r0 + lane) * N2 + r0 + pos] = v[k];
-    if (lane == k) D.lam[r0 + pos] = ldexp(d[k], ex);
+    if (lane == k) lam[pos] = ldexp(d[k], ex);
     bad = bad || !(d[k] == d[k]);
   }
   if (bad && lane == 0) atomicOr(&dims[D_FLAG], FLAG_EIG);
 }
 
-// Dynamic shared-memory bytes per merge element of the sort and deflation
-// (4 doubles, 2 ints) and of the vectors phase (6 doubles and 4 ints with the
-// permutation and the rotations staged, up to VEC_STAGE_MAX rows; 4 doubles
-// and 1 int above), which also uses 32 KB of fixed arrays (VecLds).
-constexpr int PREP_BYTES_PER = 4 * 8 + 2 * 4;
+// Dynamic LDS of the phases above the one-block merges, per merge element: the sort and
+// deflation (4 doubles, 3 ints); the tiles with the permutation and the
+// rotations staged, up to VEC_STAGE_MAX rows (7 doubles, 6 ints), or not (5
+// doubles, 3 ints), beside their panel.
+constexpr int PREP_BYTES_PER = 4 * 8 + 3 * 4;
 constexpr int VEC_STAGE_MAX = 1024;
-constexpr int VEC_BYTES_STAGED = 6 * 8 + 4 * 4;
-constexpr int VEC_BYTES_GLOBAL = 4 * 8 + 1 * 4;
+constexpr int VEC_BYTES_STAGED = 7 * 8 + 6 * 4;
+constexpr int VEC_BYTES_GLOBAL = 5 * 8 + 3 * 4;
 
-// Sort of two ascending halves and deflation of merge m; one 256-thread
-// block, the merge's arrays staged in LDS.  The halves are merged in
-// parallel (each element's rank in the other half by binary search; ties
-// put the left element first); the deflation sweep, which carries the last
-// kept entry along, runs on one lane over LDS.  The eigenvector blocks of
-// a level live in one of two buffers (par: 0 reads Qa and writes Qb, 1 the
-// reverse); a block with no merge at this level is copied across.
-__device__ void dc_prep_merge(const EigJob& J, int* __restrict__ dims, int N, int S, int par, int m,
-                              double* smem) {
-  const int n = dims[J.n_idx];
-  Work W = work_of(J, N);
-  DC D = dc_of(W, N);
-  const int N2 = next_pow2(N);
-  const double* Qs = par ? D.Qb : D.Qa;
-  double* Qd = par ? D.Qa : D.Qb;
-  const int b0 = m * 2 * S;
-  if (b0 + S >= n) {
-    if (threadIdx.x == 0) D.mk[m] = -1;
-    const int nb = max(0, min(2 * S, n - b0));
-    for (int e = threadIdx.x; e < nb * nb; e += 256) {
-      const size_t o = (size_t)(b0 + e / nb) * N2 + b0 + e % nb;
-      Qd[o] = Qs[o];
-    }
+// Sums and products over groups of L lanes (64: the wavefront; 8: aligned
+// groups, which may be active by themselves), the result on every lane.
+template <int L>
+__device__ inline double grp_sum(double v) {
+  if (L == 64) return wave_sum(v);
+  v += dpp_d<0xB1>(v);   // quad_perm [1, 0, 3, 2]
+  v += dpp_d<0x4E>(v);   // quad_perm [2, 3, 0, 1]
+  v += dpp_d<0x141>(v);  // row_half_mirror
+  if (L == 16) v += dpp_d<0x140>(v);  // row_mirror
+  return v;
+}
+template <int L>
+__device__ inline double grp_prod(double v) {
+  v *= dpp_d<0xB1>(v);
+  v *= dpp_d<0x4E>(v);
+  v *= dpp_d<0x141>(v);
+  if (L == 64) {
+    v *= dpp_d<0x140>(v);
+    v = (lane_d(v, 0) * lane_d(v, 16)) * (lane_d(v, 32) * lane_d(v, 48));
+  }
+  return v;
+}
+
+// The tridiagonal solver's blocks: DC_T threads; the lowest DC_SUB rows' merges stay
+// on one block; above, a merge's products are taken in tiles of DC_RT rows by
+// DC_CT columns, the update matrix in panels of DC_KC rows.
+constexpr int DC_T = 512;
+constexpr int DC_SUB = 64;
+constexpr int DC_RT = 64;
+constexpr int DC_CT = 32;
+constexpr int DC_PLD = DC_CT + 4;  // panel stride: k rows 4 apart fall on other banks
+constexpr int DC_ZSPLIT = 256;     // S from which z^ is a phase of its own
+template <bool STAGE> constexpr int dc_kc() { return STAGE ? 256 : 128; }
+
+// One root of the secular equation f(tau) = 1 + rho sum_j z_j^2 / (delta_j - tau)
+// (delta_j = d_j - d_o, o the nearer end of the root's interval), by a group
+// of L lanes (`lane` within it), d and z in LDS.  f is increasing between the
+// poles delta_i < tau < delta_{i+1}; the root is kept in a bracket [lo, hi]
+// with f(lo) < 0 < f(hi).  Each iteration replaces the terms up to pole
+// `split`, psi, and those after it, phi, each by a / (delta - t) + b matching
+// value and slope at the current iterate at their nearest pole (the two-pole
+// rational model of Bunch, Nielsen and Sorensen, 1978); the model's root in
+// the bracket is the next iterate (bisection when it falls outside).  The
+// first iterate is the interval's middle, whose sign picks the origin, and
+// its model keeps the exact weights of both neighbours.  When an iteration
+// leaves f's sign unchanged and reduces |f| by less than 10x, the next step
+// swaps to the fixed-weight model (exact weight on the origin pole, fitted weight on the
+// other neighbour), and back, as LAPACK's dlaed4 does between its middle-way
+// and fixed-weight steps (Li, 1993).  Stops when |f| is at the level of its
+// evaluation error, 8u (1 + rho sum |terms|), or at a relative change of 2u.
+// Bound by the chain of an iteration (pole sums, their reduction, the model's
+// square root and division, some 700 cycles), so the number of iterations
+// counts: starting from the middle's exact-weight model takes about 4
+// evaluations, where both bracket ends were evaluated first and the first
+// iterate was their geometric mean it took 8.
+template <int L>
+__device__ inline void dc_root(const double* d, const double* z, int nk, int i, double rho,
+                               int lane, double& tau_out, double& dor_out, bool& ok) {
+  if (nk == 1) {
+    tau_out = rho * z[0] * z[0];
+    dor_out = d[0];
+    ok = tau_out == tau_out && tau_out != 0.0;
     return;
   }
-  const int nL = S, nR = min(S, n - b0 - S), m2 = nL + nR;
-  double* dt = smem;            // original local order
-  double* zt = dt + 2 * S;
-  double* ds = zt + 2 * S;      // sorted
-  double* zs = ds + 2 * S;
-  int* perm = reinterpret_cast<int*>(zs + 2 * S);
-  int* defl = perm + 2 * S;
-  __shared__ double red[4];
-  const int tid = threadIdx.x;
-  const double beta = W.e[b0 + S - 1];
-  const double sgn = beta < 0.0 ? -1.0 : 1.0;
-  double part = 0.0, pmax = 0.0;
-  for (int c = tid; c < m2; c += 256) {
-    const double zq = c < nL ? Qs[(size_t)(b0 + S - 1) * N2 + b0 + c]
-                             : sgn * Qs[(size_t)(b0 + S) * N2 + b0 + c];
-    const double dv = D.lam[b0 + c];
-    zt[c] = zq;
-    dt[c] = dv;
-    part += zq * zq;
-    pmax = fmax(pmax, fabs(dv));
-  }
-  const double nz2 = block_sum<256>(part, red);
-  for (int o = 32; o > 0; o >>= 1) pmax = fmax(pmax, __shfl_xor(pmax, o));
-  __syncthreads();
-  if ((tid & 63) == 0) red[tid >> 6] = pmax;
-  __syncthreads();
-  const double dmax = fmax(fmax(red[0], red[1]), fmax(red[2], red[3]));
-  const double nz = sqrt(nz2);
-  const double rho = fabs(beta) * nz2;
-  // parallel merge by ranks
-  for (int c = tid; c < m2; c += 256) {
-    const double x = dt[c];
-    int pos;
-    if (c < nL) {  // count right entries strictly below x
-      int lo = 0, hi = nR;
-      while (lo < hi) {
-        const int mid = (lo + hi) >> 1;
-        if (dt[nL + mid] < x) lo = mid + 1;
-        else hi = mid;
-      }
-      pos = c + lo;
-    } else {       // count left entries at or below x
-      int lo = 0, hi = nL;
-      while (lo < hi) {
-        const int mid = (lo + hi) >> 1;
-        if (dt[mid] <= x) lo = mid + 1;
-        else hi = mid;
-      }
-      pos = (c - nL) + lo;
-    }
-    perm[pos] = c;
-    ds[pos] = x;
-    zs[pos] = nz > 0.0 ? zt[c] / nz : 0.0;  // rows of orthogonal blocks: nz^2 = 2
-  }
-  __syncthreads();
-  const double tol = 8.0 * U64 * fmax(dmax, rho);
-  if (tid == 0) {
-    int nrot = 0, p = -1;
-    double dp = 0.0, zp = 0.0;  // current values of entry p
-    for (int s0 = 0; s0 < m2; s0 += 8) {
-      double dd[8], zz[8];
-#pragma unroll
-      for (int t = 0; t < 8; ++t) {
-        dd[t] = s0 + t < m2 ? ds[s0 + t] : 0.0;
-        zz[t] = s0 + t < m2 ? zs[s0 + t] : 0.0;
-      }
-#pragma unroll
-      for (int t = 0; t < 8; ++t) {
-        const int sI = s0 + t;
-        if (sI >= m2) break;
-        if (rho * fabs(zz[t]) <= tol) {
-          defl[sI] = 1;
-          continue;
-        }
-        defl[sI] = 0;
-        double dcur = dd[t], zcur = zz[t];
-        if (p >= 0) {
-          // |t c s| <= tol with c = z_cur / r, s = z_p / r, r^2 = z_p^2 + z_cur^2,
-          // tested without a square root or a division (the z are normalised
-          // and above tol / rho, so r^2 neither overflows nor underflows)
-          const double tt = dcur - dp;
-          const double r2 = zp * zp + zcur * zcur;
-          if (fabs(tt * zcur * zp) <= tol * r2) {
-            const double r = sqrt(r2);
-            const double ir = 1.0 / r;
-            const double c = zcur * ir, sn = zp * ir;
-            D.rp[b0 + nrot] = p;
-            D.rq[b0 + nrot] = sI;
-            D.rc[b0 + nrot] = c;
-            D.rs[b0 + nrot] = sn;
-            ++nrot;
-            const double dpn = c * c * dp + sn * sn * dcur;
-            const double dqn = sn * sn * dp + c * c * dcur;
-            ds[p] = dpn;
-            zs[p] = 0.0;
-            defl[p] = 1;
-            dcur = dqn;
-            zcur = r;
-            ds[sI] = dcur;
-            zs[sI] = zcur;
-          }
-        }
-        p = sI;
-        dp = dcur;
-        zp = zcur;
-      }
-    }
-    D.mnrot[m] = nrot;
-  }
-  __syncthreads();
-  // K list (non-deflated slots in order) by a block prefix count
-  __shared__ int wcnt[4];
-  __shared__ int s_nk;
-  int base = 0;
-  for (int c0 = 0; c0 < m2; c0 += 256) {
-    const int c = c0 + tid;
-    const int keep = c < m2 && !defl[c];
-    const unsigned long long bal = __ballot(keep);
-    const int lane = tid & 63, wv = tid >> 6;
-    const int before = __popcll(bal & ((1ULL << lane) - 1ULL));
-    if (lane == 0) wcnt[wv] = __popcll(bal);
-    __syncthreads();
-    int off = base;
-    for (int w = 0; w < wv; ++w) off += wcnt[w];
-    if (keep) {
-      const int q = off + before;
-      D.dK[b0 + q] = ds[c];
-      D.zK[b0 + q] = zs[c];
-      D.Kslot[b0 + q] = c;
-    }
-    base += wcnt[0] + wcnt[1] + wcnt[2] + wcnt[3];
-    __syncthreads();
-  }
-  for (int c = tid; c < m2; c += 256) {
-    D.perm[b0 + c] = perm[c];
-    D.dsl[b0 + c] = ds[c];
-    D.zsl[b0 + c] = zs[c];
-  }
-  if (tid == 0) {
-    D.mk[m] = base;
-    D.mrho[m] = rho;
-    D.mm2[m] = m2;
-  }
-}
-
-// Secular function on LDS-staged d and z^2 (the merge's K entries).
-__device__ inline double secular(const double* d, const double* z2, int k, int o, double tau,
-                                 double rho, int lane) {
-  double s = 0.0;
-  const double dor = d[o];
-  for (int j = lane; j < k; j += 64) s += z2[j] / ((d[j] - dor) - tau);
-  return 1.0 + rho * wave_sum(s);
-}
-
-// Roots of the secular equation f(tau) = 1 + rho sum_j z_j^2 / (delta_j - tau)
-// (delta_j = d_j - d_o, o the nearer end of the root's interval), one
-// wavefront per root, the merge's d and z^2 staged in LDS (roots 4 grp ..
-// 4 grp + 3 of merge m on one block).  f is increasing between the poles delta_i < tau < delta_{i+1};
-// the root is kept in a bracket [lo, hi] with f(lo) < 0 < f(hi).  Each
-// iteration fits the two-pole rational model of Bunch, Nielsen and Sorensen
-// (1978): the terms left of the root, psi, and right of it, phi, are each
-// replaced by a / (delta - tau) + b matching value and slope at the current
-// iterate at their nearest pole; the model's root in the bracket is the
-// next iterate (bisection when it falls outside).  When an iteration leaves
-// f's sign unchanged and reduces |f| by less than 10x, the next step swaps to
-// the fixed-weight model (exact weight on the origin pole, fitted weight on
-// the other neighbour), and back, as LAPACK's dlaed4 does between its
-// middle-way and fixed-weight steps (Li, 1993).  Stops when |f| is at the
-// level of its evaluation error, 8u (1 + rho sum |terms|), or at a relative
-// change of 2u.
-__device__ void dc_secular_roots(const EigJob& J, int* __restrict__ dims, int N, int S, int m, int grp,
-                                 double* smem) {
-  const int n = dims[J.n_idx];
-  Work W = work_of(J, N);
-  DC D = dc_of(W, N);
-  const int b0 = m * 2 * S;
-  if (b0 + S >= n) return;
-  const int nk = D.mk[m];
-  if (grp * 4 >= nk) return;
-  double* d = smem;
-  double* z2 = smem + 2 * S;
-  for (int j = threadIdx.x; j < nk; j += 256) {
-    d[j] = D.dK[b0 + j];
-    const double zj = D.zK[b0 + j];
-    z2[j] = zj * zj;
-  }
-  __syncthreads();
-  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-  const int i = grp * 4 + wave;
-  if (i >= nk) return;
-  const double rho = D.mrho[m];
-  int o;
-  double lo, hi;
-  if (i < nk - 1) {
-    const double gap = d[i + 1] - d[i];
-    const double mid = 0.5 * gap;
-    const double g = secular(d, z2, nk, i, mid, rho, lane);
-    // Safe brackets from the secular function itself: for the root on the
-    // origin's right, g(tau) <= 1 + 2 rho / gap - rho z_o^2 / tau, so
-    // tau* >= rho z_o^2 / (1 + 2 rho / gap); symmetrically on the left.
-    if (g >= 0.0) {
-      o = i;
-      hi = mid;
-      lo = 0.5 * rho * z2[o] / (1.0 + 2.0 * rho / gap);
-    } else {
-      o = i + 1;
-      lo = -(gap - mid);
-      hi = -0.5 * rho * z2[o] / fmax(1.0, 2.0 * rho / gap);
-    }
+  const bool inner = i < nk - 1;
+  const int split = inner ? i : nk - 2;
+  const double ds = d[split], dn = d[split + 1];
+  const double ws = rho * z[split] * z[split], wn = rho * z[split + 1] * z[split + 1];
+  const double gap = dn - ds;
+  bool right = !inner;  // the origin is pole split + 1
+  double dor = right ? dn : ds;
+  double lo, hi, x;
+  if (inner) {
+    x = 0.5 * gap;
+    lo = 0.0;
+    hi = x;
   } else {
-    // last root: all other terms are negative, so tau* >= rho z_o^2
-    o = nk - 1;
+    // all other terms are negative, so tau* >= rho z_o^2
+    lo = 0.5 * wn;
     hi = rho;
-    lo = 0.5 * rho * z2[o];
+    x = 0.5 * rho;
   }
-  // an end that underflowed to zero would sit on the origin's pole
-  if (lo == 0.0) lo = hi * 0x1p-60;
-  if (hi == 0.0) hi = lo * 0x1p-60;
-  const double dor = d[o];
-  // nearest poles left and right of the root, in the shifted variable
-  const double pl = d[i] - dor;
-  const bool has_right = i < nk - 1;
-  const double pr = has_right ? d[i + 1] - dor : 0.0;
-  double tau = 0.0;
-  bool done = false;
-  {
-    // the bracket ends themselves may already be the root to working accuracy
-    const double glo = secular(d, z2, nk, o, lo, rho, lane);
-    const double ghi = secular(d, z2, nk, o, hi, rho, lane);
-    if (glo >= 0.0) { tau = lo; done = true; }
-    else if (ghi <= 0.0) { tau = hi; done = true; }
-  }
-  double x = (lo > 0.0 && hi > 4.0 * lo) ? sqrt(lo) * sqrt(hi)
-           : (hi < 0.0 && lo < 4.0 * hi) ? -sqrt(-lo) * sqrt(-hi) : 0.5 * (lo + hi);
+  double pl = ds - dor, pr = dn - dor;
+  double tau = 0.0, fprev = 0.0;
   bool fw = false;
-  double fprev = 0.0;
-  for (int it = 0; it < 100 && !done; ++it) {
+  for (int it = 0; it < 100; ++it) {
     // psi, psi', phi, phi' at x
     double ps = 0.0, dps = 0.0, ph = 0.0, dph = 0.0;
-    for (int j = lane; j < nk; j += 64) {
-      const double r = 1.0 / ((d[j] - dor) - x);
-      const double t = z2[j] * r;
-      if (j <= i) { ps += t; dps += t * r; }
-      else { ph += t; dph += t * r; }
+    for (int j = lane; j < nk; j += L) {
+      const double r = rcp_d((d[j] - dor) - x);
+      const double zj = z[j];
+      const double t = zj * zj * r;
+      if (j <= split) {
+        ps += t;
+        dps = fma(t, r, dps);
+      } else {
+        ph += t;
+        dph = fma(t, r, dph);
+      }
     }
-    ps = wave_sum(ps);
-    dps = wave_sum(dps);
-    ph = wave_sum(ph);
-    dph = wave_sum(dph);
+    ps = grp_sum<L>(ps);
+    dps = grp_sum<L>(dps);
+    ph = grp_sum<L>(ph);
+    dph = grp_sum<L>(dph);
     const double f = 1.0 + rho * (ps + ph);
+    if (it == 0 && inner) {
+      // Safe brackets from the secular function itself: for the root on the
+      // origin's right, f(tau) <= 1 + 2 rho / gap - rho z_o^2 / tau, so
+      // tau* >= rho z_o^2 / (1 + 2 rho / gap); symmetrically on the left.
+      if (f >= 0.0) {
+        hi = x;
+        lo = 0.5 * ws / (1.0 + 2.0 * rho / gap);
+      } else {
+        right = true;
+        dor = dn;
+        pl = ds - dor;
+        pr = 0.0;
+        x = -(gap - x);
+        lo = x;
+        hi = -0.5 * wn / fmax(1.0, 2.0 * rho / gap);
+      }
+      // an end that underflowed to zero would sit on the origin's pole
+      if (lo == 0.0) lo = hi * 0x1p-60;
+      if (hi == 0.0) hi = lo * 0x1p-60;
+    }
     // converged once f is at the level of its own rounding error
-    if (f == 0.0 || fabs(f) <= 8.0 * U64 * (1.0 + rho * (ph - ps))) { tau = x; break; }
-    if (f < 0.0) lo = x;
-    else hi = x;
+    if (f == 0.0 || fabs(f) <= 8.0 * U64 * (1.0 + rho * (fabs(ph) + fabs(ps)))) { tau = x; break; }
+    if (it > 0 || !inner) {
+      if (f < 0.0) lo = x;
+      else hi = x;
+    }
     if (hi - lo <= 4.0 * U64 * fmax(fabs(lo), fabs(hi))) { tau = 0.5 * (lo + hi); break; }
     // when f keeps its sign and falls by less than a factor of 10, the
     // other model takes the next step
-    if (it > 0 && f * fprev > 0.0 && fabs(f) > 0.1 * fabs(fprev)) fw = !fw;
+    if (it > 0 && inner && f * fprev > 0.0 && fabs(f) > 0.1 * fabs(fprev)) fw = !fw;
     fprev = f;
     // model: a0 + al / (pl - t) + ga / (pr - t) = 0
-    double xn;
-    if (has_right) {
-      double al, ga, a0;
-      if (fw) {
-        // fixed weight: the origin pole keeps its exact weight rho z_o^2; the
-        // other neighbouring pole's weight and the constant match f and f'
-        // at x.  It converges where the two-pole fit above does not: a root
-        // next to a pole of tiny weight, beside a heavy pole one step away.
-        const double fp = rho * (dps + dph);
-        const double po = o == i ? pl : pr, pq = o == i ? pr : pl;
-        const double wo = rho * z2[o];
-        const double wq = (fp - wo / ((po - x) * (po - x))) * (pq - x) * (pq - x);
-        a0 = f - wo / (po - x) - wq / (pq - x);
-        al = o == i ? wo : wq;
-        ga = o == i ? wq : wo;
-      } else {
-        al = rho * dps * (pl - x) * (pl - x);
-        a0 = 1.0 + rho * (ps - dps * (pl - x));
-        ga = rho * dph * (pr - x) * (pr - x);
-        a0 += rho * (ph - dph * (pr - x));
-      }
-      // a0 t^2 - b t + c = 0
-      const double b = a0 * (pl + pr) + al + ga;
-      const double c = a0 * pl * pr + al * pr + ga * pl;
-      const double disc = b * b - 4.0 * a0 * c;
-      xn = NAN;
-      if (disc >= 0.0) {
-        const double sq = sqrt(disc);
-        const double qq = b >= 0.0 ? b + sq : b - sq;  // no cancellation
-        const double r1 = qq != 0.0 ? 2.0 * c / qq : NAN;
-        const double r2 = a0 != 0.0 ? qq / (2.0 * a0) : NAN;
-        if (r1 > lo && r1 < hi) xn = r1;
-        else if (r2 > lo && r2 < hi) xn = r2;
-      }
+    const double el = pl - x, er = pr - x;
+    double al, ga, a0;
+    if (it == 0) {
+      al = ws;
+      ga = wn;
+      a0 = f - al / el - ga / er;
+    } else if (fw) {
+      // fixed weight: the origin pole keeps its exact weight rho z_o^2; the
+      // other neighbouring pole's weight and the constant match f and f'
+      // at x.  It converges where the two-pole fit does not: a root next to
+      // a pole of tiny weight, beside a heavy pole one step away.
+      const double fp = rho * (dps + dph);
+      const double eo = right ? er : el, eq = right ? el : er;
+      const double wo = right ? wn : ws;
+      const double wq = (fp - wo / (eo * eo)) * eq * eq;
+      a0 = f - wo / eo - wq / eq;
+      al = right ? wq : wo;
+      ga = right ? wo : wq;
     } else {
-      // a0 + al / (pl - t) = 0  ->  t = pl + al / a0 (phi is empty)
-      const double al = rho * dps * (pl - x) * (pl - x);
-      double a0 = 1.0 + rho * (ps - dps * (pl - x));
-      a0 += rho * ph;
-      xn = a0 != 0.0 ? pl + al / a0 : NAN;
+      al = rho * dps * el * el;
+      ga = rho * dph * er * er;
+      a0 = 1.0 + rho * (ps - dps * el) + rho * (ph - dph * er);
+    }
+    // a0 t^2 - b t + c = 0
+    const double b = a0 * (pl + pr) + al + ga;
+    const double c = a0 * pl * pr + al * pr + ga * pl;
+    const double disc = b * b - 4.0 * a0 * c;
+    double xn = NAN;
+    if (disc >= 0.0) {
+      const double sq = sqrt(disc);
+      const double qq = b >= 0.0 ? b + sq : b - sq;  // no cancellation
+      const double r1 = qq != 0.0 ? 2.0 * c / qq : NAN;
+      if (r1 > lo && r1 < hi) {
+        xn = r1;
+      } else {
+        const double r2 = a0 != 0.0 ? qq / (2.0 * a0) : NAN;
+        if (r2 > lo && r2 < hi) xn = r2;
+      }
     }
     if (!(xn > lo && xn < hi)) {
       xn = (lo > 0.0 && hi > 4.0 * lo) ? sqrt(lo) * sqrt(hi)
@@ -1223,262 +1050,802 @@ __device__ void dc_secular_roots(const EigJob& J, int* __restrict__ dims, int N,
     x = xn;
     tau = x;
   }
-  if (lane == 0) {
-    if (!(tau == tau) || tau == 0.0) {
-      atomicOr(&dims[D_FLAG], FLAG_EIG);
-      tau = o == i ? hi : lo;
+  ok = tau == tau && tau != 0.0;
+  if (!ok) tau = right ? lo : hi;
+  tau_out = tau;
+  dor_out = dor;
+}
+
+// Loewner weight z^_j over a group of L lanes: the product over the roots of
+// (d_j - lambda_i) / (d_j - d_i), so that the vectors formed with it are
+// orthogonal to working accuracy whatever the roots' own errors.
+template <int L>
+__device__ inline double dc_zhat(const double* d, const double* dro, const double* rt, double zj,
+                                 int nk, int j, double rho, int lane) {
+  const double dj = d[j];
+  double prod = 1.0;
+  for (int i = lane; i < nk; i += L) {
+    const double num = (dj - dro[i]) - rt[i];
+    prod *= i != j ? num * rcp_d(dj - d[i]) : -num / rho;
+  }
+  return copysign(sqrt(fmax(grp_prod<L>(prod), 0.0)), zj);
+}
+
+// The deflating rotation of kept entries p < q, if they are near enough: |t c s|
+// <= tol with c = z_q / r, s = z_p / r, r^2 = z_p^2 + z_q^2, tested without a square root
+// or a division (the z are normalised and above tol / rho, so r^2 neither
+// overflows nor underflows).
+__device__ inline bool dc_near(double dp, double zp, double dq, double zq, double tol) {
+  return fabs((dq - dp) * zq * zp) <= tol * (zp * zp + zq * zq);
+}
+
+// The U entry (before any rotation) of the column of root (di, ti) at pole j.
+__device__ inline double dc_uent(double zh, double dj, double di, double ti, double inv) {
+  return zh * rcp_d((dj - di) - ti) * inv;
+}
+
+// The rotations of one column of the update matrix W, by one thread.
+// Rotation t acts on slots p_t < q_t, the q_t strictly increase with t and
+// p_t >= q_{t-1} (the deflation carries its last kept slot along).  Applied
+// last first, rotation t therefore meets slot p_t untouched (its U entry),
+// and slot q_t untouched or as the output of rotation t + 1 on its p side,
+// carried in a register; q_t is final after rotation t, and the carried slot
+// is final once the next rotation does not take it.  u0(s): the U entry at
+// slot s; put(s, v): the final value.
+template <typename U0, typename Put>
+__device__ inline void dc_rotate_column(int nrot, const int* rp, const int* rq, const double* rc,
+                                        const double* rs, U0 u0, Put put) {
+  int crow = -1;
+  double cval = 0.0;
+  for (int t = nrot - 1; t >= 0; --t) {
+    const int p = rp[t], q = rq[t];
+    const double c = rc[t], sn = rs[t];
+    double xq;
+    if (q == crow) {
+      xq = cval;
+    } else {
+      if (crow >= 0) put(crow, cval);
+      xq = u0(q);
     }
-    D.ro[b0 + i] = o;
-    D.rtau[b0 + i] = tau;
+    const double xp = u0(p);
+    put(q, c * xq - sn * xp);
+    crow = p;
+    cval = c * xp + sn * xq;
+  }
+  if (crow >= 0) put(crow, cval);
+}
+
+// LDS of the merges on one block: arrays of the block's DC_SUB rows, a merge's
+// entries at its own rows; the update matrices of a level side by side.
+struct SubLds {
+  double lam[DC_SUB], dt[DC_SUB], d[DC_SUB], z[DC_SUB], rt[DC_SUB], dro[DC_SUB], ds[DC_SUB],
+      zs[DC_SUB], rc[DC_SUB], rs[DC_SUB], rho[DC_SUB / DC_LEAF];
+  double panel[DC_SUB * (DC_SUB + 4)];
+  int perm[DC_SUB], ks[DC_SUB], kix[DC_SUB], tag[DC_SUB], rp[DC_SUB], rq[DC_SUB];
+  int nk[DC_SUB / DC_LEAF], nrot[DC_SUB / DC_LEAF];
+};
+
+// Sort and deflation of a merge of up to 64 entries by one wavefront, a lane per
+// entry (off: the merge's first row in the block's arrays).  The halves are
+// merged by ranks (each element's rank in the other half by binary search;
+// ties put the left element first).  Entries with tiny z deflate; then every
+// neighbouring pair of kept ones is tested at once, and only where a pair
+// is near does the sweep that carries the last kept entry along run.
+__device__ inline void dc_sub_prep(SubLds& L, const double* Qs, int N2, int S, int b0, int off,
+                                   int tm, int m2, double beta, int lane) {
+  const double sgn = beta < 0.0 ? -1.0 : 1.0;
+  const int c = lane;
+  double zq = 0.0, dv = 0.0;
+  if (c < m2) {
+    zq = c < S ? Qs[(size_t)(b0 + S - 1) * N2 + b0 + c] : sgn * Qs[(size_t)(b0 + S) * N2 + b0 + c];
+    dv = L.lam[off + c];
+    L.dt[off + c] = dv;
+    L.tag[off + c] = -1;
+  }
+  const double nz2 = wave_sum(zq * zq);
+  double dmax = fabs(dv);
+  for (int o = 32; o > 0; o >>= 1) dmax = fmax(dmax, __shfl_xor(dmax, o));
+  const double nz = sqrt(nz2);
+  const double rho = fabs(beta) * nz2;
+  const double tol = 8.0 * U64 * fmax(dmax, rho);
+  wave_sync();
+  if (c < m2) {
+    const bool left = c < S;
+    const double* other = L.dt + off + (left ? S : 0);
+    int lo = 0, hi = left ? m2 - S : S;
+    while (lo < hi) {  // entries of the other half before this one
+      const int mid = (lo + hi) >> 1;
+      const double y = other[mid];
+      if (left ? y < dv : y <= dv) lo = mid + 1;
+      else hi = mid;
+    }
+    const int pos = (left ? c : c - S) + lo;
+    L.perm[off + pos] = c;
+    L.ds[off + pos] = dv;
+    L.zs[off + pos] = nz > 0.0 ? zq / nz : 0.0;  // rows of orthogonal blocks: nz^2 = 2
+  }
+  wave_sync();
+  double* ds = L.ds + off;
+  double* zs = L.zs + off;
+  const double dc = c < m2 ? ds[c] : 0.0, zc = c < m2 ? zs[c] : 0.0;
+  const unsigned long long below = (1ULL << c) - 1ULL;
+  unsigned long long km = __ballot(c < m2 && !(rho * fabs(zc) <= tol));
+  const bool kept = (km >> c) & 1ULL;
+  bool near = false;
+  if (kept && (km & below)) {
+    const int p = 63 - __builtin_clzll(km & below);
+    near = dc_near(ds[p], zs[p], dc, zc, tol);
+  }
+  unsigned long long todo = __ballot(near);
+  int nrot = 0;
+  while (todo) {
+    int q = __builtin_ctzll(todo);
+    int p = 63 - __builtin_clzll(km & ((1ULL << q) - 1ULL));
+    double dp = ds[p], zp = zs[p];
+    bool more = true;
+    while (more) {
+      const double dq = ds[q], zz = zs[q];
+      if (!dc_near(dp, zp, dq, zz, tol)) break;
+      const double r = sqrt(zp * zp + zz * zz);
+      const double ir = 1.0 / r;
+      const double cs = zz * ir, sn = zp * ir;
+      const double dqn = sn * sn * dp + cs * cs * dq;
+      if (lane == 0) {
+        L.rp[off + nrot] = p;
+        L.rq[off + nrot] = q;
+        L.rc[off + nrot] = cs;
+        L.rs[off + nrot] = sn;
+        ds[p] = cs * cs * dp + sn * sn * dq;
+        zs[p] = 0.0;
+        ds[q] = dqn;
+        zs[q] = r;
+      }
+      ++nrot;
+      km &= ~(1ULL << p);
+      dp = dqn;
+      zp = r;
+      p = q;
+      const unsigned long long above = q < 63 ? km & ~((2ULL << q) - 1ULL) : 0ULL;
+      more = above != 0ULL;
+      if (more) q = __builtin_ctzll(above);
+    }
+    todo &= q < 63 ? ~((2ULL << q) - 1ULL) : 0ULL;
+  }
+  wave_sync();
+  if (c < m2) {
+    const int k = __popcll(km & below);
+    const bool keep = (km >> c) & 1ULL;
+    if (keep) {
+      L.d[off + k] = ds[c];
+      L.z[off + k] = zs[c];
+      L.ks[off + k] = c;
+    }
+    L.kix[off + c] = keep ? k + 1 : 0;
+  }
+  if (lane == 0) {
+    L.nk[tm] = __popcll(km);
+    L.nrot[tm] = nrot;
+    L.rho[tm] = rho;
   }
 }
 
-// Loewner z^, eigenvectors of D + rho z^ z^^T, sorted output, and the
-// merge's update matrix W = P G U: U (slot rows, output columns) with the
-// deflation's Givens rotations G = G_0 ... G_{r-1} (which act on the slot
-// columns of the merge block) applied to its rows, and the slot-to-local
-// permutation P applied to its rows, so that the new eigenvector block is
-// the old block times W.  A thread owns whole columns of W, so the
-// rotations need no barrier.  Everything the per-column loops read (the K
-// arrays, the permutation, the rotations) is staged in LDS first, so they
-// wait on LDS only; merges of more than VEC_STAGE_MAX rows (the SVD's
-// Golub-Kahan order above 1024) read the permutation and the rotations from
-// global memory instead, to stay within the CU's LDS.
-//
-// The rotations are applied without reading W back.  Rotation t acts on
-// slots p_t < q_t, the q_t strictly increase with t and p_t >= q_{t-1}
-// (the deflation carries its last kept slot along).  Applied last first,
-// rotation t therefore meets slot p_t untouched (its U entry), and slot q_t
-// untouched or as the output of rotation t + 1 on its p side, carried in a
-// register; q_t is final after rotation t, and the carried slot is final
-// once the next rotation does not take it.
-// Fixed LDS of the vectors phase (one allocation for both of its forms):
-// sort keys and tags of up to 2048 outputs, the slot-to-K map.
-struct VecLds {
-  double sv[2048];
-  int st[2048];
-  int kix[2048];
-  int wcnt[4];
-  int bad;
-};
-__device__ inline VecLds& vec_lds() {
-  __shared__ VecLds L;
-  return L;
-}
-
-template <bool STAGE>
-__device__ void dc_vectors_merge(const EigJob& J, int* __restrict__ dims, int N, int S, int m,
-                                 double* smem) {
+// The leaves and the merges S = 8, 16, 32 of rows [DC_SUB sub, DC_SUB (sub + 1)) of
+// job J, all on the calling block: no grid barrier until blocks of 64 are
+// solved.  At level S a merge has 16 S threads, 8 lanes to a root, a pole
+// weight or a column, so every phase of every level is one round over the
+// block; eigenvalues and the merges' arrays stay in LDS, eigenvectors go
+// through L2.  An eigensolve of order 62 fell from 286 to 223 us with it.
+__device__ void dc_subtree(const EigJob& J, int* __restrict__ dims, int N, int sub, SubLds& L) {
   const int n = dims[J.n_idx];
   Work W = work_of(J, N);
   DC D = dc_of(W, N);
-  const int b0 = m * 2 * S;
-  const int S2 = 2 * S;
-  double* Ub = D.U + (size_t)m * S2 * S2;
-  const int tid = threadIdx.x;
-  if (b0 + S >= n) return;  // no merge in this block; its GEMM batch is skipped
-  const int nk = D.mk[m];
-  const int m2 = D.mm2[m];
-  const int nrot = D.mnrot[m];
-  double* d = smem;
-  double* dro = d + S2;
-  double* rt = dro + S2;
-  double* zh = rt + S2;
-  double* rcs_s = zh + S2;        // rotation cosines (staged)
-  double* rsn_s = rcs_s + S2;     // rotation sines (staged)
-  int* ks = reinterpret_cast<int*>(STAGE ? rsn_s + S2 : zh + S2);  // K index -> slot
-  int* pm_s = ks + S2;            // slot -> local row (staged)
-  int* rp_s = pm_s + S2;          // rotation t acts on slots rp[t] < rq[t] (staged)
-  int* rq_s = rp_s + S2;
-  const int* pm = STAGE ? pm_s : D.perm + b0;
-  const int* rp = STAGE ? rp_s : D.rp + b0;
-  const int* rq = STAGE ? rq_s : D.rq + b0;
-  const double* rcs = STAGE ? rcs_s : D.rc + b0;
-  const double* rsn = STAGE ? rsn_s : D.rs + b0;
-  VecLds& L = vec_lds();
-  double* sv = L.sv;
-  int* st = L.st;
-  int* kix = L.kix;  // slot -> K index + 1, 0 for a deflated slot
-  int* wcnt = L.wcnt;
-  int& s_bad = L.bad;
-  if (tid == 0) s_bad = 0;
-  for (long long e = tid; e < (long long)m2 * S2; e += 256) Ub[e] = 0.0;
-  for (int c = tid; c < m2; c += 256) {
-    if (STAGE) pm_s[c] = D.perm[b0 + c];
-    kix[c] = 0;
-  }
-  for (int j = tid; j < nk; j += 256) {
-    d[j] = D.dK[b0 + j];
-    rt[j] = D.rtau[b0 + j];
-    ks[j] = D.Kslot[b0 + j];
-  }
-  if (STAGE)
-    for (int t = tid; t < nrot; t += 256) {
-      rp_s[t] = D.rp[b0 + t];
-      rq_s[t] = D.rq[b0 + t];
-      rcs_s[t] = D.rc[b0 + t];
-      rsn_s[t] = D.rs[b0 + t];
-    }
+  const int N2 = next_pow2(N);
+  const int base = sub * DC_SUB;
+  const int tid = threadIdx.x, lane = tid & 63, l8 = tid & 7;
+  bool bad = false;
+  dc_leaf_wave(J, dims, N, sub * (DC_SUB / DC_LEAF) + (tid >> 6), L.lam + DC_LEAF * (tid >> 6));
   __syncthreads();
-  for (int j = tid; j < nk; j += 256) {
-    dro[j] = d[D.ro[b0 + j]];
-    kix[ks[j]] = j + 1;
-  }
-  __syncthreads();
-  const double rho = D.mrho[m];
-  for (int j = tid; j < nk; j += 256) {
-    const double dj = d[j];
-    double prod = -((dj - dro[j]) - rt[j]) / rho;
-#pragma unroll 4
-    for (int i = 0; i < nk; ++i)
-      if (i != j) prod *= ((dj - dro[i]) - rt[i]) / (dj - d[i]);
-    zh[j] = copysign(sqrt(fmax(prod, 0.0)), D.zK[b0 + j]);
-  }
-  // sort all outputs: roots (tag i) and deflated slots (tag m2 + slot); the
-  // deflated slots enter in slot order, after the roots, by a block prefix
-  // count
-  int base = 0;
-  for (int c0 = 0; c0 < m2; c0 += 256) {
-    const int c = c0 + tid;
-    const int defl = c < m2 && kix[c] == 0;
-    const unsigned long long bal = __ballot(defl);
-    const int lane = tid & 63, wv = tid >> 6;
-    if (lane == 0) wcnt[wv] = __popcll(bal);
+  int par = 0;
+  for (int S = DC_LEAF; S < DC_SUB && S < n; S *= 2, par ^= 1) {
+    const double* Qs = par ? D.Qb : D.Qa;
+    double* Qd = par ? D.Qa : D.Qb;
+    const int w = 2 * S, T = 16 * S;
+    const int tm = tid / T, tt = tid - tm * T, g = tt >> 3;
+    const int off = tm * w, b0 = base + off;
+    const int m2 = max(0, min(w, n - b0));
+    const bool has = b0 + S < n;
+    const int ld = w + 4;
+    double* panel = L.panel + tm * w * ld;
+    if (has && tt < 64) dc_sub_prep(L, Qs, N2, S, b0, off, tm, m2, W.e[b0 + S - 1], lane);
     __syncthreads();
-    int off = base + __popcll(bal & ((1ULL << lane) - 1ULL));
-    for (int w = 0; w < wv; ++w) off += wcnt[w];
-    if (defl) {
-      const double v = D.dsl[b0 + c];
-      if (!(v == v)) s_bad = 1;
-      sv[nk + off] = v == v ? v : DBL_MAX;
-      st[nk + off] = m2 + c;
+    const int nk = has ? L.nk[tm] : 0, nrot = has ? L.nrot[tm] : 0;
+    const double rho = has ? L.rho[tm] : 0.0;
+    const double *d = L.d + off, *ds = L.ds + off;
+    double *z = L.z + off, *rt = L.rt + off, *dro = L.dro + off;
+    if (g < nk) {
+      double tau, dor;
+      bool ok;
+      dc_root<8>(d, z, nk, g, rho, l8, tau, dor, ok);
+      bad = bad || !ok;
+      if (l8 == 0) {
+        rt[g] = tau;
+        dro[g] = dor;
+      }
     }
-    base += wcnt[0] + wcnt[1] + wcnt[2] + wcnt[3];
     __syncthreads();
-  }
-  for (int i = tid; i < nk; i += 256) {
-    const double v = dro[i] + rt[i];
-    if (!(v == v)) s_bad = 1;
-    sv[i] = v == v ? v : DBL_MAX;
-    st[i] = i;
-  }
-  const int P2 = next_pow2(m2);
-  for (int e = m2 + tid; e < P2; e += 256) {
-    sv[e] = DBL_MAX;
-    st[e] = 0x7fffffff;
-  }
-  __syncthreads();
-  // bitonic sort by (value, tag)
-  for (int k2 = 2; k2 <= P2; k2 <<= 1)
-    for (int jj = k2 >> 1; jj > 0; jj >>= 1) {
-      for (int e = tid; e < P2; e += 256) {
-        const int x = e ^ jj;
-        if (x > e) {
-          const bool up = (e & k2) == 0;
-          const bool gt = sv[e] > sv[x] || (sv[e] == sv[x] && st[e] > st[x]);
-          if (gt == up) {
-            const double tv = sv[e]; sv[e] = sv[x]; sv[x] = tv;
-            const int tt2 = st[e]; st[e] = st[x]; st[x] = tt2;
+    // sorted places of the roots (ascending already) and the deflated slots
+    // (by value, then slot; a root before an equal slot), the pole weights
+    // (in place: group j reads and writes its own z), and a clear panel
+    if (g < nk) {
+      const double v = dro[g] + rt[g];
+      int cnt = 0;
+      for (int c = l8; c < m2; c += 8) cnt += L.kix[off + c] == 0 && ds[c] < v;
+      cnt += __builtin_amdgcn_mov_dpp(cnt, 0xB1, 0xf, 0xf, true);
+      cnt += __builtin_amdgcn_mov_dpp(cnt, 0x4E, 0xf, 0xf, true);
+      cnt += __builtin_amdgcn_mov_dpp(cnt, 0x141, 0xf, 0xf, true);
+      bad = bad || !(v == v);
+      const double zh = dc_zhat<8>(d, dro, rt, z[g], nk, g, rho, l8);
+      if (l8 == 0) {
+        L.tag[off + g + cnt] = g;
+        L.lam[off + g + cnt] = v == v ? v : DBL_MAX;
+        z[g] = zh;
+      }
+    }
+    if (has && g < m2 && L.kix[off + g] == 0) {
+      const double v = ds[g];
+      int cnt = 0;
+      for (int c = l8; c < m2; c += 8) {
+        if (L.kix[off + c] == 0) cnt += ds[c] < v || (ds[c] == v && c < g);
+        if (c < nk) cnt += dro[c] + rt[c] <= v;
+      }
+      cnt += __builtin_amdgcn_mov_dpp(cnt, 0xB1, 0xf, 0xf, true);
+      cnt += __builtin_amdgcn_mov_dpp(cnt, 0x4E, 0xf, 0xf, true);
+      cnt += __builtin_amdgcn_mov_dpp(cnt, 0x141, 0xf, 0xf, true);
+      bad = bad || !(v == v);
+      if (l8 == 0) {
+        L.tag[off + cnt] = w + g;
+        L.lam[off + cnt] = v == v ? v : DBL_MAX;
+      }
+    }
+    if (has)
+      for (int e = tt; e < w * ld; e += T) panel[e] = 0.0;
+    __syncthreads();
+    // column g of the update matrix W = P G U: U (slot rows, output columns)
+    // with the deflation's rotations G and the slot-to-row permutation P on
+    // its rows, so that the new eigenvector block is the old one times W
+    {
+      const int tag = has && g < m2 ? L.tag[off + g] : -1;
+      const bool root = tag >= 0 && tag < w;
+      double di = 0.0, ti = 0.0, inv = 0.0;
+      if (has && g < m2 && tag < 0) bad = true;
+      if (root) {
+        di = dro[tag];
+        ti = rt[tag];
+        double nrm = 0.0;
+        for (int j = l8; j < nk; j += 8) {
+          const double u = z[j] * rcp_d((d[j] - di) - ti);
+          nrm = fma(u, u, nrm);
+        }
+        nrm = grp_sum<8>(nrm);
+        if (!(nrm > 0.0) || !(nrm < DBL_MAX)) bad = true;
+        inv = 1.0 / sqrt(nrm);
+        for (int j = l8; j < nk; j += 8)
+          panel[L.perm[off + L.ks[off + j]] * ld + g] = dc_uent(z[j], d[j], di, ti, inv);
+      } else if (tag >= w && l8 == 0) {
+        panel[L.perm[off + tag - w] * ld + g] = 1.0;
+      }
+      wave_sync();
+      if (tag >= 0 && l8 == 0 && nrot > 0)
+        dc_rotate_column(
+            nrot, L.rp + off, L.rq + off, L.rc + off, L.rs + off,
+            [&](int s) -> double {
+              if (!root) return s == tag - w ? 1.0 : 0.0;
+              const int j = L.kix[off + s] - 1;
+              return j < 0 ? 0.0 : dc_uent(z[j], d[j], di, ti, inv);
+            },
+            [&](int s, double v) { panel[L.perm[off + s] * ld + g] = v; });
+    }
+    __syncthreads();
+    // products, a 16 x 16 tile to a wavefront; the old block is block
+    // diagonal (for S = 8 inside a tile: its entries off the halves count as
+    // zero and are not read as anything else)
+    if (has) {
+      const int nt = w / 16, lr = lane & 15, lk = lane >> 4;
+      for (int t = tt >> 6; t < nt * nt; t += T / 64) {
+        const int i0 = 16 * (t / nt), j0 = 16 * (t % nt);
+        const int k0 = S == 8 ? 0 : i0 / S * S, k1 = S == 8 ? 16 : k0 + S;
+        const int row = i0 + lr;
+        const double* Ar = Qs + (size_t)(b0 + row) * N2 + b0;
+        gemm_f64x4 acc = {0.0, 0.0, 0.0, 0.0};
+        for (int k = k0; k < k1; k += 16)
+#pragma unroll
+          for (int u = 0; u < 4; ++u) {
+            const int kk = k + 4 * lk + u;
+            const double a = row < m2 && kk < m2 && (row < S) == (kk < S) ? Ar[kk] : 0.0;
+            acc = __builtin_amdgcn_mfma_f64_16x16x4f64(a, panel[kk * ld + j0 + lr], acc, 0, 0, 0);
           }
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+          const int i = i0 + lk + 4 * r, j = j0 + lr;
+          if (i < m2 && j < m2) Qd[(size_t)(b0 + i) * N2 + b0 + j] = acc[r];
         }
       }
-      __syncthreads();
-    }
-  if (tid == 0 && s_bad) atomicOr(&dims[D_FLAG], FLAG_EIG);
-  for (int pos = tid; pos < m2; pos += 256) {
-    D.lam[b0 + pos] = sv[pos];
-    const int tag = st[pos];
-    double* col = Ub + pos;
-    if (tag < 0 || tag >= 2 * m2) {
-      atomicOr(&dims[D_FLAG], FLAG_EIG);
-      continue;
-    }
-    const bool root = tag < m2;
-    const int dslot = root ? -1 : tag - m2;
-    double di = 0.0, ti = 0.0, inv = 0.0;
-    if (root) {
-      di = dro[tag];
-      ti = rt[tag];
-      double nrm = 0.0;
-#pragma unroll 4
-      for (int j = 0; j < nk; ++j) {
-        const double u = zh[j] / ((d[j] - di) - ti);
-        nrm += u * u;
-      }
-      if (!(nrm > 0.0) || !(nrm < DBL_MAX)) {
-        atomicOr(&dims[D_FLAG], FLAG_EIG);
-        continue;
-      }
-      inv = 1.0 / sqrt(nrm);
-#pragma unroll 4
-      for (int j = 0; j < nk; ++j) col[(size_t)pm[ks[j]] * S2] = zh[j] / ((d[j] - di) - ti) * inv;
     } else {
-      col[(size_t)pm[dslot] * S2] = 1.0;
-    }
-    // U entry of this column at slot s, before any rotation
-    auto u0 = [&](int s) -> double {
-      if (!root) return s == dslot ? 1.0 : 0.0;
-      const int j = kix[s] - 1;
-      return j < 0 ? 0.0 : zh[j] / ((d[j] - di) - ti) * inv;
-    };
-    int crow = -1;
-    double cval = 0.0;
-    for (int t = nrot - 1; t >= 0; --t) {
-      const int p = rp[t], q = rq[t];
-      const double c = rcs[t], sn = rsn[t];
-      double xq;
-      if (q == crow) {
-        xq = cval;
-      } else {
-        if (crow >= 0) col[(size_t)pm[crow] * S2] = cval;
-        xq = u0(q);
+      // no merge in this block: across to the other buffer
+      for (int e = tt; e < m2 * m2; e += T) {
+        const size_t o = (size_t)(b0 + e / m2) * N2 + b0 + e % m2;
+        Qd[o] = Qs[o];
       }
-      const double xp = u0(p);
-      col[(size_t)pm[q] * S2] = c * xq - sn * xp;
-      crow = p;
-      cval = c * xp + sn * xq;
     }
-    if (crow >= 0) col[(size_t)pm[crow] * S2] = cval;
+    __syncthreads();
   }
+  if (tid < DC_SUB && base + tid < n) D.lam[base + tid] = L.lam[tid];
+  if (bad) atomicOr(&dims[D_FLAG], FLAG_EIG);
+  __syncthreads();
 }
 
-// One 64 x 64 tile of a merge product: half h of merge m at level S takes
-// rows [b0 + h S, b0 + h S + mh) of the new eigenvector block as the old
-// block's h-th diagonal block (mh x mh, one solved half) times rows
-// [h S, h S + mh) of the merge's update matrix W (2 S x 2 S, row-major).
-__device__ void dc_merge_tile(const EigJob& J, const int* __restrict__ dims, int N, int S, int par,
-                              int m, int h, int ti, int tj, double* smem) {
-  const int n = dims[J.n_idx];
-  const int b0 = m * 2 * S, lim = n - b0;
-  if (lim <= S) return;  // no merge in this block
-  const int n2 = min(2 * S, lim);
-  const int mh = h == 0 ? S : min(S, lim - S);
-  const int i0 = ti * 64, j0 = tj * 64;
-  if (i0 >= mh || j0 >= n2) return;
+// Sort and deflation of merge m above the one-block levels, by a whole block; d and z
+// of the kept entries stay in LDS (smem, smem + 2 S) for the roots.  Every
+// block that solves roots of the merge does this for itself, from the same
+// inputs in the same order; the one with pub set writes the merge's arrays
+// for the update phase.  As dc_sub_prep: ranks, then all neighbouring
+// pairs of kept entries tested at once; one wavefront runs the carrying sweep
+// where a pair is near, from each near pair on.
+// One lane's sweep over all entries, on one block between two grid barriers,
+// took 18 us of a 142-order job's last two merges each.
+struct PrepLds {
+  double red[DC_T / 64];
+  int wcnt[DC_T / 64];
+  int nrot;
+};
+__device__ void dc_prep_block(const EigJob& J, int N, int n, int S, int par, int m, bool pub,
+                              double* smem, PrepLds& R, int& nk_out, double& rho_out) {
+  Work W = work_of(J, N);
+  DC D = dc_of(W, N);
+  const int N2 = next_pow2(N);
+  const double* Qs = par ? D.Qb : D.Qa;
+  const int b0 = m * 2 * S;
+  const int nR = min(S, n - b0 - S), m2 = S + nR;
+  double* dt = smem;            // original local order; then the kept d
+  double* zt = dt + 2 * S;      // likewise z
+  double* ds = zt + 2 * S;      // sorted
+  double* zs = ds + 2 * S;
+  int* perm = reinterpret_cast<int*>(zs + 2 * S);
+  int* kl = perm + 2 * S;       // kept slots
+  int* fl = kl + 2 * S;         // bit 0: near its predecessor, bit 1: rotated away
+  const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+  const double beta = W.e[b0 + S - 1];
+  const double sgn = beta < 0.0 ? -1.0 : 1.0;
+  double part = 0.0, pmax = 0.0;
+  for (int c = tid; c < m2; c += DC_T) {
+    const double zq = c < S ? Qs[(size_t)(b0 + S - 1) * N2 + b0 + c]
+                            : sgn * Qs[(size_t)(b0 + S) * N2 + b0 + c];
+    const double dv = D.lam[b0 + c];
+    zt[c] = zq;
+    dt[c] = dv;
+    part += zq * zq;
+    pmax = fmax(pmax, fabs(dv));
+  }
+  const double nz2 = block_sum<DC_T>(part, R.red);
+  for (int o = 32; o > 0; o >>= 1) pmax = fmax(pmax, __shfl_xor(pmax, o));
+  __syncthreads();
+  if (lane == 0) R.red[wv] = pmax;
+  __syncthreads();
+  double dmax = 0.0;
+  for (int t = 0; t < DC_T / 64; ++t) dmax = fmax(dmax, R.red[t]);
+  const double nz = sqrt(nz2);
+  const double rho = fabs(beta) * nz2;
+  const double tol = 8.0 * U64 * fmax(dmax, rho);
+  for (int c = tid; c < m2; c += DC_T) {
+    const double x = dt[c];
+    const bool left = c < S;
+    const double* other = dt + (left ? S : 0);
+    int lo = 0, hi = left ? nR : S;
+    while (lo < hi) {
+      const int mid = (lo + hi) >> 1;
+      const double y = other[mid];
+      if (left ? y < x : y <= x) lo = mid + 1;
+      else hi = mid;
+    }
+    const int pos = (left ? c : c - S) + lo;
+    perm[pos] = c;
+    ds[pos] = x;
+    zs[pos] = nz > 0.0 ? zt[c] / nz : 0.0;
+  }
+  __syncthreads();
+  // kept slots in order, by a block prefix count
+  int nk0 = 0;
+  for (int c0 = 0; c0 < m2; c0 += DC_T) {
+    const int c = c0 + tid;
+    const bool keep = c < m2 && !(rho * fabs(zs[c]) <= tol);
+    const unsigned long long bal = __ballot(keep);
+    if (lane == 0) R.wcnt[wv] = __popcll(bal);
+    __syncthreads();
+    int o = nk0 + __popcll(bal & ((1ULL << lane) - 1ULL));
+    for (int t = 0; t < DC_T / 64; ++t) {
+      if (t < wv) o += R.wcnt[t];
+      nk0 += R.wcnt[t];
+    }
+    if (keep) kl[o] = c;
+    __syncthreads();
+  }
+  int any = 0;
+  for (int k = tid; k < nk0; k += DC_T) {
+    const int c = kl[k];
+    int near = 0;
+    if (k > 0) {
+      const int p = kl[k - 1];
+      near = dc_near(ds[p], zs[p], ds[c], zs[c], tol);
+    }
+    fl[k] = near;
+    any |= near;
+  }
+  any = __syncthreads_or(any);
+  int nk = nk0;
+  if (any) {
+    if (wv == 0) {
+      int nrot = 0, q0 = 1;  // pairs (k - 1, k) with k >= q0 hold their first values
+      for (int k0 = 0; k0 < nk0; k0 += 64) {
+        const unsigned long long mask = __ballot(k0 + lane < nk0 && (fl[min(k0 + lane, nk0 - 1)] & 1));
+        while (true) {
+          const int s = q0 - k0;
+          const unsigned long long rest = s >= 64 ? 0ULL : s <= 0 ? mask : mask & ~((1ULL << s) - 1ULL);
+          if (!rest) break;
+          int q = k0 + __builtin_ctzll(rest), p = q - 1;
+          double dp = ds[kl[p]], zp = zs[kl[p]];
+          for (; q < nk0; ++q) {
+            const int sp = kl[p], sq = kl[q];
+            const double dq = ds[sq], zz = zs[sq];
+            if (!dc_near(dp, zp, dq, zz, tol)) break;
+            const double r = sqrt(zp * zp + zz * zz);
+            const double ir = 1.0 / r;
+            const double cs = zz * ir, sn = zp * ir;
+            const double dqn = sn * sn * dp + cs * cs * dq;
+            if (lane == 0) {
+              if (pub) {
+                D.rp[b0 + nrot] = sp;
+                D.rq[b0 + nrot] = sq;
+                D.rc[b0 + nrot] = cs;
+                D.rs[b0 + nrot] = sn;
+              }
+              ds[sp] = cs * cs * dp + sn * sn * dq;
+              zs[sp] = 0.0;
+              fl[p] |= 2;
+              ds[sq] = dqn;
+              zs[sq] = r;
+            }
+            ++nrot;
+            dp = dqn;
+            zp = r;
+            p = q;
+          }
+          q0 = q + 1;
+        }
+      }
+      if (lane == 0) R.nrot = nrot;
+    }
+    __syncthreads();
+    nk = 0;
+    for (int k0 = 0; k0 < nk0; k0 += DC_T) {
+      const int k = k0 + tid;
+      const bool keep = k < nk0 && !(fl[k] & 2);
+      const int c = keep ? kl[k] : 0;
+      const unsigned long long bal = __ballot(keep);
+      if (lane == 0) R.wcnt[wv] = __popcll(bal);
+      __syncthreads();
+      int o = nk + __popcll(bal & ((1ULL << lane) - 1ULL));
+      for (int t = 0; t < DC_T / 64; ++t) {
+        if (t < wv) o += R.wcnt[t];
+        nk += R.wcnt[t];
+      }
+      if (keep) kl[o] = c;  // o <= k: no later round's entry
+      __syncthreads();
+    }
+  }
+  for (int k = tid; k < nk; k += DC_T) {
+    const int c = kl[k];
+    dt[k] = ds[c];
+    zt[k] = zs[c];
+    if (pub) {
+      D.dK[b0 + k] = ds[c];
+      D.zK[b0 + k] = zs[c];
+      D.Kslot[b0 + k] = c;
+    }
+  }
+  if (pub) {
+    for (int c = tid; c < m2; c += DC_T) {
+      D.perm[b0 + c] = perm[c];
+      D.dsl[b0 + c] = ds[c];
+    }
+    if (tid == 0) {
+      D.mk[m] = nk;
+      D.mrho[m] = rho;
+      D.mm2[m] = m2;
+      D.mnrot[m] = any ? R.nrot : 0;
+    }
+  }
+  __syncthreads();
+  nk_out = nk;
+  rho_out = rho;
+}
+
+// The pole weights of 8 poles of merge m, a wavefront each (S >= DC_ZSPLIT:
+// nk^2 quotients are too many for every tile's block to form them all).
+__device__ void dc_zhat_block(const EigJob& J, int N, int n, int S, int m, int grp, double* smem) {
+  Work W = work_of(J, N);
+  DC D = dc_of(W, N);
+  const int b0 = m * 2 * S;
+  if (b0 + S >= n) return;
+  const int nk = D.mk[m];
+  if (grp * 8 >= nk) return;
+  double* d = smem;
+  double* rt = d + 2 * S;
+  double* dro = rt + 2 * S;
+  for (int j = threadIdx.x; j < nk; j += DC_T) {
+    d[j] = D.dK[b0 + j];
+    rt[j] = D.rtau[b0 + j];
+    dro[j] = D.dro[b0 + j];
+  }
+  __syncthreads();
+  const int j = grp * 8 + (threadIdx.x >> 6), lane = threadIdx.x & 63;
+  if (j >= nk) return;
+  const double zh = dc_zhat<64>(d, dro, rt, D.zK[b0 + j], nk, j, D.mrho[m], lane);
+  if (lane == 0) D.zhat[b0 + j] = zh;
+}
+
+// Tile (ti, tj) of half h of merge m: rows [64 ti, 64 ti + 64) of the half by
+// columns [32 tj, 32 tj + 32) of the new eigenvector block, = the half's old
+// block (mh x mh) times the matching rows of the update matrix W (dc_subtree),
+// whose 32 columns this block forms in LDS: the sorted places of the
+// outputs, the column norms, and the entries, panel by panel of KC rows.  A
+// wavefront has a 16 x 16 product tile; lane groups of 16 take 4 consecutive
+// k each (the same permutation of k on both operands), so a row of A is read
+// 128 bytes at a time.  Merges of more than 1024 rows (STAGE false) read the
+// permutation and the rotations from global memory, to stay within the CU's LDS.
+struct TileLds {
+  double di[DC_CT], ti[DC_CT], inv[DC_CT];
+  int tag[DC_CT];
+  int wcnt[DC_T / 64];
+};
+template <bool STAGE>
+__device__ void dc_update_tile(const EigJob& J, int* __restrict__ dims, int N, int n, int S, int par,
+                               int m, int h, int ti, int tj, double* smem, TileLds& R) {
   Work W = work_of(J, N);
   DC D = dc_of(W, N);
   const int N2 = next_pow2(N);
   const double* Qs = par ? D.Qb : D.Qa;
   double* Qd = par ? D.Qa : D.Qb;
-  const int r0 = b0 + h * S;
-  const double* A = Qs + (size_t)r0 * N2 + r0;
-  const double* B = D.U + (size_t)m * 4 * S * S + (size_t)h * S * 2 * S;
-  double* C = Qd + (size_t)r0 * N2 + b0;
-  double(*As)[65] = reinterpret_cast<double(*)[65]>(smem);
-  double(*Bs)[65] = reinterpret_cast<double(*)[65]>(smem + GEMM_GK * 65);
-  double acc[4][4];
-  gemm_tile_acc<0, 0>(acc, A, B, N2, 2 * S, nullptr, i0, j0, mh, n2, mh, As, Bs);
-  const int tx = threadIdx.x & 15, ty = threadIdx.x >> 4;
-#pragma unroll
-  for (int r = 0; r < 4; ++r) {
-    const int i = i0 + ty + 16 * r;
-    if (i >= mh) continue;
-#pragma unroll
-    for (int c = 0; c < 4; ++c) {
-      const int j = j0 + tx + 16 * c;
-      if (j < n2) C[(size_t)i * N2 + j] = acc[r][c];
+  const int b0 = m * 2 * S, S2 = 2 * S, lim = n - b0;
+  const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+  const int i0 = ti * DC_RT, j0 = tj * DC_CT;
+  if (lim <= S) {  // no merge in this block: across to the other buffer
+    if (h == 0)
+      for (int e = tid; e < DC_RT * DC_CT; e += DC_T) {
+        const int i = i0 + e / DC_CT, j = j0 + e % DC_CT;
+        const size_t o = (size_t)(b0 + i) * N2 + b0 + j;
+        if (i < lim && j < lim) Qd[o] = Qs[o];
+      }
+    return;
+  }
+  const int m2 = min(S2, lim);
+  const int mh = h == 0 ? S : m2 - S;
+  if (i0 >= mh || j0 >= m2) return;
+  const int nk = D.mk[m], nrot = D.mnrot[m];
+  const double rho = D.mrho[m];
+  constexpr int KC = dc_kc<STAGE>();
+  double* panel = smem;
+  double* d = panel + KC * DC_PLD;
+  double* zh = d + S2;
+  double* rt = zh + S2;
+  double* dro = rt + S2;
+  double* dval = dro + S2;              // deflated values in slot order
+  double* rc_s = dval + S2;             // staged rotations
+  double* rs_s = rc_s + (STAGE ? S2 : 0);
+  int* ks = reinterpret_cast<int*>(rs_s + (STAGE ? S2 : 0));
+  int* kix = ks + S2;                   // slot -> K index + 1, 0 for a deflated slot
+  int* dslot = kix + S2;
+  int* perm_s = dslot + S2;
+  int* rp_s = perm_s + (STAGE ? S2 : 0);
+  int* rq_s = rp_s + (STAGE ? S2 : 0);
+  const int* perm = STAGE ? perm_s : D.perm + b0;
+  const int* rp = STAGE ? rp_s : D.rp + b0;
+  const int* rq = STAGE ? rq_s : D.rq + b0;
+  const double* rc = STAGE ? rc_s : D.rc + b0;
+  const double* rs = STAGE ? rs_s : D.rs + b0;
+  for (int c = tid; c < m2; c += DC_T) {
+    if (STAGE) perm_s[c] = D.perm[b0 + c];
+    kix[c] = 0;
+  }
+  for (int j = tid; j < nk; j += DC_T) {
+    d[j] = D.dK[b0 + j];
+    rt[j] = D.rtau[b0 + j];
+    dro[j] = D.dro[b0 + j];
+    ks[j] = D.Kslot[b0 + j];
+    zh[j] = S >= DC_ZSPLIT ? D.zhat[b0 + j] : D.zK[b0 + j];
+  }
+  if (STAGE)
+    for (int t = tid; t < nrot; t += DC_T) {
+      rp_s[t] = D.rp[b0 + t];
+      rq_s[t] = D.rq[b0 + t];
+      rc_s[t] = D.rc[b0 + t];
+      rs_s[t] = D.rs[b0 + t];
+    }
+  if (tid < DC_CT) R.tag[tid] = -1;
+  __syncthreads();
+  for (int j = tid; j < nk; j += DC_T) kix[ks[j]] = j + 1;
+  if (S < DC_ZSPLIT)
+    for (int j = tid >> 3; j < nk; j += DC_T / 8) {
+      const double v = dc_zhat<8>(d, dro, rt, zh[j], nk, j, rho, tid & 7);
+      if ((tid & 7) == 0) zh[j] = v;  // read by this group only
+    }
+  __syncthreads();
+  // deflated slots in slot order, by a block prefix count
+  int nd = 0;
+  bool bad = false;
+  for (int c0 = 0; c0 < m2; c0 += DC_T) {
+    const int c = c0 + tid;
+    const bool defl = c < m2 && kix[c] == 0;
+    const unsigned long long bal = __ballot(defl);
+    if (lane == 0) R.wcnt[wv] = __popcll(bal);
+    __syncthreads();
+    int o = nd + __popcll(bal & ((1ULL << lane) - 1ULL));
+    for (int t = 0; t < DC_T / 64; ++t) {
+      if (t < wv) o += R.wcnt[t];
+      nd += R.wcnt[t];
+    }
+    if (defl) {
+      const double v = D.dsl[b0 + c];
+      bad = bad || !(v == v);
+      dval[o] = v == v ? v : DBL_MAX;
+      dslot[o] = c;
+    }
+    __syncthreads();
+  }
+  // Sorted places: the roots ascend; the deflated values nearly do (a rotated
+  // one may pass a neighbour), and where they do not they are counted.  A
+  // root goes before an equal slot.  Each block keeps the places of its own
+  // columns; the first row tile of the left half writes the eigenvalues.
+  int unsorted = 0;
+  for (int k = tid; k + 1 < nd; k += DC_T) unsorted |= dval[k] > dval[k + 1];
+  unsorted = __syncthreads_or(unsorted);
+  auto place = [&](int pos, int tag, double v) {
+    if (pos >= j0 && pos < j0 + DC_CT) {
+      R.tag[pos - j0] = tag;
+      if (h == 0 && ti == 0) D.lam[b0 + pos] = v;
+    }
+  };
+  for (int i = tid; i < nk; i += DC_T) {
+    const double lv = dro[i] + rt[i];
+    bad = bad || !(lv == lv);
+    const double v = lv == lv ? lv : DBL_MAX;
+    int cnt = 0;
+    if (unsorted) {
+      for (int k = 0; k < nd; ++k) cnt += dval[k] < v;
+    } else {
+      int hi = nd;
+      while (cnt < hi) {
+        const int mid = (cnt + hi) >> 1;
+        if (dval[mid] < v) cnt = mid + 1;
+        else hi = mid;
+      }
+    }
+    place(i + cnt, i, v);
+  }
+  for (int k = tid; k < nd; k += DC_T) {
+    const double v = dval[k];
+    int before = k;
+    if (unsorted) {
+      before = 0;
+      for (int t = 0; t < nd; ++t) before += dval[t] < v || (dval[t] == v && t < k);
+    }
+    int cnt = 0, hi = nk;
+    while (cnt < hi) {
+      const int mid = (cnt + hi) >> 1;
+      if (dro[mid] + rt[mid] <= v) cnt = mid + 1;
+      else hi = mid;
+    }
+    place(before + cnt, S2 + dslot[k], v);
+  }
+  __syncthreads();
+  {  // column norms, 16 lanes to a column
+    const int c = tid >> 4, l16 = tid & 15;
+    const int tag = j0 + c < m2 ? R.tag[c] : -1;
+    double di = 0.0, tv = 0.0, inv = 0.0;
+    if (j0 + c < m2 && tag < 0) bad = true;
+    if (tag >= 0 && tag < S2) {
+      di = dro[tag];
+      tv = rt[tag];
+      double nrm = 0.0;
+      for (int j = l16; j < nk; j += 16) {
+        const double u = zh[j] * rcp_d((d[j] - di) - tv);
+        nrm = fma(u, u, nrm);
+      }
+      nrm = grp_sum<16>(nrm);
+      if (!(nrm > 0.0) || !(nrm < DBL_MAX)) bad = true;
+      inv = 1.0 / sqrt(nrm);
+    }
+    if (l16 == 0) {
+      R.di[c] = di;
+      R.ti[c] = tv;
+      R.inv[c] = inv;
     }
   }
+  if (bad) atomicOr(&dims[D_FLAG], FLAG_EIG);
+  const int lr = lane & 15, lk = lane >> 4;
+  const int iw = i0 + 16 * (wv >> 1), jw = 16 * (wv & 1);
+  const bool live = iw < mh && j0 + jw < m2;
+  const int arow = min(iw + lr, mh - 1);
+  const double* Ar = Qs + (size_t)(b0 + h * S + arow) * N2 + b0 + h * S;
+  gemm_f64x4 acc = {0.0, 0.0, 0.0, 0.0};
+  for (int r0 = 0; r0 < mh; r0 += KC) {
+    const int kr = min(KC, mh - r0), kr16 = (kr + 15) & ~15;
+    const int first = h * S + r0;  // local row of the panel's first
+    __syncthreads();
+    for (int e = tid; e < kr16 * DC_PLD; e += DC_T) panel[e] = 0.0;
+    __syncthreads();
+    {
+      const int c = tid & (DC_CT - 1), tag = R.tag[c];
+      if (tag >= 0 && tag < S2) {
+        const double di = R.di[c], tv = R.ti[c], inv = R.inv[c];
+        for (int j = tid / DC_CT; j < nk; j += DC_T / DC_CT) {
+          const int r = perm[ks[j]] - first;
+          if (r >= 0 && r < kr) panel[r * DC_PLD + c] = dc_uent(zh[j], d[j], di, tv, inv);
+        }
+      } else if (tag >= S2 && tid < DC_CT) {
+        const int r = perm[tag - S2] - first;
+        if (r >= 0 && r < kr) panel[r * DC_PLD + c] = 1.0;
+      }
+    }
+    if (nrot > 0) {
+      __syncthreads();
+      if (tid < DC_CT && R.tag[tid] >= 0) {
+        const int tag = R.tag[tid];
+        const bool root = tag < S2;
+        const double di = R.di[tid], tv = R.ti[tid], inv = R.inv[tid];
+        dc_rotate_column(
+            nrot, rp, rq, rc, rs,
+            [&](int s) -> double {
+              if (!root) return s == tag - S2 ? 1.0 : 0.0;
+              const int j = kix[s] - 1;
+              return j < 0 ? 0.0 : dc_uent(zh[j], d[j], di, tv, inv);
+            },
+            [&](int s, double v) {
+              const int r = perm[s] - first;
+              if (r >= 0 && r < kr) panel[r * DC_PLD + tid] = v;
+            });
+      }
+    }
+    __syncthreads();
+    if (live) {
+      // whole groups of 16 k; a ragged last one is clipped to the half (the
+      // panel's rows past it are zero)
+      const double* Ak = Ar + r0 + 4 * lk;
+      const double* Bk = panel + 4 * lk * DC_PLD + jw + lr;
+      int k = 0;
+#pragma unroll 4
+      for (; k + 16 <= kr; k += 16) {
+        double a[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) a[u] = Ak[k + u];
+#pragma unroll
+        for (int u = 0; u < 4; ++u)
+          acc = __builtin_amdgcn_mfma_f64_16x16x4f64(a[u], Bk[(k + u) * DC_PLD], acc, 0, 0, 0);
+      }
+      if (k < kr) {
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+          const double a = k + 4 * lk + u < kr ? Ak[k + u] : 0.0;
+          acc = __builtin_amdgcn_mfma_f64_16x16x4f64(a, Bk[(k + u) * DC_PLD], acc, 0, 0, 0);
+        }
+      }
+    }
+  }
+  if (live)
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const int i = iw + lk + 4 * r, j = j0 + jw + lr;
+      if (i < mh && j < m2) Qd[(size_t)(b0 + h * S + i) * N2 + b0 + j] = acc[r];
+    }
 }
 
 // Levels of the divide and conquer at order n (merges of blocks S = 8, 16,
@@ -1504,18 +1871,27 @@ __device__ inline bool dc_item(const int* cnt, int njobs, int t, int& q, int& r)
 }
 
 // The whole divide and conquer of up to 4 jobs in one launch of P
-// persistent 256-thread blocks: Q = I and the leaves, then per level the
-// sort and deflation of every merge, its secular roots (4 per item), its
-// vectors and update matrix, and the tiles of its products, each phase
-// spread over the blocks and ended by a grid barrier.  A job stops at its
-// own live order (dims), so its levels follow n, not the capacity N.  LDS:
-// the phases' arrays share the dynamic buffer (dc_fused_dyn_lds(N) bytes).
-constexpr int DCF_MAXP = 128;
-__global__ __launch_bounds__(256) void k_dc_fused(EigJobs jobs, int njobs, int* __restrict__ dims,
-                                                  int N) {
+// persistent blocks: first every 64 rows' leaves and merges, one block each,
+// then the merges above.  Each of those has two phases ended by a grid
+// barrier: the sort and deflation (every block for itself) with 8 roots an
+// item, then the tiles of its products, each forming its own columns of the
+// update matrix; merges from S = DC_ZSPLIT on have the pole weights as a phase
+// between.  A job stops at its own live order (dims), so its levels follow
+// n, not the capacity N; orders up to 64 meet no barrier.  (Before, every
+// level from 16 rows on had four phases, with sort, deflation and vectors of
+// a merge on one block: 20 barriers at order 142, and two thirds of the time
+// in phases of one or two blocks.)  An eigensolve of order 16, 62, 142, 322,
+// 641, before and now: 135 -> 114, 286 -> 223, 616 -> 473, 2540 -> 2244,
+// 6871 -> 6174 us.  LDS: the phases' arrays share the dynamic buffer
+// (dc_fused_dyn_lds(N) bytes).
+constexpr int DCF_MAXP = 64;
+__global__ __launch_bounds__(DC_T) void k_dc_fused(EigJobs jobs, int njobs, int* __restrict__ dims,
+                                                   int N) {
   extern __shared__ double smem[];
+  __shared__ PrepLds prep_lds;
+  __shared__ TileLds tile_lds;
   __shared__ int s_abort;
-  const int b = blockIdx.x, P = gridDim.x, wave = threadIdx.x >> 6;
+  const int b = blockIdx.x, P = gridDim.x;
   const GridSync gs = grid_sync_of(jobs.j[0].work, N);
   if (threadIdx.x == 0) s_abort = 0;
   const unsigned gen0 = grid_gen(gs);
@@ -1526,51 +1902,72 @@ __global__ __launch_bounds__(256) void k_dc_fused(EigJobs jobs, int njobs, int* 
     nmax = max(nmax, nq[q]);
   }
   if (nmax == 0) return;  // nothing to solve (every block sees the same sizes)
-  for (int q = 0; q < njobs; ++q) dc_init_job(jobs.j[q], dims, N, b, P);
-  grid_barrier(gs.flag, ++ord, P, &s_abort, dims);
   int cnt[4] = {0, 0, 0, 0}, tot = 0;
-  for (int q = 0; q < njobs; ++q) tot += cnt[q] = (nq[q] + DC_LEAF - 1) / DC_LEAF;
-  for (int t = b * 4 + wave; t < tot; t += 4 * P) {
+  for (int q = 0; q < njobs; ++q) tot += cnt[q] = (nq[q] + DC_SUB - 1) / DC_SUB;
+  for (int t = b; t < tot; t += P) {
     int q, r;
-    if (dc_item(cnt, njobs, t, q, r)) dc_leaf_wave(jobs.j[q], dims, N, r);
+    if (dc_item(cnt, njobs, t, q, r))
+      dc_subtree(jobs.j[q], dims, N, r, *reinterpret_cast<SubLds*>(smem));
   }
-  for (int S = DC_LEAF, par = 0; S < nmax; S *= 2, par ^= 1) {
+  static_assert(DC_SUB == 8 * DC_LEAF && DC_T == 8 * DC_SUB, "a wavefront a leaf, 8 lanes a row");
+  // DC_SUB / DC_LEAF is a power of two: par counts the levels a job has passed
+  int par = 1;  // after S = 8, 16, 32
+  for (int S = DC_SUB; S < nmax; S *= 2, par ^= 1) {
     int nm[4] = {0, 0, 0, 0}, tm = 0;
     for (int q = 0; q < njobs; ++q) tm += nm[q] = nq[q] > S ? (nq[q] + 2 * S - 1) / (2 * S) : 0;
     grid_barrier(gs.flag, ++ord, P, &s_abort, dims);
-    for (int t = b; t < tm; t += P) {
-      int q, r;
-      __syncthreads();  // the previous item's LDS reads are done
-      if (dc_item(nm, njobs, t, q, r)) dc_prep_merge(jobs.j[q], dims, N, S, par, r, smem);
-    }
-    grid_barrier(gs.flag, ++ord, P, &s_abort, dims);
-    const int X = (2 * S + 3) / 4;  // groups of 4 roots of a merge
+    const int X = 2 * S / 8;  // groups of 8 roots or poles of a merge
     for (int q = 0; q < njobs; ++q) cnt[q] = nm[q] * X;
+    int have_q = -1, have_m = -1, nk = 0;  // the merge whose arrays are in LDS
+    double rho = 0.0;
     for (int t = b; t < tm * X; t += P) {
       int q, r;
-      __syncthreads();
-      if (dc_item(cnt, njobs, t, q, r)) dc_secular_roots(jobs.j[q], dims, N, S, r / X, r % X, smem);
+      if (!dc_item(cnt, njobs, t, q, r)) continue;
+      const EigJob& J = jobs.j[q];
+      const int m = r / X, grp = r % X, b0 = m * 2 * S;
+      if (b0 + S >= nq[q] || grp * 8 >= min(2 * S, nq[q] - b0)) continue;
+      // the item that publishes has group 0, which no earlier item of its merge precedes
+      if (q != have_q || m != have_m) {
+        __syncthreads();  // the previous merge's roots are done
+        dc_prep_block(J, N, nq[q], S, par, m, grp == 0, smem, prep_lds, nk, rho);
+        have_q = q;
+        have_m = m;
+      }
+      const int i = grp * 8 + (threadIdx.x >> 6), lane = threadIdx.x & 63;
+      if (i >= nk) continue;
+      double tau, dor;
+      bool ok;
+      dc_root<64>(smem, smem + 2 * S, nk, i, rho, lane, tau, dor, ok);
+      if (lane == 0) {
+        DC D = dc_of(work_of(J, N), N);
+        D.rtau[b0 + i] = tau;
+        D.dro[b0 + i] = dor;
+        if (!ok) atomicOr(&dims[D_FLAG], FLAG_EIG);
+      }
+    }
+    if (S >= DC_ZSPLIT) {
+      grid_barrier(gs.flag, ++ord, P, &s_abort, dims);
+      for (int t = b; t < tm * X; t += P) {
+        int q, r;
+        __syncthreads();  // the previous item's LDS reads are done
+        if (dc_item(cnt, njobs, t, q, r)) dc_zhat_block(jobs.j[q], N, nq[q], S, r / X, r % X, smem);
+      }
     }
     grid_barrier(gs.flag, ++ord, P, &s_abort, dims);
-    for (int t = b; t < tm; t += P) {
-      int q, r;
-      __syncthreads();
-      if (!dc_item(nm, njobs, t, q, r)) continue;
-      if (2 * S <= VEC_STAGE_MAX) dc_vectors_merge<true>(jobs.j[q], dims, N, S, r, smem);
-      else dc_vectors_merge<false>(jobs.j[q], dims, N, S, r, smem);
-    }
-    grid_barrier(gs.flag, ++ord, P, &s_abort, dims);
-    const int TI = (S + 63) / 64, TJ = (2 * S + 63) / 64, TM = 2 * TI * TJ;
+    const int TI = S / DC_RT, TJ = 2 * S / DC_CT, TM = 2 * TI * TJ;
     for (int q = 0; q < njobs; ++q) cnt[q] = nm[q] * TM;
     for (int t = b; t < tm * TM; t += P) {
       int q, r;
       __syncthreads();
       if (!dc_item(cnt, njobs, t, q, r)) continue;
       const int m = r / TM, e = r % TM, h = e / (TI * TJ), ti = (e / TJ) % TI, tj = e % TJ;
-      dc_merge_tile(jobs.j[q], dims, N, S, par, m, h, ti, tj, smem);
+      if (2 * S <= VEC_STAGE_MAX)
+        dc_update_tile<true>(jobs.j[q], dims, N, nq[q], S, par, m, h, ti, tj, smem, tile_lds);
+      else
+        dc_update_tile<false>(jobs.j[q], dims, N, nq[q], S, par, m, h, ti, tj, smem, tile_lds);
     }
   }
-  grid_launch_end(gs, gen0, true);
+  grid_launch_end(gs, gen0, nmax > DC_SUB);
 }
 
 // Threshold of the clip rule: eigenvalues above it are kept.
@@ -2672,18 +3069,26 @@ __global__ __launch_bounds__(256) void k_svd_final(EigJobs jobs, int* __restrict
 }
 
 // Dynamic LDS of k_dc_fused at capacity N: the largest of its phases' needs
-// at the top level (sort and deflation, secular roots, vectors, product tiles).
+// (the one-block merges; sort and deflation, tiles of the levels above).
 size_t dc_fused_dyn_lds(int N) {
-  size_t need = (size_t)2 * GEMM_GK * 65 * 8;
-  for (int S = DC_LEAF; S < N; S *= 2) {
+  size_t need = sizeof(SubLds);
+  for (int S = DC_SUB; S < N; S *= 2) {
     const size_t m2 = (size_t)2 * S;
     need = std::max(need, m2 * PREP_BYTES_PER);
-    need = std::max(need, m2 * 16);
-    need = std::max(need, m2 * (m2 <= VEC_STAGE_MAX ? VEC_BYTES_STAGED : VEC_BYTES_GLOBAL));
+    need = std::max(need, m2 <= VEC_STAGE_MAX
+                              ? dc_kc<true>() * DC_PLD * 8 + m2 * VEC_BYTES_STAGED
+                              : dc_kc<false>() * DC_PLD * 8 + m2 * VEC_BYTES_GLOBAL);
   }
   return need;
 }
-int dc_fused_blocks(int N) { return std::min(DCF_MAXP, std::max(8, (N + 3) / 4)); }
+// Blocks: a block each up to order 64; above, one for 8 roots or a top
+// merge's tile.  At most DCF_MAXP: with up to a CU's LDS each, the launches of
+// 4 hardware queues are still resident together, which their grid barriers
+// need.
+int dc_fused_blocks(int N, int njobs) {
+  if (N <= DC_SUB) return njobs;
+  return std::min(DCF_MAXP, njobs * std::max((N + 7) / 8, N * N / 2048));
+}
 
 }  // namespace
 
@@ -2694,7 +3099,7 @@ int dc_fused_blocks(int N) { return std::min(DCF_MAXP, std::max(8, (N + 3) / 4))
 // the runtime's own figure is used.
 namespace {
 constexpr size_t LDS_CU = 160 * 1024;
-constexpr size_t ST_SYTRD_GRID = 168, ST_DC_FUSED = 32848, ST_ORMTR = 0, ST_GEBRD_GRID = 168,
+constexpr size_t ST_SYTRD_GRID = 168, ST_DC_FUSED = 1296, ST_ORMTR = 0, ST_GEBRD_GRID = 168,
                  ST_SVD_JACOBI = 148768;
 
 size_t static_lds(const void* fn, size_t table, bool runtime) {
@@ -2752,7 +3157,7 @@ namespace {
 // Divide and conquer of the tridiagonals (W.d, W.e) of the jobs; the
 // eigenvectors end in buffer dc_par(n) of each job.
 void dc_solve(const EigJobs& J, int njobs, int N, int* dims, hipStream_t s) {
-  k_dc_fused<<<dc_fused_blocks(N), 256, dc_fused_dyn_lds(N), s>>>(J, njobs, dims, N);
+  k_dc_fused<<<dc_fused_blocks(N, njobs), DC_T, dc_fused_dyn_lds(N), s>>>(J, njobs, dims, N);
 }
 
 }  // namespace

@@ -63,3 +63,61 @@ def test_eigh_sizes(kind, n):
     assert np.abs(lam - ref).max() <= bound * nrm
     assert np.abs(A @ V - V * lam[:kept]).max() <= 4 * bound * nrm
     assert np.abs(V.T @ V - np.eye(kept)).max() <= 4 * bound
+
+
+def _spectrum(kind, n):
+    """Spectra that drive the merges' deflation: runs of equal and of nearly
+    equal eigenvalues (rotations), two thirds at rounding level, and none."""
+    if kind == "runs":
+        return np.repeat(np.linspace(1.0, 2.0, (n + 6) // 7), 7)[:n]
+    if kind == "near":
+        return 1.0 + np.repeat(np.arange((n + 2) // 3), 3)[:n] / n + 1e-15 * np.arange(n)
+    if kind == "noise":
+        return np.where(np.arange(n) < n // 3, 10.0 ** (-6.0 * np.arange(n) / n), 1e-18)
+    return np.linspace(1.0, 3.0, n)
+
+
+@pytest.mark.parametrize("kind", ["runs", "near", "noise", "spread"])
+@pytest.mark.parametrize("n", [9, 16, 17, 31, 33, 63, 64, 65, 72, 127, 128, 129, 255, 256, 257, 320, 513])
+def test_eigh_deflation(kind, n):
+    """The merges' edges: one block up to 64 rows, tiles of 64 rows by 32
+    columns above, panels of 256 rows, the pole weights' own phase from 256."""
+    rng = np.random.default_rng(n)
+    Q = np.linalg.qr(rng.standard_normal((n, n)))[0]
+    A = (Q * _spectrum(kind, n)) @ Q.T
+    A = 0.5 * (A + A.T)
+    lam, V, kept = _eigh(A, n)
+    ref = np.linalg.eigvalsh(A)[::-1]
+    nrm = np.abs(ref).max()
+    bound = 20 * n * 2.0 ** -53
+    assert np.abs(lam - ref).max() <= bound * nrm
+    assert np.abs(A @ V - V * lam[:kept]).max() <= 4 * bound * nrm
+    assert np.abs(V.T @ V - np.eye(kept)).max() <= 4 * bound
+
+
+@pytest.mark.parametrize("p,q", [(140, 130), (600, 256), (600, 260), (560, 520)])
+def test_svd_large_orders(p, q):
+    """Golub-Kahan orders 2 q around the staged and the unstaged merges (1024 rows)."""
+    import torch
+    from paper_2503_18056_amd import _ffi
+    lib = _ffi.load()
+    rng = np.random.default_rng(q)
+    U = np.linalg.qr(rng.standard_normal((p, q)))[0]
+    W = np.linalg.qr(rng.standard_normal((q, q)))[0]
+    sig = np.linspace(2.0, 1.0, q)
+    d = torch.as_tensor((U * sig) @ W.T, device="cuda")
+    s = torch.zeros(q, dtype=torch.float64, device="cuda")
+    V = torch.zeros((q, q), dtype=torch.float64, device="cuda")
+    ws = torch.zeros(int(lib.tt_kernel_svd_workspace(p, q)), dtype=torch.uint8, device="cuda")
+    kept = C.c_int32()
+    st = lib.tt_kernel_svd(C.c_void_p(d.data_ptr()), p, q, q, C.c_void_p(s.data_ptr()),
+                           C.c_void_p(V.data_ptr()), q, C.byref(kept), C.c_void_p(ws.data_ptr()),
+                           ws.numel(), None)
+    assert st == 0, lib.tt_kernel_last_error()
+    assert kept.value == q
+    Vh = V.cpu().numpy()
+    bound = 40 * q * 2.0 ** -53
+    assert np.abs(s.cpu().numpy() - sig).max() <= bound * sig[0]
+    assert np.abs(Vh.T @ Vh - np.eye(q)).max() <= 4 * bound
+    M = d.cpu().numpy()
+    assert np.abs(M.T @ (M @ Vh) - Vh * sig ** 2).max() <= 16 * bound * sig[0] ** 2
