@@ -5,7 +5,7 @@
 // Pipeline (one job per matrix, several jobs run side by side):
 //   1. Householder tridiagonalisation A = Q T Q^T (the only step with O(n)
 //      sequential dependences): the matrix in one block's registers up to
-//      order 192, above that split by rows over 64 blocks' LDS.
+//      order 192, above that the rows split over 16 to 64 blocks' registers.
 //   2. Eigenpairs of T by divide and conquer from 8x8 leaves, all levels in
 //      one persistent launch: the merges up to 64 rows on one block each, above
 //      that one wavefront per secular root and products in tiles over the
@@ -176,21 +176,25 @@ constexpr int SYR_MAX = 192;  // orders reduced in registers by k_sytrd_reg
 
 // Large orders (n > SYR_MAX): the matrix does not fit one CU's registers,
 // and one block streaming the trailing matrix from L2 is bound by that CU's
-// share of the memory system.  Instead P blocks per job (32 when their rows
-// fit LDS, else SYTRD_GRID_P) each keep the rows i = b (mod P) of the full
-// symmetric square in their own LDS
-// (at most ceil(N / P) rows), and step k, which needs T_k (the matrix after
-// reflectors 0..k-1), runs as:
-//   - every block forms row k of T_k from row k of T_{k-1} (published by its
-//     owner) and the previous reflector's (v, w), and v_k, tau_k from it,
+// share of the memory system.  Instead P blocks per job each keep 16 rows, 4 to
+// a wavefront, in registers for the whole reduction, and step k, which needs
+// T_k (the matrix after reflectors 0..k-1), runs as:
+//   - every wavefront forms row k of T_k from row k of T_{k-1} (published by
+//     its owner) and the previous reflector's (v, w), and v_k, tau_k from it,
 //     redundantly (same data and fixed-order sums, so identical everywhere);
-//   - each block applies T_k = T_{k-1} - v w^T - w v^T to its rows in LDS and
-//     in the same pass forms p_k = tau_k T_k,22 v_k on them and its share of
-//     p_k^T v_k; the owner of row k+1 publishes it;
+//   - each applies T_k = T_{k-1} - v w^T - w v^T to its rows and in the same
+//     pass forms p_k = tau_k T_k,22 v_k on them and its share of p_k^T v_k;
+//     the owner of row k+1 publishes it;
 //   - one grid barrier; w_k = p_k - (tau_k / 2)(p_k^T v_k) v_k then follows
-//     from the published p_k and the partial dots summed in block order.
-// Only p, the partial dots and one row cross blocks per step.  The grid (at
-// most 4 x 64 blocks of 256 threads) is a small part of what the chip holds
+//     from the published p_k and the partial dots summed in a fixed order.
+// Only p, the partial dots and one row cross blocks per step, by relaxed
+// agent-scope accesses (xput, xget).  Bound by the exchange: at order 322
+// (32 blocks) a step is about 1.7 us of barrier, 1.0 us of loads behind it,
+// 0.5 us of the row and its reflector and 0.7 us of updates.  With the rows in
+// LDS and a barrier that released and acquired it was 2.4, 0.7, 0.9 and 2.1.
+// An eigensolve of order 206, 322, 641, 1024, before and now: 1364 -> 984,
+// 2244 -> 1579, 6174 -> 5039, 11790 -> 9575 us.
+// The grid (at most 4 x 64 blocks of 256 threads) is a small part of what the chip holds
 // resident, so an ordinary launch has all blocks resident together (a
 // cooperative launch would drain the queue on every call, also when all jobs
 // are small and the kernel returns at once); every wait is bounded by
@@ -200,12 +204,12 @@ constexpr int SYR_MAX = 192;  // orders reduced in registers by k_sytrd_reg
 constexpr int SYTRD_GRID_P = 64;
 constexpr int SYTRD_GRID_T = 256;
 constexpr int SYTRD_GRID_NMAX = 1024;                          // largest order
-constexpr int SYG_M = SYTRD_GRID_NMAX / SYTRD_GRID_T;          // columns per thread
-constexpr int SYG_T = SYTRD_GRID_NMAX / 64;                    // columns per lane
+constexpr int SYG_R = 4;  // rows of a wavefront
+constexpr int SYG_T = SYTRD_GRID_NMAX / 64;  // columns per lane at most
 constexpr unsigned SYTRD_SPIN_MAX = 1u << 24;
 
 struct SytrdGridBufs {
-  double *Rp, *Pv, *Dv;  // published rows (2 x N), p (2 x N), block partial dots (2 x P)
+  double *Rp, *Pv, *Dv;  // published rows (2 x N), p (2 x N), wavefront partial dots (2 x 4 P)
 };
 __device__ __host__ inline SytrdGridBufs sytrd_grid_bufs(double* work, int N) {
   // inside the divide-and-conquer area, which is free until the reduction ends
@@ -217,18 +221,7 @@ __device__ __host__ inline SytrdGridBufs sytrd_grid_bufs(double* work, int N) {
   B.Dv = B.Pv + 2 * (size_t)N;
   return B;
 }
-// Blocks per job: the fewest of 32, 48, 64 whose rows fit LDS (fewer blocks
-// make the grid barrier and the partial-dot sum cheaper).
 constexpr size_t GRID_DYN_LDS_MAX = 158 * 1024;  // dynamic LDS a grid reduction may ask for
-inline size_t sytrd_grid_lds_p(int N, int P) {
-  return ((size_t)((N + P - 1) / P) * N + 3 * (size_t)N) * 8;
-}
-inline int sytrd_grid_blocks(int N) {
-  for (int P = 32; P < SYTRD_GRID_P; P += 16)
-    if (sytrd_grid_lds_p(N, P) <= GRID_DYN_LDS_MAX) return P;
-  return SYTRD_GRID_P;
-}
-inline size_t sytrd_grid_lds(int N) { return sytrd_grid_lds_p(N, sytrd_grid_blocks(N)); }
 
 // Grid barriers of the multi-block kernels.  A job's work area ends with one
 // flag per block and a launch generation.  Each launch takes its barrier
@@ -295,169 +288,228 @@ __device__ inline void grid_barrier(unsigned* flag, unsigned ordinal, int P, int
   __syncthreads();
 }
 
-__global__ __launch_bounds__(SYTRD_GRID_T) void k_sytrd_grid(EigJobs jobs, int* __restrict__ dims,
-                                                             int N) {
-  const int b = blockIdx.x, P = gridDim.x;
-  const EigJob J = jobs.j[blockIdx.y];
-  const int n = dims[J.n_idx];
-  if (n <= SYR_MAX) return;  // k_sytrd_reg (the same decision on all blocks of the job)
+// Exchange between the blocks of a launch without fences: the values are
+// written and read with relaxed agent-scope accesses, which pass the caches
+// that are not coherent across XCDs, so a barrier needs neither the write-back
+// nor the invalidation of an L2 that release and acquire take.
+__device__ inline void xput(double* p, double v) {
+  __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ inline double xget(const double* p) {
+  return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+// grid_barrier for values exchanged by xput and xget: every wavefront waits for
+// its stores' acknowledgements (vmcnt 0) before the block's flag is raised.
+__device__ inline void grid_barrier_relaxed(unsigned* flag, unsigned ordinal, int P, int* s_abort,
+                                            int* dims) {
+  __atomic_signal_fence(__ATOMIC_SEQ_CST);
+  __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt 0, expcnt 7, lgkmcnt 15
+  __syncthreads();
+  if (threadIdx.x < 64 && !*s_abort) {
+    const int lane = threadIdx.x;
+    if (lane == 0)
+      __hip_atomic_store(&flag[blockIdx.x], ordinal, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    unsigned spins = 0;
+    while (true) {
+      bool ok = true;
+      for (int q = lane; q < P; q += 64)
+        ok = ok && (int)(__hip_atomic_load(&flag[q], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) -
+                         ordinal) >= 0;
+      if (__all(ok)) break;
+      if (++spins > SYTRD_SPIN_MAX) {
+        if (lane == 0) {
+          *s_abort = 1;
+          atomicOr(&dims[D_FLAG], FLAG_BARRIER);
+        }
+        break;
+      }
+    }
+  }
+  __syncthreads();
+  __atomic_signal_fence(__ATOMIC_SEQ_CST);
+}
+
+// One block's part, for n <= 64 NT on P blocks of 4 wavefronts: wavefront w of block b
+// holds the rows b + P (w + 4 r), r < 4, a lane the columns lane + 64 t.
+template <int NT>
+__device__ void sytrd_grid_rows(const EigJob& J, int* __restrict__ dims, int N, int n, int P,
+                                double* lds, int* s_abort) {
+  const int b = blockIdx.x;
   Work W = work_of(J, N);
   const SytrdGridBufs G = sytrd_grid_bufs(J.work, N);
-  const double* A = J.A;
-  const long long lda = J.lda;
-  extern __shared__ double lds[];
-  const int RB = (N + P - 1) / P;
-  double* Lr = lds;                   // own rows: row i at Lr + (i / P) N
-  double* sv = Lr + (size_t)RB * N;   // v_k (and row k of T_k before scaling)
-  double* svp = sv + N;               // v_{k-1}
-  double* swp = svp + N;              // w_{k-1}
-  __shared__ double red[16];
-  __shared__ double s_tau, s_scal, s_taup, s_d;
-  __shared__ int s_abort;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  for (int li = wave; li * P + b < n; li += 4) {
-    const double* ra = A + (long long)(li * P + b) * lda;
-    for (int j = lane; j < n; j += 64) Lr[(size_t)li * N + j] = ra[j];
+  double* lv = lds + wave * 3 * NT * 64;  // v_{k-1}, w_{k-1}, v_k of this wavefront
+  double* lw = lv + NT * 64;
+  double* ln = lw + NT * 64;
+  double a[SYG_R][NT], v[NT], w[NT];
+#pragma unroll
+  for (int r = 0; r < SYG_R; ++r) {
+    const int i = b + P * (wave + SYTRD_GRID_T / 64 * r);
+#pragma unroll
+    for (int t = 0; t < NT; ++t) {
+      const int j = lane + 64 * t;
+      a[r][t] = i < n && j < n ? J.A[(long long)i * J.lda + j] : 0.0;
+    }
   }
-  for (int i = tid; i < N; i += SYTRD_GRID_T) svp[i] = swp[i] = 0.0;
-  if (tid == 0) { s_taup = 0.0; s_abort = 0; }
-  __syncthreads();
+#pragma unroll
+  for (int t = 0; t < NT; ++t) v[t] = w[t] = 0.0;
   const GridSync gs = grid_sync_of(J.work, N);
   const unsigned gen0 = grid_gen(gs);
   unsigned ordinal = gen0 * GRID_ORD_SPAN;
+  const bool writer = b == 0 && wave == 0;
+  double taup = 0.0;
   for (int k = 0; k <= n - 2; ++k) {
-    // w_{k-1} on indices >= k from the published p_{k-1} and partial dots
-    // (every wave sums the P partials the same way), fused with row k of T_k.
-    // Every load of the step is issued before the first use: one round trip.
+    // w_{k-1} on indices >= k from the published p_{k-1} and partial dots,
+    // fused with row k of T_k; all loads of the step in flight together
     const int par = (k - 1) & 1;
     const double* pp = G.Pv + (size_t)par * N;
-    const double* src = k == 0 ? A : G.Rp + (size_t)par * N;
-    const double dpv = (k >= 1 && lane < P) ? G.Dv[(size_t)par * SYTRD_GRID_P + lane] : 0.0;
-    const double ppk = k >= 1 ? pp[k] : 0.0;
-    double ppv[SYG_M], srv[SYG_M];
+    const double* src = G.Rp + (size_t)par * N;
+    double x[NT], hc = 0.0, ppk = 0.0;
+    if (k == 0) {
 #pragma unroll
-    for (int m = 0; m < SYG_M; ++m) {
-      const int j = k + tid + SYTRD_GRID_T * m;
-      ppv[m] = (k >= 1 && j < n) ? pp[j] : 0.0;
-      srv[m] = j < n ? src[j] : 0.0;
-    }
-    const double hc = k >= 1 ? 0.5 * s_taup * wave_sum(dpv) : 0.0;
-    const double vk0 = svp[k];
-    const double wk0 = k >= 1 ? ppk - hc * vk0 : 0.0;
-    if (k == n - 2) {
-#pragma unroll
-      for (int m = 0; m < SYG_M; ++m) {
-        const int j = k + tid + SYTRD_GRID_T * m;
-        if (j < n) swp[j] = ppv[m] - hc * svp[j];
-      }
-      __syncthreads();
+      for (int t = 0; t < NT; ++t) x[t] = lane + 64 * t < n ? J.A[lane + 64 * t] : 0.0;
     } else {
-      // row k of T_k (columns >= k)
-      double part = 0.0;
+      double pv[NT], dp[SYTRD_GRID_P / 16];
 #pragma unroll
-      for (int m = 0; m < SYG_M; ++m) {
-        const int j = k + tid + SYTRD_GRID_T * m;
-        if (j >= n) continue;
-        const double wj = k >= 1 ? ppv[m] - hc * svp[j] : 0.0;
-        swp[j] = wj;
-        const double r = srv[m] - vk0 * wj - wk0 * svp[j];
-        if (j == k) s_d = r;
-        sv[j] = r;
-        if (j >= k + 2) part += r * r;
+      for (int t = 0; t < NT; ++t) {
+        const int j = lane + 64 * t;
+        const bool live = j >= k && j < n;
+        pv[t] = live ? xget(pp + j) : 0.0;
+        x[t] = live ? xget(src + j) : 0.0;
       }
-      const double sumsq = block_sum<SYTRD_GRID_T>(part, red);
-      if (tid == 0) {
-        const double alpha = sv[k + 1];
-        double e;
-        if (sumsq == 0.0) {
-          s_tau = 0.0;
-          s_scal = 0.0;
-          e = alpha;
-        } else {
-          const double beta = -copysign(sqrt(alpha * alpha + sumsq), alpha);
-          s_tau = (beta - alpha) / beta;
-          s_scal = 1.0 / (alpha - beta);
-          e = beta;
-        }
-        if (b == 0) {
-          W.d[k] = s_d;
-          W.e[k] = e;
-          W.tau[k] = s_tau;
-        }
-      }
-      __syncthreads();
-      const double tau = s_tau, scal = s_scal;
-      for (int j = k + 1 + tid; j < n; j += SYTRD_GRID_T) {
-        const double v = j == k + 1 ? 1.0 : sv[j] * scal;
-        sv[j] = v;
-        if (b == 0) W.H[(long long)k * N + j] = v;
-      }
-      __syncthreads();
-      // own rows: T_k = T_{k-1} - v w^T - w v^T, and p_k = tau T_k,22 v_k.
-      // Lane l handles the columns j = k + 1 + l + 64 t of every row it
-      // updates, so it keeps v_{k-1}, w_{k-1} and v_k at those columns in
-      // registers: per element only the row entry moves through LDS.
-      double* pk = G.Pv + (size_t)(k & 1) * N;
-      double* rpub = G.Rp + (size_t)(k & 1) * N;
-      const int i0 = k + 1 + ((b - (k + 1)) % P + P) % P;
-      const int j0 = k + 1 + lane;
-      double cv[SYG_T], cw[SYG_T], cs[SYG_T];
 #pragma unroll
-      for (int t = 0; t < SYG_T; ++t) {
-        const int j = j0 + 64 * t;
-        const bool ok = j < n;
-        cv[t] = ok ? svp[j] : 0.0;
-        cw[t] = ok ? swp[j] : 0.0;
-        cs[t] = ok ? sv[j] : 0.0;
-      }
-      double wpart = 0.0;
-      for (int i = i0 + wave * P; i < n; i += 4 * P) {
-        const double vi = svp[i], wi = swp[i];
-        double* r = Lr + (size_t)(i / P) * N;
-        const bool publish = i == k + 1;
-        double acc = 0.0;
+      for (int m = 0; m < SYTRD_GRID_P / 16; ++m)
+        dp[m] = lane + 64 * m < 4 * P ? xget(G.Dv + (size_t)par * 4 * SYTRD_GRID_P + lane + 64 * m) : 0.0;
+      ppk = xget(pp + k);
+      double s = 0.0;
 #pragma unroll
-        for (int t = 0; t < SYG_T; ++t) {
-          if (k + 1 + 64 * t >= n) break;
-          const int j = j0 + 64 * t;
-          if (j < n) {
-            const double x = r[j] - vi * cw[t] - wi * cv[t];
-            r[j] = x;
-            if (publish) rpub[j] = x;
-            acc += x * cs[t];
-          }
-        }
-        acc = wave_sum(acc);
-        const double pv = tau * acc;
-        if (lane == 0) pk[i] = pv;
-        wpart += pv * sv[i];
+      for (int m = 0; m < SYTRD_GRID_P / 16; ++m) s += dp[m];
+      hc = 0.5 * taup * wave_sum(s);
+      const double wk0 = ppk - hc;  // v_{k-1} starts with 1
+#pragma unroll
+      for (int t = 0; t < NT; ++t) {
+        w[t] = lane + 64 * t >= k ? pv[t] - hc * v[t] : 0.0;
+        x[t] = x[t] - w[t] - wk0 * v[t];
       }
-      __syncthreads();
-      if (lane == 0) red[wave] = wpart;
-      __syncthreads();
-      if (tid == 0) {
-        G.Dv[(size_t)(k & 1) * SYTRD_GRID_P + b] = ((red[0] + red[1]) + red[2]) + red[3];
-        s_taup = tau;
-      }
-      for (int j = k + 1 + tid; j < n; j += SYTRD_GRID_T) svp[j] = sv[j];
-      grid_barrier(gs.flag, ++ordinal, P, &s_abort, dims);
     }
-    if (k == n - 2 && tid == 0) {
-      // the last 2 x 2 block of T_{n-2}, from its owners' rows of T_{n-3}
-      const int i0 = n - 2, i1 = n - 1;
-      if (i0 % P == b) {
-        const double* r = Lr + (size_t)(i0 / P) * N;
-        W.d[i0] = r[i0] - 2.0 * svp[i0] * swp[i0];
-        W.e[i0] = r[i1] - svp[i0] * swp[i1] - swp[i0] * svp[i1];
-        W.tau[i0] = 0.0;
+    double part = 0.0, al = 0.0;
+#pragma unroll
+    for (int t = 0; t < NT; ++t) {
+      const int j = lane + 64 * t;
+      lv[j] = v[t];
+      lw[j] = w[t];
+      if (j >= k + 2) part += x[t] * x[t];
+      if (j == k + 1) al = x[t];
+    }
+    if (k == n - 2) break;
+    const double sumsq = wave_sum(part), alpha = wave_sum(al);
+    double tau, scal, beta;
+    householder(alpha, sumsq, tau, scal, beta);
+    double vn[NT];
+#pragma unroll
+    for (int t = 0; t < NT; ++t) {
+      const int j = lane + 64 * t;
+      vn[t] = j > k + 1 ? x[t] * scal : j == k + 1 ? 1.0 : 0.0;
+      ln[j] = vn[t];
+    }
+    wave_sync();
+    // own rows: T_k = T_{k-1} - v w^T - w v^T, and p_k = tau T_k,22 v_k
+    double acc[SYG_R], wpart = 0.0;
+#pragma unroll
+    for (int r = 0; r < SYG_R; ++r) {
+      acc[r] = 0.0;
+      const int i = b + P * (wave + SYTRD_GRID_T / 64 * r);
+      if (i <= k || i >= n) continue;
+      const double vi = lv[i], wi = lw[i];
+#pragma unroll
+      for (int t = 0; t < NT; ++t) {
+        if (64 * t + 63 <= k) continue;
+        a[r][t] = a[r][t] - vi * w[t] - wi * v[t];
+        acc[r] += a[r][t] * vn[t];
       }
-      if (i1 % P == b) {
-        const double* r = Lr + (size_t)(i1 / P) * N;
-        W.d[i1] = r[i1] - 2.0 * svp[i1] * swp[i1];
+      if (i == k + 1) {
+        double* rpub = G.Rp + (size_t)(k & 1) * N;
+#pragma unroll
+        for (int t = 0; t < NT; ++t)
+          if (lane + 64 * t > k && lane + 64 * t < n) xput(rpub + lane + 64 * t, a[r][t]);
+      }
+    }
+#pragma unroll
+    for (int r = 0; r < SYG_R; ++r) acc[r] = wave_sum(acc[r]);
+#pragma unroll
+    for (int r = 0; r < SYG_R; ++r) {
+      const int i = b + P * (wave + SYTRD_GRID_T / 64 * r);
+      if (i <= k || i >= n) continue;
+      const double pv = tau * acc[r];
+      if (lane == 0) xput(G.Pv + (size_t)(k & 1) * N + i, pv);
+      wpart += pv * ln[i];
+    }
+    if (lane == 0) xput(G.Dv + (size_t)(k & 1) * 4 * SYTRD_GRID_P + 4 * b + wave, wpart);
+#pragma unroll
+    for (int t = 0; t < NT; ++t) v[t] = vn[t];
+    taup = tau;
+    grid_barrier_relaxed(gs.flag, ++ordinal, P, s_abort, dims);
+    if (writer) {
+#pragma unroll
+      for (int t = 0; t < NT; ++t) {
+        const int j = lane + 64 * t;
+        if (j == k) W.d[k] = x[t];
+        if (j > k && j < n) W.H[(long long)k * N + j] = v[t];
+      }
+      if (lane == 0) {
+        W.e[k] = beta;
+        W.tau[k] = tau;
       }
     }
   }
-  grid_launch_end(gs, gen0, ordinal != gen0 * GRID_ORD_SPAN);
+  // the last 2 x 2 block of T_{n-2}, from its owners' rows of T_{n-3}
+  wave_sync();
+#pragma unroll
+  for (int r = 0; r < SYG_R; ++r) {
+    const int i = b + P * (wave + SYTRD_GRID_T / 64 * r);
+    if (i < n - 2 || i >= n) continue;
+    const double vi = lv[i], wi = lw[i];
+#pragma unroll
+    for (int t = 0; t < NT; ++t) {
+      const int j = lane + 64 * t;
+      const double y = a[r][t] - vi * w[t] - wi * v[t];
+      if (j == i) W.d[i] = y;
+      if (i == n - 2 && j == n - 1) {
+        W.e[i] = y;
+        W.tau[i] = 0.0;
+      }
+    }
+  }
+  grid_launch_end(gs, gen0, true);
+}
+
+// Blocks of a live order n: 16 rows to a block, 4 to a wavefront.
+__device__ __host__ inline int sytrd_grid_blocks(int n) {
+  return n <= 256 ? 16 : n <= 512 ? 32 : SYTRD_GRID_P;
+}
+__device__ __host__ inline int sytrd_grid_chunks(int n) {
+  return n <= 256 ? 4 : n <= 384 ? 6 : n <= 512 ? 8 : n <= 704 ? 11 : 16;
+}
+inline size_t sytrd_grid_lds(int N) {
+  return (size_t)sytrd_grid_chunks(N) * 64 * 3 * (SYTRD_GRID_T / 64) * 8;
+}
+
+__global__ __launch_bounds__(SYTRD_GRID_T) void k_sytrd_grid(EigJobs jobs, int* __restrict__ dims,
+                                                             int N) {
+  extern __shared__ double lds[];
+  __shared__ int s_abort;
+  const EigJob J = jobs.j[blockIdx.y];
+  const int n = dims[J.n_idx];
+  if (n <= SYR_MAX) return;  // k_sytrd_reg (the same decision on all blocks of the job)
+  const int P = sytrd_grid_blocks(n);
+  if (blockIdx.x >= P) return;
+  if (threadIdx.x == 0) s_abort = 0;
+  __syncthreads();
+  if (n <= 256) sytrd_grid_rows<4>(J, dims, N, n, P, lds, &s_abort);
+  else if (n <= 384) sytrd_grid_rows<6>(J, dims, N, n, P, lds, &s_abort);
+  else if (n <= 512) sytrd_grid_rows<8>(J, dims, N, n, P, lds, &s_abort);
+  else if (n <= 704) sytrd_grid_rows<11>(J, dims, N, n, P, lds, &s_abort);
+  else sytrd_grid_rows<16>(J, dims, N, n, P, lds, &s_abort);
 }
 
 // The same reduction with the matrix in registers (n <= SYR_MAX), one block
@@ -3099,7 +3151,7 @@ int dc_fused_blocks(int N, int njobs) {
 // the runtime's own figure is used.
 namespace {
 constexpr size_t LDS_CU = 160 * 1024;
-constexpr size_t ST_SYTRD_GRID = 168, ST_DC_FUSED = 1296, ST_ORMTR = 0, ST_GEBRD_GRID = 168,
+constexpr size_t ST_SYTRD_GRID = 8, ST_DC_FUSED = 1296, ST_ORMTR = 0, ST_GEBRD_GRID = 168,
                  ST_SVD_JACOBI = 148768;
 
 size_t static_lds(const void* fn, size_t table, bool runtime) {

@@ -95,6 +95,20 @@ def test_eigh_deflation(kind, n):
     assert np.abs(V.T @ V - np.eye(kept)).max() <= 4 * bound
 
 
+@pytest.mark.parametrize("kind", ["dense", "zeros"])
+@pytest.mark.parametrize("n", [193, 208, 255, 256, 257, 383, 384, 385, 512, 704, 705, 1023])
+def test_eigh_grid_orders(kind, n):
+    """The reduction over several blocks: 16 rows a block, its column classes."""
+    A = _matrix(kind, n)
+    lam, V, kept = _eigh(A, n + 1)
+    ref = np.linalg.eigvalsh(A)[::-1]
+    nrm = np.abs(ref).max()
+    bound = 20 * n * 2.0 ** -53
+    assert np.abs(lam - ref).max() <= bound * nrm
+    assert np.abs(A @ V - V * lam[:kept]).max() <= 4 * bound * nrm
+    assert np.abs(V.T @ V - np.eye(kept)).max() <= 4 * bound
+
+
 @pytest.mark.parametrize("p,q", [(140, 130), (600, 256), (600, 260), (560, 520)])
 def test_svd_large_orders(p, q):
     """Golub-Kahan orders 2 q around the staged and the unstaged merges (1024 rows)."""
