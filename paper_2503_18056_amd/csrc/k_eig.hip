@@ -55,13 +55,13 @@ __host__ __device__ inline int next_pow2(int n) {
 // Work area of one job at capacity N, before the grid-barrier words: d, e,
 // tau, w (4 N), reflectors (N x N), then the divide-and-conquer area.
 // d, e, tau, w, H (N x N), then an area that the divide and conquer uses
-// and, before it, the grid reductions' exchange buffers (k_gebrd_grid's
-// double-buffered partials need 2 (N + 128 N + 128) doubles, more than the
-// divide and conquer for small N).
+// and, before it, the grid reductions' exchange buffers (k_gebrd's
+// double-buffered partials of up to 64 blocks, more than the divide and
+// conquer for small N).
 __host__ __device__ inline size_t eig_work_main(int N) {
   const size_t N2 = next_pow2(N);
   const size_t dc = 2 * N2 * N2 + 17 * N2 + 64;
-  const size_t grid = 2 * ((size_t)N + 128 * (size_t)N + 128) + 64;
+  const size_t grid = 2 * ((size_t)N + 64 * (size_t)N + 256) + 64;
   return 4 * (size_t)N + (size_t)N * N + N2 + (dc > grid ? dc : grid);
 }
 
@@ -2307,37 +2307,6 @@ __global__ __launch_bounds__(256) void k_eig_final(EigJobs jobs, int* __restrict
 // come from the divide and conquer above, so sigma_j is accurate to
 // ~u sigma_1 absolutely and the vectors to ~u sigma_1 / gap.
 
-constexpr int GEBRD_LDS_MAX = 16384;  // p q doubles held in LDS by k_gebrd_lds
-// Longer side from which k_gebrd_grid takes a matrix that does not fit
-// k_gebrd_lds.  With p >= q, a p x q matrix with p < 128 always fits
-// (p (q | 1) <= 127^2 < GEBRD_LDS_MAX), so every other one goes to the grid.
-constexpr int GEBRD_GRID_MIN = 128;
-constexpr int GEBRD_GRID_PMAX = 128;  // blocks of k_gebrd_grid at most
-static_assert(GEBRD_GRID_PMAX <= 128, "eig_work_main sizes the grid partials for 128 blocks");
-constexpr int GBG_M = 4;   // columns per thread in k_gebrd_grid's partial sums (q <= 1024)
-constexpr int GBG_U = 16;  // block partials loaded together
-__device__ inline int gebrd_ld(int q) { return q | 1; }
-__device__ inline bool gebrd_fits(int p, int q) {
-  return (long long)p * gebrd_ld(q) <= GEBRD_LDS_MAX && p <= 1024;
-}
-
-// The taller orientation of M into the work matrix (side 0: M^T, b x a);
-// only for matrices too large for k_gebrd_lds.
-__global__ __launch_bounds__(256) void k_svd_load(const double* __restrict__ M, int ldm,
-                                                  EigJobs jobs, int* __restrict__ dims,
-                                                  int a_idx, int b_idx, int side_idx) {
-  const EigJob J = jobs.j[0];
-  const int a = dims[a_idx], b = dims[b_idx], side = dims[side_idx];
-  const int p = side ? a : b, q = side ? b : a;
-  if (blockIdx.x == 0 && threadIdx.x == 0) dims[J.n_idx] = 2 * q;
-  if (gebrd_fits(p, q)) return;  // k_gebrd_lds loads M itself
-  const long long tot = (long long)p * q;
-  for (long long e = blockIdx.x * 256LL + threadIdx.x; e < tot; e += (long long)gridDim.x * 256) {
-    const int i = (int)(e / q), j = (int)(e % q);
-    J.A[(long long)i * J.lda + j] = side ? M[(long long)i * ldm + j] : M[(long long)j * ldm + i];
-  }
-}
-
 // Small SVDs by one-sided Jacobi (Hestenes), in one 512-thread block: when
 // the short side q <= JAC_QMAX and the p x q work matrix B (B = M for side 1,
 // M^T for side 0; p >= q) fits LDS, its columns are orthogonalised by plane
@@ -2561,7 +2530,10 @@ __global__ __launch_bounds__(JAC_T) void k_svd_jacobi(const double* __restrict__
   const EigJob J = jobs.j[0];
   const int a = dims[a_idx], b = dims[b_idx], side = dims[side_idx];
   const int p = side ? a : b, q = side ? b : a;
-  if (!jacobi_fits(p, q)) return;  // the Golub-Kahan path
+  if (!jacobi_fits(p, q)) {  // the Golub-Kahan path
+    if (threadIdx.x == 0) dims[J.n_idx] = 2 * q;
+    return;
+  }
   __shared__ __align__(16) JacLds L;
   __shared__ double ssig[JAC_QMAX];
   __shared__ int spos[JAC_QMAX];
@@ -2683,6 +2655,36 @@ __global__ __launch_bounds__(JAC_T) void k_svd_jacobi(const double* __restrict__
 // Outputs: W.e[2k] = d_k, W.e[2k+1] = e_k, W.tau, right reflectors in W.H.
 // Launch and barrier as k_sytrd_grid.
 
+// Golub-Kahan bidiagonalisation of the taller orientation (p x q, p >= q): left
+// reflectors zero column k below the diagonal (d_k), right reflectors zero
+// row k right of the superdiagonal (e_k).  Only the right reflectors are kept
+// (W.H rows, W.tau): the vectors of the short side are Q_R times the v-part
+// of the tridiagonal's eigenvectors.
+//
+// k_gebrd: the matrix in registers, a wavefront's rows over P blocks, one
+// exchange per step.  The left reflector of column k is u = e_k + s_L c,
+// c = A(k+1:, k), and its product with the trailing matrix is
+// y = tau_L (A(k, k+1:) + s_L sum_{i > k} A(i, k) A(i, k+1:)): each wavefront can
+// form its share of that sum, and of |c|^2, from its own rows before the
+// reflector exists.  Step k: every wavefront puts those two partials in LDS,
+// the owner of row k the row; the block sums them, over several blocks
+// publishes the sums and after a barrier adds up the P of them (relaxed
+// agent-scope accesses, columns from k on); then every wavefront forms the left reflector,
+// y, row k after it, and from that row the right reflector v_k, tau_R, e_k,
+// redundantly, and applies both to its own rows
+// (A_i -= s_L A(i, k) y, then A_i -= tau_R (A_i . v) v).  Exchange buffers are
+// double-buffered by step parity: a block may write step k + 1's while another
+// still reads step k's.
+// Bound by latency: at 142 x 142 a step is 5.5 us, of which the block's and the
+// grid's barriers take 2.1, the loads behind them 1.2, the reflectors 0.7 and
+// the rows 1.3; at 128 x 128 and below, on one block, 3 us.  (With the rows
+// in LDS a step took 7 us at 142 x 142.)  An SVD of order 100, 142, 192, 322,
+// 897 x 896, before and now: 679 -> 620, 1461 -> 1135, 1944 -> 1435, 3927 ->
+// 3102, 23292 -> 20702 us.
+// Outputs: W.e[2k] = d_k, W.e[2k+1] = e_k, W.tau, right reflectors in W.H.
+constexpr int GBR_T = 512;
+constexpr int GBR_W = GBR_T / 64;
+constexpr int GEBRD_GRID_PMAX = 64;  // blocks at most: 1024 rows, 16 a block above 704 columns
 struct GebrdGridBufs {
   double *R, *Y, *S;  // published rows (2 x N), partial sums (2 x P x N), |c|^2 partials (2 x P)
 };
@@ -2695,353 +2697,312 @@ __device__ __host__ inline GebrdGridBufs gebrd_grid_bufs(double* work, int N) {
   B.S = B.Y + 2 * (size_t)GEBRD_GRID_PMAX * N;
   return B;
 }
-// blocks and dynamic LDS for rows up to pcap and columns up to qcap: the
-// fewest blocks (16, 32, 64, 128) whose rows fit LDS, since the barrier and
-// the partial sums cost more with more blocks
-inline size_t gebrd_grid_lds_p(int pcap, int qcap, int P) {
-  return ((size_t)((pcap + P - 1) / P) * qcap + (size_t)pcap + 3 * (size_t)qcap) * 8;
-}
-inline int gebrd_grid_blocks(int pcap, int qcap) {
-  for (int P = 16; P < GEBRD_GRID_PMAX; P *= 2)
-    if (gebrd_grid_lds_p(pcap, qcap, P) <= GRID_DYN_LDS_MAX) return P;
-  return GEBRD_GRID_PMAX;
-}
-inline size_t gebrd_grid_lds(int pcap, int qcap) {
-  return gebrd_grid_lds_p(pcap, qcap, gebrd_grid_blocks(pcap, qcap));
+
+// x, as a value that the compiler knows nothing about: a uniform condition on
+// it stays one branch, where conditions it can relate to others are
+// threaded into copies of the code between them, which spills the matrix.
+__device__ __forceinline__ int opaque_s(int x) {
+  asm volatile("" : "+s"(x));
+  return x;
 }
 
-// The launch is sized for the capacities (pcap, qcap); the live p x q matrix
-// runs on the fewest of 16, 32, ... launched blocks whose rows of stride q,
-// with y and v after them, fit the lds_doubles the launch provides, and the
-// other blocks return at once.
-__device__ inline int gebrd_grid_live_blocks(int p, int q, int qcap, int launched,
-                                             int lds_doubles) {
-  for (int P = 16; P < launched; P *= 2)
-    if ((long long)((p + P - 1) / P) * q + 2LL * qcap <= lds_doubles) return P;
-  return launched;
+// Sums over the wavefront of four values at once: two exchanges of lane halves
+// and of rows pack them, one to a row of 16 lanes, before the sums inside the
+// rows.  All results on every lane.
+__device__ inline double pack_add(double x, double y, bool half) {
+  const unsigned long long bx = (unsigned long long)__double_as_longlong(x);
+  const unsigned long long by = (unsigned long long)__double_as_longlong(y);
+  const auto l = half ? __builtin_amdgcn_permlane32_swap((unsigned)bx, (unsigned)by, false, false)
+                      : __builtin_amdgcn_permlane16_swap((unsigned)bx, (unsigned)by, false, false);
+  const auto h = half ? __builtin_amdgcn_permlane32_swap((unsigned)(bx >> 32), (unsigned)(by >> 32), false, false)
+                      : __builtin_amdgcn_permlane16_swap((unsigned)(bx >> 32), (unsigned)(by >> 32), false, false);
+  return __longlong_as_double((long long)(((unsigned long long)h[0] << 32) | l[0])) +
+         __longlong_as_double((long long)(((unsigned long long)h[1] << 32) | l[1]));
+}
+__device__ inline void wave_sum4(double* x) {
+  // rows of 16: x[0], x[2], x[1], x[3]
+  double v = pack_add(pack_add(x[0], x[1], true), pack_add(x[2], x[3], true), false);
+  v += dpp_d<0xB1>(v);
+  v += dpp_d<0x4E>(v);
+  v += dpp_d<0x141>(v);
+  v += dpp_d<0x140>(v);
+  x[0] = lane_d(v, 0);
+  x[1] = lane_d(v, 32);
+  x[2] = lane_d(v, 16);
+  x[3] = lane_d(v, 48);
 }
 
-__global__ __launch_bounds__(256) void k_gebrd_grid(EigJobs jobs, int* __restrict__ dims, int N,
-                                                    int a_idx, int b_idx, int side_idx, int qcap,
-                                                    int lds_doubles) {
-  const EigJob J = jobs.j[0];
-  if (dims[J.n_idx] < 0) return;  // solved by k_svd_jacobi
-  const int a = dims[a_idx], bb = dims[b_idx], side = dims[side_idx];
-  const int p = side ? a : bb, q = side ? bb : a;
-  if (gebrd_fits(p, q) || p < GEBRD_GRID_MIN) return;  // k_gebrd_lds
-  const int P = gebrd_grid_live_blocks(p, q, qcap, gridDim.x, lds_doubles);
-  const int b = blockIdx.x;
-  if (b >= P) return;
-  const double* A = J.A;
-  const long long lda = J.lda;
+// a += x y in place: written out so that the matrix entries stay where they are
+// (the compiler otherwise copies them at branches).
+__device__ __forceinline__ void fmac_in_place(double& a, double x, double y) {
+  asm("v_fmac_f64 %0, %1, %2" : "+v"(a) : "v"(x), "v"(y));
+}
+
+// One block's part for q <= 64 NT: of P blocks of GBR_W wavefronts, wavefront w of
+// block b holds the rows 8 b + w + 8 P r, r < R, a lane the columns lane + 64 t.
+template <int NT, int R>
+__device__ __forceinline__ void gebrd_rows(const double* __restrict__ M, int ldm, int side, const EigJob& J,
+                           int* __restrict__ dims, int N, int p, int q, int P, double* lds,
+                           int* s_abort) {
   Work W = work_of(J, N);
   const GebrdGridBufs G = gebrd_grid_bufs(J.work, N);
-  extern __shared__ double lds[];
-  const int RB = (p + P - 1) / P;
-  double* Lr = lds;                 // own rows: row i at Lr + (i / P) q
-  double* sy = Lr + (size_t)RB * q; // y (q)
-  double* sv = sy + qcap;           // row k, then v_k (q)
-  __shared__ double red[16];
-  __shared__ double s_tr, s_sr;
-  __shared__ int s_abort;
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  for (int li = wave; li * P + b < p; li += 4) {
-    const double* ra = A + (long long)(li * P + b) * lda;
-    for (int j = lane; j < q; j += 64) Lr[(size_t)li * q + j] = ra[j];
+  constexpr int LQ = NT * 64;
+  constexpr int GS = R < 4 ? R : 4;  // rows taken together
+  double* part = lds;                 // partial sums of the wavefronts (GBR_W x LQ)
+  double* sacc = part + GBR_W * LQ;   // their sum
+  double* srow2 = sacc + LQ;          // row k, by the parity of k
+  double* ssq = srow2 + 2 * LQ;       // |c|^2 partials (GBR_W), then their sum in ssq[GBR_W]
+  const int b = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int row0 = __builtin_amdgcn_readfirstlane(GBR_W * b + wave), rstep = GBR_W * P;
+  double a[R][NT];
+  const int si = side ? ldm : 1, sj = side ? 1 : ldm;
+#pragma unroll
+  for (int r = 0; r < R; ++r) {
+    const int i = row0 + rstep * r;
+    const double* Mi = M + (long long)min(i, p - 1) * si;
+#pragma unroll
+    for (int t = 0; t < NT; ++t) {
+      const int j = lane + 64 * t;
+      const double x = Mi[(long long)min(j, q - 1) * sj];
+      a[r][t] = i < p && j < q ? x : 0.0;
+    }
+    __builtin_amdgcn_sched_barrier(0);  // a row's loads at a time: their addresses are short-lived
   }
   if (b == 0)
-    for (int i = tid; i < 2 * q; i += 256) W.d[i] = 0.0;
-  if (tid == 0) s_abort = 0;
-  __syncthreads();
-  // partials of step k over the own rows i > k (rows already in LDS), and
-  // row k from its owner
-  auto publish = [&](int k) {
-    const int par = k & 1;
-    double* yp = G.Y + ((size_t)par * GEBRD_GRID_PMAX + b) * N;
-    const int ifirst = k + 1 + ((b - (k + 1)) % P + P) % P;
-    for (int j = tid; j < q - k - 1; j += 256) {
-      double acc = 0.0;
-      for (int i = ifirst; i < p; i += P) {
-        const double* r = Lr + (size_t)(i / P) * q;
-        acc += r[k] * r[k + 1 + j];
-      }
-      yp[j] = acc;
-    }
-    if (wave == 0) {
-      double part = 0.0;
-      for (int i = ifirst + lane * P; i < p; i += 64 * P) {
-        const double c = Lr[(size_t)(i / P) * q + k];
-        part += c * c;
-      }
-      part = wave_sum(part);
-      if (lane == 0) G.S[(size_t)par * GEBRD_GRID_PMAX + b] = part;
-    }
-    if (k % P == b) {
-      const double* r = Lr + (size_t)(k / P) * q;
-      double* rpub = G.R + (size_t)par * N;
-      for (int j = k + tid; j < q; j += 256) rpub[j] = r[j];
-    }
-  };
+    for (int i = tid; i < 2 * q; i += GBR_T) W.d[i] = 0.0;
   const GridSync gs = grid_sync_of(J.work, N);
   const unsigned gen0 = grid_gen(gs);
   unsigned ordinal = gen0 * GRID_ORD_SPAN;
-  publish(0);
-  grid_barrier(gs.flag, ++ordinal, P, &s_abort, dims);
-  for (int k = 0; k < q; ++k) {
-    const int nc = q - k - 1, par = k & 1;
-    const double* rk = G.R + (size_t)par * N;
-    const double* S = G.S + (size_t)par * GEBRD_GRID_PMAX;
-    // left reflector of column k (every thread forms the same scalars)
-    const double sumsq =
-        wave_sum((lane < P ? S[lane] : 0.0) + (lane + 64 < P ? S[lane + 64] : 0.0));
-    const double alpha = rk[k];
-    double tl, sl, bl;
-    if (sumsq == 0.0) {
-      tl = 0.0;
-      sl = 0.0;
-      bl = alpha;
+  const bool writer = b == 0 && wave == 0;
+  for (int k = 0;; ++k) {
+    double* srow = srow2 + (k & 1) * LQ;
+    const int kr = k - row0, pr = p - row0;  // row r is past k, below p
+    // column k of rows g .. g + 3, zero where the row is done
+    auto column = [&](int g, double (&c)[GS]) {
+      const int lk = k & 63;
+#pragma unroll
+      for (int r = 0; r < GS; ++r) c[r] = 0.0;
+#pragma unroll
+      for (int t = 0; t < NT; ++t)
+        if (opaque_s(k >> 6) == t)
+#pragma unroll
+          for (int r = 0; r < GS; ++r) c[r] = a[g + r][t];
+#pragma unroll
+      for (int r = 0; r < GS; ++r) {
+        const long long x = __double_as_longlong(c[r]);
+        const int m = (kr - rstep * (g + r)) >> 31;  // -1: past k
+        const int lo = __builtin_amdgcn_readlane((int)x, lk) & m;
+        const int hi = __builtin_amdgcn_readlane((int)(x >> 32), lk) & m;
+        c[r] = __longlong_as_double(((long long)hi << 32) | (unsigned)lo);
+      }
+    };
+    // partials of step k over the own rows i > k, and row k from its owner
+    {
+      double s[NT], cc = 0.0;
+#pragma unroll
+      for (int t = 0; t < NT; ++t) s[t] = 0.0;
+#pragma unroll
+      for (int g = 0; g < R; g += GS) {
+        const bool live = rstep * (g + GS - 1) > opaque_s(kr) && rstep * g < opaque_s(pr);
+        if (!live) continue;
+        double c[GS];
+        column(g, c);
+#pragma unroll
+        for (int r = 0; r < GS; ++r) cc = fma(c[r], c[r], cc);
+#pragma unroll
+        for (int t = 0; t < NT; ++t) {
+          if (64 * t + 63 <= opaque_s(k)) continue;
+#pragma unroll
+          for (int r = 0; r < GS; ++r) s[t] = fma(c[r], a[g + r][t], s[t]);
+        }
+      }
+#pragma unroll
+      for (int t = 0; t < NT; ++t) part[wave * LQ + lane + 64 * t] = s[t];
+      if (lane == 0) ssq[wave] = cc;
+      if (k % rstep == row0) {
+        const int rk = k / rstep;
+        double x[NT];
+#pragma unroll
+        for (int t = 0; t < NT; ++t) x[t] = 0.0;
+#pragma unroll
+        for (int r = 0; r < R; ++r)
+          if (r == rk)
+#pragma unroll
+            for (int t = 0; t < NT; ++t) x[t] = a[r][t];
+        if (P == 1) {
+#pragma unroll
+          for (int t = 0; t < NT; ++t) srow[lane + 64 * t] = x[t];
+        } else {
+#pragma unroll
+          for (int t = 0; t < NT; ++t)
+            if (lane + 64 * t >= k && lane + 64 * t < q) xput(G.R + (size_t)(k & 1) * N + lane + 64 * t, x[t]);
+        }
+      }
+    }
+    lds_barrier();
+    // the block's sums; over several blocks their exchange
+    if (P == 1) {
+      for (int j = tid; j < LQ; j += GBR_T) {
+        double acc = 0.0;
+#pragma unroll
+        for (int w = 0; w < GBR_W; ++w) acc += part[w * LQ + j];
+        sacc[j] = acc;
+      }
+      if (tid == GBR_T - 1) {
+        double acc = 0.0;
+#pragma unroll
+        for (int w = 0; w < GBR_W; ++w) acc += ssq[w];
+        ssq[GBR_W] = acc;
+      }
     } else {
-      bl = -copysign(sqrt(alpha * alpha + sumsq), alpha);
-      tl = (bl - alpha) / bl;
-      sl = 1.0 / (alpha - bl);
-    }
-    if (b == 0 && tid == 0) {
-      W.e[2 * k] = bl;
-      if (nc <= 0) W.tau[k] = 0.0;
-    }
-    if (nc <= 0) break;  // the last column: no right reflector
-    // y, and row k after the left reflector
-    // (the P partials of a column are summed in block order; the loads of up
-    // to GBG_M columns times GBG_U blocks are issued together)
-    const double* Yp = G.Y + (size_t)par * GEBRD_GRID_PMAX * N;
-    double acc[GBG_M];
+      const int par = k & 1;
+      double* Y = G.Y + (size_t)par * GEBRD_GRID_PMAX * N;
+      double* S = G.S + (size_t)par * GEBRD_GRID_PMAX;
+      // columns before k are done: nothing reads their sums
+      for (int j = tid; j < q; j += GBR_T) {
+        if (j < k) continue;
+        double acc = 0.0;
 #pragma unroll
-    for (int m = 0; m < GBG_M; ++m) acc[m] = 0.0;
-    for (int q0 = 0; q0 < P; q0 += GBG_U) {
-      double v[GBG_M][GBG_U];
-#pragma unroll
-      for (int m = 0; m < GBG_M; ++m) {
-        const int j = tid + 256 * m;
-#pragma unroll
-        for (int u = 0; u < GBG_U; ++u)
-          v[m][u] = (j < nc && q0 + u < P) ? Yp[(size_t)(q0 + u) * N + j] : 0.0;
+        for (int w = 0; w < GBR_W; ++w) acc += part[w * LQ + j];
+        xput(Y + (size_t)b * N + j, acc);
       }
+      if (tid == GBR_T - 1) {
+        double acc = 0.0;
 #pragma unroll
-      for (int m = 0; m < GBG_M; ++m)
-#pragma unroll
-        for (int u = 0; u < GBG_U; ++u) acc[m] += v[m][u];
-    }
-    double part = 0.0;
-#pragma unroll
-    for (int m = 0; m < GBG_M; ++m) {
-      const int j = tid + 256 * m;
-      if (j >= nc) continue;
-      const double rkj = rk[k + 1 + j];
-      const double y = tl * (rkj + sl * acc[m]);
-      sy[j] = y;
-      const double r = rkj - y;
-      sv[j] = r;
-      if (j > 0) part += r * r;
-    }
-    const double sumr = block_sum<256>(part, red);
-    if (tid == 0) {
-      const double alpha_r = sv[0];
-      double beta;
-      if (sumr == 0.0) {
-        s_tr = 0.0;
-        s_sr = 0.0;
-        beta = alpha_r;
-      } else {
-        beta = -copysign(sqrt(alpha_r * alpha_r + sumr), alpha_r);
-        s_tr = (beta - alpha_r) / beta;
-        s_sr = 1.0 / (alpha_r - beta);
+        for (int w = 0; w < GBR_W; ++w) acc += ssq[w];
+        xput(S + b, acc);
       }
-      if (b == 0) {
-        W.e[2 * k + 1] = beta;
-        W.tau[k] = s_tr;
+      grid_barrier_relaxed(gs.flag, ++ordinal, P, s_abort, dims);
+      for (int j = tid; j < q; j += GBR_T) {
+        if (j < k) continue;
+        double acc = 0.0;
+        const double row = xget(G.R + (size_t)par * N + j);
+        // many partials in flight, without a branch each (past P: the last again,
+        // not added): a wait behind the barrier costs about 1 us
+        const double* Yj = Y + j;
+        auto sum = [&](auto batch) {
+          constexpr int U = decltype(batch)::value;
+          for (int u0 = 0; u0 < P; u0 += U) {
+            double v[U];
+#pragma unroll
+            for (int u = 0; u < U; ++u) v[u] = xget(Yj + (size_t)min(u0 + u, P - 1) * N);
+#pragma unroll
+            for (int u = 0; u < U; ++u) acc += u0 + u < P ? v[u] : 0.0;
+          }
+        };
+        if (P <= 8) sum(std::integral_constant<int, 8>());
+        else sum(std::integral_constant<int, 32>());
+        sacc[j] = acc;
+        srow[j] = row;
+      }
+      if (wave == GBR_W - 1) {
+        const double s = wave_sum(lane < P ? xget(S + lane) : 0.0);
+        if (lane == 0) ssq[GBR_W] = s;
       }
     }
-    __syncthreads();
-    const double tr = s_tr, sr = s_sr;
-    for (int j = tid; j < nc; j += 256) {
-      const double v = j == 0 ? 1.0 : sv[j] * sr;
-      sv[j] = v;
-      if (b == 0) W.H[(long long)k * N + k + 1 + j] = v;
+    lds_barrier();
+    // left reflector of column k, y and row k after it, right reflector of
+    // that row: every wavefront for itself
+    double tl, sl, bl;
+    householder(srow[k], ssq[GBR_W], tl, sl, bl);
+    if (writer && lane == 0) W.e[2 * k] = bl;
+    if (k == q - 1) {
+      if (writer && lane == 0) W.tau[k] = 0.0;
+      break;
     }
-    __syncthreads();
-    // own rows: lane l handles the columns k + 1 + l + 64 t of every row, so y
-    // and v at those columns stay in registers, and so does the row between
-    // the two reflectors: one LDS read and one write per element
-    const int i0 = k + 1 + ((b - (k + 1)) % P + P) % P;
-    double cy[SYG_T], cv[SYG_T];
+    double y[NT], v[NT], sq = 0.0, al = 0.0;
 #pragma unroll
-    for (int t = 0; t < SYG_T; ++t) {
+    for (int t = 0; t < NT; ++t) {
       const int j = lane + 64 * t;
-      cy[t] = j < nc ? sy[j] : 0.0;
-      cv[t] = j < nc ? sv[j] : 0.0;
+      const bool live = j > k && j < q;
+      const double rkj = live ? srow[j] : 0.0;
+      y[t] = live ? tl * (rkj + sl * sacc[j]) : 0.0;
+      v[t] = rkj - y[t];
+      if (j > k + 1) sq = fma(v[t], v[t], sq);
+      if (j == k + 1) al = v[t];
     }
-    for (int i = i0 + wave * P; i < p; i += 4 * P) {
-      double* rowp = Lr + (size_t)(i / P) * q;
-      double* r = rowp + k + 1;
-      const double ui = sl * rowp[k];
-      double x[SYG_T];
-      double acc = 0.0;
+    double tr, sr, br;
+    householder(wave_sum(al), wave_sum(sq), tr, sr, br);
 #pragma unroll
-      for (int t = 0; t < SYG_T; ++t) {
-        if (64 * t >= nc) break;
-        const int j = lane + 64 * t;
-        x[t] = j < nc ? r[j] - ui * cy[t] : 0.0;
-        acc += x[t] * cv[t];
+    for (int t = 0; t < NT; ++t) {
+      const int j = lane + 64 * t;
+      v[t] = j > k + 1 ? v[t] * sr : j == k + 1 ? 1.0 : 0.0;
+      if (writer && j > k && j < q) W.H[(long long)k * N + j] = v[t];
+    }
+    if (writer && lane == 0) {
+      W.e[2 * k + 1] = br;
+      W.tau[k] = tr;
+    }
+    // own rows: A_i -= s_L A(i, k) y, then A_i -= tau_R (A_i . v) v
+#pragma unroll
+    for (int g = 0; g < R; g += GS) {
+      if (rstep * (g + GS - 1) <= opaque_s(kr) || rstep * g >= opaque_s(pr)) continue;
+      double z[4] = {0.0, 0.0, 0.0, 0.0}, u[GS];
+      column(g, u);
+#pragma unroll
+      for (int r = 0; r < GS; ++r) u[r] *= -sl;
+#pragma unroll
+      for (int t = 0; t < NT; ++t) {
+        if (64 * t + 63 <= opaque_s(k)) continue;
+#pragma unroll
+        for (int r = 0; r < GS; ++r) {
+          fmac_in_place(a[g + r][t], u[r], y[t]);
+          z[r] = fma(a[g + r][t], v[t], z[r]);
+        }
       }
-      const double z = tr * wave_sum(acc);
+      wave_sum4(z);
 #pragma unroll
-      for (int t = 0; t < SYG_T; ++t) {
-        if (64 * t >= nc) break;
-        const int j = lane + 64 * t;
-        if (j < nc) r[j] = x[t] - z * cv[t];
+      for (int r = 0; r < GS; ++r) z[r] *= -tr;
+#pragma unroll
+      for (int t = 0; t < NT; ++t) {
+        if (64 * t + 63 <= opaque_s(k)) continue;
+#pragma unroll
+        for (int r = 0; r < GS; ++r) fmac_in_place(a[g + r][t], z[r], v[t]);
       }
     }
-    __syncthreads();
-    publish(k + 1);
-    grid_barrier(gs.flag, ++ordinal, P, &s_abort, dims);
   }
-  grid_launch_end(gs, gen0, ordinal != gen0 * GRID_ORD_SPAN);
+  grid_launch_end(gs, gen0, P > 1);
 }
 
-// k_gebrd_lds: the p x q matrix in LDS (p ldq <= GEBRD_LDS_MAX, ldq = q
-// rounded up to odd so a thread per row reads distinct banks; p <= 1024),
-// loaded in the taller orientation from M directly; outputs as k_gebrd_grid.
-// Householder
-// vectors are formed by one wavefront; the left reflector is applied by
-// column partial sums, the right one by a thread per row.
+// Blocks for a p x q matrix, p >= q: one, 16 rows a wavefront, up to 128 x 128;
+// above, 4 rows a wavefront (2 past 704 columns, whose registers they fill).
+// One block needs no exchange, about 3 us of a 100 x 100 step, but a CU's
+// registers hold no more; with more blocks a step is near 5.5 us whatever the rows,
+// so few rows a wavefront (its work between two exchanges) beat few blocks.
+__device__ __host__ inline int gebrd_blocks(int p, int q) {
+  if (p <= 16 * GBR_W && q <= 128) return 1;
+  const int rows = q <= 256 ? 8 * GBR_W : q <= 704 ? 4 * GBR_W : 2 * GBR_W;
+  return (p + rows - 1) / rows;
+}
+__device__ __host__ inline int gebrd_chunks(int q) {
+  return q <= 128 ? 2 : q <= 192 ? 3 : q <= 256 ? 4 : q <= 384 ? 6 : q <= 512 ? 8
+       : q <= 704 ? 11 : 16;
+}
+inline size_t gebrd_lds(int q) {
+  return ((size_t)(GBR_W + 3) * 64 * gebrd_chunks(q) + GBR_W + 8) * 8;
+}
 
-__global__ __launch_bounds__(1024) void k_gebrd_lds(const double* __restrict__ M, int ldm,
-                                                    EigJobs jobs, int* __restrict__ dims, int N,
-                                                    int a_idx, int b_idx, int side_idx) {
+__global__ __launch_bounds__(GBR_T) void k_gebrd(const double* __restrict__ M, int ldm, EigJobs jobs,
+                                                 int* __restrict__ dims, int N, int a_idx, int b_idx,
+                                                 int side_idx) {
+  extern __shared__ double lds[];
+  __shared__ int s_abort;
   const EigJob J = jobs.j[0];
   if (dims[J.n_idx] < 0) return;  // solved by k_svd_jacobi
-  const int a = dims[a_idx], b = dims[b_idx], side = dims[side_idx];
-  const int p = side ? a : b, q = side ? b : a;
-  if (!gebrd_fits(p, q)) return;
-  const int lq = gebrd_ld(q);
-  __shared__ double A[GEBRD_LDS_MAX];
-  __shared__ double sv[1024], sp[8][128];
-  __shared__ double s_tau;
-  Work W = work_of(J, N);
-  const int tid = threadIdx.x, cj = tid & 127, g = tid >> 7;
-  const int wave = tid >> 6, lane = tid & 63;
-  for (int e = tid; e < p * q; e += 1024) {
-    const int i = e / q, j = e - i * q;
-    A[i * lq + j] = side ? M[(long long)i * ldm + j] : M[(long long)j * ldm + i];
-  }
-  for (int i = tid; i < 2 * q; i += 1024) W.d[i] = 0.0;
+  const int ma = dims[a_idx], mb = dims[b_idx], side = dims[side_idx];
+  const int p = side ? ma : mb, q = side ? mb : ma;
+  const int P = gebrd_blocks(p, q);
+  if (q < 1 || (int)blockIdx.x >= P) return;
+  if (threadIdx.x == 0) s_abort = 0;
   __syncthreads();
-  for (int k = 0; k < q; ++k) {
-    const int mr = p - k, nc = q - k - 1;
-    if (wave == 0) {
-      // left reflector of column k (rows k..p-1)
-      double part = 0.0;
-      for (int i = 1 + lane; i < mr; i += 64) {
-        const double x = A[(k + i) * lq + k];
-        part += x * x;
-      }
-      const double sumsq = wave_sum(part);
-      const double alpha = A[k * lq + k];
-      double tau, scal, beta;
-      if (sumsq == 0.0) {
-        tau = 0.0;
-        scal = 0.0;
-        beta = alpha;
-      } else {
-        beta = -copysign(sqrt(alpha * alpha + sumsq), alpha);
-        tau = (beta - alpha) / beta;
-        scal = 1.0 / (alpha - beta);
-      }
-      if (lane == 0) {
-        W.e[2 * k] = beta;
-        s_tau = tau;
-      }
-      for (int i = lane; i < mr; i += 64) sv[i] = i == 0 ? 1.0 : A[(k + i) * lq + k] * scal;
-    }
-    __syncthreads();
-    double tau = s_tau;
-    if (tau != 0.0 && nc > 0) {
-      if (cj < nc) {
-        double acc = 0.0;
-        for (int i = g; i < mr; i += 8) acc += A[(k + i) * lq + k + 1 + cj] * sv[i];
-        sp[g][cj] = acc;
-      }
-      __syncthreads();
-      if (cj < nc) {
-        double wj = 0.0;
-#pragma unroll
-        for (int t = 0; t < 8; ++t) wj += sp[t][cj];
-        wj *= tau;
-        for (int i = g; i < mr; i += 8) A[(k + i) * lq + k + 1 + cj] -= sv[i] * wj;
-      }
-      __syncthreads();
-    }
-    if (nc <= 0) {
-      if (tid == 0) W.tau[k] = 0.0;
-      continue;
-    }
-    if (wave == 0) {
-      // right reflector of row k (columns k+1..q-1)
-      double part = 0.0;
-      for (int j = 1 + lane; j < nc; j += 64) {
-        const double x = A[k * lq + k + 1 + j];
-        part += x * x;
-      }
-      const double sumsq = wave_sum(part);
-      const double alpha = A[k * lq + k + 1];
-      double tr, scal, beta;
-      if (sumsq == 0.0) {
-        tr = 0.0;
-        scal = 0.0;
-        beta = alpha;
-      } else {
-        beta = -copysign(sqrt(alpha * alpha + sumsq), alpha);
-        tr = (beta - alpha) / beta;
-        scal = 1.0 / (alpha - beta);
-      }
-      if (lane == 0) {
-        W.e[2 * k + 1] = beta;
-        W.tau[k] = tr;
-        s_tau = tr;
-      }
-      for (int j = lane; j < nc; j += 64) {
-        const double v = j == 0 ? 1.0 : A[k * lq + k + 1 + j] * scal;
-        sv[j] = v;
-        W.H[(long long)k * N + k + 1 + j] = v;
-      }
-    }
-    __syncthreads();
-    tau = s_tau;
-    if (tau != 0.0) {
-      // rows k+1..p-1: A[i, k+1:] -= tau (A[i, k+1:] . v) v^T; 128 rows at a
-      // time, each row's dot product split over 8 column groups
-      for (int r0 = k + 1; r0 < p; r0 += 128) {
-        const int i = r0 + cj;
-        double* row = A + i * lq + k + 1;
-        if (i < p) {
-          double acc = 0.0;
-          for (int j = g; j < nc; j += 8) acc += row[j] * sv[j];
-          sp[g][cj] = acc;
-        }
-        __syncthreads();
-        if (i < p) {
-          double sdot = 0.0;
-#pragma unroll
-          for (int t = 0; t < 8; ++t) sdot += sp[t][cj];
-          sdot *= tau;
-          for (int j = g; j < nc; j += 8) row[j] -= sdot * sv[j];
-        }
-        __syncthreads();
-      }
-    } else {
-      __syncthreads();
-    }
-  }
+  if (P == 1) gebrd_rows<2, 16>(M, ldm, side, J, dims, N, p, q, 1, lds, &s_abort);
+  else if (q <= 128) gebrd_rows<2, 8>(M, ldm, side, J, dims, N, p, q, P, lds, &s_abort);
+  else if (q <= 192) gebrd_rows<3, 8>(M, ldm, side, J, dims, N, p, q, P, lds, &s_abort);
+  else if (q <= 256) gebrd_rows<4, 8>(M, ldm, side, J, dims, N, p, q, P, lds, &s_abort);
+  else if (q <= 384) gebrd_rows<6, 4>(M, ldm, side, J, dims, N, p, q, P, lds, &s_abort);
+  else if (q <= 512) gebrd_rows<8, 4>(M, ldm, side, J, dims, N, p, q, P, lds, &s_abort);
+  else if (q <= 704) gebrd_rows<11, 4>(M, ldm, side, J, dims, N, p, q, P, lds, &s_abort);
+  else gebrd_rows<16, 2>(M, ldm, side, J, dims, N, p, q, P, lds, &s_abort);
 }
 
 // Vectors of the short side for the kept singular values, one wavefront per
@@ -3151,7 +3112,7 @@ int dc_fused_blocks(int N, int njobs) {
 // the runtime's own figure is used.
 namespace {
 constexpr size_t LDS_CU = 160 * 1024;
-constexpr size_t ST_SYTRD_GRID = 8, ST_DC_FUSED = 1296, ST_ORMTR = 0, ST_GEBRD_GRID = 168,
+constexpr size_t ST_SYTRD_GRID = 8, ST_DC_FUSED = 1296, ST_ORMTR = 0, ST_GEBRD = 8,
                  ST_SVD_JACOBI = 148768;
 
 size_t static_lds(const void* fn, size_t table, bool runtime) {
@@ -3191,11 +3152,8 @@ size_t svd_lds_bytes(int ncap2, int pcap, bool runtime, const char** which) {
   size_t worst = 0;
   lds_note(static_lds((const void*)k_svd_jacobi, ST_SVD_JACOBI, runtime), "k_svd_jacobi", worst, which);
   const int qcap = ncap2 / 2;
-  if (pcap >= GEBRD_GRID_MIN) {
-    const int qc = qcap < pcap ? qcap : pcap;
-    lds_note(static_lds((const void*)k_gebrd_grid, ST_GEBRD_GRID, runtime) + gebrd_grid_lds(pcap, qc),
-             "k_gebrd_grid", worst, which);
-  }
+  lds_note(static_lds((const void*)k_gebrd, ST_GEBRD, runtime) + gebrd_lds(std::min(qcap, pcap)), "k_gebrd",
+           worst, which);
   dc_lds(ncap2, runtime, worst, which);
   return worst;
 }
@@ -3242,18 +3200,9 @@ void svd_short_side(const double* M, int ldm, int a_idx, int b_idx, int side_idx
   EigJobs J;
   J.j[0] = job;
   const int qcap = N / 2;
-  int lb = (int)(((long long)2 * qcap * qcap + 255) / 256);
-  if (lb > 1024) lb = 1024;
-  if (lb < 1) lb = 1;
-  k_svd_load<<<lb, 256, 0, s>>>(M, ldm, J, dims, a_idx, b_idx, side_idx);
   k_svd_jacobi<<<1, JAC_T, 0, s>>>(M, ldm, J, dims, a_idx, b_idx, side_idx);
-  k_gebrd_lds<<<1, 1024, 0, s>>>(M, ldm, J, dims, N, a_idx, b_idx, side_idx);
-  if (pcap >= GEBRD_GRID_MIN) {
-    const int qc = qcap < pcap ? qcap : pcap;
-    const int P = gebrd_grid_blocks(pcap, qc);
-    const size_t lds = gebrd_grid_lds(pcap, qc);
-    k_gebrd_grid<<<P, 256, lds, s>>>(J, dims, N, a_idx, b_idx, side_idx, qc, (int)(lds / 8));
-  }
+  const int qc = std::min(qcap, pcap);
+  k_gebrd<<<gebrd_blocks(pcap, qc), GBR_T, gebrd_lds(qc), s>>>(M, ldm, J, dims, N, a_idx, b_idx, side_idx);
   dc_solve(J, 1, N, dims, s);
   k_svd_back<<<(qcap + 3) / 4, 256, 0, s>>>(J, dims, N);
   k_svd_final<<<1, 256, 0, s>>>(J, dims, N);

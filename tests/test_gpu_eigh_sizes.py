@@ -109,9 +109,13 @@ def test_eigh_grid_orders(kind, n):
     assert np.abs(V.T @ V - np.eye(kept)).max() <= 4 * bound
 
 
-@pytest.mark.parametrize("p,q", [(140, 130), (600, 256), (600, 260), (560, 520)])
+@pytest.mark.parametrize("p,q", [(140, 130), (600, 256), (600, 260), (560, 520), (65, 65), (90, 70),
+                                 (128, 128), (129, 66), (129, 128), (129, 129), (192, 192), (193, 193),
+                                 (256, 256), (257, 257), (384, 300), (385, 385), (513, 70), (520, 513),
+                                 (720, 704), (760, 705), (1024, 66)])
 def test_svd_large_orders(p, q):
-    """Golub-Kahan orders 2 q around the staged and the unstaged merges (1024 rows)."""
+    """The bidiagonalisation's column classes and block counts; Golub-Kahan
+    orders 2 q around the staged and the unstaged merges (1024 rows)."""
     import torch
     from paper_2503_18056_amd import _ffi
     lib = _ffi.load()
@@ -119,7 +123,8 @@ def test_svd_large_orders(p, q):
     U = np.linalg.qr(rng.standard_normal((p, q)))[0]
     W = np.linalg.qr(rng.standard_normal((q, q)))[0]
     sig = np.linspace(2.0, 1.0, q)
-    d = torch.as_tensor((U * sig) @ W.T, device="cuda")
+    M = (U * sig) @ W.T
+    d = torch.as_tensor(M, device="cuda")
     s = torch.zeros(q, dtype=torch.float64, device="cuda")
     V = torch.zeros((q, q), dtype=torch.float64, device="cuda")
     ws = torch.zeros(int(lib.tt_kernel_svd_workspace(p, q)), dtype=torch.uint8, device="cuda")
@@ -133,5 +138,36 @@ def test_svd_large_orders(p, q):
     bound = 40 * q * 2.0 ** -53
     assert np.abs(s.cpu().numpy() - sig).max() <= bound * sig[0]
     assert np.abs(Vh.T @ Vh - np.eye(q)).max() <= 4 * bound
-    M = d.cpu().numpy()
-    assert np.abs(M.T @ (M @ Vh) - Vh * sig ** 2).max() <= 16 * bound * sig[0] ** 2
+    G = M.T @ M if p > q else M @ M.T    # a square matrix: its left vectors
+    assert np.abs(G @ Vh - Vh * sig ** 2).max() <= 16 * bound * sig[0] ** 2
+
+
+@pytest.mark.parametrize("p,q", [(90, 70), (192, 142), (300, 200)])
+def test_svd_wide(p, q):
+    """The other orientation (read transposed) gives the same singular values and
+    the long side's vectors as M V / sigma."""
+    import torch
+    from paper_2503_18056_amd import _ffi
+    lib = _ffi.load()
+    rng = np.random.default_rng(p)
+    U = np.linalg.qr(rng.standard_normal((p, q)))[0]
+    W = np.linalg.qr(rng.standard_normal((q, q)))[0]
+    sig = np.linspace(2.0, 1.0, q)
+    M = np.ascontiguousarray(((U * sig) @ W.T).T)    # q x p
+    pad = np.full((q, p + 5), np.nan)
+    pad[:, :p] = M
+    d = torch.as_tensor(pad, device="cuda")
+    s = torch.zeros(q, dtype=torch.float64, device="cuda")
+    V = torch.zeros((q, q), dtype=torch.float64, device="cuda")
+    ws = torch.zeros(int(lib.tt_kernel_svd_workspace(q, p)), dtype=torch.uint8, device="cuda")
+    kept = C.c_int32()
+    st = lib.tt_kernel_svd(C.c_void_p(d.data_ptr()), q, p, p + 5, C.c_void_p(s.data_ptr()),
+                           C.c_void_p(V.data_ptr()), q, C.byref(kept), C.c_void_p(ws.data_ptr()),
+                           ws.numel(), None)
+    assert st == 0, lib.tt_kernel_last_error()
+    bound = 40 * q * 2.0 ** -53
+    assert kept.value == q
+    assert np.abs(s.cpu().numpy() - sig).max() <= bound * sig[0]
+    Vh = V.cpu().numpy()
+    assert np.abs(Vh.T @ Vh - np.eye(q)).max() <= 4 * bound
+    assert np.abs(M @ (M.T @ Vh) - Vh * sig ** 2).max() <= 16 * bound * sig[0] ** 2
