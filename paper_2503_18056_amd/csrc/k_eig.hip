@@ -10,7 +10,7 @@
 //      one persistent launch: the merges up to 64 rows on one block each, above
 //      that one wavefront per secular root and products in tiles over the
 //      blocks, with grid barriers between the phases.
-//   3. Back-transformation V = Q Z, one wavefront per kept vector.
+//   3. Back-transformation V = Q Z, a wavefront per kept vector.
 //   4. Descending order, sign gauge (largest |entry| positive), clip rule.
 // The same divide and conquer also serves the small SVD of M (section 5).
 #include <float.h>
@@ -2058,41 +2058,50 @@ __host__ __device__ inline int ormtr_chunk(int N) {
   c = c < ORM_G ? ORM_G : (c > ORM_CH ? ORM_CH : c);
   return c - c % ORM_G;
 }
-__host__ __device__ inline size_t ormtr_lds_doubles(int N) {
-  const int ch = ormtr_chunk(N);
-  return (size_t)ch * ormtr_ld(N) + (size_t)(ch / ORM_G) * 16 + ch;
+// for every live order up to N
+inline size_t ormtr_lds_doubles(int N) {
+  return (size_t)std::min(std::max(ORM_CH * ormtr_ld(N), ORM_G * ormtr_ld(N)), ORM_LDS_DBL) +
+         (ORM_CH / ORM_G) * 16 + ORM_CH;
 }
 
 // VPW vectors per wavefront (4 VPW per block): every block stages all the
-// reflectors, so at large orders (capacity above 640), where the blocks
+// reflectors, so at large orders (above 640), where the blocks
 // outnumber the CUs and the staging traffic (blocks x reflector bytes) bounds
 // the launch, each wavefront carries four vectors through the same staged
-// chunks; below that one vector a wavefront is faster.
-template <int NCH, int VPW>
-__global__ __launch_bounds__(256) void k_ormtr(EigJobs jobs, int* __restrict__ dims, int N) {
-  const EigJob J = jobs.j[blockIdx.y];
-  const int n = dims[J.n_idx];
-  const int par = dc_par(n);
+// chunks; below that one vector a wavefront is faster.  The choice follows the
+// live order: at capacity 641 the back-transformations of a step of live
+// orders up to 206 took 72 us on average by the capacity's choice, 26 by their own.
+// SVD: the vectors of the short side instead, n = q of a tridiagonal of order
+// 2 q: y is the even entries of the tridiagonal's eigenvector, normalised (the
+// +-sigma pair's mixing only rescales its v-part), and the reflectors are the
+// bidiagonalisation's right ones.
+template <bool SVD, int NCH, int VPW>
+__device__ __forceinline__ void ormtr_vectors(const EigJob& J, int* __restrict__ dims, int N, int nt,
+                                              double* hs) {
+  const int n = SVD ? nt / 2 : nt;
+  const int par = dc_par(nt);
   Work W = work_of(J, N);
   DC D = dc_of(W, N);
   const int N2 = next_pow2(N);
-  const int ch = ormtr_chunk(N), ld = ormtr_ld(N), gpc = ch / ORM_G;
+  const int ch = ormtr_chunk(n), ld = ormtr_ld(n), gpc = ch / ORM_G;
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
   const int j0 = blockIdx.x * 4 * VPW;
   if (j0 >= n) return;
-  const double thr = keep_threshold(J, D.lam, n);
+  const int c0 = nt - n;  // the n largest of the tridiagonal's nt
+  const double* lam = D.lam + c0;
+  const double thr = keep_threshold(J, D.lam, nt);
   // eigenvalues ascend, so the block's last vector is its largest
-  if (!(D.lam[min(j0 + 4 * VPW - 1, n - 1)] > thr)) return;
+  if (!(lam[min(j0 + 4 * VPW - 1, n - 1)] > thr)) return;
   // vector v of this wavefront: j = j0 + 4 v + wave
   bool active[VPW];
   bool any = false;
 #pragma unroll
   for (int v = 0; v < VPW; ++v) {
     const int j = j0 + 4 * v + wave;
-    active[v] = j < n && D.lam[j] > thr;
+    active[v] = j < n && lam[j] > thr;
     any = any || active[v];
   }
-  extern __shared__ double hs[];  // ch reflectors (rows 0 .. ld - 1), each group's T, the taus
+  // hs: ch reflectors (rows 0 .. ld - 1), each group's T, the taus
   double* Ts = hs + (size_t)ch * ld;
   double* taus = Ts + (size_t)gpc * 16;
   double y[VPW][NCH];
@@ -2101,9 +2110,21 @@ __global__ __launch_bounds__(256) void k_ormtr(EigJobs jobs, int* __restrict__ d
 #pragma unroll
     for (int c = 0; c < NCH; ++c) {
       const int i = lane + 64 * c, j = j0 + 4 * v + wave;
-      y[v][c] = active[v] && i < n ? (par ? D.Qb : D.Qa)[(size_t)i * N2 + j] : 0.0;
+      y[v][c] = active[v] && i < n ? (par ? D.Qb : D.Qa)[(size_t)(SVD ? 2 * i : i) * N2 + c0 + j] : 0.0;
     }
-  const int nref = n - 2;  // reflectors 0 .. n - 3
+  if (SVD) {
+#pragma unroll
+    for (int v = 0; v < VPW; ++v) {
+      double part = 0.0;
+#pragma unroll
+      for (int c = 0; c < NCH; ++c) part = fma(y[v][c], y[v][c], part);
+      const double nrm = sqrt(wave_sum(part));
+      const double inv = nrm > 0.0 ? 1.0 / nrm : 0.0;
+#pragma unroll
+      for (int c = 0; c < NCH; ++c) y[v][c] *= inv;
+    }
+  }
+  const int nref = SVD ? n - 1 : n - 2;  // reflectors 0 .. nref - 1
   const int ngrp = nref > 0 ? (nref + ORM_G - 1) / ORM_G : 0;
   for (int g1 = ngrp - 1; g1 >= 0; g1 -= gpc) {
     const int g0 = max(0, g1 - gpc + 1), kbase = ORM_G * g0, nr = ORM_G * (g1 - g0 + 1);
@@ -2224,6 +2245,19 @@ __global__ __launch_bounds__(256) void k_ormtr(EigJobs jobs, int* __restrict__ d
   }
 }
 
+template <bool SVD>
+__global__ __launch_bounds__(256) void k_ormtr(EigJobs jobs, int* __restrict__ dims, int N) {
+  extern __shared__ double hs[];
+  const EigJob& J = jobs.j[blockIdx.y];
+  const int nt = dims[J.n_idx];
+  if (nt < 0) return;  // an SVD solved by k_svd_jacobi
+  const int n = SVD ? nt / 2 : nt;
+  if (n <= 192) ormtr_vectors<SVD, 3, 1>(J, dims, N, nt, hs);
+  else if (n <= 384) ormtr_vectors<SVD, 6, 1>(J, dims, N, nt, hs);
+  else if (n <= 640) ormtr_vectors<SVD, 10, 1>(J, dims, N, nt, hs);
+  else ormtr_vectors<SVD, 16, 4>(J, dims, N, nt, hs);
+}
+
 // Sign gauge of columns c < ncol of V (rows < nrow): the largest-magnitude
 // entry (first on ties) made positive; a wavefront per column (256-thread
 // block, four columns at a time).
@@ -2251,9 +2285,12 @@ __device__ void gauge_columns(double* V, int ldv, int nrow, int ncol) {
 // block takes 16 columns of the gauge (and recounts the kept eigenvalues from
 // an LDS copy of them); block 0 also writes the count and the scalings.
 constexpr int FINAL_COLS = 4;  // one column per wavefront: the gauge is latency-bound
+template <bool SVD>
 __global__ __launch_bounds__(256) void k_eig_final(EigJobs jobs, int* __restrict__ dims, int N) {
   const EigJob J = jobs.j[blockIdx.y];
-  const int n = dims[J.n_idx];
+  const int nt = dims[J.n_idx];  // order of the tridiagonal
+  if (nt < 0) return;  // an SVD solved by k_svd_jacobi
+  const int n = SVD ? nt / 2 : nt;
   const int c0 = blockIdx.x * FINAL_COLS;
   if (c0 >= n && blockIdx.x > 0) return;  // block 0 always writes the count
   Work W = work_of(J, N);
@@ -2261,12 +2298,12 @@ __global__ __launch_bounds__(256) void k_eig_final(EigJobs jobs, int* __restrict
   __shared__ int s_low, s_bad;
   __shared__ double sl[1024];
   const int tid = threadIdx.x;
-  const double thr = keep_threshold(J, D.lam, n);
+  const double thr = keep_threshold(J, D.lam, nt);
   if (tid == 0) {
     s_low = -1;
     s_bad = 0;
   }
-  for (int c = tid; c < n; c += 256) sl[c] = D.lam[c];
+  for (int c = tid; c < n; c += 256) sl[c] = D.lam[nt - n + c];
   __syncthreads();
   // ascending eigenvalues: the kept ones are those above the highest index
   // whose value is not above the threshold (a NaN counts as not above)
@@ -2288,7 +2325,7 @@ __global__ __launch_bounds__(256) void k_eig_final(EigJobs jobs, int* __restrict
       const double l = sl[n - 1 - c];
       J.lam[c] = l;
       if (c < kept) {
-        const double s = sqrt(l);
+        const double s = SVD ? l : sqrt(l);
         J.sq[c] = s;
         J.isq[c] = 1.0 / s;
       }
@@ -2630,30 +2667,6 @@ __global__ __launch_bounds__(JAC_T) void k_svd_jacobi(const double* __restrict__
     if (lane < q) J.V[(size_t)lane * J.ldv + pos] = pos < kept && val < 0.0 ? -x : x;
   }
 }
-
-// Householder bidiagonalisation of the p x q work matrix (p >= q): left
-// reflectors zero column k below the diagonal (d_k), right reflectors zero
-// row k right of the superdiagonal (e_k).  Only the right reflectors are kept
-// (W.H rows, W.tau): the vectors of the short side are Q_R times the v-part
-// of the tridiagonal's eigenvectors.  Two kernels: k_gebrd_lds when the
-// matrix fits one block's LDS, else k_gebrd_grid.
-//
-// k_gebrd_grid: P blocks, each holding the rows i = b (mod P) in LDS (row
-// stride q), with one grid barrier per step.  The left reflector of column k is
-// u = e_k + s_L c, c = A(k+1:, k), and its product with the trailing matrix is
-// y = tau_L (A(k, k+1:) + s_L sum_{i > k} A(i, k) A(i, k+1:)): each block can
-// form its share of that sum, and of |c|^2, from its own rows before the
-// reflector exists.  So before the barrier that opens step k every block
-// publishes those two partials over its own rows i > k, and the owner of row
-// k publishes the row; step k then runs without another barrier:
-//   every block sums the P partials in block order, forms the left reflector
-//   (alpha = A(k, k)), y, row k after it, and from that row the right
-//   reflector v_k, tau_R, e_k, redundantly; it applies both reflectors to its
-//   own rows in LDS (A_i -= s_L A(i, k) y, then A_i -= tau_R (A_i . v) v) and
-//   publishes the partials of step k + 1 (double-buffered by step parity: a
-//   block may write step k + 1's while another still reads step k's).
-// Outputs: W.e[2k] = d_k, W.e[2k+1] = e_k, W.tau, right reflectors in W.H.
-// Launch and barrier as k_sytrd_grid.
 
 // Golub-Kahan bidiagonalisation of the taller orientation (p x q, p >= q): left
 // reflectors zero column k below the diagonal (d_k), right reflectors zero
@@ -3005,82 +3018,6 @@ __global__ __launch_bounds__(GBR_T) void k_gebrd(const double* __restrict__ M, i
   else gebrd_rows<16, 2>(M, ldm, side, J, dims, N, p, q, P, lds, &s_abort);
 }
 
-// Vectors of the short side for the kept singular values, one wavefront per
-// vector: y = the even entries of the tridiagonal's eigenvector, normalised,
-// then y <- G_0 G_1 ... G_{q-2} y with the right reflectors.
-__global__ __launch_bounds__(256) void k_svd_back(EigJobs jobs, int* __restrict__ dims, int N) {
-  const EigJob J = jobs.j[0];
-  const int n = dims[J.n_idx], q = n / 2;
-  if (n < 0) return;  // solved by k_svd_jacobi
-  const int par = dc_par(n);
-  Work W = work_of(J, N);
-  DC D = dc_of(W, N);
-  const int N2 = next_pow2(N);
-  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-  const int c = blockIdx.x * 4 + wave;
-  __shared__ double ys[4][1024];
-  if (c >= q) return;
-  const double thr = keep_threshold(J, D.lam, n);
-  const int col = n - 1 - c;
-  if (!(D.lam[col] > thr)) return;
-  double* y = ys[wave];
-  // mixing of the +-sigma pair only rescales the v-part: normalise it
-  double part0 = 0.0;
-  for (int i = lane; i < q; i += 64) {
-    const double x = (par ? D.Qb : D.Qa)[(size_t)(2 * i) * N2 + col];
-    y[i] = x;
-    part0 += x * x;
-  }
-  const double nrm = sqrt(wave_sum(part0));
-  const double inv = nrm > 0.0 ? 1.0 / nrm : 0.0;
-  for (int i = lane; i < q; i += 64) y[i] *= inv;
-  for (int k = q - 2; k >= 0; --k) {
-    const double tau = W.tau[k];
-    if (tau == 0.0) continue;
-    const double* v = W.H + (size_t)k * N;
-    double part = 0.0;
-    for (int i = k + 1 + lane; i < q; i += 64) part += v[i] * y[i];
-    const double dot = wave_sum(part) * tau;
-    for (int i = k + 1 + lane; i < q; i += 64) y[i] -= dot * v[i];
-  }
-  for (int i = lane; i < q; i += 64) J.V[(size_t)i * J.ldv + c] = y[i];
-}
-
-// Descending singular values, kept count, scalings and sign gauge.
-__global__ __launch_bounds__(256) void k_svd_final(EigJobs jobs, int* __restrict__ dims, int N) {
-  const EigJob J = jobs.j[0];
-  const int n = dims[J.n_idx], q = n / 2;
-  if (n < 0) return;  // solved by k_svd_jacobi
-  Work W = work_of(J, N);
-  DC D = dc_of(W, N);
-  __shared__ int s_kept;
-  const int tid = threadIdx.x;
-  const double thr = keep_threshold(J, D.lam, n);
-  if (tid == 0) {
-    int k = 0, bad = 0, run = 1;
-    for (int c = 0; c < q; ++c) {
-      const double sg = D.lam[n - 1 - c];
-      if (!(sg == sg)) bad = 1;
-      if (run && sg > thr) ++k;
-      else run = 0;
-    }
-    s_kept = k;
-    dims[J.kept_idx] = k;
-    if (bad) atomicOr(&dims[D_FLAG], FLAG_EIG);
-  }
-  __syncthreads();
-  const int kept = s_kept;
-  for (int c = tid; c < q; c += 256) {
-    const double sg = D.lam[n - 1 - c];
-    J.lam[c] = sg;
-    if (c < kept) {
-      J.sq[c] = sg;
-      J.isq[c] = 1.0 / sg;
-    }
-  }
-  gauge_columns(J.V, J.ldv, q, kept);
-}
-
 // Dynamic LDS of k_dc_fused at capacity N: the largest of its phases' needs
 // (the one-block merges; sort and deflation, tiles of the levels above).
 size_t dc_fused_dyn_lds(int N) {
@@ -3143,7 +3080,7 @@ size_t eig_lds_bytes(int N, bool runtime, const char** which) {
     lds_note(static_lds((const void*)k_sytrd_grid, ST_SYTRD_GRID, runtime) + sytrd_grid_lds(N),
              "k_sytrd_grid", worst, which);
   dc_lds(N, runtime, worst, which);
-  lds_note(static_lds((const void*)k_ormtr<16, 4>, ST_ORMTR, runtime) + ormtr_lds_doubles(N) * 8,
+  lds_note(static_lds((const void*)k_ormtr<false>, ST_ORMTR, runtime) + ormtr_lds_doubles(N) * 8,
            "k_ormtr", worst, which);
   return worst;
 }
@@ -3154,6 +3091,8 @@ size_t svd_lds_bytes(int ncap2, int pcap, bool runtime, const char** which) {
   const int qcap = ncap2 / 2;
   lds_note(static_lds((const void*)k_gebrd, ST_GEBRD, runtime) + gebrd_lds(std::min(qcap, pcap)), "k_gebrd",
            worst, which);
+  lds_note(static_lds((const void*)k_ormtr<true>, ST_ORMTR, runtime) + ormtr_lds_doubles(qcap) * 8,
+           "k_ormtr", worst, which);
   dc_lds(ncap2, runtime, worst, which);
   return worst;
 }
@@ -3183,15 +3122,8 @@ void eig_batched(const EigJob* jobs, int njobs, int N, int* dims, hipStream_t s)
                                                                                          N);
   }
   dc_solve(J, njobs < 4 ? njobs : 4, N, dims, s);
-  {
-    const dim3 g((N + 3) / 4, njobs), g4((N + 15) / 16, njobs);
-    const size_t lds = ormtr_lds_doubles(N) * 8;
-    if (N <= 192) k_ormtr<3, 1><<<g, 256, lds, s>>>(J, dims, N);
-    else if (N <= 384) k_ormtr<6, 1><<<g, 256, lds, s>>>(J, dims, N);
-    else if (N <= 640) k_ormtr<10, 1><<<g, 256, lds, s>>>(J, dims, N);
-    else k_ormtr<16, 4><<<g4, 256, lds, s>>>(J, dims, N);
-  }
-  k_eig_final<<<dim3((N + FINAL_COLS - 1) / FINAL_COLS, njobs), 256, 0, s>>>(J, dims, N);
+  k_ormtr<false><<<dim3((N + 3) / 4, njobs), 256, ormtr_lds_doubles(N) * 8, s>>>(J, dims, N);
+  k_eig_final<false><<<dim3((N + FINAL_COLS - 1) / FINAL_COLS, njobs), 256, 0, s>>>(J, dims, N);
 }
 
 void svd_short_side(const double* M, int ldm, int a_idx, int b_idx, int side_idx,
@@ -3204,8 +3136,8 @@ void svd_short_side(const double* M, int ldm, int a_idx, int b_idx, int side_idx
   const int qc = std::min(qcap, pcap);
   k_gebrd<<<gebrd_blocks(pcap, qc), GBR_T, gebrd_lds(qc), s>>>(M, ldm, J, dims, N, a_idx, b_idx, side_idx);
   dc_solve(J, 1, N, dims, s);
-  k_svd_back<<<(qcap + 3) / 4, 256, 0, s>>>(J, dims, N);
-  k_svd_final<<<1, 256, 0, s>>>(J, dims, N);
+  k_ormtr<true><<<(qcap + 3) / 4, 256, ormtr_lds_doubles(qcap) * 8, s>>>(J, dims, N);
+  k_eig_final<true><<<(qcap + FINAL_COLS - 1) / FINAL_COLS, 256, 0, s>>>(J, dims, N);
 }
 
 }  // namespace tt
