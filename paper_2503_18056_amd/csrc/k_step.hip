@@ -261,6 +261,24 @@ __global__ void k_hll_inflow(int ns, const double* __restrict__ bc_e0, const int
   }
 }
 
+// A wavefront per row, so padding needs no division; bound by the writes.
+__global__ __launch_bounds__(256) void k_pad_cores(const double* __restrict__ Xs, double* __restrict__ X,
+                                                   int ns, int r1, int ldX,
+                                                   const double* __restrict__ Ts, double* __restrict__ Th,
+                                                   int lt, int lt_cap, int r2, int r2c,
+                                                   const double* __restrict__ Ps, double* __restrict__ Ph,
+                                                   int n) {
+  const int lane = threadIdx.x & 63, nw = gridDim.x * 4;
+  const int w0 = blockIdx.x * 4 + (threadIdx.x >> 6);
+  for (int i = w0; i < ns; i += nw)
+    for (int j = lane; j < ldX; j += 64)
+      X[(long long)i * ldX + j] = j < r1 ? Xs[(long long)i * r1 + j] : 0.0;
+  for (int i = w0; i < lt_cap; i += nw)
+    for (int j = lane; j < r2c; j += 64)
+      Th[(long long)i * r2c + j] = i < lt && j < r2 ? Ts[(long long)i * r2 + j] : 0.0;
+  for (int e = w0 * 64 + lane; e < n; e += nw * 64) Ph[e] = Ps[e];
+}
+
 // Core conversion between FP64 and FP32 storage (rows x cols, leading dims).
 template <typename TA, typename TB>
 __global__ void k_convert(const TA* __restrict__ a, int lda, TB* __restrict__ b, int ldb, int rows,
@@ -827,6 +845,11 @@ void launch_hll_weights(const StepGeom& G, int dim, const double* rho, const dou
 void launch_hll_inflow(const StepGeom& G, const double* bc_e0, const int* code, int nbc,
                        const double* W, double* bc_e, hipStream_t st) {
   if (nbc > 0) k_hll_inflow<<<(G.ns + 255) / 256, 256, 0, st>>>(G.ns, bc_e0, code, nbc, W, bc_e);
+}
+void launch_pad_cores(const double* Xs, double* X, int ns, int r1, int ldX, const double* Ts,
+                      double* Th, int lt, int lt_cap, int r2, int r2c, const double* Ps, double* Ph,
+                      int n, hipStream_t st) {
+  k_pad_cores<<<1024, 256, 0, st>>>(Xs, X, ns, r1, ldX, Ts, Th, lt, lt_cap, r2, r2c, Ps, Ph, n);
 }
 void launch_convert(const double* a, int lda, float* b, int ldb, int rows, int cols, hipStream_t st) {
   k_convert<double, float><<<1024, 256, 0, st>>>(a, lda, b, ldb, rows, cols);
