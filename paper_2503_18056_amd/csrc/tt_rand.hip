@@ -91,96 +91,107 @@ __global__ __launch_bounds__(256) void k_chol_inv(const double* __restrict__ G, 
   }
 }
 
-// The same for k <= CHOL_LDS_K, LDS-resident (k (k + 1) doubles of dynamic LDS):
-// right-looking Cholesky (per pivot: scale its row, update the trailing
-// upper triangle), then R^{-1} in place column by column (column j from the
-// inverted leading block and R's column j), so that every step is parallel
-// over rows and the serial chain is k steps of LDS work.
-constexpr int CHOL_LDS_K = 128;
+// The same for k <= CHOL_REG_K in registers: thread (ty, tx) of 16 x 16 holds the
+// entries (ty + 16 a, tx + 16 b), a, b < KB, of one k x k array whose upper part is
+// G's trailing matrix and whose strictly lower part is the elimination's
+// inverse E (G = E^{-1} D E^{-T}): step j subtracts (u_i / d) w from every row
+// i > j, u the pivot row, d its diagonal, w_l = u_l except 1 at l = j, over the
+// columns l >= i (G's) and l <= j (E's).  Row i is final at step i, so
+// R = D^{-1/2} (its upper part) and R^{-1} = (D^{-1/2} E)^T are scaled and written
+// after the loop.  One block barrier a step: the owners of row j + 1 publish it
+// in LDS as they update.  Bound by that chain (barrier, LDS reads, division:
+// 0.6 us a step at k = 64).  The factors of a sketch to ranks (64, 16) take 37
+// and 6 us; in LDS, with three barriers a pivot and two a column of the
+// inverse, they averaged 58.
+constexpr int CHOL_REG_K = 128;
 
-__global__ __launch_bounds__(256) void k_chol_inv_lds(const double* __restrict__ G, int ldg, int k,
+template <int KB>
+__global__ __launch_bounds__(256) void k_chol_inv_reg(const double* __restrict__ G, int ldg, int k,
                                                       long long shift_rows, double* __restrict__ R,
                                                       double* __restrict__ Ri, int ldr,
                                                       int* __restrict__ dims) {
-  extern __shared__ double A[];  // k x k, ld lk = k + 1 (odd: rows in distinct banks)
-  __shared__ double red[256];
-  const int t = threadIdx.x, lk = k + 1;
-  double a = 0.0;
-  for (int i = t; i < k; i += 256) a += G[(long long)i * ldg + i];
-  red[t] = a;
+  __shared__ double row[2][16 * KB], piv[16 * KB], red[4];
+  const int t = threadIdx.x, tx = t & 15, ty = t >> 4;
+  double tr = 0.0;
+  for (int i = t; i < k; i += 256) tr += G[(long long)i * ldg + i];
+  for (int o = 32; o > 0; o >>= 1) tr += __shfl_xor(tr, o);
+  if ((t & 63) == 0) red[t >> 6] = tr;
   __syncthreads();
-  for (int o = 128; o > 0; o >>= 1) {
-    if (t < o) red[t] += red[t + o];
-    __syncthreads();
-  }
+  tr = (red[0] + red[1]) + (red[2] + red[3]);
   const double shift =
-      shift_rows > 0 ? 11.0 * ((double)shift_rows * k + (double)k * (k + 1)) * UNIT_ROUNDOFF * red[0] : 0.0;
-  for (int e = t; e < k * k; e += 256) {
-    const int i = e / k, l = e % k;
-    A[i * lk + l] = l >= i ? G[(long long)i * ldg + l] + (l == i ? shift : 0.0) : 0.0;
-  }
+      shift_rows > 0 ? 11.0 * ((double)shift_rows * k + (double)k * (k + 1)) * UNIT_ROUNDOFF * tr : 0.0;
+  double m[KB][KB];
+#pragma unroll
+  for (int a = 0; a < KB; ++a)
+#pragma unroll
+    for (int b = 0; b < KB; ++b) {
+      const int i = ty + 16 * a, l = tx + 16 * b;
+      m[a][b] = i < k && l >= i && l < k ? G[(long long)i * ldg + l] + (l == i ? shift : 0.0) : 0.0;
+    }
+  if (ty == 0)
+#pragma unroll
+    for (int b = 0; b < KB; ++b) row[0][tx + 16 * b] = m[0][b];
   __syncthreads();
   for (int j = 0; j < k; ++j) {
-    __syncthreads();  // the previous pivot's trailing update is complete
-    const double d = A[j * lk + j];
-    const bool bad = !(d > 0.0);
-    const double rjj = bad ? 1.0 : sqrt(d);
-    if (bad && t == 0) atomicOr(&dims[D_FLAG], FLAG_CHOL);
-    __syncthreads();
-    const double inv = 1.0 / rjj;
-    for (int l = j + t; l < k; l += 256) A[j * lk + l] = l == j ? rjj : A[j * lk + l] * inv;
-    __syncthreads();
-    for (int i = j + 1 + (t >> 4); i < k; i += 16) {
-      const double rji = A[j * lk + i];
-      for (int l = i + (t & 15); l < k; l += 16) A[i * lk + l] -= rji * A[j * lk + l];
+    const double* u = row[j & 1];
+    const double d0 = u[j];
+    const bool bad = !(d0 > 0.0);
+    const double d = bad ? 1.0 : d0;
+    if (t == 0) {
+      piv[j] = d;
+      if (bad) atomicOr(&dims[D_FLAG], FLAG_CHOL);
     }
-  }
-  __syncthreads();
-  for (int e = t; e < k * k; e += 256) {
-    const int i = e / k, l = e % k;
-    R[(long long)i * ldr + l] = l >= i ? A[i * lk + l] : 0.0;
-  }
-  // in place: after column j, A[0:j+1, 0:j+1] holds the leading block of
-  // R^{-1}; row i's dot product for column j is split between threads i and
-  // i + 128 (halves of l in [i, j)), each with four independent partial sums
-  const int ri = t & 127, half = t >> 7;
-  for (int j = 0; j < k; ++j) {
-    const double ajj = 1.0 / A[j * lk + j];
-    double v = 0.0;
-    if (ri < j) {
-      const int mid = (ri + j) >> 1;
-      const int l0 = half ? mid : ri, l1 = half ? j : mid;
-      double v0 = 0.0, v1 = 0.0, v2 = 0.0, v3 = 0.0;
-      int l = l0;
-      for (; l + 3 < l1; l += 4) {
-        v0 += A[ri * lk + l] * A[l * lk + j];
-        v1 += A[ri * lk + l + 1] * A[(l + 1) * lk + j];
-        v2 += A[ri * lk + l + 2] * A[(l + 2) * lk + j];
-        v3 += A[ri * lk + l + 3] * A[(l + 3) * lk + j];
-      }
-      for (; l < l1; ++l) v0 += A[ri * lk + l] * A[l * lk + j];
-      v = (v0 + v1) + (v2 + v3);
+    double w[KB], we[KB];
+#pragma unroll
+    for (int b = 0; b < KB; ++b) {
+      const int l = tx + 16 * b;
+      w[b] = u[l];
+      we[b] = l < j ? w[b] : l == j ? 1.0 : 0.0;
     }
-    red[t] = v;
-    __syncthreads();
-    if (t < j) A[t * lk + j] = -(red[t] + red[t + 128]) * ajj;
-    if (t == 0) A[j * lk + j] = ajj;
+    double f[KB];
+#pragma unroll
+    for (int a = 0; a < KB; ++a) f[a] = ty + 16 * a > j ? u[ty + 16 * a] : 0.0;
+    const double rd = -1.0 / d;
+#pragma unroll
+    for (int a = 0; a < KB; ++a) {
+      if (16 * a + 15 <= j) continue;
+      f[a] *= rd;
+#pragma unroll
+      for (int b = 0; b < KB; ++b)
+        m[a][b] = fma(f[a], a < b || (a == b && tx >= ty) ? w[b] : we[b], m[a][b]);
+    }
+    if (ty == ((j + 1) & 15)) {
+#pragma unroll
+      for (int a = 0; a < KB; ++a)
+        if (a == (j + 1) >> 4)
+#pragma unroll
+          for (int b = 0; b < KB; ++b) row[(j + 1) & 1][tx + 16 * b] = m[a][b];
+    }
     __syncthreads();
   }
-  for (int e = t; e < k * k; e += 256) {
-    const int i = e / k, l = e % k;
-    Ri[(long long)i * ldr + l] = l >= i ? A[i * lk + l] : 0.0;
+#pragma unroll
+  for (int a = 0; a < KB; ++a) {
+    const int i = ty + 16 * a;
+    if (i >= k) continue;
+    const double r = sqrt(piv[i]), inv = 1.0 / r;
+#pragma unroll
+    for (int b = 0; b < KB; ++b) {
+      const int l = tx + 16 * b;
+      if (l >= k) continue;
+      R[(long long)i * ldr + l] = l > i ? m[a][b] * inv : l == i ? r : 0.0;
+      Ri[(long long)l * ldr + i] = l < i ? m[a][b] * inv : l == i ? inv : 0.0;
+    }
   }
 }
 
-// One factorisation: the LDS kernel when k fits, else the global one.
+// One factorisation: the register kernel when k fits, else the global one.
 void chol_inv(const double* G, int ldg, int k, long long shift_rows, double* R, double* Ri, int ldr,
               int* dims, hipStream_t s) {
-  if (k <= CHOL_LDS_K)
-    k_chol_inv_lds<<<1, 256, (size_t)k * (k + 1) * sizeof(double), s>>>(G, ldg, k, shift_rows, R, Ri, ldr,
-                                                                          dims);
-  else
-    k_chol_inv<<<1, 256, 0, s>>>(G, ldg, k, shift_rows, R, Ri, ldr, dims);
+  if (k <= 16) k_chol_inv_reg<1><<<1, 256, 0, s>>>(G, ldg, k, shift_rows, R, Ri, ldr, dims);
+  else if (k <= 32) k_chol_inv_reg<2><<<1, 256, 0, s>>>(G, ldg, k, shift_rows, R, Ri, ldr, dims);
+  else if (k <= 64) k_chol_inv_reg<4><<<1, 256, 0, s>>>(G, ldg, k, shift_rows, R, Ri, ldr, dims);
+  else if (k <= CHOL_REG_K) k_chol_inv_reg<8><<<1, 256, 0, s>>>(G, ldg, k, shift_rows, R, Ri, ldr, dims);
+  else k_chol_inv<<<1, 256, 0, s>>>(G, ldg, k, shift_rows, R, Ri, ldr, dims);
 }
 
 __global__ void k_set_ranks(int* __restrict__ dims, int r1, int r2) {
