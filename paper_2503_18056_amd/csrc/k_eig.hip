@@ -10,8 +10,8 @@
 //      one persistent launch: the merges up to 64 rows on one block each, above
 //      that one wavefront per secular root and products in tiles over the
 //      blocks, with grid barriers between the phases.
-//   3. Back-transformation V = Q Z, a wavefront per kept vector.
-//   4. Descending order, sign gauge (largest |entry| positive), clip rule.
+//   3. Back-transformation V = Q Z, a wavefront per kept vector, with the
+//      descending order, sign gauge (largest |entry| positive) and clip rule.
 // The same divide and conquer also serves the small SVD of M (section 5).
 #include <float.h>
 #include <string.h>
@@ -2237,10 +2237,71 @@ __device__ __forceinline__ void ormtr_vectors(const EigJob& J, int* __restrict__
   for (int w = 0; w < VPW; ++w) {
     if (!active[w]) continue;
     const int col = n - 1 - (j0 + 4 * w + wave);
+    // sign gauge: the largest |entry| (first on ties) positive
+    double best = -1.0, val = 0.0;
+    int bi = 0x7fffffff;
+#pragma unroll
+    for (int c = 0; c < NCH; ++c)
+      if (lane + 64 * c < n && fabs(y[w][c]) > best) {
+        best = fabs(y[w][c]);
+        val = y[w][c];
+        bi = lane + 64 * c;
+      }
+    for (int o = 32; o > 0; o >>= 1) {
+      const double b2 = __shfl_xor(best, o), v2 = __shfl_xor(val, o);
+      const int i2 = __shfl_xor(bi, o);
+      if (b2 > best || (b2 == best && i2 < bi)) {
+        best = b2;
+        val = v2;
+        bi = i2;
+      }
+    }
 #pragma unroll
     for (int c = 0; c < NCH; ++c) {
       const int i = lane + 64 * c;
-      if (i < n) J.V[(size_t)i * J.ldv + col] = y[w][c];
+      if (i < n) J.V[(size_t)i * J.ldv + col] = val < 0.0 ? -y[w][c] : y[w][c];
+    }
+  }
+}
+
+// Descending eigenvalues (SVD: singular values), the kept count, sq and isq, by
+// one block.
+template <bool SVD>
+__device__ __forceinline__ void eig_counts(const EigJob& J, int* __restrict__ dims, int N, int nt) {
+  const int n = SVD ? nt / 2 : nt;
+  Work W = work_of(J, N);
+  const double* lam = dc_of(W, N).lam;
+  const double thr = keep_threshold(J, lam, nt);
+  lam += nt - n;
+  __shared__ int s_low, s_bad;
+  const int tid = threadIdx.x;
+  if (tid == 0) {
+    s_low = -1;
+    s_bad = 0;
+  }
+  __syncthreads();
+  // ascending: the kept ones are those above the highest index whose value is
+  // not above the threshold (a NaN counts as not above)
+  int low = -1, bad = 0;
+  for (int j = tid; j < n; j += 256) {
+    if (!(lam[j] == lam[j])) bad = 1;
+    if (!(lam[j] > thr)) low = j;
+  }
+  if (low >= 0) atomicMax(&s_low, low);
+  if (bad) s_bad = 1;
+  __syncthreads();
+  const int kept = n - 1 - s_low;
+  if (tid == 0) {
+    dims[J.kept_idx] = kept;
+    if (s_bad) atomicOr(&dims[D_FLAG], FLAG_EIG);
+  }
+  for (int c = tid; c < n; c += 256) {
+    const double l = lam[n - 1 - c];
+    J.lam[c] = l;
+    if (c < kept) {
+      const double s = SVD ? l : sqrt(l);
+      J.sq[c] = s;
+      J.isq[c] = 1.0 / s;
     }
   }
 }
@@ -2248,91 +2309,16 @@ __device__ __forceinline__ void ormtr_vectors(const EigJob& J, int* __restrict__
 template <bool SVD>
 __global__ __launch_bounds__(256) void k_ormtr(EigJobs jobs, int* __restrict__ dims, int N) {
   extern __shared__ double hs[];
-  const EigJob& J = jobs.j[blockIdx.y];
+  const EigJob J = jobs.j[blockIdx.y];
   const int nt = dims[J.n_idx];
   if (nt < 0) return;  // an SVD solved by k_svd_jacobi
   const int n = SVD ? nt / 2 : nt;
+  // block 0 holds the smallest, the likeliest not kept
+  if (blockIdx.x == 0) eig_counts<SVD>(J, dims, N, nt);
   if (n <= 192) ormtr_vectors<SVD, 3, 1>(J, dims, N, nt, hs);
   else if (n <= 384) ormtr_vectors<SVD, 6, 1>(J, dims, N, nt, hs);
   else if (n <= 640) ormtr_vectors<SVD, 10, 1>(J, dims, N, nt, hs);
   else ormtr_vectors<SVD, 16, 4>(J, dims, N, nt, hs);
-}
-
-// Sign gauge of columns c < ncol of V (rows < nrow): the largest-magnitude
-// entry (first on ties) made positive; a wavefront per column (256-thread
-// block, four columns at a time).
-__device__ void gauge_columns(double* V, int ldv, int nrow, int ncol) {
-  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-  for (int c = wave; c < ncol; c += 4) {
-    double best = -1.0, val = 0.0;
-    int bi = 0x7fffffff;
-    for (int i = lane; i < nrow; i += 64) {
-      const double v = V[(size_t)i * ldv + c];
-      if (fabs(v) > best) { best = fabs(v); val = v; bi = i; }
-    }
-    for (int o = 32; o > 0; o >>= 1) {
-      const double b2 = __shfl_xor(best, o), v2 = __shfl_xor(val, o);
-      const int i2 = __shfl_xor(bi, o);
-      if (b2 > best || (b2 == best && i2 < bi)) { best = b2; val = v2; bi = i2; }
-    }
-    if (val < 0.0)
-      for (int i = lane; i < nrow; i += 64) V[(size_t)i * ldv + c] = -V[(size_t)i * ldv + c];
-  }
-}
-
-// ---------------------------------------------------------------------------
-// 4. Descending eigenvalues, kept count, sqrt scalings and sign gauge.  Each
-// block takes 16 columns of the gauge (and recounts the kept eigenvalues from
-// an LDS copy of them); block 0 also writes the count and the scalings.
-constexpr int FINAL_COLS = 4;  // one column per wavefront: the gauge is latency-bound
-template <bool SVD>
-__global__ __launch_bounds__(256) void k_eig_final(EigJobs jobs, int* __restrict__ dims, int N) {
-  const EigJob J = jobs.j[blockIdx.y];
-  const int nt = dims[J.n_idx];  // order of the tridiagonal
-  if (nt < 0) return;  // an SVD solved by k_svd_jacobi
-  const int n = SVD ? nt / 2 : nt;
-  const int c0 = blockIdx.x * FINAL_COLS;
-  if (c0 >= n && blockIdx.x > 0) return;  // block 0 always writes the count
-  Work W = work_of(J, N);
-  DC D = dc_of(W, N);
-  __shared__ int s_low, s_bad;
-  __shared__ double sl[1024];
-  const int tid = threadIdx.x;
-  const double thr = keep_threshold(J, D.lam, nt);
-  if (tid == 0) {
-    s_low = -1;
-    s_bad = 0;
-  }
-  for (int c = tid; c < n; c += 256) sl[c] = D.lam[nt - n + c];
-  __syncthreads();
-  // ascending eigenvalues: the kept ones are those above the highest index
-  // whose value is not above the threshold (a NaN counts as not above)
-  int low = -1, bad = 0;
-  for (int j = tid; j < n; j += 256) {
-    if (!(sl[j] == sl[j])) bad = 1;
-    if (!(sl[j] > thr)) low = j;
-  }
-  if (low >= 0) atomicMax(&s_low, low);
-  if (bad) s_bad = 1;
-  __syncthreads();
-  const int kept = n - 1 - s_low;
-  if (tid == 0 && blockIdx.x == 0) {
-    dims[J.kept_idx] = kept;
-    if (s_bad) atomicOr(&dims[D_FLAG], FLAG_EIG);
-  }
-  if (blockIdx.x == 0) {
-    for (int c = tid; c < n; c += 256) {
-      const double l = sl[n - 1 - c];
-      J.lam[c] = l;
-      if (c < kept) {
-        const double s = SVD ? l : sqrt(l);
-        J.sq[c] = s;
-        J.isq[c] = 1.0 / s;
-      }
-    }
-  }
-  const int c1 = min(c0 + FINAL_COLS, kept);
-  if (c0 < c1) gauge_columns(J.V + c0, J.ldv, n, c1 - c0);
 }
 
 // ---------------------------------------------------------------------------
@@ -3123,7 +3109,6 @@ void eig_batched(const EigJob* jobs, int njobs, int N, int* dims, hipStream_t s)
   }
   dc_solve(J, njobs < 4 ? njobs : 4, N, dims, s);
   k_ormtr<false><<<dim3((N + 3) / 4, njobs), 256, ormtr_lds_doubles(N) * 8, s>>>(J, dims, N);
-  k_eig_final<false><<<dim3((N + FINAL_COLS - 1) / FINAL_COLS, njobs), 256, 0, s>>>(J, dims, N);
 }
 
 void svd_short_side(const double* M, int ldm, int a_idx, int b_idx, int side_idx,
@@ -3137,7 +3122,6 @@ void svd_short_side(const double* M, int ldm, int a_idx, int b_idx, int side_idx
   k_gebrd<<<gebrd_blocks(pcap, qc), GBR_T, gebrd_lds(qc), s>>>(M, ldm, J, dims, N, a_idx, b_idx, side_idx);
   dc_solve(J, 1, N, dims, s);
   k_ormtr<true><<<(qcap + 3) / 4, 256, ormtr_lds_doubles(qcap) * 8, s>>>(J, dims, N);
-  k_eig_final<true><<<(qcap + FINAL_COLS - 1) / FINAL_COLS, 256, 0, s>>>(J, dims, N);
 }
 
 }  // namespace tt
