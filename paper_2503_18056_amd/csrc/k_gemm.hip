@@ -25,9 +25,9 @@ template <> struct GrShape<0> { static constexpr int WAVES = 16, TPW = 1; };
 // Generic GEMM (vector FP64, 64x64 tiles, 32-deep K slabs staged in LDS,
 // the next slab prefetched into registers).
 template <int TA, int TB>
-__global__ __launch_bounds__(256) void k_gemm(GemmDesc g, const int* __restrict__ dims) {
+__device__ __forceinline__ void gemm_block(const GemmDesc& g, const int* __restrict__ dims, int z,
+                                           double (*As)[65], double (*Bs)[65]) {
   if (g.cond_idx >= 0 && dims[g.cond_idx] != g.cond_val) return;
-  const int z = blockIdx.z;
   const int bidx = g.bclip_idx;
   int m = eval_dim(dims, g.m), n = eval_dim(dims, g.n), k = eval_dim(dims, g.k);
   const long long coff = (long long)z * g.sC;
@@ -51,8 +51,6 @@ __global__ __launch_bounds__(256) void k_gemm(GemmDesc g, const int* __restrict_
     B = g.B + (TB == 0 ? k0 * g.ldb : k0);
     if (kscale) kscale += k0;
   }
-  __shared__ double As[GEMM_GK][65];
-  __shared__ double Bs[GEMM_GK][65];
   const int tid = threadIdx.x, tx = tid & 15, ty = tid >> 4;
   double acc[4][4];
   gemm_tile_acc<TA, TB>(acc, A, B, g.lda, g.ldb, kscale, i0, j0, m, n, k, As, Bs);
@@ -72,6 +70,22 @@ __global__ __launch_bounds__(256) void k_gemm(GemmDesc g, const int* __restrict_
   }
 }
 
+template <int TA, int TB>
+__global__ __launch_bounds__(256) void k_gemm(GemmDesc g, const int* __restrict__ dims) {
+  __shared__ double As[GEMM_GK][65], Bs[GEMM_GK][65];
+  gemm_block<TA, TB>(g, dims, blockIdx.z, As, Bs);
+}
+// Two products that do not depend on each other (or of which the dims table
+// picks one) in one launch, by blockIdx.z: at rank sizes a launch of its own
+// costs about 4 us of a step whatever it does.
+template <int TA0, int TB0, int TA1, int TB1>
+__global__ __launch_bounds__(256) void k_gemm_pair(GemmDesc g0, GemmDesc g1,
+                                                   const int* __restrict__ dims) {
+  __shared__ double As[GEMM_GK][65], Bs[GEMM_GK][65];
+  if (blockIdx.z == 0) gemm_block<TA0, TB0>(g0, dims, 0, As, Bs);
+  else gemm_block<TA1, TB1>(g1, dims, 0, As, Bs);
+}
+
 __global__ void k_sum_partials(const double* __restrict__ part, long long zstride, int nz,
                                double* __restrict__ out, int ldo, int ldp, DimExpr mdim,
                                DimExpr ndim, const int* __restrict__ dims, double beta) {
@@ -80,6 +94,7 @@ __global__ void k_sum_partials(const double* __restrict__ part, long long zstrid
   for (long long e = blockIdx.x * 256LL + threadIdx.x; e < tot; e += (long long)gridDim.x * 256) {
     const int i = (int)(e / n), j = (int)(e % n);
     double acc = 0.0;
+#pragma unroll 8
     for (int z = 0; z < nz; ++z) acc += part[z * zstride + (long long)i * ldp + j];
     double* o = out + (long long)i * ldo + j;
     *o = beta == 0.0 ? acc : acc + beta * *o;
@@ -103,6 +118,20 @@ void gemm(const GemmDesc& g, int mcap, int ncap, int batch, const int* dims, hip
   else if (g.transA && !g.transB) k_gemm<1, 0><<<grid, 256, 0, s>>>(g, dims);
   else if (!g.transA && g.transB) k_gemm<0, 1><<<grid, 256, 0, s>>>(g, dims);
   else k_gemm<1, 1><<<grid, 256, 0, s>>>(g, dims);
+}
+// the transposes of the two pairs that a bond's truncation has
+void gemm_pair(const GemmDesc& g0, const GemmDesc& g1, int mcap, int ncap, const int* dims,
+               hipStream_t s) {
+  if (mcap <= 0 || ncap <= 0) return;
+  const dim3 grid((ncap + 63) / 64, (mcap + 63) / 64, 2);
+  if (g0.transA && !g0.transB && !g1.transA && !g1.transB)
+    k_gemm_pair<1, 0, 0, 0><<<grid, 256, 0, s>>>(g0, g1, dims);
+  else if (!g0.transA && !g0.transB && g1.transA && g1.transB)
+    k_gemm_pair<0, 0, 1, 1><<<grid, 256, 0, s>>>(g0, g1, dims);
+  else {
+    gemm(g0, mcap, ncap, 1, dims, s);
+    gemm(g1, mcap, ncap, 1, dims, s);
+  }
 }
 
 // ---------------------------------------------------------------------------

@@ -569,13 +569,19 @@ __global__ void k_mside(int* __restrict__ dims, int ka, int kb, int km, int side
 //   while sigma_r - sigma_{r+1} <= max(eta sigma_1, R u sigma_1^2 / sigma_r);
 //   cap: r = rmax and, if that splits a cluster, cut before it (keep rmax if
 //   it starts at 1).
-__global__ void k_rank(const double* __restrict__ sig, int* __restrict__ dims,
+// One thread's sequential rule on values that the wavefront stages in LDS: from
+// global memory each was a load on its chain, 18 us for 192 values.
+__global__ __launch_bounds__(64) void k_rank(const double* __restrict__ sig, int* __restrict__ dims,
                        double* __restrict__ diag, RankArgs ra) {
-  if (threadIdx.x != 0 || blockIdx.x != 0) return;
+  __shared__ double sg[1024];  // max(sigma, 0): orders go up to 1024
   const int n = dims[ra.km];
   const int kc = dims[ra.kc];
+  for (int j = threadIdx.x; j < n; j += 64) sg[j] = fmax(sig[j], 0.0);
+  __syncthreads();
+  if (threadIdx.x != 0 || blockIdx.x != 0) return;
   double norm2 = 0.0;
-  for (int j = 0; j < n; ++j) norm2 += fmax(sig[j], 0.0) * fmax(sig[j], 0.0);
+#pragma unroll 8
+  for (int j = 0; j < n; ++j) norm2 += sg[j] * sg[j];
   double delta2;
   if (ra.bond == 1) {
     delta2 = ra.tol * ra.tol * norm2 / 2.0;
@@ -585,7 +591,7 @@ __global__ void k_rank(const double* __restrict__ sig, int* __restrict__ dims,
   } else {
     delta2 = diag[G_DELTA2];
   }
-  const double s0 = n > 0 ? fmax(sig[0], 0.0) : 0.0;
+  const double s0 = n > 0 ? sg[0] : 0.0;
   int r = 1, zero = 0;
   if (n == 0 || !(s0 > 0.0) || kc == 0) {
     zero = 1;
@@ -594,14 +600,14 @@ __global__ void k_rank(const double* __restrict__ sig, int* __restrict__ dims,
     double tail = 0.0;
     r = n;
     for (int k = n - 1; k >= 1; --k) {
-      tail += fmax(sig[k], 0.0) * fmax(sig[k], 0.0);
+      tail += sg[k] * sg[k];
       if (tail <= delta2) r = k;
       else break;
     }
     // sigma_j and sigma_{j+1} (1-based j) are tied when they differ by no more
     // than the Gram route resolves: max(eta s1, R u s1^2 / sigma_j)
     const double noise = (double)dims[ra.rdim] * 1.1102230246251565e-16;
-#define SIG(j) fmax(sig[(j)], 0.0)
+#define SIG(j) sg[(j)]
 #define TIED(j) (SIG((j) - 1) - SIG(j) <= fmax(ra.eta * s0, SIG((j) - 1) > 0.0 ? noise * s0 * s0 / SIG((j) - 1) : 1.79e308))
     // ... but never into a singular value below the resolution sqrt(R u) s1,
     // where every gap is within the noise

@@ -450,19 +450,17 @@ void truncate_bond(tt_ctx* c, int bond, const EigSlot& ea, const EigSlot& eb, Ei
   // side 0: W = M^T U~ ; side 1: U~ = M V~ S~^-1
   GemmDesc g0 = gd(M, Rcap, 1, em.V, N, 0, Wm, rcap, dimv(kb), dimv(rn), dimv(ka));
   g0.cond_idx = side; g0.cond_val = 0;
-  gemm(g0, Rcap, rcap, 1, c->dims, s);
   GemmDesc g1 = gd(M, Rcap, 0, em.V, N, 0, Ur, rcap, dimv(ka), dimv(rn), dimv(kb));
   g1.cond_idx = side; g1.cond_val = 1;
   g1.colscale = em.isq;
-  gemm(g1, Rcap, rcap, 1, c->dims, s);
+  gemm_pair(g0, g1, Rcap, rcap, c->dims, s);
   launch_svd_vectors(em.V, N, em.sq, Ur, rcap, Wm, rcap, c->dims, ka, kb, side, rn, zero, rcap, s);
   // P = V_A S_A^-1 U~  (R x r');  M_upd = (V_B S_B^-1 V~ S~)^T  (r' x R)
   GemmDesc gp = gd(ea.V, N, 0, Ur, rcap, 0, P, rcap, dimv(Rdim), dimv(rn), dimv(kea));
   gp.kscale = ea.isq;
-  gemm(gp, Rcap, rcap, 1, c->dims, s);
   GemmDesc gm = gd(Wm, rcap, 1, eb.V, N, 1, Mupd, Rcap, dimv(rn), dimv(Rdim), dimv(keb));
   gm.kscale = eb.isq;
-  gemm(gm, rcap, Rcap, 1, c->dims, s);
+  gemm_pair(gp, gm, Rcap, Rcap, c->dims, s);
 }
 
 // Gram-SVD rounding (App. A Algorithm 1, d = 3) of the TT held in

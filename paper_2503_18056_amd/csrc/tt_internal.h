@@ -94,6 +94,9 @@ struct GemmDesc {
   int ksplit;
 };
 void gemm(const GemmDesc& g, int mcap, int ncap, int batch, const int* dims, hipStream_t s);
+// Two independent products (unbatched), one launch, grids of the larger capacities.
+void gemm_pair(const GemmDesc& g0, const GemmDesc& g1, int mcap, int ncap, const int* dims,
+               hipStream_t s);
 // out[i][j] = sum_{z < nz} part[z][i][j] (fixed order) + beta out[i][j],
 // i < m, j < n (dynamic).
 void sum_partials(const double* part, long long zstride, int nz, double* out, int ldo, int ldp,
