@@ -538,9 +538,9 @@ __global__ __launch_bounds__(SYTRD_GRID_T) void k_sytrd_grid(EigJobs jobs, int* 
 // Entries past n are zero, and stay so.  The loop issues no global memory
 // access: the reflectors and d, e, tau stay in LDS and are written out after
 // it.  One matrix, before and now: order 62
-// 86 -> 70 us, 142 303 -> 229 us, 160 350 -> 270 us, 192 (k_sytrd_grid before)
-// 1013 -> 349 us; a step is about 2300 cycles of dependent latency with one
-// wavefront and 3700 with nine, barrier waits included.
+// 86 -> 68 us, 142 303 -> 199 us, 160 350 -> 237 us, 192 (k_sytrd_grid before)
+// 1013 -> 315 us.  (With wavefronts whose columns are done still forming the
+// step's scalars, 142 took 229 us: three wavefronts then shared a SIMD.)
 constexpr int SYR_WAVES = SYR_MAX / 16;
 constexpr int SYR_T = 64 * SYR_WAVES;
 constexpr int SYR_RC = SYR_MAX / 4;   // rows a lane holds
@@ -659,7 +659,14 @@ __global__ __launch_bounds__(SYR_T) void k_sytrd_reg(EigJobs jobs, int* __restri
     constexpr int Q = decltype(qtag)::value;
     const int s4 = k & ~3;
     lds_barrier();  // (B1)
+    // a wavefront whose columns are all done only keeps the barriers' count
     const bool live = 16 * wave + 15 > k;
+    if (!live) {
+      if (g == 0) L.ps[j] = 0.0;
+      if (l == 0) L.red[wave] = 0.0;
+      lds_barrier();  // (B2)
+      return;
+    }
     const double alpha = L.al, dkk = L.dk;
     double xm[3], y[4] = {0.0, 0.0, 0.0, 0.0}, part = 0.0;
 #pragma unroll
@@ -668,20 +675,18 @@ __global__ __launch_bounds__(SYR_T) void k_sytrd_reg(EigJobs jobs, int* __restri
       part = fma(xm[m], xm[m], part);
     }
     const double xj = L.xs[j], aj = L.as[j];
-    if (live) {
 #pragma unroll
-      for (int q = 0; q < SYR_RC / 8; ++q) {
-        if (s4 + 32 * q >= n) continue;
-        if (q & 1) fmac8_dot<1>(y, xm[q / 2], a + 8 * q);
-        else fmac8_dot<0>(y, xm[q / 2], a + 8 * q);
-      }
+    for (int q = 0; q < SYR_RC / 8; ++q) {
+      if (s4 + 32 * q >= n) continue;
+      if (q & 1) fmac8_dot<1>(y, xm[q / 2], a + 8 * q);
+      else fmac8_dot<0>(y, xm[q / 2], a + 8 * q);
     }
     const double sumsq = wave_sum(part);
     double tau, scal, beta;
     householder(alpha, sumsq, tau, scal, beta);
     const double yj = rows_sum((y[0] + y[1]) + (y[2] + y[3]));
     const double vj = j == k + 1 ? 1.0 : scal * xj;
-    const double pj = live && j > k ? tau * fma(scal, yj, aj) : 0.0;
+    const double pj = j > k ? tau * fma(scal, yj, aj) : 0.0;
     if (g == 0) {
       if (j < n) {
         L.ps[j] = pj;
@@ -694,14 +699,16 @@ __global__ __launch_bounds__(SYR_T) void k_sytrd_reg(EigJobs jobs, int* __restri
     kp += dpp_d<0x4E>(kp);
     kp += dpp_d<0x141>(kp);
     kp += dpp_d<0x140>(kp);
-    if (l == 0) L.red[wave] = kp;
-    if (tid == 0) {
-      L.sde[0][k] = dkk;
-      L.sde[1][k] = beta;
-      L.sde[2][k] = tau;
+    if (l == 0) {
+      L.red[wave] = kp;
+      if (wave == nw - 1) {  // live to the end
+        L.sde[0][k] = dkk;
+        L.sde[1][k] = beta;
+        L.sde[2][k] = tau;
+      }
     }
     lds_barrier();  // (B2)
-    if (live) {
+    {
       double kd[4] = {0.0, 0.0, 0.0, 0.0};
 #pragma unroll
       for (int w = 0; w < SYR_WAVES; ++w) kd[w & 3] += L.red[w];
