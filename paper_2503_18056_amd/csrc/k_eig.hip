@@ -798,23 +798,29 @@ __device__ inline DC dc_of(const Work& W, int N) {
 // [DC_LEAF r, DC_LEAF (r + 1)) of
 // T torn only at its two boundary off-diagonals (its diagonal loses |e| at a
 // torn boundary; inside the leaf T keeps its off-diagonals).  One wavefront
-// runs the implicit QL iteration with Wilkinson's shift on a leaf, all in
+// runs the implicit QL iteration with Wilkinson's shift on a leaf, in
 // registers with compile-time indexes: every lane carries the same d and e
 // (scaled by a power of two to a largest entry near 1), lane i row i of the
-// vectors.  An off-diagonal is dropped at u / 8 of the leaf's Frobenius norm
-// (the merges above deflate at 8 u ||T|| anyway) or at u of its diagonal
-// neighbours.  The eigenvalues are sorted ascending with their vectors, and
-// written where the merges up to blocks of 8 would have left them:
-// lam[leaf] and the diagonal block of Q.
-// Bound by the latency of the rotations' chain (one reciprocal root and about
-// ten dependent operations each, some 60 rotations a leaf): the leaves of an order-62 job take
-// about 8 us; cyclic Jacobi through LDS, a lane per entry, took 33.
+// vectors.  A found eigenvalue goes to LDS with its vector and the arrays
+// shift down by one, so one copy of the iteration's code serves all eight.
+// An off-diagonal is dropped at u / 8 of the leaf's Frobenius norm (the
+// merges above deflate at 8 u ||T|| anyway) or at u of its diagonal neighbours.
+// The eigenvalues are sorted ascending with their vectors, and written where
+// the merges up to blocks of 8 would have left them: lam[leaf] and the
+// diagonal block of Q.
+// Bound by the instructions of the rotations (some 90 a leaf at 8 rows, one
+// reciprocal root and about 45 instructions each, which a lone wavefront
+// issues every 7 cycles): 15 us at order 16, 26 at 62, with the first loads.
+// Cyclic Jacobi through LDS, a lane per entry, took 8 us more at order 16 and 25 at 62.
 constexpr int DC_LEAF = 8;
+struct LeafLds {
+  double lam[DC_LEAF], V[DC_LEAF][DC_LEAF + 1];
+};
 
 // Leaf `leaf` of job J, by the calling wavefront (lane = threadIdx.x % 64), its
 // eigenvalues to lam[0 .. 7].
 __device__ void dc_leaf_wave(const EigJob& J, int* __restrict__ dims, int N, int leaf,
-                             double* lam) {
+                             double* lam, LeafLds& L) {
   const int n = max(0, dims[J.n_idx]);
   Work W = work_of(J, N);
   DC D = dc_of(W, N);
@@ -850,33 +856,30 @@ __device__ void dc_leaf_wave(const EigJob& J, int* __restrict__ dims, int N, int
     fro += d[k] * d[k] + 2.0 * e[k] * e[k];
   }
   const double tiny = 0.125 * U64 * sqrt(fro);
-#pragma unroll
-  for (int l = 0; l < DC_LEAF - 1; ++l) {
+  for (int l = 0; l < nb; ++l) {
     for (int it = 0; it < 40; ++it) {
-      // the unreduced block that starts at l ends at row m; dm = d[m]
-      int m = l;
-      double dm = d[l];
+      // the unreduced block that starts at 0 ends at row m; dm = d[m]
+      int m = 0;
+      double dm = d[0];
       bool open = true;
 #pragma unroll
-      for (int k = l; k < DC_LEAF - 1; ++k) {
+      for (int k = 0; k < DC_LEAF - 1; ++k) {
         const double ae = fabs(e[k]);
-        if (ae <= tiny || ae <= U64 * (fabs(d[k]) + fabs(d[k + 1]))) {
-          if (open) e[k] = 0.0;
-          open = false;
-        }
-        if (open) {
-          m = k + 1;
-          dm = d[k + 1];
-        }
+        const bool drop = ae <= tiny || ae <= U64 * (fabs(d[k]) + fabs(d[k + 1]));
+        e[k] = open && drop ? 0.0 : e[k];
+        open = open && !drop;
+        m = open ? k + 1 : m;
+        dm = open ? d[k + 1] : dm;
       }
-      if (m == l) break;
-      // shift: the eigenvalue of the leading 2 x 2 nearer d[l]
-      const double del = d[l + 1] - d[l], two = 2.0 * e[l];
+      m = __builtin_amdgcn_readfirstlane(m);  // the same on every lane
+      if (m == 0) break;
+      // shift: the eigenvalue of the leading 2 x 2 nearer d[0]
+      const double del = d[1] - d[0], two = 2.0 * e[0];
       const double hyp = sqrt(del * del + two * two);
-      double g = dm - d[l] + e[l] * two / (del + copysign(hyp, del));
+      double g = dm - d[0] + e[0] * two / (del + copysign(hyp, del));
       double c = 1.0, s = 1.0, p = 0.0;
 #pragma unroll
-      for (int i = DC_LEAF - 2; i >= l; --i) {
+      for (int i = DC_LEAF - 2; i >= 0; --i) {
         if (i < m) {
           const double f = s * e[i], b = c * e[i];
           const double h = f * f + g * g;
@@ -894,25 +897,33 @@ __device__ void dc_leaf_wave(const EigJob& J, int* __restrict__ dims, int N, int
           v[i] = c * y - s * x;
         }
       }
-      d[l] -= p;
-      e[l] = g;
+      d[0] -= p;
+      e[0] = g;
     }
-  }
-  // ascending (stable: the index breaks ties); a NaN is flagged, its position
-  // stays within the leaf
-  bool bad = !(fro == fro);
+    if (lane == 0) L.lam[l] = d[0];
+    if (lane < DC_LEAF) L.V[lane][l] = v[0];
 #pragma unroll
-  for (int k = 0; k < DC_LEAF; ++k) {
-    if (k >= nb) continue;
+    for (int k = 0; k + 1 < DC_LEAF; ++k) {
+      d[k] = d[k + 1];
+      e[k] = e[k + 1];
+      v[k] = v[k + 1];
+    }
+    d[DC_LEAF - 1] = 0.0;
+    e[DC_LEAF - 1] = 0.0;
+    v[DC_LEAF - 1] = 0.0;
+  }
+  wave_sync();
+  // ascending (stable: the index breaks ties), an entry a lane; a NaN is
+  // flagged, its position stays within the leaf
+  const int i = lane / DC_LEAF, k = lane % DC_LEAF;
+  if (k < nb) {
+    const double x = L.lam[k];
     int pos = 0;
-#pragma unroll
-    for (int j = 0; j < DC_LEAF; ++j)
-      if (j < nb && j != k) pos += d[j] < d[k] || (d[j] == d[k] && j < k);
-    if (lane < nb) D.Qa[(size_t)(r0 + lane) * N2 + r0 + pos] = v[k];
-    if (lane == k) lam[pos] = ldexp(d[k], ex);
-    bad = bad || !(d[k] == d[k]);
+    for (int j = 0; j < nb; ++j) pos += L.lam[j] < x || (L.lam[j] == x && j < k);
+    if (i < nb) D.Qa[(size_t)(r0 + i) * N2 + r0 + pos] = L.V[i][k];
+    if (i == 0) lam[pos] = ldexp(x, ex);
+    if (i == 0 && (!(x == x) || !(fro == fro))) atomicOr(&dims[D_FLAG], FLAG_EIG);
   }
-  if (bad && lane == 0) atomicOr(&dims[D_FLAG], FLAG_EIG);
 }
 
 // Dynamic LDS of the phases above the one-block merges, per merge element: the sort and
@@ -966,7 +977,8 @@ template <bool STAGE> constexpr int dc_kc() { return STAGE ? 256 : 128; }
 // `split`, psi, and those after it, phi, each by a / (delta - t) + b matching
 // value and slope at the current iterate at their nearest pole (the two-pole
 // rational model of Bunch, Nielsen and Sorensen, 1978); the model's root in
-// the bracket is the next iterate (bisection when it falls outside).  The
+// the bracket is the next iterate (bisection when it falls outside, or is not a
+// number: the model's divisions and root take the fast forms).  The
 // first iterate is the interval's middle, whose sign picks the origin, and
 // its model keeps the exact weights of both neighbours.  When an iteration
 // leaves f's sign unchanged and reduces |f| by less than 10x, the next step
@@ -1066,7 +1078,7 @@ __device__ inline void dc_root(const double* d, const double* z, int nk, int i, 
     if (it == 0) {
       al = ws;
       ga = wn;
-      a0 = f - al / el - ga / er;
+      a0 = f - al * rcp_d(el) - ga * rcp_d(er);
     } else if (fw) {
       // fixed weight: the origin pole keeps its exact weight rho z_o^2; the
       // other neighbouring pole's weight and the constant match f and f'
@@ -1075,8 +1087,8 @@ __device__ inline void dc_root(const double* d, const double* z, int nk, int i, 
       const double fp = rho * (dps + dph);
       const double eo = right ? er : el, eq = right ? el : er;
       const double wo = right ? wn : ws;
-      const double wq = (fp - wo / (eo * eo)) * eq * eq;
-      a0 = f - wo / eo - wq / eq;
+      const double ro = rcp_d(eo), wq = (fp - wo * ro * ro) * eq * eq;
+      a0 = f - wo * ro - wq * rcp_d(eq);
       al = right ? wq : wo;
       ga = right ? wo : wq;
     } else {
@@ -1090,13 +1102,13 @@ __device__ inline void dc_root(const double* d, const double* z, int nk, int i, 
     const double disc = b * b - 4.0 * a0 * c;
     double xn = NAN;
     if (disc >= 0.0) {
-      const double sq = sqrt(disc);
+      const double sq = disc > 0.0 ? disc * rsqrt_d(disc) : 0.0;
       const double qq = b >= 0.0 ? b + sq : b - sq;  // no cancellation
-      const double r1 = qq != 0.0 ? 2.0 * c / qq : NAN;
+      const double r1 = 2.0 * c * rcp_d(qq);
       if (r1 > lo && r1 < hi) {
         xn = r1;
       } else {
-        const double r2 = a0 != 0.0 ? qq / (2.0 * a0) : NAN;
+        const double r2 = qq * rcp_d(2.0 * a0);
         if (r2 > lo && r2 < hi) xn = r2;
       }
     }
@@ -1302,7 +1314,8 @@ __device__ void dc_subtree(const EigJob& J, int* __restrict__ dims, int N, int s
   const int base = sub * DC_SUB;
   const int tid = threadIdx.x, lane = tid & 63, l8 = tid & 7;
   bool bad = false;
-  dc_leaf_wave(J, dims, N, sub * (DC_SUB / DC_LEAF) + (tid >> 6), L.lam + DC_LEAF * (tid >> 6));
+  dc_leaf_wave(J, dims, N, sub * (DC_SUB / DC_LEAF) + (tid >> 6), L.lam + DC_LEAF * (tid >> 6),
+               reinterpret_cast<LeafLds*>(L.panel)[tid >> 6]);
   __syncthreads();
   int par = 0;
   for (int S = DC_LEAF; S < DC_SUB && S < n; S *= 2, par ^= 1) {
@@ -1968,6 +1981,7 @@ __global__ __launch_bounds__(DC_T) void k_dc_fused(EigJobs jobs, int njobs, int*
     if (dc_item(cnt, njobs, t, q, r))
       dc_subtree(jobs.j[q], dims, N, r, *reinterpret_cast<SubLds*>(smem));
   }
+  static_assert(8 * sizeof(LeafLds) <= sizeof(SubLds::panel), "the leaves' LDS");
   static_assert(DC_SUB == 8 * DC_LEAF && DC_T == 8 * DC_SUB, "a wavefront a leaf, 8 lanes a row");
   // DC_SUB / DC_LEAF is a power of two: par counts the levels a job has passed
   int par = 1;  // after S = 8, 16, 32
