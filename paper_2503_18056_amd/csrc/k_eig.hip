@@ -2704,6 +2704,7 @@ __global__ __launch_bounds__(JAC_T) void k_svd_jacobi(const double* __restrict__
 // Outputs: W.e[2k] = d_k, W.e[2k+1] = e_k, W.tau, right reflectors in W.H.
 constexpr int GBR_T = 512;
 constexpr int GBR_W = GBR_T / 64;
+constexpr int GEBRD_QMAX = 1024;     // columns at most
 constexpr int GEBRD_GRID_PMAX = 64;  // blocks at most: 1024 rows, 16 a block above 704 columns
 struct GebrdGridBufs {
   double *R, *Y, *S;  // published rows (2 x N), partial sums (2 x P x N), |c|^2 partials (2 x P)
@@ -3083,8 +3084,10 @@ void dc_lds(int N, bool rt, size_t& worst, const char** which) {
 
 size_t eig_lds_bytes(int N, bool runtime, const char** which) {
   size_t worst = 0;
+  // (an order past the columns that its registers hold counts as not fitting)
   if (N > SYR_MAX)
-    lds_note(static_lds((const void*)k_sytrd_grid, ST_SYTRD_GRID, runtime) + sytrd_grid_lds(N),
+    lds_note(static_lds((const void*)k_sytrd_grid, ST_SYTRD_GRID, runtime) + sytrd_grid_lds(N) +
+                 (N > SYTRD_GRID_NMAX ? LDS_CU : 0),
              "k_sytrd_grid", worst, which);
   dc_lds(N, runtime, worst, which);
   lds_note(static_lds((const void*)k_ormtr<false>, ST_ORMTR, runtime) + ormtr_lds_doubles(N) * 8,
@@ -3096,8 +3099,10 @@ size_t svd_lds_bytes(int ncap2, int pcap, bool runtime, const char** which) {
   size_t worst = 0;
   lds_note(static_lds((const void*)k_svd_jacobi, ST_SVD_JACOBI, runtime), "k_svd_jacobi", worst, which);
   const int qcap = ncap2 / 2;
-  lds_note(static_lds((const void*)k_gebrd, ST_GEBRD, runtime) + gebrd_lds(std::min(qcap, pcap)), "k_gebrd",
-           worst, which);
+  const int qc = std::min(qcap, pcap);
+  lds_note(static_lds((const void*)k_gebrd, ST_GEBRD, runtime) + gebrd_lds(qc) +
+               (qc > GEBRD_QMAX || gebrd_blocks(pcap, qc) > GEBRD_GRID_PMAX ? LDS_CU : 0),
+           "k_gebrd", worst, which);
   lds_note(static_lds((const void*)k_ormtr<true>, ST_ORMTR, runtime) + ormtr_lds_doubles(qcap) * 8,
            "k_ormtr", worst, which);
   dc_lds(ncap2, runtime, worst, which);
