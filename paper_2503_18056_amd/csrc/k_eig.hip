@@ -775,7 +775,7 @@ __global__ __launch_bounds__(SYR_T) void k_sytrd_reg(EigJobs jobs, int* __restri
 //   1 + rho sum_j z_j^2 / (d_j - lambda) = 0,
 // solved in the shifted variable lambda = d_origin + tau; the eigenvectors
 // use the Loewner-recomputed z^ so that they are orthogonal to working
-// accuracy.  Vector updates Q <- Q_rot U are tiled products (dc_merge_tile).
+// accuracy.  Vector updates Q <- Q_rot U are tiled products (dc_subtree, dc_update_tile).
 struct DC {
   double *lam, *Qa, *Qb, *dsl, *dro, *rc, *rs, *rtau, *zhat, *dK, *zK, *mrho;
   int *perm, *Kslot, *rp, *rq, *mk, *mnrot, *mm2;
