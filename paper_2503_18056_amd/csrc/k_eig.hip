@@ -20,6 +20,7 @@
 #include <type_traits>
 
 #include "gemm_tile.h"
+#include "grid_sync.h"
 #include "tt_internal.h"
 
 namespace tt {
@@ -207,6 +208,8 @@ constexpr int SYTRD_GRID_NMAX = 1024;                          // largest order
 constexpr int SYG_R = 4;  // rows of a wavefront
 constexpr int SYG_T = SYTRD_GRID_NMAX / 64;  // columns per lane at most
 constexpr unsigned SYTRD_SPIN_MAX = 1u << 24;
+static_assert(SYTRD_GRID_P <= SYNC_MAXP && SYTRD_GRID_NMAX < (int)(GRID_ORD_DC - GRID_ORD_REDUCE),
+              "a flag a block, an ordinal a column");
 
 struct SytrdGridBufs {
   double *Rp, *Pv, *Dv;  // published rows (2 x N), p (2 x N), wavefront partial dots (2 x 4 P)
@@ -223,36 +226,10 @@ __device__ __host__ inline SytrdGridBufs sytrd_grid_bufs(double* work, int N) {
 }
 constexpr size_t GRID_DYN_LDS_MAX = 158 * 1024;  // dynamic LDS a grid reduction may ask for
 
-// Grid barriers of the multi-block kernels.  A job's work area ends with one
-// flag per block and a launch generation.  Each launch takes its barrier
-// ordinals from gen * GRID_ORD_SPAN + 1, 2, ..., so they exceed every value
-// an earlier launch left in the flags (compared in serial-number arithmetic,
-// which survives the 32-bit wrap), and block 0 advances the generation at its
-// end.  Every block reads the generation before its first barrier and block 0
-// passes that barrier only after all have arrived, so no block can see the
-// advanced value.  Nothing needs resetting between launches (the area starts
-// zeroed with the rest of the workspace).
-constexpr int SYNC_MAXP = 256;                 // blocks one barrier may join
-constexpr unsigned GRID_ORD_SPAN = 1u << 16;   // barriers one launch may pass
-constexpr size_t SYNC_DOUBLES = SYNC_MAXP / 2 + 8;
-struct GridSync {
-  unsigned* flag;  // SYNC_MAXP
-  unsigned* gen;
-};
-__device__ inline GridSync grid_sync_of(double* work, int N) {
-  GridSync g;
-  g.flag = reinterpret_cast<unsigned*>(work + eig_work_main(N));
-  g.gen = g.flag + SYNC_MAXP;
-  return g;
-}
-__device__ inline unsigned grid_gen(const GridSync& g) {
-  return __hip_atomic_load(g.gen, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
-// At the end of a launch that passed at least one barrier: block 0 advances
-// the generation (gen0 as read at the start).
-__device__ inline void grid_launch_end(const GridSync& g, unsigned gen0, bool used) {
-  if (used && blockIdx.x == 0 && threadIdx.x == 0)
-    __hip_atomic_store(g.gen, gen0 + 1u, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT);
+// A job's barrier flags (grid_sync.h).
+constexpr size_t SYNC_DOUBLES = SYNC_MAXP / 2;
+__device__ inline unsigned* grid_flags(double* work, int N) {
+  return reinterpret_cast<unsigned*>(work + eig_work_main(N));
 }
 
 // Barrier with ordinal `ordinal` over the P <= SYNC_MAXP blocks of one launch:
@@ -271,8 +248,8 @@ __device__ inline void grid_barrier(unsigned* flag, unsigned ordinal, int P, int
     while (true) {
       bool ok = true;
       for (int q = lane; q < P; q += 64)
-        ok = ok && (int)(__hip_atomic_load(&flag[q], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) -
-                         ordinal) >= 0;
+        ok = ok && grid_arrived(
+                       __hip_atomic_load(&flag[q], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT), ordinal);
       if (__all(ok)) break;
       __builtin_amdgcn_s_sleep(1);
       if (++spins > SYTRD_SPIN_MAX) {
@@ -313,8 +290,8 @@ __device__ inline void grid_barrier_relaxed(unsigned* flag, unsigned ordinal, in
     while (true) {
       bool ok = true;
       for (int q = lane; q < P; q += 64)
-        ok = ok && (int)(__hip_atomic_load(&flag[q], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) -
-                         ordinal) >= 0;
+        ok = ok && grid_arrived(
+                       __hip_atomic_load(&flag[q], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT), ordinal);
       if (__all(ok)) break;
       if (++spins > SYTRD_SPIN_MAX) {
         if (lane == 0) {
@@ -353,9 +330,8 @@ __device__ void sytrd_grid_rows(const EigJob& J, int* __restrict__ dims, int N, 
   }
 #pragma unroll
   for (int t = 0; t < NT; ++t) v[t] = w[t] = 0.0;
-  const GridSync gs = grid_sync_of(J.work, N);
-  const unsigned gen0 = grid_gen(gs);
-  unsigned ordinal = gen0 * GRID_ORD_SPAN;
+  unsigned* flags = grid_flags(J.work, N);
+  unsigned ordinal = GRID_ORD_REDUCE;
   const bool writer = b == 0 && wave == 0;
   double taup = 0.0;
   for (int k = 0; k <= n - 2; ++k) {
@@ -448,7 +424,7 @@ __device__ void sytrd_grid_rows(const EigJob& J, int* __restrict__ dims, int N, 
 #pragma unroll
     for (int t = 0; t < NT; ++t) v[t] = vn[t];
     taup = tau;
-    grid_barrier_relaxed(gs.flag, ++ordinal, P, s_abort, dims);
+    grid_barrier_relaxed(flags, ++ordinal, P, s_abort, dims);
     if (writer) {
 #pragma unroll
       for (int t = 0; t < NT; ++t) {
@@ -480,7 +456,6 @@ __device__ void sytrd_grid_rows(const EigJob& J, int* __restrict__ dims, int N, 
       }
     }
   }
-  grid_launch_end(gs, gen0, true);
 }
 
 // Blocks of a live order n: 16 rows to a block, 4 to a wavefront.
@@ -624,6 +599,7 @@ struct SyrLds {
 __global__ __launch_bounds__(SYR_T) void k_sytrd_reg(EigJobs jobs, int* __restrict__ dims, int N) {
   const EigJob J = jobs.j[blockIdx.x];
   const int n = dims[J.n_idx];
+  grid_clear(grid_flags(J.work, N), threadIdx.x, SYR_T);
   if (n < 1 || n > SYR_MAX) return;  // k_sytrd_grid
   // the wavefront index is uniform: in a scalar register
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), nw = (n + 15) >> 4;
@@ -1957,6 +1933,7 @@ __device__ inline bool dc_item(const int* cnt, int njobs, int t, int& q, int& r)
 // 6871 -> 6174 us.  LDS: the phases' arrays share the dynamic buffer
 // (dc_fused_dyn_lds(N) bytes).
 constexpr int DCF_MAXP = 64;
+static_assert(DCF_MAXP <= SYNC_MAXP, "a flag a block");
 __global__ __launch_bounds__(DC_T) void k_dc_fused(EigJobs jobs, int njobs, int* __restrict__ dims,
                                                    int N) {
   extern __shared__ double smem[];
@@ -1964,10 +1941,9 @@ __global__ __launch_bounds__(DC_T) void k_dc_fused(EigJobs jobs, int njobs, int*
   __shared__ TileLds tile_lds;
   __shared__ int s_abort;
   const int b = blockIdx.x, P = gridDim.x;
-  const GridSync gs = grid_sync_of(jobs.j[0].work, N);
+  unsigned* flags = grid_flags(jobs.j[0].work, N);
   if (threadIdx.x == 0) s_abort = 0;
-  const unsigned gen0 = grid_gen(gs);
-  unsigned ord = gen0 * GRID_ORD_SPAN;
+  unsigned ord = GRID_ORD_DC;
   int nq[4] = {0, 0, 0, 0}, nmax = 0;
   for (int q = 0; q < njobs; ++q) {
     nq[q] = max(0, dims[jobs.j[q].n_idx]);  // -1: an SVD solved by k_svd_jacobi
@@ -1988,7 +1964,7 @@ __global__ __launch_bounds__(DC_T) void k_dc_fused(EigJobs jobs, int njobs, int*
   for (int S = DC_SUB; S < nmax; S *= 2, par ^= 1) {
     int nm[4] = {0, 0, 0, 0}, tm = 0;
     for (int q = 0; q < njobs; ++q) tm += nm[q] = nq[q] > S ? (nq[q] + 2 * S - 1) / (2 * S) : 0;
-    grid_barrier(gs.flag, ++ord, P, &s_abort, dims);
+    grid_barrier(flags, ++ord, P, &s_abort, dims);
     const int X = 2 * S / 8;  // groups of 8 roots or poles of a merge
     for (int q = 0; q < njobs; ++q) cnt[q] = nm[q] * X;
     int have_q = -1, have_m = -1, nk = 0;  // the merge whose arrays are in LDS
@@ -2019,14 +1995,14 @@ __global__ __launch_bounds__(DC_T) void k_dc_fused(EigJobs jobs, int njobs, int*
       }
     }
     if (S >= DC_ZSPLIT) {
-      grid_barrier(gs.flag, ++ord, P, &s_abort, dims);
+      grid_barrier(flags, ++ord, P, &s_abort, dims);
       for (int t = b; t < tm * X; t += P) {
         int q, r;
         __syncthreads();  // the previous item's LDS reads are done
         if (dc_item(cnt, njobs, t, q, r)) dc_zhat_block(jobs.j[q], N, nq[q], S, r / X, r % X, smem);
       }
     }
-    grid_barrier(gs.flag, ++ord, P, &s_abort, dims);
+    grid_barrier(flags, ++ord, P, &s_abort, dims);
     const int TI = S / DC_RT, TJ = 2 * S / DC_CT, TM = 2 * TI * TJ;
     for (int q = 0; q < njobs; ++q) cnt[q] = nm[q] * TM;
     for (int t = b; t < tm * TM; t += P) {
@@ -2040,7 +2016,6 @@ __global__ __launch_bounds__(DC_T) void k_dc_fused(EigJobs jobs, int njobs, int*
         dc_update_tile<false>(jobs.j[q], dims, N, nq[q], S, par, m, h, ti, tj, smem, tile_lds);
     }
   }
-  grid_launch_end(gs, gen0, nmax > DC_SUB);
 }
 
 // Threshold of the clip rule: eigenvalues above it are kept.
@@ -2577,9 +2552,10 @@ __device__ int jacobi_sweeps(JacLds& L, int p, int q, int maxsw) {
 }
 
 __global__ __launch_bounds__(JAC_T) void k_svd_jacobi(const double* __restrict__ M, int ldm,
-                                                      EigJobs jobs, int* __restrict__ dims,
+                                                      EigJobs jobs, int* __restrict__ dims, int N,
                                                       int a_idx, int b_idx, int side_idx) {
   const EigJob J = jobs.j[0];
+  grid_clear(grid_flags(J.work, N), threadIdx.x, JAC_T);
   const int a = dims[a_idx], b = dims[b_idx], side = dims[side_idx];
   const int p = side ? a : b, q = side ? b : a;
   if (!jacobi_fits(p, q)) {  // the Golub-Kahan path
@@ -2714,6 +2690,8 @@ constexpr int GBR_T = 512;
 constexpr int GBR_W = GBR_T / 64;
 constexpr int GEBRD_QMAX = 1024;     // columns at most
 constexpr int GEBRD_GRID_PMAX = 64;  // blocks at most: 1024 rows, 16 a block above 704 columns
+static_assert(GEBRD_GRID_PMAX <= SYNC_MAXP && GEBRD_QMAX < (int)(GRID_ORD_DC - GRID_ORD_REDUCE),
+              "a flag a block, an ordinal a column");
 struct GebrdGridBufs {
   double *R, *Y, *S;  // published rows (2 x N), partial sums (2 x P x N), |c|^2 partials (2 x P)
 };
@@ -2799,9 +2777,8 @@ __device__ __forceinline__ void gebrd_rows(const double* __restrict__ M, int ldm
   }
   if (b == 0)
     for (int i = tid; i < 2 * q; i += GBR_T) W.d[i] = 0.0;
-  const GridSync gs = grid_sync_of(J.work, N);
-  const unsigned gen0 = grid_gen(gs);
-  unsigned ordinal = gen0 * GRID_ORD_SPAN;
+  unsigned* flags = grid_flags(J.work, N);
+  unsigned ordinal = GRID_ORD_REDUCE;
   const bool writer = b == 0 && wave == 0;
   for (int k = 0;; ++k) {
     double* srow = srow2 + (k & 1) * LQ;
@@ -2901,7 +2878,7 @@ __device__ __forceinline__ void gebrd_rows(const double* __restrict__ M, int ldm
         for (int w = 0; w < GBR_W; ++w) acc += ssq[w];
         xput(S + b, acc);
       }
-      grid_barrier_relaxed(gs.flag, ++ordinal, P, s_abort, dims);
+      grid_barrier_relaxed(flags, ++ordinal, P, s_abort, dims);
       for (int j = tid; j < q; j += GBR_T) {
         if (j < k) continue;
         double acc = 0.0;
@@ -2990,7 +2967,6 @@ __device__ __forceinline__ void gebrd_rows(const double* __restrict__ M, int ldm
       }
     }
   }
-  grid_launch_end(gs, gen0, P > 1);
 }
 
 // Blocks for a p x q matrix, p >= q: one, 16 rows a wavefront, up to 128 x 128;
@@ -3151,7 +3127,7 @@ void svd_short_side(const double* M, int ldm, int a_idx, int b_idx, int side_idx
   EigJobs J;
   J.j[0] = job;
   const int qcap = N / 2;
-  k_svd_jacobi<<<1, JAC_T, 0, s>>>(M, ldm, J, dims, a_idx, b_idx, side_idx);
+  k_svd_jacobi<<<1, JAC_T, 0, s>>>(M, ldm, J, dims, N, a_idx, b_idx, side_idx);
   const int qc = std::min(qcap, pcap);
   k_gebrd<<<gebrd_blocks(pcap, qc), GBR_T, gebrd_lds(qc), s>>>(M, ldm, J, dims, N, a_idx, b_idx, side_idx);
   dc_solve(J, 1, N, dims, s);
