@@ -27,7 +27,13 @@
  *  - All arrays are row-major float64.  Host core layouts:
  *      X  [N_s][r1],  Th [r1][N_theta][r2],  Ph [r2][N_phi],
  *    with spatial index i = ix + nx*(iy + ny*iz).
- *  - A context is not thread-safe; distinct contexts are independent.
+ *  - A context is not thread-safe; distinct contexts are independent and
+ *    may be used from several threads and streams at once.  The large-order
+ *    eigensolvers wait for their own blocks on the GPU, so what steps or
+ *    rounds at the same time on one GPU has to fit it: up to four contexts, or
+ *    two whose concatenated rank capacity is above 512 (one of those counts
+ *    for two).  More may end a call with TT_ERR_NUMERIC (a barrier that timed
+ *    out) where live orders above 192 meet.
  *  - After TT_ERR_NUMERIC (non-finite values, Newton or eigensolver
  *    failure) the context is poisoned: stepping returns TT_ERR_STATE until
  *    tt_set_cores installs a new state.

@@ -195,16 +195,28 @@ constexpr int SYR_MAX = 192;  // orders reduced in registers by k_sytrd_reg
 // LDS and a barrier that released and acquired it was 2.4, 0.7, 0.9 and 2.1.
 // An eigensolve of order 206, 322, 641, 1024, before and now: 1364 -> 984,
 // 2244 -> 1579, 6174 -> 5039, 11790 -> 9575 us.
-// The grid (at most 4 x 64 blocks of 256 threads) is a small part of what the chip holds
-// resident, so an ordinary launch has all blocks resident together (a
-// cooperative launch would drain the queue on every call, also when all jobs
-// are small and the kernel returns at once); every wait is bounded by
-// SYTRD_SPIN_MAX polls, after which the barrier-timeout flag is raised and
-// the kernel runs out.  Outputs (d, e, tau, reflectors in H): d, e the tridiagonal, row k of H and
+// The launch is an ordinary one (a cooperative one would drain the queue on every
+// call, also when all jobs are small and the kernel returns at once), so its
+// blocks must be resident together beside those of other streams' launches.  A
+// process has 4 hardware queues and the chip 256 CUs: every launch with grid
+// barriers keeps to GRID_CUS CUs, but the reductions of capacities above
+// SYG_WIDE, which keep to GRID_CUS_WIDE.  Up to SYG_WIDE a block has at most 256
+// registers a lane, so two fit a CU, and 4 jobs of 32 blocks fit 64.  Above, a
+// block takes a CU (about 490 registers; in 256 it spills, and orders 641 and
+// 897 took 5836 and 11532 us instead of 5113 and 8370), and two jobs of 64
+// blocks run side by side, a third after them.  So contexts may step at the same
+// time as long as their CUs add up to 256: four of them, or two above SYG_WIDE.  (With
+// all jobs side by side at one block a CU, as it was, three jobs took 96 CUs up to
+// order 512 and 192 above, and two contexts could wait for each other's CUs.)
+// Every wait is bounded by SYTRD_SPIN_MAX polls, after which the barrier-timeout
+// flag is raised and the kernel runs out.
+// Outputs (d, e, tau, reflectors in H): d, e the tridiagonal, row k of H and
 // tau[k] the reflector H_k = I - tau_k v v^T (v_{k+1} = 1).
+constexpr int GRID_CUS = 64, GRID_CUS_WIDE = 128;
+constexpr int SYG_WIDE = 512;
 constexpr int SYTRD_GRID_P = 64;
 constexpr int SYTRD_GRID_T = 256;
-constexpr int SYTRD_GRID_NMAX = 1024;                          // largest order
+constexpr int SYTRD_GRID_NMAX = 1024;  // largest order
 constexpr int SYG_R = 4;  // rows of a wavefront
 constexpr int SYG_T = SYTRD_GRID_NMAX / 64;  // columns per lane at most
 constexpr unsigned SYTRD_SPIN_MAX = 1u << 24;
@@ -468,23 +480,36 @@ __device__ __host__ inline int sytrd_grid_chunks(int n) {
 inline size_t sytrd_grid_lds(int N) {
   return (size_t)sytrd_grid_chunks(N) * 64 * 3 * (SYTRD_GRID_T / 64) * 8;
 }
+// Jobs of a launch that are reduced side by side; the others follow on the
+// same blocks.
+inline int sytrd_grid_jobs(int N, int njobs) {
+  return N <= SYG_WIDE ? njobs : std::min(njobs, GRID_CUS_WIDE / SYTRD_GRID_P);
+}
+static_assert(4 * (SYG_WIDE / 16) / 2 <= GRID_CUS && 2 * SYTRD_GRID_P <= GRID_CUS_WIDE, "CUs of a launch");
 
-__global__ __launch_bounds__(SYTRD_GRID_T) void k_sytrd_grid(EigJobs jobs, int* __restrict__ dims,
-                                                             int N) {
+// WIDE: capacities above SYG_WIDE.  Up to there 256 registers a lane do, and two
+// blocks fit a CU.
+template <bool WIDE>
+__global__ __launch_bounds__(SYTRD_GRID_T) __attribute__((amdgpu_waves_per_eu(WIDE ? 1 : 2))) void k_sytrd_grid(
+    EigJobs jobs, int njobs, int* __restrict__ dims, int N) {
   extern __shared__ double lds[];
   __shared__ int s_abort;
-  const EigJob J = jobs.j[blockIdx.y];
-  const int n = dims[J.n_idx];
-  if (n <= SYR_MAX) return;  // k_sytrd_reg (the same decision on all blocks of the job)
-  const int P = sytrd_grid_blocks(n);
-  if (blockIdx.x >= P) return;
-  if (threadIdx.x == 0) s_abort = 0;
-  __syncthreads();
-  if (n <= 256) sytrd_grid_rows<4>(J, dims, N, n, P, lds, &s_abort);
-  else if (n <= 384) sytrd_grid_rows<6>(J, dims, N, n, P, lds, &s_abort);
-  else if (n <= 512) sytrd_grid_rows<8>(J, dims, N, n, P, lds, &s_abort);
-  else if (n <= 704) sytrd_grid_rows<11>(J, dims, N, n, P, lds, &s_abort);
-  else sytrd_grid_rows<16>(J, dims, N, n, P, lds, &s_abort);
+  for (int q = blockIdx.y; q < njobs; q += gridDim.y) {
+    const EigJob J = jobs.j[q];
+    const int n = dims[J.n_idx];
+    if (n <= SYR_MAX) continue;  // k_sytrd_reg (the same decision on all blocks of the job)
+    const int P = sytrd_grid_blocks(n);
+    if (blockIdx.x >= P) continue;
+    if (WIDE) __syncthreads();  // the job before is done with the LDS
+    if (threadIdx.x == 0) s_abort = 0;
+    __syncthreads();
+    if (n <= 256) sytrd_grid_rows<4>(J, dims, N, n, P, lds, &s_abort);
+    else if (n <= 384) sytrd_grid_rows<6>(J, dims, N, n, P, lds, &s_abort);
+    else if (!WIDE || n <= 512) sytrd_grid_rows<8>(J, dims, N, n, P, lds, &s_abort);
+    else if (n <= 704) sytrd_grid_rows<11>(J, dims, N, n, P, lds, &s_abort);
+    else sytrd_grid_rows<16>(J, dims, N, n, P, lds, &s_abort);
+    if (!WIDE) break;  // a block has one job
+  }
 }
 
 // The same reduction with the matrix in registers (n <= SYR_MAX), one block
@@ -1933,7 +1958,7 @@ __device__ inline bool dc_item(const int* cnt, int njobs, int t, int& q, int& r)
 // 6871 -> 6174 us.  LDS: the phases' arrays share the dynamic buffer
 // (dc_fused_dyn_lds(N) bytes).
 constexpr int DCF_MAXP = 64;
-static_assert(DCF_MAXP <= SYNC_MAXP, "a flag a block");
+static_assert(DCF_MAXP <= SYNC_MAXP && DCF_MAXP <= GRID_CUS, "a flag a block, a CU a block");
 __global__ __launch_bounds__(DC_T) void k_dc_fused(EigJobs jobs, int njobs, int* __restrict__ dims,
                                                    int N) {
   extern __shared__ double smem[];
@@ -2690,6 +2715,7 @@ constexpr int GBR_T = 512;
 constexpr int GBR_W = GBR_T / 64;
 constexpr int GEBRD_QMAX = 1024;     // columns at most
 constexpr int GEBRD_GRID_PMAX = 64;  // blocks at most: 1024 rows, 16 a block above 704 columns
+static_assert(GEBRD_GRID_PMAX <= GRID_CUS, "a block fills a CU: 8 wavefronts of 256 registers");
 static_assert(GEBRD_GRID_PMAX <= SYNC_MAXP && GEBRD_QMAX < (int)(GRID_ORD_DC - GRID_ORD_REDUCE),
               "a flag a block, an ordinal a column");
 struct GebrdGridBufs {
@@ -3024,9 +3050,8 @@ size_t dc_fused_dyn_lds(int N) {
   return need;
 }
 // Blocks: a block each up to order 64; above, one for 8 roots or a top
-// merge's tile.  At most DCF_MAXP: with up to a CU's LDS each, the launches of
-// 4 hardware queues are still resident together, which their grid barriers
-// need.
+// merge's tile.  At most DCF_MAXP: with up to a CU's LDS each they keep to
+// GRID_CUS CUs (the residence that grid barriers need, k_sytrd_grid).
 int dc_fused_blocks(int N, int njobs) {
   if (N <= DC_SUB) return njobs;
   return std::min(DCF_MAXP, njobs * std::max((N + 7) / 8, N * N / 2048));
@@ -3070,7 +3095,7 @@ size_t eig_lds_bytes(int N, bool runtime, const char** which) {
   size_t worst = 0;
   // (an order past the columns that its registers hold counts as not fitting)
   if (N > SYR_MAX)
-    lds_note(static_lds((const void*)k_sytrd_grid, ST_SYTRD_GRID, runtime) + sytrd_grid_lds(N) +
+    lds_note(static_lds((const void*)k_sytrd_grid<true>, ST_SYTRD_GRID, runtime) + sytrd_grid_lds(N) +
                  (N > SYTRD_GRID_NMAX ? LDS_CU : 0),
              "k_sytrd_grid", worst, which);
   dc_lds(N, runtime, worst, which);
@@ -3114,8 +3139,9 @@ void eig_batched(const EigJob* jobs, int njobs, int N, int* dims, hipStream_t s)
   k_sytrd_reg<<<njobs, SYR_T, 0, s>>>(J, dims, N);
   if (N > SYR_MAX) {
     const int nj = njobs < 4 ? njobs : 4;
-    k_sytrd_grid<<<dim3(sytrd_grid_blocks(N), nj), SYTRD_GRID_T, sytrd_grid_lds(N), s>>>(J, dims,
-                                                                                         N);
+    const dim3 grid(sytrd_grid_blocks(N), sytrd_grid_jobs(N, nj));
+    if (N > SYG_WIDE) k_sytrd_grid<true><<<grid, SYTRD_GRID_T, sytrd_grid_lds(N), s>>>(J, nj, dims, N);
+    else k_sytrd_grid<false><<<grid, SYTRD_GRID_T, sytrd_grid_lds(N), s>>>(J, nj, dims, N);
   }
   dc_solve(J, njobs < 4 ? njobs : 4, N, dims, s);
   k_ormtr<false><<<dim3((N + 3) / 4, njobs), 256, ormtr_lds_doubles(N) * 8, s>>>(J, dims, N);
