@@ -857,6 +857,7 @@ __device__ void dc_leaf_wave(const EigJob& J, int* __restrict__ dims, int N, int
     fro += d[k] * d[k] + 2.0 * e[k] * e[k];
   }
   const double tiny = 0.125 * U64 * sqrt(fro);
+  bool bad = !(fro == fro);
   for (int l = 0; l < nb; ++l) {
     for (int it = 0; it < 40; ++it) {
       // the unreduced block that starts at 0 ends at row m; dm = d[m]
@@ -901,7 +902,10 @@ __device__ void dc_leaf_wave(const EigJob& J, int* __restrict__ dims, int N, int
       d[0] -= p;
       e[0] = g;
     }
-    if (lane == 0) L.lam[l] = d[0];
+    // (a NaN is flagged and sorts as the largest number, so that the places
+    // below stay a permutation)
+    bad = bad || !(d[0] == d[0]);
+    if (lane == 0) L.lam[l] = d[0] == d[0] ? d[0] : DBL_MAX;
     if (lane < DC_LEAF) L.V[lane][l] = v[0];
 #pragma unroll
     for (int k = 0; k + 1 < DC_LEAF; ++k) {
@@ -914,8 +918,7 @@ __device__ void dc_leaf_wave(const EigJob& J, int* __restrict__ dims, int N, int
     v[DC_LEAF - 1] = 0.0;
   }
   wave_sync();
-  // ascending (stable: the index breaks ties), an entry a lane; a NaN is
-  // flagged, its position stays within the leaf
+  // ascending (stable: the index breaks ties), an entry a lane
   const int i = lane / DC_LEAF, k = lane % DC_LEAF;
   if (k < nb) {
     const double x = L.lam[k];
@@ -923,8 +926,8 @@ __device__ void dc_leaf_wave(const EigJob& J, int* __restrict__ dims, int N, int
     for (int j = 0; j < nb; ++j) pos += L.lam[j] < x || (L.lam[j] == x && j < k);
     if (i < nb) D.Qa[(size_t)(r0 + i) * N2 + r0 + pos] = L.V[i][k];
     if (i == 0) lam[pos] = ldexp(x, ex);
-    if (i == 0 && (!(x == x) || !(fro == fro))) atomicOr(&dims[D_FLAG], FLAG_EIG);
   }
+  if (bad && lane == 0) atomicOr(&dims[D_FLAG], FLAG_EIG);
 }
 
 // Dynamic LDS of the phases above the one-block merges, per merge element: the sort and
@@ -1315,6 +1318,9 @@ __device__ void dc_subtree(const EigJob& J, int* __restrict__ dims, int N, int s
   const int base = sub * DC_SUB;
   const int tid = threadIdx.x, lane = tid & 63, l8 = tid & 7;
   bool bad = false;
+  // a place that no entry takes (halves that a flagged merge left out of order)
+  // still names a row of the block
+  if (tid < DC_SUB) L.perm[tid] = 0;
   dc_leaf_wave(J, dims, N, sub * (DC_SUB / DC_LEAF) + (tid >> 6), L.lam + DC_LEAF * (tid >> 6),
                reinterpret_cast<LeafLds*>(L.panel)[tid >> 6]);
   __syncthreads();
