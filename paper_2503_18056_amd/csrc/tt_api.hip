@@ -247,10 +247,7 @@ size_t carve(tt_ctx* x, char* base) {
   x->Xnf = x->mixed ? cv.take<float>((size_t)ns * x->ldX) : nullptr;
   x->Xcatf = x->mixed ? cv.take<float>((size_t)ns * x->ldC) : nullptr;
   x->colmax = x->mixed ? cv.take<unsigned>((size_t)std::max(x->R1c, x->r1c) + 64) : nullptr;
-  GramPlan p1 = gram_plan(ns, x->R1c, x->ldC), p2 = gram_plan(ns, x->r1c, x->ldX);
-  x->gpart = cv.take<double>(std::max(std::max(gram_partial_doubles(p1), gram_partial_doubles(p2)),
-                                      std::max((size_t)nt * x->R1c * x->R1c,
-                                               (size_t)nt * x->R2c * x->R2c)));
+  x->gpart = cv.take<double>(gpart_doubles(x));
   x->GA = cv.take<double>((size_t)x->R1c * x->R1c);
   x->GB1 = cv.take<double>((size_t)x->R1c * x->R1c);
   x->GR3 = cv.take<double>((size_t)x->R2c * x->R2c);
@@ -597,6 +594,16 @@ void energy_of_state(tt_ctx* c, double* E) {
 namespace tt {
 
 tt_status ctx_fail(tt_ctx* c, tt_status code, const std::string& msg) { return fail(c, code, msg); }
+
+size_t gpart_doubles(const tt_ctx* x) {
+  // a step's rounding, tt_round's, and the second one of TT_ROUND_TWICE (one
+  // column, the source's, beside the state's)
+  const GramPlan plans[] = {gram_plan(x->ns, x->R1c, x->ldC), gram_plan(x->ns, x->r1c, x->ldX),
+                            gram_plan(x->ns, x->r1c + 1, x->ldC)};
+  size_t n = std::max((size_t)x->nt * x->R1c * x->R1c, (size_t)x->nt * x->R2c * x->R2c);
+  for (const GramPlan& p : plans) n = std::max(n, gram_partial_doubles(p));
+  return n;
+}
 
 void step_body_frozen(tt_ctx* c) {
   hipStream_t s = c->st;

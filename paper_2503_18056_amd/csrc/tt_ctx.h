@@ -146,6 +146,9 @@ tt_status ctx_fail(tt_ctx* c, tt_status code, const std::string& msg);
 // of the step): X_cat, Theta_cat, Phi_cat and every rounding intermediate
 // stay in the context; X' is in Xn (FP64) or Xnf (mixed).
 void step_body_frozen(tt_ctx* c);
+// Doubles of the partial-tile buffer gpart: the Gram plans of every capacity that
+// a rounding is called at, and the N_theta partial products of the small Grams.
+size_t gpart_doubles(const tt_ctx* c);
 // Adjoint buffers (appended to the workspace when ckpt_every > 0).
 void grad_carve(tt_ctx* c, Carve& cv);
 // Before step number c->nhist: store a checkpoint if one is due.
