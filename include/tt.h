@@ -147,7 +147,9 @@ size_t tt_workspace_bytes(const tt_config* cfg, int32_t n_inflow);
  *  X0, Th0, Ph0: host initial cores with ranks r1, r2 (<= the rank caps).
  *  dev_workspace: device, >= tt_workspace_bytes(cfg, n_inflow) bytes,
  *      caller-owned, must outlive the context; the library allocates no
- *      other device memory.
+ *      other device memory.  (One that is short of partial tiles of the
+ *      N_s-long Gram only is taken as well: above 384 columns it runs on
+ *      fewer row slices then, at least one per 1024 rows or 64.)
  *  hip_stream: a hipStream_t (NULL = default stream), caller-owned.
  *  out: receives the context.
  * Host inputs are validated before any device work: every value finite,

@@ -6,7 +6,8 @@
  * against a plain reference on random inputs.  All matrix pointers are
  * device memory, row-major float64, caller-owned.  `ws` is caller-owned
  * device scratch of at least the bytes returned by the matching
- * *_workspace() query.  Each call runs on `stream` (a hipStream_t, NULL =
+ * *_workspace() query (the Grams above 384 columns take less as well, down
+ * to the partial tiles of one row slice per 1024 rows, 8 to 64 of them).  Each call runs on `stream` (a hipStream_t, NULL =
  * default) and returns after a stream synchronisation.  Errors:
  * TT_ERR_INVALID_ARG (sizes, null pointers), TT_ERR_OOM (ws too small),
  * TT_ERR_DEVICE (HIP failure); messages via tt_last_error(NULL).
@@ -58,9 +59,11 @@ tt_status tt_kernel_gram(const double* A, int32_t K, int32_t n, int32_t lda, dou
  * G = A^T A as tt_kernel_gram, with no workspace argument.  Its scratch (a
  * 64-int size table and the per-block partial Gram tiles) lives in a
  * library-owned 32 MiB device array per GPU, held until the process ends;
- * the call allocates nothing.  Sizes whose partial tiles do not fit (about
- * 256 row blocks x ceil(n/32)(ceil(n/32)+1)/2 tiles of 8 KiB for n <= 384,
- * e.g. every K for n <= 160) return TT_ERR_INVALID_ARG.  All calls on one
+ * the call allocates nothing.  Sizes whose partial tiles do not fit return
+ * TT_ERR_INVALID_ARG: for n <= 384 about 256 row blocks x
+ * ceil(n/32)(ceil(n/32)+1)/2 tiles of 8 KiB (every K fits for n <= 160),
+ * above, with t = ceil(n/128), one row slice per 1024 rows (a multiple of 8,
+ * 8 to 64) x t(t+1)/2 tiles of 128 KiB.  All calls on one
  * GPU share the array and every call overwrites it: calls that overlap on
  * one GPU (other streams, other threads) race and must be serialised by the
  * caller. */

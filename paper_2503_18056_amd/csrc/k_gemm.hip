@@ -416,7 +416,7 @@ __global__ void k_gram_rows(const T* __restrict__ A, int lda, int K, int rows_pe
 __global__ void k_gram_rows_reduce(const double* __restrict__ partial, int nblk, DimExpr ndim,
                                    const int* __restrict__ dims, double* __restrict__ G, int ldg);
 
-GramPlan gram_plan(int K, int ncap, int lda) {
+GramPlan gram_plan(int K, int ncap, int lda, size_t room) {
   GramPlan p;
   p.K = K;
   p.ncap = ncap;
@@ -437,13 +437,21 @@ GramPlan gram_plan(int K, int ncap, int lda) {
   // slices, 37.0 with 64, whose blocks took 7 ms each and left the last
   // round three quarters empty), and of fewer where that gives less than 768
   // blocks, down to 256 rows (16384 x 641: 0.19 ms with 32 slices, 0.32 with
-  // 16; 4096 x 537: 0.077 against 0.115 ms)
+  // 16; 4096 x 537: 0.077 against 0.115 ms).  Where the partial tiles have
+  // less room than that, as many as fit, down to slices of 1024 rows, at most 64
+  // (a workspace of that size, and the fixed scratch of tt_kernel_gram_noalloc,
+  // are taken).
   p.wtiles = (ncap + GW_T - 1) / GW_T;
   p.wpairs = p.wtiles * (p.wtiles + 1) / 2;
   int ws = K / 256 < 768 / p.wpairs ? K / 256 : 768 / p.wpairs;
   if (ws < K / 8192) ws = K / 8192;
   ws = ws < GW_XCD ? GW_XCD : (ws > 256 ? 256 : ws);
   ws = ws / GW_XCD * GW_XCD;
+  int wm = K / 1024;
+  wm = (wm < GW_XCD ? GW_XCD : (wm > 64 ? 64 : wm)) / GW_XCD * GW_XCD;
+  p.wmin = wm < ws ? wm : ws;
+  const size_t fit = room / ((size_t)p.wpairs * GW_T * GW_T) / GW_XCD * GW_XCD;
+  if (fit < (size_t)ws) ws = fit < (size_t)p.wmin ? p.wmin : (int)fit;
   p.wkslice = ((K + ws - 1) / ws + GW_KB - 1) / GW_KB * GW_KB;
   p.wslices = ws;
   return p;
@@ -452,6 +460,9 @@ GramPlan gram_plan(int K, int ncap, int lda) {
 size_t gram_partial_doubles(const GramPlan& p) {
   if (p.rows_mode) return (size_t)p.nblk * p.ntask_cap * 1024;
   return (size_t)p.wslices * p.wpairs * GW_T * GW_T;
+}
+size_t gram_partial_min_doubles(const GramPlan& p) {
+  return p.rows_mode ? gram_partial_doubles(p) : (size_t)p.wmin * p.wpairs * GW_T * GW_T;
 }
 
 template <typename T>

@@ -247,7 +247,7 @@ size_t carve(tt_ctx* x, char* base) {
   x->Xnf = x->mixed ? cv.take<float>((size_t)ns * x->ldX) : nullptr;
   x->Xcatf = x->mixed ? cv.take<float>((size_t)ns * x->ldC) : nullptr;
   x->colmax = x->mixed ? cv.take<unsigned>((size_t)std::max(x->R1c, x->r1c) + 64) : nullptr;
-  x->gpart = cv.take<double>(gpart_doubles(x));
+  x->gpart = cv.take<double>(x->gpart_n);
   x->GA = cv.take<double>((size_t)x->R1c * x->R1c);
   x->GB1 = cv.take<double>((size_t)x->R1c * x->R1c);
   x->GR3 = cv.take<double>((size_t)x->R2c * x->R2c);
@@ -486,7 +486,7 @@ void round_pipeline(tt_ctx* c, const double* xc, int ldxc, int ncap1, double tol
                  R1c, R1c, c->dims, s);
   }
   {
-    GramPlan plan = gram_plan(c->ns, ncap1, ldxc);
+    GramPlan plan = gram_plan(c->ns, ncap1, ldxc, c->gpart_n);
     {
       Prof p(c, P_GRAM);
       if (xcf) gram_split_partial(plan, xcf, dimv(D_RC1), c->colmax, c->gpart, c->dims, s, c->gram_slices);
@@ -595,13 +595,13 @@ namespace tt {
 
 tt_status ctx_fail(tt_ctx* c, tt_status code, const std::string& msg) { return fail(c, code, msg); }
 
-size_t gpart_doubles(const tt_ctx* x) {
+size_t gpart_doubles(const tt_ctx* x, bool least) {
   // a step's rounding, tt_round's, and the second one of TT_ROUND_TWICE (one
   // column, the source's, beside the state's)
   const GramPlan plans[] = {gram_plan(x->ns, x->R1c, x->ldC), gram_plan(x->ns, x->r1c, x->ldX),
                             gram_plan(x->ns, x->r1c + 1, x->ldC)};
   size_t n = std::max((size_t)x->nt * x->R1c * x->R1c, (size_t)x->nt * x->R2c * x->R2c);
-  for (const GramPlan& p : plans) n = std::max(n, gram_partial_doubles(p));
+  for (const GramPlan& p : plans) n = std::max(n, least ? gram_partial_min_doubles(p) : gram_partial_doubles(p));
   return n;
 }
 
@@ -814,6 +814,7 @@ size_t tt_workspace_bytes(const tt_config* cfg, int32_t n_inflow) {
     g_err = "concatenated rank capacity above 1024 (lower rmax)";
     return 0;
   }
+  tmp.gpart_n = gpart_doubles(&tmp, false);
   return carve(&tmp, nullptr);
 }
 
@@ -879,7 +880,16 @@ tt_status tt_create(const tt_config* cfg, const double* kappa, const double* rho
     delete c;
     return fail(nullptr, TT_ERR_INVALID_ARG, "concatenated rank capacity above 1024 (lower rmax)");
   }
+  // a workspace short of some of the Gram's partial tiles does with fewer row slices
+  c->gpart_n = gpart_doubles(c, false);
   c->ws_need = carve(c, nullptr);
+  if (ws_bytes < c->ws_need) {
+    const size_t all = c->gpart_n;
+    c->gpart_n = gpart_doubles(c, true);
+    const size_t least = carve(c, nullptr);
+    if (ws_bytes > least) c->gpart_n = std::min(all, c->gpart_n + (ws_bytes - least) / 256 * 32);
+    c->ws_need = carve(c, nullptr);
+  }
   if (!dev_workspace || ws_bytes < c->ws_need) {
     delete c;
     return fail(nullptr, TT_ERR_OOM, "workspace too small: need " + std::to_string(tt_workspace_bytes(cfg, n_inflow)) + " bytes");

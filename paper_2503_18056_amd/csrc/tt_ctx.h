@@ -103,6 +103,7 @@ struct tt_ctx {
   float *Xf, *Xnf, *Xcatf;   // FP32 state / update / concatenation (mixed form only)
   unsigned* colmax;          // per-column max |X_cat| bits for the sliced Gram
   double *Thcat, *Phcat, *Xcat, *gpart;
+  size_t gpart_n = 0;        // doubles of gpart
   double *GA, *GB1, *GR3, *GL2, *T1;
   tt::EigSlot E[6];  // bond 1: 0 G_A, 1 G_B1, 2 G_R3, 3 SVD of M1; bond 2: 4 G_L2, 5 SVD of M2
   double *M1, *C1, *Wm1, *Ur1, *P1, *Mupd1, *Thp;
@@ -147,8 +148,9 @@ tt_status ctx_fail(tt_ctx* c, tt_status code, const std::string& msg);
 // stay in the context; X' is in Xn (FP64) or Xnf (mixed).
 void step_body_frozen(tt_ctx* c);
 // Doubles of the partial-tile buffer gpart: the Gram plans of every capacity that
-// a rounding is called at, and the N_theta partial products of the small Grams.
-size_t gpart_doubles(const tt_ctx* c);
+// a rounding is called at, and the N_theta partial products of the small Grams;
+// least: with the fewest row slices that the plans may take.
+size_t gpart_doubles(const tt_ctx* c, bool least);
 // Adjoint buffers (appended to the workspace when ckpt_every > 0).
 void grad_carve(tt_ctx* c, Carve& cv);
 // Before step number c->nhist: store a checkpoint if one is due.

@@ -107,15 +107,19 @@ void sum_partials(const double* part, long long zstride, int nz, double* out, in
 struct GramPlan {
   int K, ncap, lda;
   // above 384 columns (FP64 and the sliced FP32 form): 128-column tile
-  // pairs, wslices row slices of wkslice rows
-  int wtiles, wpairs, wslices, wkslice;
+  // pairs, wslices row slices of wkslice rows; the fewest slices it may take
+  int wtiles, wpairs, wslices, wkslice, wmin;
   // row-slice form (ncap <= 384): nblk blocks of rows_per_blk rows, up to
   // ntask_cap upper-triangular 32x32 tasks each
   bool rows_mode;
   int nblk, rows_per_blk, ntask_cap;
 };
-GramPlan gram_plan(int K, int ncap, int lda);
+// room: doubles there are for the partial tiles.  A plan needs them all
+// (gram_partial_doubles) or, for want of room, works with fewer row slices down to
+// gram_partial_min_doubles; the caller refuses less.
+GramPlan gram_plan(int K, int ncap, int lda, size_t room = (size_t)-1);
 size_t gram_partial_doubles(const GramPlan& p);
+size_t gram_partial_min_doubles(const GramPlan& p);
 void gram_tall(const GramPlan& p, const double* A, DimExpr n, double* partial, double* G,
                int ldg, const int* dims, hipStream_t s);
 void gram_tall_partial(const GramPlan& p, const double* A, DimExpr n, double* partial,

@@ -180,15 +180,18 @@ tt_status tt_kernel_gram(const double* A, int32_t K, int32_t n, int32_t lda, dou
                          int32_t ldg, void* ws, size_t ws_bytes, void* stream) {
   if (!A || !G || !ws || K < 1 || n < 1 || lda < n || ldg < n)
     return kfail(TT_ERR_INVALID_ARG, "bad gram arguments");
-  if (ws_bytes < tt_kernel_gram_workspace(K, n, lda)) return kfail(TT_ERR_OOM, "workspace too small");
+  const size_t fixed = align256(64 * sizeof(int));
+  const GramPlan plan = gram_plan(K, n, lda, ws_bytes > fixed ? (ws_bytes - fixed) / 8 : 0);
+  if (ws_bytes < fixed + align256(gram_partial_doubles(plan) * 8))
+    return kfail(TT_ERR_OOM, "workspace too small");
   hipStream_t s = (hipStream_t)stream;
   int* dims = (int*)ws;
-  double* part = (double*)((char*)ws + align256(64 * sizeof(int)));
+  double* part = (double*)((char*)ws + fixed);
   int hd[64];
   memset(hd, 0, sizeof(hd));
   hd[0] = n;
   KCHK(hipMemcpyAsync(dims, hd, sizeof(hd), hipMemcpyHostToDevice, s));
-  gram_tall(gram_plan(K, n, lda), A, dimv(0), part, G, ldg, dims, s);
+  gram_tall(plan, A, dimv(0), part, G, ldg, dims, s);
   KCHK(hipGetLastError());
   KCHK(hipStreamSynchronize(s));
   return TT_OK;
@@ -198,7 +201,7 @@ tt_status tt_kernel_gram_noalloc(const double* A, int32_t K, int32_t n, int32_t 
                                  int32_t ldg, void* stream) {
   if (!A || !G || K < 1 || n < 1 || lda < n || ldg < n)
     return kfail(TT_ERR_INVALID_ARG, "bad gram arguments");
-  const GramPlan plan = gram_plan(K, n, lda);
+  const GramPlan plan = gram_plan(K, n, lda, (NOALLOC_BYTES - align256(64 * sizeof(int))) / 8);
   const size_t need = align256(64 * sizeof(int)) + align256(gram_partial_doubles(plan) * 8);
   if (need > NOALLOC_BYTES)
     return kfail(TT_ERR_INVALID_ARG, "gram_noalloc: the partial tiles need " + std::to_string(need) +
@@ -226,9 +229,11 @@ tt_status tt_kernel_gram_f32(const float* A, int32_t K, int32_t n, int32_t lda, 
                              int32_t ldg, void* ws, size_t ws_bytes, void* stream) {
   if (!A || !G || !ws || K < 1 || n < 1 || n > 1024 || lda < n || ldg < n)
     return kfail(TT_ERR_INVALID_ARG, "bad gram_f32 arguments");
-  if (ws_bytes < tt_kernel_gram_f32_workspace(K, n, lda)) return kfail(TT_ERR_OOM, "workspace too small");
+  const size_t fixed = align256(64 * sizeof(int)) + align256(((size_t)n + 64) * sizeof(unsigned));
+  const GramPlan plan = gram_plan(K, n, lda, ws_bytes > fixed ? (ws_bytes - fixed) / 8 : 0);
+  if (ws_bytes < fixed + align256(gram_partial_doubles(plan) * 8))
+    return kfail(TT_ERR_OOM, "workspace too small");
   hipStream_t s = (hipStream_t)stream;
-  const GramPlan plan = gram_plan(K, n, lda);
   char* p = (char*)ws;
   int* dims = (int*)p;
   p += align256(64 * sizeof(int));

@@ -328,8 +328,8 @@ extern "C" tt_status tt_round_randomized(tt_ctx* c, const double* omega1, int32_
   gemm_tall(ns, c->X, c->ldX, W1, k1, Z, ldz, dimc(r1), dimc(k1), r1, k1, c->dims, s);
   // the sketch's k1 columns (row-slice form up to 384), when its partial
   // tiles fit the Gram partial buffer
-  GramPlan p1 = gram_plan(ns, k1, ldz);
-  if (gram_partial_doubles(p1) > gpart_doubles(c)) p1 = gram_plan(ns, R1c, ldz);
+  GramPlan p1 = gram_plan(ns, k1, ldz, c->gpart_n);
+  if (gram_partial_doubles(p1) > c->gpart_n) p1 = gram_plan(ns, R1c, ldz, c->gpart_n);
   cholqr(c, Tall{ns, Z, ldz, true}, k1, o1, c->Xn, c->ldX, &p1);
   double* M1 = c->Mupd1;  // k1 x r1 = Q1^T X, ld R1c
   contract_tall(c, c->Xn, c->ldX, c->X, c->ldX, ns, k1, r1, M1, R1c);
