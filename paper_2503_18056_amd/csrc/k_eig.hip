@@ -813,7 +813,80 @@ __device__ inline DC dc_of(const Work& W, int N) {
 // reciprocal root and about 45 instructions each, which a lone wavefront
 // issues every 7 cycles): 15 us at order 16, 26 at 62, with the first loads.
 // Cyclic Jacobi through LDS, a lane per entry, took 8 us more at order 16 and 25 at 62.
+
+// The implicit QL iteration on a leaf's d, e, v (rows past nb are decoupled
+// zeros; an off-diagonal at or below `tiny` is dropped): emit(l, eigenvalue,
+// this lane's entry of its vector) for l < nb.  Returns whether every
+// eigenvalue split off within LEAF_MAXIT iterations (it takes two or three).
 constexpr int DC_LEAF = 8;
+constexpr int LEAF_MAXIT = 40;
+template <typename Emit>
+__device__ __forceinline__ bool leaf_ql(double (&d)[DC_LEAF], double (&e)[DC_LEAF], double (&v)[DC_LEAF], int nb,
+                                        double tiny, Emit emit) {
+  bool conv = true;
+  for (int l = 0; l < nb; ++l) {
+    bool split = false;
+    for (int it = 0; it < LEAF_MAXIT; ++it) {
+      // the unreduced block that starts at 0 ends at row m; dm = d[m]
+      int m = 0;
+      double dm = d[0];
+      bool open = true;
+#pragma unroll
+      for (int k = 0; k < DC_LEAF - 1; ++k) {
+        const double ae = fabs(e[k]);
+        const bool drop = ae <= tiny || ae <= U64 * (fabs(d[k]) + fabs(d[k + 1]));
+        e[k] = open && drop ? 0.0 : e[k];
+        open = open && !drop;
+        m = open ? k + 1 : m;
+        dm = open ? d[k + 1] : dm;
+      }
+      m = __builtin_amdgcn_readfirstlane(m);  // the same on every lane
+      if (m == 0) {
+        split = true;
+        break;
+      }
+      // shift: the eigenvalue of the leading 2 x 2 nearer d[0]
+      const double del = d[1] - d[0], two = 2.0 * e[0];
+      const double hyp = sqrt(del * del + two * two);
+      double g = dm - d[0] + e[0] * two / (del + copysign(hyp, del));
+      double c = 1.0, s = 1.0, p = 0.0;
+#pragma unroll
+      for (int i = DC_LEAF - 2; i >= 0; --i) {
+        if (i < m) {
+          const double f = s * e[i], b = c * e[i];
+          const double h = f * f + g * g;
+          const double rh = h > 1e-280 ? rsqrt_d(h) : 0.0;
+          if (i + 1 < m) e[i + 1] = h * rh;
+          s = f * rh;
+          c = rh > 0.0 ? g * rh : 1.0;
+          const double dn = d[i + 1] - p;
+          const double w = (d[i] - dn) * s + 2.0 * c * b;
+          p = s * w;
+          d[i + 1] = dn + p;
+          g = c * w - b;
+          const double x = v[i + 1], y = v[i];
+          v[i + 1] = s * y + c * x;
+          v[i] = c * y - s * x;
+        }
+      }
+      d[0] -= p;
+      e[0] = g;
+    }
+    conv = conv && split;
+    emit(l, d[0], v[0]);
+#pragma unroll
+    for (int k = 0; k + 1 < DC_LEAF; ++k) {
+      d[k] = d[k + 1];
+      e[k] = e[k + 1];
+      v[k] = v[k + 1];
+    }
+    d[DC_LEAF - 1] = 0.0;
+    e[DC_LEAF - 1] = 0.0;
+    v[DC_LEAF - 1] = 0.0;
+  }
+  return conv;
+}
+
 struct LeafLds {
   double lam[DC_LEAF], V[DC_LEAF][DC_LEAF + 1];
 };
@@ -856,67 +929,15 @@ __device__ void dc_leaf_wave(const EigJob& J, int* __restrict__ dims, int N, int
     e[k] = ldexp(e[k], -ex);
     fro += d[k] * d[k] + 2.0 * e[k] * e[k];
   }
-  const double tiny = 0.125 * U64 * sqrt(fro);
   bool bad = !(fro == fro);
-  for (int l = 0; l < nb; ++l) {
-    for (int it = 0; it < 40; ++it) {
-      // the unreduced block that starts at 0 ends at row m; dm = d[m]
-      int m = 0;
-      double dm = d[0];
-      bool open = true;
-#pragma unroll
-      for (int k = 0; k < DC_LEAF - 1; ++k) {
-        const double ae = fabs(e[k]);
-        const bool drop = ae <= tiny || ae <= U64 * (fabs(d[k]) + fabs(d[k + 1]));
-        e[k] = open && drop ? 0.0 : e[k];
-        open = open && !drop;
-        m = open ? k + 1 : m;
-        dm = open ? d[k + 1] : dm;
-      }
-      m = __builtin_amdgcn_readfirstlane(m);  // the same on every lane
-      if (m == 0) break;
-      // shift: the eigenvalue of the leading 2 x 2 nearer d[0]
-      const double del = d[1] - d[0], two = 2.0 * e[0];
-      const double hyp = sqrt(del * del + two * two);
-      double g = dm - d[0] + e[0] * two / (del + copysign(hyp, del));
-      double c = 1.0, s = 1.0, p = 0.0;
-#pragma unroll
-      for (int i = DC_LEAF - 2; i >= 0; --i) {
-        if (i < m) {
-          const double f = s * e[i], b = c * e[i];
-          const double h = f * f + g * g;
-          const double rh = h > 1e-280 ? rsqrt_d(h) : 0.0;
-          if (i + 1 < m) e[i + 1] = h * rh;
-          s = f * rh;
-          c = rh > 0.0 ? g * rh : 1.0;
-          const double dn = d[i + 1] - p;
-          const double w = (d[i] - dn) * s + 2.0 * c * b;
-          p = s * w;
-          d[i + 1] = dn + p;
-          g = c * w - b;
-          const double x = v[i + 1], y = v[i];
-          v[i + 1] = s * y + c * x;
-          v[i] = c * y - s * x;
-        }
-      }
-      d[0] -= p;
-      e[0] = g;
-    }
+  const bool conv = leaf_ql(d, e, v, nb, 0.125 * U64 * sqrt(fro), [&](int l, double x, double y) {
     // (a NaN is flagged and sorts as the largest number, so that the places
     // below stay a permutation)
-    bad = bad || !(d[0] == d[0]);
-    if (lane == 0) L.lam[l] = d[0] == d[0] ? d[0] : DBL_MAX;
-    if (lane < DC_LEAF) L.V[lane][l] = v[0];
-#pragma unroll
-    for (int k = 0; k + 1 < DC_LEAF; ++k) {
-      d[k] = d[k + 1];
-      e[k] = e[k + 1];
-      v[k] = v[k + 1];
-    }
-    d[DC_LEAF - 1] = 0.0;
-    e[DC_LEAF - 1] = 0.0;
-    v[DC_LEAF - 1] = 0.0;
-  }
+    bad = bad || !(x == x);
+    if (lane == 0) L.lam[l] = x == x ? x : DBL_MAX;
+    if (lane < DC_LEAF) L.V[lane][l] = y;
+  });
+  bad = bad || !conv;
   wave_sync();
   // ascending (stable: the index breaks ties), an entry a lane
   const int i = lane / DC_LEAF, k = lane % DC_LEAF;
@@ -995,6 +1016,7 @@ template <bool STAGE> constexpr int dc_kc() { return STAGE ? 256 : 128; }
 // counts: starting from the middle's exact-weight model takes about 4
 // evaluations, where both bracket ends were evaluated first and the first
 // iterate was their geometric mean it took 8.
+constexpr int ROOT_MAXIT = 100;
 template <int L>
 __device__ inline void dc_root(const double* d, const double* z, int nk, int i, double rho,
                                int lane, double& tau_out, double& dor_out, bool& ok) {
@@ -1025,7 +1047,8 @@ __device__ inline void dc_root(const double* d, const double* z, int nk, int i, 
   double pl = ds - dor, pr = dn - dor;
   double tau = 0.0, fprev = 0.0;
   bool fw = false;
-  for (int it = 0; it < 100; ++it) {
+  bool conv = false;
+  for (int it = 0; it < ROOT_MAXIT; ++it) {
     // psi, psi', phi, phi' at x
     double ps = 0.0, dps = 0.0, ph = 0.0, dph = 0.0;
     for (int j = lane; j < nk; j += L) {
@@ -1066,12 +1089,20 @@ __device__ inline void dc_root(const double* d, const double* z, int nk, int i, 
       if (hi == 0.0) hi = lo * 0x1p-60;
     }
     // converged once f is at the level of its own rounding error
-    if (f == 0.0 || fabs(f) <= 8.0 * U64 * (1.0 + rho * (fabs(ph) + fabs(ps)))) { tau = x; break; }
+    if (f == 0.0 || fabs(f) <= 8.0 * U64 * (1.0 + rho * (fabs(ph) + fabs(ps)))) {
+      tau = x;
+      conv = true;
+      break;
+    }
     if (it > 0 || !inner) {
       if (f < 0.0) lo = x;
       else hi = x;
     }
-    if (hi - lo <= 4.0 * U64 * fmax(fabs(lo), fabs(hi))) { tau = 0.5 * (lo + hi); break; }
+    if (hi - lo <= 4.0 * U64 * fmax(fabs(lo), fabs(hi))) {
+      tau = 0.5 * (lo + hi);
+      conv = true;
+      break;
+    }
     // when f keeps its sign and falls by less than a factor of 10, the
     // other model takes the next step
     if (it > 0 && inner && f * fprev > 0.0 && fabs(f) > 0.1 * fabs(fprev)) fw = !fw;
@@ -1119,14 +1150,23 @@ __device__ inline void dc_root(const double* d, const double* z, int nk, int i, 
     if (!(xn > lo && xn < hi)) {
       xn = (lo > 0.0 && hi > 4.0 * lo) ? sqrt(lo) * sqrt(hi)
          : (hi < 0.0 && lo < 4.0 * hi) ? -sqrt(-lo) * sqrt(-hi) : 0.5 * (lo + hi);
-      if (!(xn > lo && xn < hi)) { tau = 0.5 * (lo + hi); break; }
+      if (!(xn > lo && xn < hi)) {  // no number between the ends (or a NaN)
+        tau = 0.5 * (lo + hi);
+        conv = true;
+        break;
+      }
     }
-    if (fabs(xn - x) <= 2.0 * U64 * fabs(xn)) { tau = xn; break; }
+    if (fabs(xn - x) <= 2.0 * U64 * fabs(xn)) {
+      tau = xn;
+      conv = true;
+      break;
+    }
     x = xn;
     tau = x;
   }
   ok = tau == tau && tau != 0.0;
   if (!ok) tau = right ? lo : hi;
+  ok = ok && conv;
   tau_out = tau;
   dor_out = dor;
 }
