@@ -825,8 +825,8 @@ __device__ __forceinline__ bool leaf_ql(double (&d)[DC_LEAF], double (&e)[DC_LEA
                                         double tiny, Emit emit) {
   bool conv = true;
   for (int l = 0; l < nb; ++l) {
-    bool split = false;
-    for (int it = 0; it < LEAF_MAXIT; ++it) {
+    int it = 0;
+    for (; it < LEAF_MAXIT; ++it) {
       // the unreduced block that starts at 0 ends at row m; dm = d[m]
       int m = 0;
       double dm = d[0];
@@ -841,10 +841,7 @@ __device__ __forceinline__ bool leaf_ql(double (&d)[DC_LEAF], double (&e)[DC_LEA
         dm = open ? d[k + 1] : dm;
       }
       m = __builtin_amdgcn_readfirstlane(m);  // the same on every lane
-      if (m == 0) {
-        split = true;
-        break;
-      }
+      if (m == 0) break;
       // shift: the eigenvalue of the leading 2 x 2 nearer d[0]
       const double del = d[1] - d[0], two = 2.0 * e[0];
       const double hyp = sqrt(del * del + two * two);
@@ -872,7 +869,7 @@ __device__ __forceinline__ bool leaf_ql(double (&d)[DC_LEAF], double (&e)[DC_LEA
       d[0] -= p;
       e[0] = g;
     }
-    conv = conv && split;
+    conv = conv && it < LEAF_MAXIT;
     emit(l, d[0], v[0]);
 #pragma unroll
     for (int k = 0; k + 1 < DC_LEAF; ++k) {
@@ -929,15 +926,18 @@ __device__ void dc_leaf_wave(const EigJob& J, int* __restrict__ dims, int N, int
     e[k] = ldexp(e[k], -ex);
     fro += d[k] * d[k] + 2.0 * e[k] * e[k];
   }
-  bool bad = !(fro == fro);
-  const bool conv = leaf_ql(d, e, v, nb, 0.125 * U64 * sqrt(fro), [&](int l, double x, double y) {
-    // (a NaN is flagged and sorts as the largest number, so that the places
-    // below stay a permutation)
-    bad = bad || !(x == x);
-    if (lane == 0) L.lam[l] = x == x ? x : DBL_MAX;
+  // a leaf with a NaN is flagged and solved as a zero one, so that the places
+  // below stay a permutation (numbers give numbers)
+  const bool nan = !(fro == fro);
+#pragma unroll
+  for (int k = 0; k < DC_LEAF; ++k) {
+    d[k] = nan ? 0.0 : d[k];
+    e[k] = nan ? 0.0 : e[k];
+  }
+  const bool conv = leaf_ql(d, e, v, nb, 0.125 * U64 * sqrt(nan ? 0.0 : fro), [&](int l, double x, double y) {
+    if (lane == 0) L.lam[l] = x;
     if (lane < DC_LEAF) L.V[lane][l] = y;
   });
-  bad = bad || !conv;
   wave_sync();
   // ascending (stable: the index breaks ties), an entry a lane
   const int i = lane / DC_LEAF, k = lane % DC_LEAF;
@@ -948,7 +948,7 @@ __device__ void dc_leaf_wave(const EigJob& J, int* __restrict__ dims, int N, int
     if (i < nb) D.Qa[(size_t)(r0 + i) * N2 + r0 + pos] = L.V[i][k];
     if (i == 0) lam[pos] = ldexp(x, ex);
   }
-  if (bad && lane == 0) atomicOr(&dims[D_FLAG], FLAG_EIG);
+  if ((nan || !conv) && lane == 0) atomicOr(&dims[D_FLAG], FLAG_EIG);
 }
 
 // Dynamic LDS of the phases above the one-block merges, per merge element: the sort and
@@ -1047,8 +1047,8 @@ __device__ inline void dc_root(const double* d, const double* z, int nk, int i, 
   double pl = ds - dor, pr = dn - dor;
   double tau = 0.0, fprev = 0.0;
   bool fw = false;
-  bool conv = false;
-  for (int it = 0; it < ROOT_MAXIT; ++it) {
+  int it = 0;
+  for (; it < ROOT_MAXIT; ++it) {
     // psi, psi', phi, phi' at x
     double ps = 0.0, dps = 0.0, ph = 0.0, dph = 0.0;
     for (int j = lane; j < nk; j += L) {
@@ -1089,20 +1089,12 @@ __device__ inline void dc_root(const double* d, const double* z, int nk, int i, 
       if (hi == 0.0) hi = lo * 0x1p-60;
     }
     // converged once f is at the level of its own rounding error
-    if (f == 0.0 || fabs(f) <= 8.0 * U64 * (1.0 + rho * (fabs(ph) + fabs(ps)))) {
-      tau = x;
-      conv = true;
-      break;
-    }
+    if (f == 0.0 || fabs(f) <= 8.0 * U64 * (1.0 + rho * (fabs(ph) + fabs(ps)))) { tau = x; break; }
     if (it > 0 || !inner) {
       if (f < 0.0) lo = x;
       else hi = x;
     }
-    if (hi - lo <= 4.0 * U64 * fmax(fabs(lo), fabs(hi))) {
-      tau = 0.5 * (lo + hi);
-      conv = true;
-      break;
-    }
+    if (hi - lo <= 4.0 * U64 * fmax(fabs(lo), fabs(hi))) { tau = 0.5 * (lo + hi); break; }
     // when f keeps its sign and falls by less than a factor of 10, the
     // other model takes the next step
     if (it > 0 && inner && f * fprev > 0.0 && fabs(f) > 0.1 * fabs(fprev)) fw = !fw;
@@ -1150,23 +1142,15 @@ __device__ inline void dc_root(const double* d, const double* z, int nk, int i, 
     if (!(xn > lo && xn < hi)) {
       xn = (lo > 0.0 && hi > 4.0 * lo) ? sqrt(lo) * sqrt(hi)
          : (hi < 0.0 && lo < 4.0 * hi) ? -sqrt(-lo) * sqrt(-hi) : 0.5 * (lo + hi);
-      if (!(xn > lo && xn < hi)) {  // no number between the ends (or a NaN)
-        tau = 0.5 * (lo + hi);
-        conv = true;
-        break;
-      }
+      if (!(xn > lo && xn < hi)) { tau = 0.5 * (lo + hi); break; }
     }
-    if (fabs(xn - x) <= 2.0 * U64 * fabs(xn)) {
-      tau = xn;
-      conv = true;
-      break;
-    }
+    if (fabs(xn - x) <= 2.0 * U64 * fabs(xn)) { tau = xn; break; }
     x = xn;
     tau = x;
   }
   ok = tau == tau && tau != 0.0;
   if (!ok) tau = right ? lo : hi;
-  ok = ok && conv;
+  ok = ok && it < ROOT_MAXIT;
   tau_out = tau;
   dor_out = dor;
 }
