@@ -147,7 +147,8 @@ size_t tt_workspace_bytes(const tt_config* cfg, int32_t n_inflow);
  *  X0, Th0, Ph0: host initial cores with ranks r1, r2 (<= the rank caps).
  *  dev_workspace: device, >= tt_workspace_bytes(cfg, n_inflow) bytes,
  *      caller-owned, must outlive the context; the library allocates no
- *      other device memory.  (One that is short of partial tiles of the
+ *      other device memory, and at most 2 MB of pinned host memory (none while
+ *      the cores set stay below 32 KB) until tt_destroy.  (One that is short of partial tiles of the
  *      N_s-long Gram only is taken as well: above 384 columns it runs on
  *      fewer row slices then, at least one per 1024 rows or 64.)
  *  hip_stream: a hipStream_t (NULL = default stream), caller-owned.

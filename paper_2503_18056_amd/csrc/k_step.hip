@@ -265,9 +265,13 @@ __global__ void k_hll_inflow(int ns, const double* __restrict__ bc_e0, const int
 __global__ __launch_bounds__(256) void k_pad_cores(const double* __restrict__ Xs, double* __restrict__ X,
                                                    int ns, int r1, int ldX,
                                                    const double* __restrict__ Ts, double* __restrict__ Th,
-                                                   int lt, int lt_cap, int r2, int r2c,
+                                                   int nt, int lt_cap, int r2, int r2c,
                                                    const double* __restrict__ Ps, double* __restrict__ Ph,
-                                                   int n) {
+                                                   int np, int* __restrict__ dims, int jac_maxsw) {
+  if (blockIdx.x == 0)
+    for (int q = threadIdx.x; q < D_NDIMS; q += 256)
+      dims[q] = q == D_R1 ? r1 : q == D_R2 ? r2 : q == D_JAC_MAXSW ? jac_maxsw : 0;
+  const int lt = r1 * nt, n = r2 * np;
   const int lane = threadIdx.x & 63, nw = gridDim.x * 4;
   const int w0 = blockIdx.x * 4 + (threadIdx.x >> 6);
   for (int i = w0; i < ns; i += nw)
@@ -853,9 +857,9 @@ void launch_hll_inflow(const StepGeom& G, const double* bc_e0, const int* code, 
   if (nbc > 0) k_hll_inflow<<<(G.ns + 255) / 256, 256, 0, st>>>(G.ns, bc_e0, code, nbc, W, bc_e);
 }
 void launch_pad_cores(const double* Xs, double* X, int ns, int r1, int ldX, const double* Ts,
-                      double* Th, int lt, int lt_cap, int r2, int r2c, const double* Ps, double* Ph,
-                      int n, hipStream_t st) {
-  k_pad_cores<<<1024, 256, 0, st>>>(Xs, X, ns, r1, ldX, Ts, Th, lt, lt_cap, r2, r2c, Ps, Ph, n);
+                      double* Th, int nt, int lt_cap, int r2, int r2c, const double* Ps, double* Ph,
+                      int np, int* dims, int jac_maxsw, hipStream_t st) {
+  k_pad_cores<<<1024, 256, 0, st>>>(Xs, X, ns, r1, ldX, Ts, Th, nt, lt_cap, r2, r2c, Ps, Ph, np, dims, jac_maxsw);
 }
 void launch_convert(const double* a, int lda, float* b, int ldb, int rows, int cols, hipStream_t st) {
   k_convert<double, float><<<1024, 256, 0, st>>>(a, lda, b, ldb, rows, cols);

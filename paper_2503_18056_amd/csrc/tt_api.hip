@@ -103,6 +103,9 @@ int inflow_blocks(const tt_config& c, int n_inflow) {
 // by blocks that fit the L1 cache, without a branch an entry (they vectorise)
 constexpr size_t FINITE_BLOCK = 2048;
 constexpr size_t PIN_DOUBLES = 128 * 1024;  // a pinned chunk: 1 MB
+// up to 32 KB pageable memory does as well, and a short-lived context is spared
+// making and freeing a pinned chunk (tt_create at 120 cells 108 us, with a chunk 147)
+constexpr size_t PAGEABLE_DOUBLES = 4096;
 bool all_finite(const double* a, size_t n) {
   for (size_t o = 0; o < n; o += FINITE_BLOCK) {
     const size_t m = std::min(FINITE_BLOCK, n - o);
@@ -113,12 +116,33 @@ bool all_finite(const double* a, size_t n) {
   return true;
 }
 
+// Pinned chunk k of the context, made when first used: no larger than the cores
+// at their rank capacities.
+tt_status pin_chunk(tt_ctx* c, int k) {
+  if (c->pin[k]) return TT_OK;
+  const size_t most = (size_t)c->ns * c->r1c + (size_t)c->r1c * c->nt * c->r2c + (size_t)c->r2c * c->np;
+  HIPCHK(c, hipHostMalloc((void**)&c->pin[k], std::min(most, PIN_DOUBLES) * 8, hipHostMallocDefault));
+  return TT_OK;
+}
+
+// Entries checked and copied by blocks that fit the L1 cache.  Returns whether
+// none was refused (it stops at the first block that has one).
+bool copy_checked(double* dst, const double* src, size_t n) {
+  for (size_t b = 0; b < n; b += FINITE_BLOCK) {
+    const size_t m = std::min(FINITE_BLOCK, n - b);
+    if (!all_finite(src + b, m)) return false;
+    memcpy(dst + b, src + b, m * 8);
+  }
+  return true;
+}
+
 // Host array -> device through the context's two pinned chunks: an entry is
 // checked and copied while its block is in cache, and a chunk is filled while
 // the other one travels.  *finite: no entry was refused (the copy stops there).
 tt_status upload_checked(tt_ctx* c, double* dst, const double* src, size_t n, bool* finite) {
   for (int k = 0; k < 2; ++k) {
-    if (!c->pin[k]) HIPCHK(c, hipHostMalloc((void**)&c->pin[k], PIN_DOUBLES * 8, hipHostMallocDefault));
+    tt_status st = pin_chunk(c, k);
+    if (st != TT_OK) return st;
     if (!c->pin_ev[k]) HIPCHK(c, hipEventCreateWithFlags(&c->pin_ev[k], hipEventDisableTiming));
   }
   for (size_t o = 0; o < n && *finite; o += PIN_DOUBLES) {
@@ -126,11 +150,7 @@ tt_status upload_checked(tt_ctx* c, double* dst, const double* src, size_t n, bo
     const int k = c->pin_next;
     c->pin_next ^= 1;
     if (c->pin_used[k]) HIPCHK(c, hipEventSynchronize(c->pin_ev[k]));
-    for (size_t b = 0; b < m && *finite; b += FINITE_BLOCK) {
-      const size_t mb = std::min(FINITE_BLOCK, m - b);
-      *finite = all_finite(src + o + b, mb);
-      memcpy(c->pin[k] + b, src + o + b, mb * 8);
-    }
+    *finite = copy_checked(c->pin[k], src + o, m);
     if (!*finite) break;
     HIPCHK(c, hipMemcpyAsync(dst + o, c->pin[k], m * 8, hipMemcpyHostToDevice, c->st));
     HIPCHK(c, hipEventRecord(c->pin_ev[k], c->st));
@@ -992,28 +1012,49 @@ tt_status tt_set_cores(tt_ctx* c, const double* X, const double* Th, const doubl
   hipStream_t s = c->st;
   // The cores go up as they are, checked on the way, into buffers that every
   // step overwrites (X', Theta_cat, Phi_cat); only then does a kernel fill the
-  // state's padded layouts, so a refused state changes nothing.  (Before:
-  // a scalar check, zeroed and padded copies in fresh pageable memory, and
-  // transfers of the whole capacities; a rounding of given cores at 6300 cells,
-  // ranks 192 and 48, took 4.03 ms, now 3.11.)
-  bool finite = true;
-  tt_status up = upload_checked(c, c->Xn, X, (size_t)c->ns * r[0], &finite);
-  if (up == TT_OK && finite) up = upload_checked(c, c->Thcat, Th, (size_t)r[0] * c->nt * r[1], &finite);
-  if (up == TT_OK && finite) up = upload_checked(c, c->Phcat, Ph, (size_t)r[1] * c->np, &finite);
-  if (up != TT_OK) return up;
-  if (!finite) {
-    HIPCHK(c, hipStreamSynchronize(s));
-    return fail(c, TT_ERR_INVALID_ARG, "non-finite cores");
+  // state's padded layouts and its dims table, so a refused state changes
+  // nothing.  (Through zeroed and padded pageable copies of the whole capacities
+  // a rounding of given cores at 6300 cells, ranks 192 and 48, took 4.03 ms, now
+  // 3.11.)  What fits one chunk and one of those buffers goes in one transfer:
+  // at 120 cells, ranks 3 and 2, a call takes 24 us, with a transfer and an event
+  // for each core and a transfer of the dims 52, through padded copies 43.
+  const size_t nX = (size_t)c->ns * r[0], nT = (size_t)r[0] * c->nt * r[1], nP = (size_t)r[1] * c->np;
+  const size_t all = nX + nT + nP;
+  double *dX = c->Xn, *dT = c->Thcat, *dP = c->Phcat;
+  double* one = all > PIN_DOUBLES ? nullptr
+              : all <= (size_t)c->R1c * c->nt * c->R2c ? c->Thcat
+              : all <= (size_t)c->ns * c->ldX ? c->Xn : nullptr;
+  if (one) {
+    double* h;
+    if (all <= PAGEABLE_DOUBLES) {
+      c->pageable.resize(all);
+      h = c->pageable.data();
+    } else {
+      tt_status up = pin_chunk(c, 0);
+      if (up != TT_OK) return up;
+      if (c->pin_used[0]) HIPCHK(c, hipEventSynchronize(c->pin_ev[0]));
+      h = c->pin[0];
+    }
+    if (!copy_checked(h, X, nX) || !copy_checked(h + nX, Th, nT) || !copy_checked(h + nX + nT, Ph, nP))
+      return fail(c, TT_ERR_INVALID_ARG, "non-finite cores");
+    dX = one;
+    dT = one + nX;
+    dP = dT + nT;
+    HIPCHK(c, hipMemcpyAsync(one, h, all * 8, hipMemcpyHostToDevice, s));
+  } else {
+    bool finite = true;
+    tt_status up = upload_checked(c, dX, X, nX, &finite);
+    if (up == TT_OK && finite) up = upload_checked(c, dT, Th, nT, &finite);
+    if (up == TT_OK && finite) up = upload_checked(c, dP, Ph, nP, &finite);
+    if (up != TT_OK) return up;
+    if (!finite) {
+      HIPCHK(c, hipStreamSynchronize(s));
+      return fail(c, TT_ERR_INVALID_ARG, "non-finite cores");
+    }
   }
-  launch_pad_cores(c->Xn, c->X, c->ns, r[0], c->ldX, c->Thcat, c->Th, r[0] * c->nt, c->r1c * c->nt, r[1],
-                   c->r2c, c->Phcat, c->Ph, r[1] * c->np, s);
+  launch_pad_cores(dX, c->X, c->ns, r[0], c->ldX, dT, c->Th, c->nt, c->r1c * c->nt, r[1], c->r2c, dP, c->Ph, c->np,
+                   c->dims, c->jac_maxsw, s);
   if (c->mixed) launch_convert(c->X, c->ldX, c->Xf, c->ldX, c->ns, c->ldX, s);
-  int hd[D_NDIMS];
-  memset(hd, 0, sizeof(hd));
-  hd[D_R1] = r[0];
-  hd[D_R2] = r[1];
-  hd[D_JAC_MAXSW] = c->jac_maxsw;
-  HIPCHK(c, hipMemcpyAsync(c->dims, hd, sizeof(hd), hipMemcpyHostToDevice, s));
   // frozen material without scattering: the source coefficients never change
   launch_material(c->ns, c->cfg.c, c->dt, c->cfg.a_r, 0, c->kappa, nullptr, c->rho, c->cv, c->T,
                   c->Estar, c->Tdag, c->d, c->s, c->dims, s);

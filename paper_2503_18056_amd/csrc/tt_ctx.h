@@ -112,7 +112,8 @@ struct tt_ctx {
   double* zt;  // z by stencil block, r1c x MAX_BLOCKS (energy through Y = X Zt)
   tt::GradBufs gb;
   size_t ws_need;
-  // pinned chunks of tt_set_cores' uploads, kept until the context goes
+  // host chunks of tt_set_cores' uploads, kept until the context goes
+  std::vector<double> pageable;
   double* pin[2] = {nullptr, nullptr};
   hipEvent_t pin_ev[2] = {nullptr, nullptr};  // the chunk's last transfer
   bool pin_used[2] = {false, false};

@@ -81,11 +81,12 @@ void launch_hll_weights(const StepGeom& G, int dim, const double* rho, const dou
 // with code[c] = 4 ax_c + sel_c (host-built; one code per rank-1 term).
 void launch_hll_inflow(const StepGeom& G, const double* bc_e0, const int* code, int nbc,
                        const double* W, double* bc_e, hipStream_t st);
-// Cores as a caller holds them (X ns x r1, Theta lt x r2, Phi n) into the padded
-// layouts: X ns x ldX, Theta lt_cap x r2c (zero past the live part), Phi.
+// Cores as a caller holds them (X ns x r1, Theta (r1 nt) x r2, Phi r2 x np) into the
+// padded layouts: X ns x ldX, Theta lt_cap x r2c (zero past the live part), Phi;
+// and the dims table of a new state: its ranks, the sweep cap, zeros.
 void launch_pad_cores(const double* Xs, double* X, int ns, int r1, int ldX, const double* Ts,
-                      double* Th, int lt, int lt_cap, int r2, int r2c, const double* Ps, double* Ph,
-                      int n, hipStream_t st);
+                      double* Th, int nt, int lt_cap, int r2, int r2c, const double* Ps, double* Ph,
+                      int np, int* dims, int jac_maxsw, hipStream_t st);
 void launch_convert(const double* a, int lda, float* b, int ldb, int rows, int cols, hipStream_t st);
 void launch_convert(const float* a, int lda, double* b, int ldb, int rows, int cols, hipStream_t st);
 void launch_build_phcat(const StepGeom& G, const double* Ph, const double* pfac,
