@@ -236,7 +236,6 @@ __device__ __host__ inline SytrdGridBufs sytrd_grid_bufs(double* work, int N) {
   B.Dv = B.Pv + 2 * (size_t)N;
   return B;
 }
-constexpr size_t GRID_DYN_LDS_MAX = 158 * 1024;  // dynamic LDS a grid reduction may ask for
 
 // A job's barrier flags (grid_sync.h).
 constexpr size_t SYNC_DOUBLES = SYNC_MAXP / 2;

@@ -119,19 +119,14 @@ void gemm(const GemmDesc& g, int mcap, int ncap, int batch, const int* dims, hip
   else if (!g.transA && g.transB) k_gemm<0, 1><<<grid, 256, 0, s>>>(g, dims);
   else k_gemm<1, 1><<<grid, 256, 0, s>>>(g, dims);
 }
-// the transposes of the two pairs that a bond's truncation has
+// the transposes of the two pairs that a bond's truncation has: (1, 0), (0, 0) and
+// (0, 0), (1, 1)
 void gemm_pair(const GemmDesc& g0, const GemmDesc& g1, int mcap, int ncap, const int* dims,
                hipStream_t s) {
   if (mcap <= 0 || ncap <= 0) return;
   const dim3 grid((ncap + 63) / 64, (mcap + 63) / 64, 2);
-  if (g0.transA && !g0.transB && !g1.transA && !g1.transB)
-    k_gemm_pair<1, 0, 0, 0><<<grid, 256, 0, s>>>(g0, g1, dims);
-  else if (!g0.transA && !g0.transB && g1.transA && g1.transB)
-    k_gemm_pair<0, 0, 1, 1><<<grid, 256, 0, s>>>(g0, g1, dims);
-  else {
-    gemm(g0, mcap, ncap, 1, dims, s);
-    gemm(g1, mcap, ncap, 1, dims, s);
-  }
+  if (g0.transA) k_gemm_pair<1, 0, 0, 0><<<grid, 256, 0, s>>>(g0, g1, dims);
+  else k_gemm_pair<0, 0, 1, 1><<<grid, 256, 0, s>>>(g0, g1, dims);
 }
 
 // ---------------------------------------------------------------------------
@@ -1067,7 +1062,7 @@ static void gram_split_launch(const GramPlan& p, const float* A, DimExpr n, cons
 // FP32 entries is exact in FP64, so only the sums round, at 2^-53 against the
 // slices' 2^-44 per term, and one FP64 product replaces S (S + 1) / 2 sliced
 // ones at half its rate.  Fewer slices are a coarser Gram by the caller's
-// choice, and slower (65536 x 322: FP64 0.27 ms; 4 slices 1.36 ms).
+// choice, and slower (65536 x 322: FP64 0.24 ms; 4 slices 1.36 ms).
 void gram_split_partial(const GramPlan& p, const float* A, DimExpr n, unsigned* colmax,
                         double* partial, const int* dims, hipStream_t s, int slices) {
   if (slices < 1 || slices >= GRAM_SLICES_FP64) {

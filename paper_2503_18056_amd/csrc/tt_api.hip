@@ -283,14 +283,12 @@ size_t carve(tt_ctx* x, char* base) {
     x->E[k].work = cv.take<double>(eig_work_doubles(ncap));
   }
   x->M1 = cv.take<double>((size_t)x->R1c * x->R1c);
-  x->C1 = cv.take<double>((size_t)x->R1c * x->R1c);
   x->Wm1 = cv.take<double>((size_t)x->R1c * x->r1c);
   x->Ur1 = cv.take<double>((size_t)x->R1c * x->r1c);
   x->P1 = cv.take<double>((size_t)x->R1c * x->r1c);
   x->Mupd1 = cv.take<double>((size_t)x->r1c * x->R1c);
   x->Thp = cv.take<double>((size_t)x->r1c * nt * x->R2c);
   x->M2 = cv.take<double>((size_t)x->R2c * x->R2c);
-  x->C2 = cv.take<double>((size_t)x->R2c * x->R2c);
   x->Wm2 = cv.take<double>((size_t)x->R2c * x->r2c);
   x->Ur2 = cv.take<double>((size_t)x->R2c * x->r2c);
   x->P2 = cv.take<double>((size_t)x->R2c * x->r2c);
@@ -420,7 +418,7 @@ struct Prof {
 // both Gram matrices in slots ea (A side) and eb (B side); writes P (R x r')
 // and M_upd (r' x R).
 void truncate_bond(tt_ctx* c, int bond, const EigSlot& ea, const EigSlot& eb, EigSlot& em,
-                   double* M, double* Cm, double* Wm, double* Ur, double* P, double* Mupd,
+                   double* M, double* Wm, double* Ur, double* P, double* Mupd,
                    int Rcap, int rcap, int Rdim, double tol, int rmax) {
   hipStream_t s = c->st;
   const int ka = bond == 1 ? D_KA1 : D_KA2, kb = bond == 1 ? D_KB1 : D_KB2;
@@ -443,7 +441,7 @@ void truncate_bond(tt_ctx* c, int bond, const EigSlot& ea, const EigSlot& eb, Ei
   {
     // SVD of M (App. A.2) through the Golub-Kahan tridiagonal
     Prof p(c, bond == 1 ? P_EIGM1 : P_EIGM2);
-    EigJob j{Cm, Rcap, tgk, em.lam, em.V, N, em.sq, em.isq, kc, 1.0, em.work};
+    EigJob j{nullptr, 0, tgk, em.lam, em.V, N, em.sq, em.isq, kc, 1.0, em.work};
     svd_short_side(M, Rcap, ka, kb, side, j, 2 * qcap, Rcap, c->dims, s);
   }
   RankArgs ra;
@@ -524,7 +522,7 @@ void round_pipeline(tt_ctx* c, const double* xc, int ldxc, int ncap1, double tol
         {c->GR3, R2c, D_RC2, c->E[2].lam, c->E[2].V, N, c->E[2].sq, c->E[2].isq, D_KB2, 1.0, c->E[2].work}};
     eig_batched(jobs, 3, N, c->dims, s);
   }
-  truncate_bond(c, 1, c->E[0], c->E[1], c->E[3], c->M1, c->C1, c->Wm1, c->Ur1, c->P1, c->Mupd1,
+  truncate_bond(c, 1, c->E[0], c->E[1], c->E[3], c->M1, c->Wm1, c->Ur1, c->P1, c->Mupd1,
                 R1c, c->r1c, D_RC1, tol, rmax);
   {
     Prof p(c, P_XUPD);
@@ -555,7 +553,7 @@ void round_pipeline(tt_ctx* c, const double* xc, int ldxc, int ncap1, double tol
     // sized by the bond-2 capacity: fewer divide-and-conquer levels than N
     eig_batched(&j, 1, R2c, c->dims, s);
   }
-  truncate_bond(c, 2, c->E[4], c->E[2], c->E[5], c->M2, c->C2, c->Wm2, c->Ur2, c->P2, c->Mupd2,
+  truncate_bond(c, 2, c->E[4], c->E[2], c->E[5], c->M2, c->Wm2, c->Ur2, c->P2, c->Mupd2,
                 R2c, c->r2c, D_RC2, tol, rmax);
   {
     Prof p(c, P_SMALL);

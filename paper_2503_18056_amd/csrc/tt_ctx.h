@@ -106,8 +106,8 @@ struct tt_ctx {
   size_t gpart_n = 0;        // doubles of gpart
   double *GA, *GB1, *GR3, *GL2, *T1;
   tt::EigSlot E[6];  // bond 1: 0 G_A, 1 G_B1, 2 G_R3, 3 SVD of M1; bond 2: 4 G_L2, 5 SVD of M2
-  double *M1, *C1, *Wm1, *Ur1, *P1, *Mupd1, *Thp;
-  double *M2, *C2, *Wm2, *Ur2, *P2, *Mupd2;
+  double *M1, *Wm1, *Ur1, *P1, *Mupd1, *Thp;
+  double *M2, *Wm2, *Ur2, *P2, *Mupd2;
   double *pv, *z;
   double* zt;  // z by stencil block, r1c x MAX_BLOCKS (energy through Y = X Zt)
   tt::GradBufs gb;

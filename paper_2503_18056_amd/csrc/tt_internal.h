@@ -177,7 +177,7 @@ void eig_batched(const EigJob* jobs, int njobs, int ncap, int* dims, hipStream_t
 // lam = sigma (q, descending), V = singular vectors of the short side
 // (side 0: left vectors of M, a x q; side 1: right vectors, b x q), each
 // column sign-fixed (largest |entry| positive), sq = sigma, isq = 1/sigma,
-// dims[kept_idx] = number with sigma > 2q u sigma_1.  J.A is not used; dims[J.n_idx]
+// dims[kept_idx] = number with sigma > 2q u sigma_1.  J.A and J.lda are not used; dims[J.n_idx]
 // receives 2q.  2 q_max <= ncap2 <= 2048, J.work holds eig_work_doubles(ncap2);
 // max(a, b) <= pcap <= 1024.
 void svd_short_side(const double* M, int ldm, int a_idx, int b_idx, int side_idx,

@@ -126,8 +126,7 @@ size_t tt_kernel_svd_workspace(int32_t a, int32_t b) {
   const int q = a < b ? a : b, p = a < b ? b : a;
   if (a < 1 || b < 1 || q > 1024 || p > 1024) return 0;
   const int N = 2 * q;
-  return align256(64 * sizeof(int)) + align256((size_t)p * q * 8) + align256((size_t)q * 8) * 2 +
-         align256(eig_work_doubles(N) * 8);
+  return align256(64 * sizeof(int)) + align256((size_t)q * 8) * 2 + align256(eig_work_doubles(N) * 8);
 }
 
 tt_status tt_kernel_svd(const double* M, int32_t a, int32_t b, int32_t ldm, double* sig, double* V,
@@ -146,8 +145,6 @@ tt_status tt_kernel_svd(const double* M, int32_t a, int32_t b, int32_t ldm, doub
   char* w = (char*)ws;
   int* dims = (int*)w;
   w += align256(64 * sizeof(int));
-  double* Awork = (double*)w;
-  w += align256((size_t)p * q * 8);
   double* sq = (double*)w;
   w += align256((size_t)q * 8);
   double* isq = (double*)w;
@@ -161,7 +158,7 @@ tt_status tt_kernel_svd(const double* M, int32_t a, int32_t b, int32_t ldm, doub
   hd[2] = a <= b ? 0 : 1;
   KCHK(hipMemcpyAsync(dims, hd, sizeof(hd), hipMemcpyHostToDevice, s));
   KCHK(hipMemsetAsync(work, 0, eig_work_doubles(N) * 8, s));
-  EigJob j{Awork, q, 3, sig, V, ldv, sq, isq, 4, 1.0, work};
+  EigJob j{nullptr, 0, 3, sig, V, ldv, sq, isq, 4, 1.0, work};
   svd_short_side(M, ldm, 0, 1, 2, j, N, p, dims, s);
   KCHK(hipGetLastError());
   KCHK(hipMemcpyAsync(hd, dims, sizeof(hd), hipMemcpyDeviceToHost, s));
