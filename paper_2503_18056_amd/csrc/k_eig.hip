@@ -200,14 +200,14 @@ constexpr int SYR_MAX = 192;  // orders reduced in registers by k_sytrd_reg
 // blocks must be resident together beside those of other streams' launches.  A
 // process has 4 hardware queues and the chip 256 CUs: every launch with grid
 // barriers keeps to GRID_CUS CUs, but the reductions of capacities above
-// SYG_WIDE, which keep to GRID_CUS_WIDE.  Up to SYG_WIDE a block has at most 256
-// registers a lane, so two fit a CU, and 4 jobs of 32 blocks fit 64.  Above, a
-// block takes a CU (about 490 registers; in 256 it spills, and orders 641 and
-// 897 took 5836 and 11532 us instead of 5113 and 8370), and two jobs of 64
-// blocks run side by side, a third after them.  So contexts may step at the same
-// time as long as their CUs add up to 256: four of them, or two above SYG_WIDE.  (With
-// all jobs side by side at one block a CU, as it was, three jobs took 96 CUs up to
-// order 512 and 192 above, and two contexts could wait for each other's CUs.)
+// SYG_WIDE, which keep to GRID_CUS_WIDE.  A launch has two jobs, the two sides of a
+// bond.  Up to SYG_WIDE a block has at most 256 registers a lane and two fit a CU;
+// above, a block takes a CU (about 430 registers; in 256 it spills, and orders
+// 641 and 897 took 5836 and 11532 us instead of 5113 and 8370).  So contexts may
+// step at the same time as long as their CUs add up to 256: four of them, or two
+// above SYG_WIDE.  (With three jobs a launch and one block a CU, as it was, a launch
+// took 96 CUs up to order 512 and 192 above, and two contexts could wait for
+// each other's CUs.)
 // Every wait is bounded by SYTRD_SPIN_MAX polls, after which the barrier-timeout
 // flag is raised and the kernel runs out.
 // Outputs (d, e, tau, reflectors in H): d, e the tridiagonal, row k of H and
@@ -479,36 +479,30 @@ __device__ __host__ inline int sytrd_grid_chunks(int n) {
 inline size_t sytrd_grid_lds(int N) {
   return (size_t)sytrd_grid_chunks(N) * 64 * 3 * (SYTRD_GRID_T / 64) * 8;
 }
-// Jobs of a launch that are reduced side by side; the others follow on the
-// same blocks.
-inline int sytrd_grid_jobs(int N, int njobs) {
-  return N <= SYG_WIDE ? njobs : std::min(njobs, GRID_CUS_WIDE / SYTRD_GRID_P);
-}
-static_assert(4 * (SYG_WIDE / 16) / 2 <= GRID_CUS && 2 * SYTRD_GRID_P <= GRID_CUS_WIDE, "CUs of a launch");
+// Jobs of a launch.
+constexpr int SYG_JOBS = 2;
+static_assert(SYG_JOBS * (SYG_WIDE / 16) / 2 <= GRID_CUS && SYG_JOBS * SYTRD_GRID_P <= GRID_CUS_WIDE,
+              "CUs of a launch");
 
-// WIDE: capacities above SYG_WIDE.  Up to there 256 registers a lane do, and two
-// blocks fit a CU.
+// Jobs q0 and q0 + 1.  WIDE: capacities above SYG_WIDE.  Up to there 256 registers a
+// lane do, and two blocks fit a CU.
 template <bool WIDE>
 __global__ __launch_bounds__(SYTRD_GRID_T) __attribute__((amdgpu_waves_per_eu(WIDE ? 1 : 2))) void k_sytrd_grid(
-    EigJobs jobs, int njobs, int* __restrict__ dims, int N) {
+    EigJobs jobs, int q0, int* __restrict__ dims, int N) {
   extern __shared__ double lds[];
   __shared__ int s_abort;
-  for (int q = blockIdx.y; q < njobs; q += gridDim.y) {
-    const EigJob J = jobs.j[q];
-    const int n = dims[J.n_idx];
-    if (n <= SYR_MAX) continue;  // k_sytrd_reg (the same decision on all blocks of the job)
-    const int P = sytrd_grid_blocks(n);
-    if (blockIdx.x >= P) continue;
-    if (WIDE) __syncthreads();  // the job before is done with the LDS
-    if (threadIdx.x == 0) s_abort = 0;
-    __syncthreads();
-    if (n <= 256) sytrd_grid_rows<4>(J, dims, N, n, P, lds, &s_abort);
-    else if (n <= 384) sytrd_grid_rows<6>(J, dims, N, n, P, lds, &s_abort);
-    else if (!WIDE || n <= 512) sytrd_grid_rows<8>(J, dims, N, n, P, lds, &s_abort);
-    else if (n <= 704) sytrd_grid_rows<11>(J, dims, N, n, P, lds, &s_abort);
-    else sytrd_grid_rows<16>(J, dims, N, n, P, lds, &s_abort);
-    if (!WIDE) break;  // a block has one job
-  }
+  const EigJob J = jobs.j[q0 + blockIdx.y];
+  const int n = dims[J.n_idx];
+  if (n <= SYR_MAX) return;  // k_sytrd_reg (the same decision on all blocks of the job)
+  const int P = sytrd_grid_blocks(n);
+  if (blockIdx.x >= P) return;
+  if (threadIdx.x == 0) s_abort = 0;
+  __syncthreads();
+  if (n <= 256) sytrd_grid_rows<4>(J, dims, N, n, P, lds, &s_abort);
+  else if (n <= 384) sytrd_grid_rows<6>(J, dims, N, n, P, lds, &s_abort);
+  else if (!WIDE || n <= 512) sytrd_grid_rows<8>(J, dims, N, n, P, lds, &s_abort);
+  else if (n <= 704) sytrd_grid_rows<11>(J, dims, N, n, P, lds, &s_abort);
+  else sytrd_grid_rows<16>(J, dims, N, n, P, lds, &s_abort);
 }
 
 // The same reduction with the matrix in registers (n <= SYR_MAX), one block
@@ -3168,9 +3162,11 @@ void eig_batched(const EigJob* jobs, int njobs, int N, int* dims, hipStream_t s)
   k_sytrd_reg<<<njobs, SYR_T, 0, s>>>(J, dims, N);
   if (N > SYR_MAX) {
     const int nj = njobs < 4 ? njobs : 4;
-    const dim3 grid(sytrd_grid_blocks(N), sytrd_grid_jobs(N, nj));
-    if (N > SYG_WIDE) k_sytrd_grid<true><<<grid, SYTRD_GRID_T, sytrd_grid_lds(N), s>>>(J, nj, dims, N);
-    else k_sytrd_grid<false><<<grid, SYTRD_GRID_T, sytrd_grid_lds(N), s>>>(J, nj, dims, N);
+    for (int q = 0; q < nj; q += SYG_JOBS) {
+      const dim3 grid(sytrd_grid_blocks(N), std::min(SYG_JOBS, nj - q));
+      if (N > SYG_WIDE) k_sytrd_grid<true><<<grid, SYTRD_GRID_T, sytrd_grid_lds(N), s>>>(J, q, dims, N);
+      else k_sytrd_grid<false><<<grid, SYTRD_GRID_T, sytrd_grid_lds(N), s>>>(J, q, dims, N);
+    }
   }
   dc_solve(J, njobs < 4 ? njobs : 4, N, dims, s);
   k_ormtr<false><<<dim3((N + 3) / 4, njobs), 256, ormtr_lds_doubles(N) * 8, s>>>(J, dims, N);

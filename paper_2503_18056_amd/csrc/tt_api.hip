@@ -516,11 +516,10 @@ void round_pipeline(tt_ctx* c, const double* xc, int ldxc, int ncap1, double tol
   }
   {
     Prof p(c, P_EIG1);
-    EigJob jobs[3] = {
+    EigJob jobs[2] = {
         {c->GA, R1c, D_RC1, c->E[0].lam, c->E[0].V, N, c->E[0].sq, c->E[0].isq, D_KA1, 1.0, c->E[0].work},
-        {c->GB1, R1c, D_RC1, c->E[1].lam, c->E[1].V, N, c->E[1].sq, c->E[1].isq, D_KB1, 1.0, c->E[1].work},
-        {c->GR3, R2c, D_RC2, c->E[2].lam, c->E[2].V, N, c->E[2].sq, c->E[2].isq, D_KB2, 1.0, c->E[2].work}};
-    eig_batched(jobs, 3, N, c->dims, s);
+        {c->GB1, R1c, D_RC1, c->E[1].lam, c->E[1].V, N, c->E[1].sq, c->E[1].isq, D_KB1, 1.0, c->E[1].work}};
+    eig_batched(jobs, 2, R1c, c->dims, s);
   }
   truncate_bond(c, 1, c->E[0], c->E[1], c->E[3], c->M1, c->Wm1, c->Ur1, c->P1, c->Mupd1,
                 R1c, c->r1c, D_RC1, tol, rmax);
@@ -549,9 +548,12 @@ void round_pipeline(tt_ctx* c, const double* xc, int ldxc, int ncap1, double tol
   }
   {
     Prof p(c, P_EIG2);
-    EigJob j = {c->GL2, R2c, D_RC2, c->E[4].lam, c->E[4].V, N, c->E[4].sq, c->E[4].isq, D_KA2, 1.0, c->E[4].work};
-    // sized by the bond-2 capacity: fewer divide-and-conquer levels than N
-    eig_batched(&j, 1, R2c, c->dims, s);
+    // both sides of bond 2 (G_R3 has waited since the backward sweep: beside
+    // bond 1's two it would be a third job of the widest launch)
+    EigJob jobs[2] = {
+        {c->GL2, R2c, D_RC2, c->E[4].lam, c->E[4].V, N, c->E[4].sq, c->E[4].isq, D_KA2, 1.0, c->E[4].work},
+        {c->GR3, R2c, D_RC2, c->E[2].lam, c->E[2].V, N, c->E[2].sq, c->E[2].isq, D_KB2, 1.0, c->E[2].work}};
+    eig_batched(jobs, 2, R2c, c->dims, s);
   }
   truncate_bond(c, 2, c->E[4], c->E[2], c->E[5], c->M2, c->Wm2, c->Ur2, c->P2, c->Mupd2,
                 R2c, c->r2c, D_RC2, tol, rmax);
