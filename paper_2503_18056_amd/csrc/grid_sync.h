@@ -18,9 +18,11 @@ constexpr int SYNC_MAXP = 64;              // blocks one barrier may join
 constexpr unsigned GRID_ORD_REDUCE = 0;    // the reduction's ordinals: this + 1, ..
 constexpr unsigned GRID_ORD_DC = 1u << 16; // the divide and conquer's; the reduction passes at most 1024
 
-// Thread tid of nt clears the flags (at the start of a solve).
+// Thread tid of nt clears the flags (at the start of a solve), by stores past the
+// caches, as the barriers write and read them.
 __host__ __device__ inline void grid_clear(unsigned* flag, int tid, int nt) {
-  for (int q = tid; q < SYNC_MAXP; q += nt) flag[q] = 0;
+  for (int q = tid; q < SYNC_MAXP; q += nt)
+    __hip_atomic_store(flag + q, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 __host__ __device__ inline bool grid_arrived(unsigned flag, unsigned ordinal) { return flag >= ordinal; }
 

@@ -2727,6 +2727,8 @@ __global__ __launch_bounds__(JAC_T) void k_svd_jacobi(const double* __restrict__
 // (A_i -= s_L A(i, k) y, then A_i -= tau_R (A_i . v) v).  Exchange buffers are
 // double-buffered by step parity: a block may write step k + 1's while another
 // still reads step k's.
+// One kernel for all column classes: as compiled it has 256 registers, of which 14
+// spill (60 bytes a lane), and 620 scalar ones; the widest class sets that.
 // Bound by latency: at 142 x 142 a step is 5.5 us, of which the block's and the
 // grid's barriers take 2.1, the loads behind them 1.2, the reflectors 0.7 and
 // the rows 1.3; at 128 x 128 and below, on one block, 3 us.  (With the rows
@@ -2828,6 +2830,7 @@ __device__ __forceinline__ void gebrd_rows(const double* __restrict__ M, int ldm
     for (int i = tid; i < 2 * q; i += GBR_T) W.d[i] = 0.0;
   unsigned* flags = grid_flags(J.work, N);
   unsigned ordinal = GRID_ORD_REDUCE;
+  __builtin_amdgcn_s_waitcnt(0x0F70);  // the matrix is there: no waits for it in the loop (10 us at 300 x 300)
   const bool writer = b == 0 && wave == 0;
   for (int k = 0;; ++k) {
     double* srow = srow2 + (k & 1) * LQ;
