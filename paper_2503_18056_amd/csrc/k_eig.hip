@@ -3076,11 +3076,15 @@ size_t dc_fused_dyn_lds(int N) {
   return need;
 }
 // Blocks: a block each up to order 64; above, one for 8 roots or a top
-// merge's tile.  At most DCF_MAXP: with up to a CU's LDS each they keep to
+// merge's tile, and for several jobs one for 8 places of a whole top merge: a
+// job's items are counted so, and with fewer blocks the next job's come a round
+// later (its launches in steps of two jobs of order 142 average 129 us on 64
+// blocks, 141 on 36).  At most DCF_MAXP: with up to a CU's LDS each they keep to
 // GRID_CUS CUs (the residence that grid barriers need, k_sytrd_grid).
 int dc_fused_blocks(int N, int njobs) {
   if (N <= DC_SUB) return njobs;
-  return std::min(DCF_MAXP, njobs * std::max((N + 7) / 8, N * N / 2048));
+  const int roots = njobs > 1 ? next_pow2(N) / 8 : (N + 7) / 8;
+  return std::min(DCF_MAXP, njobs * std::max(roots, N * N / 2048));
 }
 
 }  // namespace
