@@ -345,7 +345,8 @@ def slice_sweep(p, nsteps, slices=(1, 2, 3, 4, 5, 6), prof_steps=20):
     """Slice count of the FP32-mixed Gram (tt_set_gram_slices) against the
     FP64 library on the same run: for each count, the whole run's steps/s,
     the rank history against FP64's, the end state's difference from FP64's,
-    and the average Gram launch over ``prof_steps`` profiled steps after it."""
+    and the average Gram launch over ``prof_steps`` profiled steps after it.
+    Counts 4 to 6 run one path, the entries on FP64 MFMA."""
     import torch
     from paper_2503_18056_amd import TT_FP32_MIXED, TT_FP64, TTState
     warm = TTState(p, device=0, max_steps=2, precision=TT_FP32_MIXED)
